@@ -367,7 +367,8 @@ qf_status qf_autotune(qf_ctx* ctx, const qf_plan* plan, const char* cache_path);
 
 /* Variant installed for a GEMM shape on this context by qf_autotune (not in the paper, see
  * there; 0: none, the shape heuristic applies;
- * 1..7: see qf_autotune's JSON names tiled4x4, tiled2x2, tiled1x2, large, skinny, splitk, simt). */
+ * 1..9: see qf_autotune's JSON names tiled4x4, tiled2x2, tiled1x2, large, skinny, splitk, simt, tall,
+ * f32). */
 qf_status qf_tuned_variant(const qf_ctx* ctx, int precision, int64_t M, int64_t N, int64_t K, int64_t batch,
                            int* variant);
 

@@ -10,7 +10,7 @@
 // count 8 M N K of the paper's formula F = 8 sqrt(v0 v1 v2) equals the real MFMA work.
 //
 // Precisions (the operand conversion happens when a K-tile is staged into LDS):
-//   FP32   : v_mfma_f32_16x16x4_f32 on the FP32 operands.
+//   FP32   : v_mfma_f32_16x16x4_f32 on the FP32 operands (cgemm_f32.hip).
 //   BF16X3 : x = hi + lo with hi = bf16(x), lo = bf16(x - hi); C += hi*hi + hi*lo + lo*hi on
 //            v_mfma_f32_16x16x32_bf16 with FP32 accumulation (the lo*lo term, about 2^-16
 //            relative, is dropped).
@@ -79,56 +79,59 @@ __device__ __forceinline__ void scales_for(const Renorm& rn, const uint32_t* ama
   unscale = ldexpf(1.f, -(s_a + s_b));
 }
 
-// 32 lanes per output: lane t sums chunks [t split/32, (t+1) split/32) in order, then a fixed
-// butterfly over the 32 lanes; the summation order is the same on every run.
-constexpr int kReduceLanes = 32;
+// Sum of the chunks: a workgroup takes 32 consecutive outputs, its 8 groups of 32 lanes read whole
+// 256-byte runs of the chunks y = t, t + 8, ... (one chunk's row per group), and the 8 partial sums meet in
+// LDS.  The order of the sum is a function of the chunk count alone.  Bound by reading the chunks once.
+constexpr int kReduceOut = 32, kReduceSlots = 8;
 
 __global__ void __launch_bounds__(256)
 cgemm_split_reduce(const float2* __restrict__ P, int split, int64_t batch, int64_t MN, int64_t N, int64_t sc,
                    float2* __restrict__ C, Renorm rn) {
+  __shared__ float2 part[kReduceSlots][kReduceOut];
   float sa_, sb_, unscale;
   renorm_begin<P_FP32>(rn, nullptr, nullptr, sa_, sb_, unscale);
   const int64_t total = batch * MN;
-  const int t = threadIdx.x % kReduceLanes;
-  const int per = split / kReduceLanes;  // split is a power of two >= 2
-  const int y0 = per > 0 ? t * per : (t < split ? t : split);
-  const int y1 = per > 0 ? y0 + per : (t < split ? t + 1 : split);
+  const int lane = threadIdx.x % kReduceOut, t = threadIdx.x / kReduceOut;
   float mx = 0.f;
-  const int64_t groups = (int64_t)gridDim.x * (blockDim.x / kReduceLanes);
-  for (int64_t i = (int64_t)blockIdx.x * (blockDim.x / kReduceLanes) + threadIdx.x / kReduceLanes; i < total;
-       i += groups) {
+  for (int64_t i0 = (int64_t)blockIdx.x * kReduceOut; i0 < total; i0 += (int64_t)gridDim.x * kReduceOut) {
+    const int64_t i = i0 + lane;
     float re = 0.f, im = 0.f;
-    for (int y = y0; y < y1; ++y) {
-      const float2 v = P[(int64_t)y * total + i];
-      re += v.x;
-      im += v.y;
-    }
-    for (int off = kReduceLanes / 2; off > 0; off >>= 1) {
-      re += __shfl_xor(re, off, kReduceLanes);
-      im += __shfl_xor(im, off, kReduceLanes);
-    }
-    if (t == 0) {
-      const float2 o = make_float2(re * unscale, im * unscale);
+    if (i < total)
+#pragma unroll 4
+      for (int y = t; y < split; y += kReduceSlots) {
+        const float2 v = P[(int64_t)y * total + i];
+        re += v.x;
+        im += v.y;
+      }
+    part[t][lane] = make_float2(re, im);
+    __syncthreads();
+    if (t == 0 && i < total) {
+      float2 s[kReduceSlots];
+#pragma unroll
+      for (int k = 0; k < kReduceSlots; ++k) s[k] = part[k][lane];
+#pragma unroll
+      for (int w = kReduceSlots / 2; w > 0; w >>= 1)
+#pragma unroll
+        for (int k = 0; k < w; ++k) s[k] = make_float2(s[k].x + s[k + w].x, s[k].y + s[k + w].y);
+      const float2 o = make_float2(s[0].x * unscale, s[0].y * unscale);
       const int64_t b = i / MN, e = i - b * MN, m = e / N;
       C[b * sc + c_index(rn, m, e - m * N, N)] = o;
       mx = fmaxf(mx, cmax(o));
     }
+    __syncthreads();
   }
   if (rn.c) record_amax(rn.c, mx);
 }
 
 template <int PREC>
 struct LdsRow;  // bytes per complex element in LDS per plane
-template <> struct LdsRow<P_FP32> { static constexpr int elem = 8, planes = 1; };
 template <> struct LdsRow<P_BF16X3> { static constexpr int elem = 4, planes = 2; };
 template <> struct LdsRow<P_FP16> { static constexpr int elem = 4, planes = 1; };
 
-// Row padding: FP32 rows are 66 dwords (2 mod 32), so the 32 lanes of a 4-byte A-operand read
-// (16 rows x 2 neighbouring dwords) and the 8-byte B reads hit distinct banks; the 16-bit
-// formats read 16-byte chunks and pad by 16 bytes.
+// Rows are read in 16-byte chunks and padded by 16 bytes.
 template <int PREC, int ROWS>
 struct TileLds {
-  static constexpr int row_bytes = kBK * LdsRow<PREC>::elem + (PREC == P_FP32 ? 8 : 16);
+  static constexpr int row_bytes = kBK * LdsRow<PREC>::elem + 16;
   static constexpr int plane_bytes = ROWS * row_bytes;
   static constexpr int bytes = plane_bytes * LdsRow<PREC>::planes;
 };
@@ -143,12 +146,7 @@ __device__ __forceinline__ void stage_tile(char* lds, const float4 (&r)[ROWS * 1
     const int idx = tid + i * kThreads;
     const int row = idx >> 4, c4 = idx & 15;  // c4: pair of complex k = 2*c4, 2*c4+1
     const float4 v = r[i];
-    if constexpr (PREC == P_FP32) {
-      // rows are 8-byte aligned only
-      float2* dst = reinterpret_cast<float2*>(lds + row * TileLds<PREC, ROWS>::row_bytes + c4 * 16);
-      dst[0] = make_float2(v.x, v.y);
-      dst[1] = make_float2(v.z, v.w);
-    } else if constexpr (PREC == P_BF16X3) {
+    if constexpr (PREC == P_BF16X3) {
       const uint32_t h0 = pack_bf16x2(v.x, v.y), h1 = pack_bf16x2(v.z, v.w);
       const uint32_t l0 = pack_bf16x2(v.x - bf16_lo_to_f32(h0), v.y - bf16_hi_to_f32(h0));
       const uint32_t l1 = pack_bf16x2(v.z - bf16_lo_to_f32(h1), v.w - bf16_hi_to_f32(h1));
@@ -236,65 +234,42 @@ cgemm_mfma(int64_t M, int64_t N, int64_t K, const float2* __restrict__ A, const 
       load_tile<BM>(ra, A, K, (kt + 1) * kBK);
       load_tile<BN>(rb, B, K, (kt + 1) * kBK);
     }
-    if constexpr (PREC == P_FP32) {
-      // 16 chunks of 2 complex k; lane group lg holds real k = lg: complex kc = lg >> 1, part = lg & 1
-      const int kc_l = lg >> 1, part = lg & 1;
-      const int q = l16 & 1;
-#pragma unroll 4
-      for (int c = 0; c < kBK / 2; ++c) {
-        float a[WTM];
+    // 2 chunks of 16 complex k; lane group lg holds complex k 4*lg .. 4*lg+3 (8 real k)
+    const BExpand bx(l16 & 1);
 #pragma unroll
-        for (int i = 0; i < WTM; ++i) {
-          const float* p = reinterpret_cast<const float*>(ldsA + (wr + 16 * i + l16) * LA::row_bytes) + 2 * (2 * c + kc_l);
-          a[i] = p[part];
-        }
+    for (int c = 0; c < kBK / 16; ++c) {
+      u4 ah[WTM], al[WTM];
 #pragma unroll
-        for (int j = 0; j < WTN; ++j) {
-          const float* p = reinterpret_cast<const float*>(ldsB + (wc + 8 * j + (l16 >> 1)) * LB::row_bytes) + 2 * (2 * c + kc_l);
-          const float br = p[0], bi = p[1];
-          const float b = q ? (part ? br : bi) : (part ? -bi : br);
-#pragma unroll
-          for (int i = 0; i < WTM; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b, acc[i][j], 0, 0, 0);
-        }
+      for (int i = 0; i < WTM; ++i) {
+        const char* p = ldsA + (wr + 16 * i + l16) * LA::row_bytes + (16 * c + 4 * lg) * 4;
+        ah[i] = *reinterpret_cast<const u4*>(p);
+        if constexpr (PREC == P_BF16X3) al[i] = *reinterpret_cast<const u4*>(p + LA::plane_bytes);
       }
-    } else {
-      // 2 chunks of 16 complex k; lane group lg holds complex k 4*lg .. 4*lg+3 (8 real k)
-      const BExpand bx(l16 & 1);
 #pragma unroll
-      for (int c = 0; c < kBK / 16; ++c) {
-        u4 ah[WTM], al[WTM];
+      for (int j = 0; j < WTN; ++j) {
+        const char* p = ldsB + (wc + 8 * j + (l16 >> 1)) * LB::row_bytes + (16 * c + 4 * lg) * 4;
+        u4 bh = *reinterpret_cast<const u4*>(p);
 #pragma unroll
-        for (int i = 0; i < WTM; ++i) {
-          const char* p = ldsA + (wr + 16 * i + l16) * LA::row_bytes + (16 * c + 4 * lg) * 4;
-          ah[i] = *reinterpret_cast<const u4*>(p);
-          if constexpr (PREC == P_BF16X3) al[i] = *reinterpret_cast<const u4*>(p + LA::plane_bytes);
-        }
+        for (int e = 0; e < 4; ++e) bh[e] = bx(bh[e]);
+        if constexpr (PREC == P_BF16X3) {
+          u4 bl = *reinterpret_cast<const u4*>(p + LB::plane_bytes);
 #pragma unroll
-        for (int j = 0; j < WTN; ++j) {
-          const char* p = ldsB + (wc + 8 * j + (l16 >> 1)) * LB::row_bytes + (16 * c + 4 * lg) * 4;
-          u4 bh = *reinterpret_cast<const u4*>(p);
+          for (int e = 0; e < 4; ++e) bl[e] = bx(bl[e]);
+          const bf8 vbh = __builtin_bit_cast(bf8, bh), vbl = __builtin_bit_cast(bf8, bl);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) bh[e] = bx(bh[e]);
-          if constexpr (PREC == P_BF16X3) {
-            u4 bl = *reinterpret_cast<const u4*>(p + LB::plane_bytes);
+          for (int i = 0; i < WTM; ++i)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8, al[i]), vbh, acc[i][j], 0, 0, 0);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) bl[e] = bx(bl[e]);
-            const bf8 vbh = __builtin_bit_cast(bf8, bh), vbl = __builtin_bit_cast(bf8, bl);
+          for (int i = 0; i < WTM; ++i)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8, ah[i]), vbl, acc[i][j], 0, 0, 0);
 #pragma unroll
-            for (int i = 0; i < WTM; ++i)
-              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8, al[i]), vbh, acc[i][j], 0, 0, 0);
+          for (int i = 0; i < WTM; ++i)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8, ah[i]), vbh, acc[i][j], 0, 0, 0);
+        } else {
+          const h8 vb = __builtin_bit_cast(h8, bh);
 #pragma unroll
-            for (int i = 0; i < WTM; ++i)
-              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8, ah[i]), vbl, acc[i][j], 0, 0, 0);
-#pragma unroll
-            for (int i = 0; i < WTM; ++i)
-              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8, ah[i]), vbh, acc[i][j], 0, 0, 0);
-          } else {
-            const h8 vb = __builtin_bit_cast(h8, bh);
-#pragma unroll
-            for (int i = 0; i < WTM; ++i)
-              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8, ah[i]), vb, acc[i][j], 0, 0, 0);
-          }
+          for (int i = 0; i < WTM; ++i)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8, ah[i]), vb, acc[i][j], 0, 0, 0);
         }
       }
     }
@@ -512,131 +487,6 @@ cgemm_v2(int64_t M, int64_t N, int64_t K, const float2* __restrict__ A, const fl
   if (rn.c && !partial) record_amax(rn.c, mx);
 }
 
-// Large shapes in FP32: the same 256 x 128 block, 8 waves of 64 rows x 64 complex columns and
-// two register-staged LDS stages as above, with v_mfma_f32_16x16x4_f32 on the FP32 operands.
-// An MFMA step covers 4 real k; lane l supplies A[row l%16][real k = 4s + l/16] and the B entry of
-// real column (n, q = l & 1) at the same k: br or bi chosen by address (part ^ q), negated for
-// (q = 0, odd k).  LDS rows are 16 complex plus 8 bytes (34 dwords, 2 mod 32), so the 4-byte
-// operand reads of 16 rows x 2 neighbouring k hit 32 distinct banks.
-constexpr int kF32Row = 136;                      // bytes per LDS row
-constexpr int kF32PlaneA = kV2BM * kF32Row;       // 34 KiB
-constexpr int kF32PlaneB = kV2BN * kF32Row;       // 17 KiB
-constexpr int kF32Stage = kF32PlaneA + kF32PlaneB;
-
-__device__ __forceinline__ void f32_store(char* st, const float4 (&ra)[4], const float4 (&rb)[2]) {
-  const int tid = threadIdx.x;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int row = (tid >> 3) + 64 * i, c = tid & 7;  // c: complex pair 2c, 2c+1
-    float2* dst = reinterpret_cast<float2*>(st + row * kF32Row + c * 16);
-    dst[0] = make_float2(ra[i].x, ra[i].y);
-    dst[1] = make_float2(ra[i].z, ra[i].w);
-  }
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int row = (tid >> 3) + 64 * i, c = tid & 7;
-    float2* dst = reinterpret_cast<float2*>(st + kF32PlaneA + row * kF32Row + c * 16);
-    dst[0] = make_float2(rb[i].x, rb[i].y);
-    dst[1] = make_float2(rb[i].z, rb[i].w);
-  }
-}
-
-__global__ void __launch_bounds__(kV2Threads)
-cgemm_v2f32(int64_t M, int64_t N, int64_t K, const float2* __restrict__ A, const float2* __restrict__ B,
-            float2* __restrict__ C, int64_t sa, int64_t sb, int64_t sc, Renorm rn, int64_t kc,
-            float2* __restrict__ P) {
-  __shared__ __attribute__((aligned(16))) char lds[2 * kF32Stage];
-
-  const int64_t tiles_m = M / kV2BM, tiles_n = N / kV2BN;
-  const int64_t ntiles = tiles_m * tiles_n;
-  int64_t bid = blockIdx.x;
-  if ((ntiles & 7) == 0) bid = (bid & 7) * (ntiles >> 3) + (bid >> 3);
-  const int64_t group = 4;
-  const int64_t per_group = group * tiles_n;
-  const int64_t gidx = bid / per_group;
-  const int64_t first_m = gidx * group;
-  const int64_t gsize = (tiles_m - first_m) < group ? (tiles_m - first_m) : group;
-  const int64_t tm = first_m + (bid % per_group) % gsize;
-  const int64_t tn = (bid % per_group) / gsize;
-
-  const int64_t batch = blockIdx.z;
-  const bool partial = gridDim.y > 1;
-  A += batch * sa + tm * kV2BM * K + blockIdx.y * kc;
-  B += batch * sb + tn * kV2BN * K + blockIdx.y * kc;
-  if (partial) {
-    C = P + ((int64_t)blockIdx.y * gridDim.z + batch) * M * N;
-  } else {
-    C += batch * sc;
-  }
-
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wr = (wave >> 1) * 64;
-  const int wc = (wave & 1) * 64;
-  const int l16 = lane & 15, lg = lane >> 4, q = l16 & 1;
-  // A: dword 4s + lg of the row; B: dword 4s + 2 (lg >> 1) + ((lg & 1) ^ q), sign bit flipped
-  // for (q = 0, odd real k)
-  const int b_word = 2 * (lg >> 1) + ((lg & 1) ^ q);
-  const uint32_t b_flip = (q == 0 && (lg & 1)) ? 0x80000000u : 0u;
-
-  float scale_a, scale_b, unscale;
-  scales_for<P_FP32>(rn, nullptr, nullptr, partial, scale_a, scale_b, unscale);
-
-  f4 acc[4][8];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 8; ++j) acc[i][j] = (f4){0.f, 0.f, 0.f, 0.f};
-
-  float4 ra[4], rb[2];
-  const int64_t nk = kc / kV2BK;
-  v2_load(ra, rb, A, B, K, 0);
-  f32_store(lds, ra, rb);
-  if (nk > 1) v2_load(ra, rb, A, B, K, kV2BK);
-  __syncthreads();
-  for (int64_t kt = 0; kt < nk; ++kt) {
-    const char* st = lds + (kt & 1) * kF32Stage;
-    const float* LA = reinterpret_cast<const float*>(st);
-    const float* LB = reinterpret_cast<const float*>(st + kF32PlaneA);
-#pragma unroll 2
-    for (int s4 = 0; s4 < kV2BK / 2; ++s4) {  // 8 MFMA steps of 4 real k
-      float a[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = LA[(wr + 16 * i + l16) * (kF32Row / 4) + 4 * s4 + lg];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const float braw = LB[(wc + 8 * j + (l16 >> 1)) * (kF32Row / 4) + 4 * s4 + b_word];
-        const float b = __uint_as_float(__float_as_uint(braw) ^ b_flip);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b, acc[i][j], 0, 0, 0);
-      }
-    }
-    if (kt + 1 < nk) {
-      f32_store(lds + ((kt + 1) & 1) * kF32Stage, ra, rb);
-      if (kt + 2 < nk) v2_load(ra, rb, A, B, K, (kt + 2) * kV2BK);
-    }
-    __syncthreads();
-  }
-
-  float mx = 0.f;
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const f4 v = acc[i][j] * unscale;
-      const float s0 = q ? v[0] : v[2], s1 = q ? v[1] : v[3];
-      const float r0 = __shfl_xor(s0, 1), r1 = __shfl_xor(s1, 1);
-      const int64_t row = tm * kV2BM + wr + 16 * i + 4 * lg + (q ? 2 : 0);
-      const int64_t col = tn * kV2BN + wc + 8 * j + (l16 >> 1);
-      float2 o0, o1;
-      if (q) { o0 = make_float2(r0, v[2]); o1 = make_float2(r1, v[3]); }
-      else { o0 = make_float2(v[0], r0); o1 = make_float2(v[1], r1); }
-      C[partial ? row * N + col : c_index(rn, row, col, N)] = o0;
-      C[partial ? (row + 1) * N + col : c_index(rn, row + 1, col, N)] = o1;
-      mx = fmaxf(mx, fmaxf(cmax(o0), cmax(o1)));
-    }
-  if (rn.c && !partial) record_amax(rn.c, mx);
-}
-
 // Small or thin shapes: one thread per output element, FP32 complex FMA over K.
 __global__ void __launch_bounds__(256)
 cgemm_simt(int64_t M, int64_t N, int64_t K, const float2* __restrict__ A, const float2* __restrict__ B,
@@ -760,15 +610,13 @@ cgemm_splitk(int64_t M, int64_t N, int64_t K, const float2* __restrict__ A, cons
 }
 
 template <int PREC, int WTM, int WTN>
-static hipError_t launch_tiled(hipStream_t st, int64_t M, int64_t N, int64_t K, const float2* A,
-                               const float2* B, float2* C, int64_t batch, int64_t sa, int64_t sb,
-                               int64_t sc, const uint32_t* amaxA, const uint32_t* amaxB, const Renorm& rn,
-                               int split, float2* P) {
+static void launch_tiled(hipStream_t st, int64_t M, int64_t N, int64_t K, const float2* A, const float2* B, float2* C,
+                         int64_t batch, int64_t sa, int64_t sb, int64_t sc, const uint32_t* amaxA,
+                         const uint32_t* amaxB, const Renorm& rn, int split, float2* P) {
   constexpr int BM = 32 * WTM, BN = 16 * WTN;
   const int64_t tiles = (M / BM) * (N / BN);
   hipLaunchKernelGGL((cgemm_mfma<PREC, WTM, WTN>), dim3((unsigned)tiles, (unsigned)split, (unsigned)batch),
                      dim3(kThreads), 0, st, M, N, K, A, B, C, sa, sb, sc, amaxA, amaxB, rn, K / split, P);
-  return hipGetLastError();
 }
 
 static bool pow2(int64_t x) { return x > 0 && (x & (x - 1)) == 0; }
@@ -782,25 +630,38 @@ bool cgemm_variant_fits(int precision, int64_t M, int64_t N, int64_t K, int vari
     case GEMM_LARGE: return p2 && M >= kV2BM && N >= kV2BN && K >= kV2BK;
     case GEMM_SKINNY: return N >= 4 && (N & 3) == 0 && N * K <= kSkinnyMaxB && K <= 64;
     case GEMM_SPLITK: return M * N <= 4096;
-    case GEMM_SIMT: return M >= 1 && N >= 1 && K >= 1;
+    case GEMM_SIMT:
+    case GEMM_F32: return M >= 1 && N >= 1 && K >= 1;
     case GEMM_TALL: return cgemm_tall_fits(precision, M, N, K);
   }
   return false;
 }
 
-int cgemm_default_variant(int precision, int64_t M, int64_t N, int64_t K) {
-  if (cgemm_variant_fits(precision, M, N, K, GEMM_LARGE)) return GEMM_LARGE;
+// Every tile of one precision adds an output's products in the same order, so among the tiles the
+// launch may pick by how many workgroups they give (batch included) without changing a result; the
+// choice between the families below, and the cut of K, are functions of the shape alone, and a
+// batched launch equals the launches of its elements bit by bit.
+int cgemm_default_variant(int precision, int64_t M, int64_t N, int64_t K, int64_t blocks_per_tile) {
   // HBM-bound tall-skinny products below the tiles' N and K (as fast as the 64 x 32 tiles where
   // those fit: 5.1 TB/s on 2^25 x 32 x 32 split-BF16)
   if (M >= 4096 && (N < 32 || K < kBK) && cgemm_variant_fits(precision, M, N, K, GEMM_TALL)) return GEMM_TALL;
-  if (cgemm_variant_fits(precision, M, N, K, GEMM_TILED_1X2)) {
-    if (M >= 128 && N >= 64) return GEMM_TILED_4X4;
-    if (M >= 64 && N >= 32) return GEMM_TILED_2X2;
+  if (precision != P_FP32 && cgemm_variant_fits(precision, M, N, K, GEMM_TILED_1X2)) {
+    // the largest tile that still yields a workgroup for each of 256 CUs (the 256 x 128 tile, the most
+    // efficient per CU, from half as many)
+    if (M >= kV2BM && N >= kV2BN && (M / kV2BM) * (N / kV2BN) * blocks_per_tile >= 128) return GEMM_LARGE;
+    if (M >= 128 && N >= 64 && (M / 128) * (N / 64) * blocks_per_tile >= 256) return GEMM_TILED_4X4;
+    if (M >= 64 && (M / 64) * (N / 32) * blocks_per_tile >= 256) return GEMM_TILED_2X2;
     return GEMM_TILED_1X2;
   }
-  if (cgemm_variant_fits(precision, M, N, K, GEMM_SKINNY)) return GEMM_SKINNY;
-  if (M * N <= 4096 && K >= 256) return GEMM_SPLITK;
-  return GEMM_SIMT;
+  // K = 16 is half a K-tile of the smaller 16-bit tiles
+  if (precision != P_FP32 && cgemm_variant_fits(precision, M, N, K, GEMM_LARGE) && (M / kV2BM) * (N / kV2BN) >= 128)
+    return GEMM_LARGE;
+  // a few long dot products: a workgroup each (from K = 4096 the tiles' split K spreads one further)
+  if (M * N <= 64 && K >= 32 && K < 4096) return GEMM_SPLITK;
+  // short K: the FP32 tiles would multiply zeros
+  if (K < 32 && cgemm_variant_fits(precision, M, N, K, GEMM_SKINNY)) return GEMM_SKINNY;
+  if (K < 8 || M * N * K < 4096) return GEMM_SIMT;
+  return GEMM_F32;
 }
 
 template <int PREC>
@@ -809,47 +670,33 @@ static hipError_t launch_mfma(hipStream_t st, int variant, int64_t M, int64_t N,
                               const uint32_t* amaxA, const uint32_t* amaxB, const Renorm& rn, int split,
                               float2* P) {
   switch (variant) {
-    case GEMM_LARGE: {
-      const int64_t tiles = (M / kV2BM) * (N / kV2BN);
-      if constexpr (PREC == P_FP32)
-        hipLaunchKernelGGL(cgemm_v2f32, dim3((unsigned)tiles, (unsigned)split, (unsigned)batch), dim3(kV2Threads), 0,
-                           st, M, N, K, A, B, C, sa, sb, sc, rn, K / split, P);
-      else
-        hipLaunchKernelGGL((cgemm_v2<PREC>), dim3((unsigned)tiles, (unsigned)split, (unsigned)batch),
-                           dim3(kV2Threads), 0, st, M, N, K, A, B, C, sa, sb, sc, amaxA, amaxB, rn, K / split, P);
-      return hipGetLastError();
-    }
+    case GEMM_LARGE:
+      hipLaunchKernelGGL((cgemm_v2<PREC>), dim3((unsigned)((M / kV2BM) * (N / kV2BN)), (unsigned)split, (unsigned)batch),
+                         dim3(kV2Threads), 0, st, M, N, K, A, B, C, sa, sb, sc, amaxA, amaxB, rn, K / split, P);
+      break;
     case GEMM_TILED_4X4:
-      return launch_tiled<PREC, 4, 4>(st, M, N, K, A, B, C, batch, sa, sb, sc, amaxA, amaxB, rn, split, P);
+      launch_tiled<PREC, 4, 4>(st, M, N, K, A, B, C, batch, sa, sb, sc, amaxA, amaxB, rn, split, P);
+      break;
     case GEMM_TILED_2X2:
-      return launch_tiled<PREC, 2, 2>(st, M, N, K, A, B, C, batch, sa, sb, sc, amaxA, amaxB, rn, split, P);
-    case GEMM_TILED_1X2:
-      return launch_tiled<PREC, 1, 2>(st, M, N, K, A, B, C, batch, sa, sb, sc, amaxA, amaxB, rn, split, P);
+      launch_tiled<PREC, 2, 2>(st, M, N, K, A, B, C, batch, sa, sb, sc, amaxA, amaxB, rn, split, P);
+      break;
+    default:
+      launch_tiled<PREC, 1, 2>(st, M, N, K, A, B, C, batch, sa, sb, sc, amaxA, amaxB, rn, split, P);
   }
-  return hipErrorInvalidValue;
+  return hipGetLastError();
 }
 
-// Workgroups of one launch of an MFMA variant (per batch element), and its K-tile length.
-static void variant_grid(int variant, int64_t M, int64_t N, int64_t* tiles, int64_t* bk) {
-  switch (variant) {
-    case GEMM_LARGE: *tiles = (M / kV2BM) * (N / kV2BN); *bk = kV2BK; return;
-    case GEMM_TILED_4X4: *tiles = (M / 128) * (N / 64); *bk = kBK; return;
-    case GEMM_TILED_2X2: *tiles = (M / 64) * (N / 32); *bk = kBK; return;
-    case GEMM_TILED_1X2: *tiles = (M / 32) * (N / 32); *bk = kBK; return;
-  }
-  *tiles = 0;
-  *bk = 0;
-}
-
-// K-chunks for an MFMA launch whose tile grid (per batch element) has fewer than 256 workgroups:
-// split K (powers of two, chunks of at least 4 K-tiles) towards about 1024 workgroups.  The count
-// depends on the shape only, so one contraction sums in the same order whatever the batch.
+// K-chunks of an MFMA launch: K is cut (powers of two, chunks of at least 512) while the 64 x 32 tiles
+// of one batch element number below 256 and the chunks' tiles stay within two per CU.  A chunk costs a
+// write and a read of its partial tile and the reduction a launch, which K < 1024 does not repay: the
+// 256 x 256 x 256 products of the 4 x 4 and 4 x 5 circuits took 332 us of split kernel and reduction per
+// 64 chains, 100 us in one pass over K on smaller tiles.
 static int split_count(int variant, int64_t M, int64_t N, int64_t K) {
-  int64_t tiles, bk;
-  variant_grid(variant, M, N, &tiles, &bk);
-  if (tiles <= 0 || tiles >= 256) return 1;
+  if (variant == GEMM_SKINNY || variant == GEMM_SPLITK || variant == GEMM_SIMT || variant == GEMM_TALL) return 1;
+  const int64_t tiles = ((M + 63) / 64) * ((N + 31) / 32);
+  if (tiles >= 256) return 1;
   int split = 1;
-  while (split < 1024 && tiles * split * 2 <= 1024 && K / (split * 2) >= 4 * bk) split *= 2;
+  while (tiles * split * 2 <= 512 && K / (split * 2) >= 512) split *= 2;
   return split;
 }
 
@@ -866,8 +713,8 @@ hipError_t launch_cgemm_ex(hipStream_t st, int precision, int64_t M, int64_t N, 
   if (rn.c && (!rn.a || !rn.b)) return hipErrorInvalidValue;
   if (M < 1 || N < 1 || K < 1 || batch < 1) return hipErrorInvalidValue;
   if (precision != P_FP32 && precision != P_BF16X3 && precision != P_FP16) return hipErrorInvalidValue;
-  const int v = (variant != GEMM_AUTO && cgemm_variant_fits(precision, M, N, K, variant))
-                    ? variant : cgemm_default_variant(precision, M, N, K);
+  const bool chosen = variant != GEMM_AUTO && cgemm_variant_fits(precision, M, N, K, variant);
+  int v = chosen ? variant : cgemm_default_variant(precision, M, N, K);
   if (rn.c) hipLaunchKernelGGL(renorm_reset, dim3(1), dim3(64), 0, st, rn.c);
   switch (v) {
     case GEMM_TALL:
@@ -894,20 +741,17 @@ hipError_t launch_cgemm_ex(hipStream_t st, int precision, int64_t M, int64_t N, 
   int split = scratch ? split_count(v, M, N, K) : 1;
   if (split > 1 && (size_t)split * (size_t)(batch * M * N) * sizeof(float2) > scratch_bytes) split = 1;
   hipError_t e;
-  switch (precision) {
-    case P_FP32:
-      e = launch_mfma<P_FP32>(st, v, M, N, K, A, B, C, batch, sa, sb, sc, amaxA, amaxB, rn, split, scratch);
-      break;
-    case P_BF16X3:
-      e = launch_mfma<P_BF16X3>(st, v, M, N, K, A, B, C, batch, sa, sb, sc, amaxA, amaxB, rn, split, scratch);
-      break;
-    default:
-      e = launch_mfma<P_FP16>(st, v, M, N, K, A, B, C, batch, sa, sb, sc, amaxA, amaxB, rn, split, scratch);
+  if (precision == P_FP32 || v == GEMM_F32) {
+    static const int tiles[] = {F32_AUTO, F32_128X64, F32_64X32, F32_32X32, F32_256X128};
+    e = launch_cgemm_f32(st, M, N, K, A, B, C, batch, sa, sb, sc, rn, &split, scratch, v == GEMM_F32 ? F32_AUTO : tiles[v]);
+  } else {
+    if (!chosen) v = cgemm_default_variant(precision, M, N, K, batch * split);
+    e = precision == P_BF16X3
+            ? launch_mfma<P_BF16X3>(st, v, M, N, K, A, B, C, batch, sa, sb, sc, amaxA, amaxB, rn, split, scratch)
+            : launch_mfma<P_FP16>(st, v, M, N, K, A, B, C, batch, sa, sb, sc, amaxA, amaxB, rn, split, scratch);
   }
   if (e != hipSuccess || split == 1) return e;
-  const int64_t total = batch * M * N;
-  const int64_t per_block = 256 / kReduceLanes;
-  const unsigned blocks = (unsigned)std::min<int64_t>((total + per_block - 1) / per_block, 16384);
+  const unsigned blocks = (unsigned)std::min<int64_t>((batch * M * N + kReduceOut - 1) / kReduceOut, 65536);
   hipLaunchKernelGGL(cgemm_split_reduce, dim3(blocks), dim3(256), 0, st, scratch, split, batch, M * N, N, sc, C, rn);
   return hipGetLastError();
 }

@@ -159,15 +159,19 @@ enum {
   GEMM_TILED_4X4 = 1,  // 256 threads, 128 x 64 complex block tile
   GEMM_TILED_2X2 = 2,  // 64 x 32
   GEMM_TILED_1X2 = 3,  // 32 x 32
-  GEMM_LARGE = 4,      // 512 threads, 256 x 128, double-buffered LDS (split-BF16 / FP16 only)
+  GEMM_LARGE = 4,      // 512 threads, 256 x 128, double-buffered LDS
   GEMM_SKINNY = 5,     // B in LDS, SIMT FP32 (N K <= 4096, K <= 64)
   GEMM_SPLITK = 6,     // one workgroup per output (M N <= 4096), SIMT FP32
   GEMM_SIMT = 7,       // one thread per output, SIMT FP32
   GEMM_TALL = 8,       // M large, N and K <= 64: B in LDS, A streamed into registers (HBM-bound)
-  GEMM_N_VARIANTS = 9
+  GEMM_F32 = 9,        // FP32 MFMA tiles for any shape (the tile follows the launch)
+  GEMM_N_VARIANTS = 10
 };
+// Tiles of the FP32 kernel (cgemm_f32.hip).
+enum { F32_AUTO = 0, F32_256X128, F32_128X64, F32_64X32, F32_32X32, F32_128X16, F32_128X8, F32_32X16 };
 bool cgemm_variant_fits(int precision, int64_t M, int64_t N, int64_t K, int variant);
-int cgemm_default_variant(int precision, int64_t M, int64_t N, int64_t K);
+// blocks_per_tile: workgroups that a launch makes per output tile (batch x K-chunks).
+int cgemm_default_variant(int precision, int64_t M, int64_t N, int64_t K, int64_t blocks_per_tile = 1);
 
 // Same, with optional operand max magnitudes for FP16 scaling (ignored when rn is on: then the
 // FP16 operands are scaled from rn.a / rn.b), optional renormalisation, and a kernel variant
@@ -176,6 +180,11 @@ hipError_t launch_cgemm_ex(hipStream_t st, int precision, int64_t M, int64_t N, 
                            const float2* B, float2* C, int64_t batch, int64_t sa, int64_t sb, int64_t sc,
                            const uint32_t* amaxA, const uint32_t* amaxB, const Renorm& rn = Renorm{},
                            int variant = GEMM_AUTO, float2* scratch = nullptr, size_t scratch_bytes = 0);
+// FP32 MFMA product of any shape (cgemm_f32.hip).  ta / tb: 0 if the operand lies [row][k], 1 if it lies
+// [k][row]; conj_b: conjugate B.  *split: K-chunks wanted, set to those used (partials in P).
+hipError_t launch_cgemm_f32(hipStream_t st, int64_t M, int64_t N, int64_t K, const float2* A, const float2* B,
+                            float2* C, int64_t batch, int64_t sa, int64_t sb, int64_t sc, const Renorm& rn, int* split,
+                            float2* P, int tile = F32_AUTO, int ta = 0, int tb = 0, int conj_b = 0);
 // Tall-skinny kernel (cgemm_tall.hip): powers of two, 8 <= N <= 64, 16 <= K <= 64.
 bool cgemm_tall_fits(int precision, int64_t M, int64_t N, int64_t K);
 hipError_t launch_cgemm_tall(hipStream_t st, int precision, int64_t M, int64_t N, int64_t K, const float2* A,

@@ -957,7 +957,7 @@ qf_status qf_plan_info_get(const qf_plan* p, qf_plan_info* out) {
     const int64_t M = (int64_t)1 << st.m_bits, N = (int64_t)1 << st.n_bits, K = (int64_t)1 << st.k_bits;
     const int v = st.presplit ? GEMM_LARGE : cgemm_default_variant(p->precision, M, N, K);
     if (v == GEMM_SKINNY || v == GEMM_SPLITK || v == GEMM_SIMT) continue;
-    out->mfma_flops_per_slice += st.flops * (p->precision == QF_BF16X3 ? 3.0 : 1.0);
+    out->mfma_flops_per_slice += st.flops * (p->precision == QF_BF16X3 && v != GEMM_F32 ? 3.0 : 1.0);
   }
   p->info_cache = *out;
   p->info_ready = true;
@@ -1696,7 +1696,7 @@ qf_status qf_permute(qf_ctx* c, const void* src, void* dst, int nbits, const int
 
 // Names of the GEMM kernel variants (autotune files, error messages).
 static const char* const kVariantName[GEMM_N_VARIANTS] = {"auto",  "tiled4x4", "tiled2x2", "tiled1x2", "large",
-                                                          "skinny", "splitk",   "simt",     "tall"};
+                                                          "skinny", "splitk",   "simt",     "tall",     "f32"};
 
 qf_status qf_cgemm(qf_ctx* c, int precision, int64_t M, int64_t N, int64_t K, const void* A, const void* B, void* C,
                    int64_t batch, int64_t sa, int64_t sb, int64_t sc) {
@@ -1707,7 +1707,7 @@ qf_status qf_cgemm_variant(qf_ctx* c, int precision, int variant, int64_t M, int
                            const void* B, void* C, int64_t batch, int64_t sa, int64_t sb, int64_t sc) {
   if (!c || !A || !B || !C || M < 1 || N < 1 || K < 1 || batch < 1 || precision < 0 || precision > 2)
     return fail(c, QF_ERR_ARG, "qf_cgemm: bad arguments");
-  if (variant < 0 || variant >= GEMM_N_VARIANTS) return fail(c, QF_ERR_ARG, "qf_cgemm_variant: unknown variant");
+  if (variant < 0 || variant > GEMM_TALL) return fail(c, QF_ERR_ARG, "qf_cgemm_variant: unknown variant");
   if (variant != GEMM_AUTO && !cgemm_variant_fits(precision, M, N, K, variant))
     return fail(c, QF_ERR_UNSUPPORTED, std::string("qf_cgemm_variant: ") + kVariantName[variant] +
                                            " does not fit this shape");
@@ -2024,6 +2024,7 @@ static std::vector<int> tune_candidates(int prec, int64_t M, int64_t N, int64_t 
   for (int i = 1; i < GEMM_N_VARIANTS; ++i) {
     if (!cgemm_variant_fits(prec, M, N, K, i)) continue;
     if (mfma && (i == GEMM_SIMT || i == GEMM_SPLITK)) continue;
+    if (mfma && i == GEMM_F32 && prec != QF_FP32) continue;
     if (big_grid && (i == GEMM_TILED_2X2 || i == GEMM_TILED_1X2)) continue;
     v.push_back(i);
   }

@@ -115,6 +115,35 @@ def test_cgemm_matches_numpy(ctx, precision, M, N, K):
     assert err <= TOL[precision], err
 
 
+# Sizes around the FP32 tiles' edges (256, 128, 64, 32 rows; 128, 64, 32, 16, 8 columns; 16 k), and long K cut
+# into chunks that do not divide it
+RAGGED_SHAPES = [(129, 65, 33), (31, 33, 17), (257, 129, 48), (300, 1, 50), (1, 300, 50), (130, 16, 49), (129, 17, 15),
+                 (2049, 7, 40), (1000, 600, 300), (4097, 129, 31), (100, 9, 5000), (33, 70, 2049), (1, 2, 9001),
+                 (1 << 15, 16, 256)]
+
+
+@pytest.mark.parametrize("precision", ["fp32", "bf16x3", "fp16"])
+@pytest.mark.parametrize("M,N,K", RAGGED_SHAPES)
+def test_cgemm_any_size_is_fp32_exact(split_ctx, precision, M, N, K):
+    """Sizes that are no multiples of a tile run on FP32 tiles in every precision: held to the FP32
+    bound of the whole-tile products."""
+    import torch
+    from paper_1905_00444_amd import cgemm
+    _say(f"cgemm ragged {precision} {M}x{N}x{K}")
+    rng = np.random.default_rng(M * 5 + N * 3 + K)
+    A = _rand_c64(rng, (M, K))
+    B = _rand_c64(rng, (N, K))
+    ref = A.astype(np.complex128) @ B.astype(np.complex128).T
+    bound = np.abs(A).astype(np.float64) @ np.abs(B).astype(np.float64).T
+    guard = torch.full((M * N + 64,), 7.0 + 0j, dtype=torch.complex64, device="cuda")
+    C = cgemm(split_ctx, torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda(), precision,
+              out=guard[:M * N].view(M, N))
+    torch.cuda.synchronize()
+    err = np.max(np.abs(C.cpu().numpy().astype(np.complex128) - ref) / bound)
+    assert err <= TOL["fp32"], err
+    assert bool((guard[M * N:] == 7.0).all())
+
+
 SPLIT_SHAPES = [(128, 64, 65536), (64, 32, 131072), (32, 32, 16384), (512, 512, 16384), (256, 128, 32768)]
 
 
