@@ -260,6 +260,18 @@ bool cgemm_presplit_fits(int64_t M, int64_t N, int64_t K, int precision) {
          N >= kPsBN && K >= bk && K + 64 <= kPsMaxLd;
 }
 
+// Whether a plan runs a step on this kernel rather than on the smaller tiles that split while they stage
+// (same bits).  One workgroup fills a CU, so with few tiles most CUs idle: measured (us, this kernel
+// against the best smaller tile, split-BF16) 256^3 (2 tiles): 31.3 / 8.2, 1024 x 256 x 256 (8): 31.8 / 8.7,
+// 1024^3 (32): 96 / 49, 2048 x 1024 x 1024 (64): 97 / 82, 2048^2 x 1024 (128): 105 / 126, 4096 x 2048 x
+// 1024 (256): 143 / 175.  Between 32 and 128 tiles the loss is small in plans whose other steps are larger,
+// and the step keeps handing its result over as split planes, which saves its consumer a pass; below, the
+// plans are small throughout.  A function of the shape alone, so that a batched plan and its one-chain form
+// cut K alike.
+bool cgemm_presplit_pays(int64_t M, int64_t N, int64_t K, int precision) {
+  return cgemm_presplit_fits(M, N, K, precision) && (M / kPsBM) * (N / kPsBN) >= 32;
+}
+
 // Split-BF16: A, B each a hi plane followed by a lo plane (rows x K bfloat16 pairs each,
 // consecutive rows lda (ldb) words apart, the lo plane rows * lda (rows * ldb) words after the hi
 // plane), batch strides in complex elements of one plane-pair (= rows * ld).  FP16: one plane of

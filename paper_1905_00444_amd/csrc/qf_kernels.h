@@ -145,6 +145,7 @@ hipError_t launch_chain_counter(hipStream_t st, int64_t* chain0, int64_t value, 
 // FP16 GEMM on operands scaled and converted by the permute (one plane); precision P_BF16X3 / P_FP16
 // (cgemm_common.h), 1 / 2 as qf_precision.
 bool cgemm_presplit_fits(int64_t M, int64_t N, int64_t K, int precision = 1);
+bool cgemm_presplit_pays(int64_t M, int64_t N, int64_t K, int precision);
 hipError_t launch_cgemm_presplit(hipStream_t st, int64_t M, int64_t N, int64_t K, const void* A, const void* B,
                                  float2* C, int64_t batch, int64_t sa, int64_t sb, int64_t sc,
                                  const Renorm& rn = Renorm{}, int64_t lda = 0, int64_t ldb = 0, int precision = 1);

@@ -664,7 +664,7 @@ qf_status qf_plan_create(qf_ctx* ctx, qf_circuit* circ, const qf_plan_desc* d, q
     // large steps run on operands that their permutes convert once: split into bfloat16 hi and lo
     // planes (split-BF16), or scaled to fp16 from the operand's renormalisation exponent (FP16)
     st.presplit = !p->backward && (p->precision == QF_BF16X3 || (p->precision == QF_FP16 && p->renorm)) &&
-                  cgemm_presplit_fits((int64_t)1 << xf, (int64_t)1 << yf, (int64_t)1 << K.size(), p->precision);
+                  cgemm_presplit_pays((int64_t)1 << xf, (int64_t)1 << yf, (int64_t)1 << K.size(), p->precision);
     if (st.presplit) {
       for (Operand* op : {&st.A, &st.B}) {
         if (!op->permute) p->permute_bytes += 16.0 * std::ldexp(1.0, op->nbits);
