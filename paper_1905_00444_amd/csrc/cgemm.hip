@@ -762,16 +762,30 @@ hipError_t launch_cgemm(hipStream_t st, int precision, int64_t M, int64_t N, int
 }
 
 // Max |re|, |im| of a complex64 array into *amax (as float bits; non-negative floats order
-// like their bit patterns).  *amax must be zero before the launch.
+// like their bit patterns).  *amax must be zero before the launch.  One atomic per workgroup and at most
+// 512 workgroups: atomics on one address are served about 10 ns apart, and one per wave over 2048
+// workgroups cost 50 us for a 32 KiB operand.  Four 8-byte loads in flight per lane keep a large array
+// at the card's read rate.
+constexpr int kAmaxBlocks = 512, kAmaxUnroll = 4;
+
 __global__ void __launch_bounds__(256)
 amax_kernel(const float2* __restrict__ x, int64_t n, uint32_t* amax) {
+  __shared__ float red[4];
   float m = 0.f;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    const float2 v = x[i];
-    m = fmaxf(m, fmaxf(fabsf(v.x), fabsf(v.y)));
+  const int64_t step = (int64_t)gridDim.x * blockDim.x;
+  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  for (; i + (kAmaxUnroll - 1) * step < n; i += kAmaxUnroll * step) {
+    float2 v[kAmaxUnroll];
+#pragma unroll
+    for (int u = 0; u < kAmaxUnroll; ++u) v[u] = x[i + u * step];
+#pragma unroll
+    for (int u = 0; u < kAmaxUnroll; ++u) m = fmaxf(m, cmax(v[u]));
   }
+  for (; i < n; i += step) m = fmaxf(m, cmax(x[i]));
   for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
-  if ((threadIdx.x & 63) == 0) atomicMax(amax, __float_as_uint(m));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+  __syncthreads();
+  if (threadIdx.x == 0) atomicMax(amax, __float_as_uint(fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]))));
 }
 
 __global__ void zero_u32(uint32_t* p, int n) {
@@ -781,8 +795,7 @@ __global__ void zero_u32(uint32_t* p, int n) {
 
 hipError_t launch_amax(hipStream_t st, const float2* x, int64_t n, uint32_t* amax) {
   hipLaunchKernelGGL(zero_u32, dim3(1), dim3(64), 0, st, amax, 1);
-  unsigned blocks = (unsigned)((n + 255) / 256);
-  if (blocks > 2048) blocks = 2048;
+  const unsigned blocks = (unsigned)std::min<int64_t>((n + 1023) / 1024, kAmaxBlocks);
   hipLaunchKernelGGL(amax_kernel, dim3(blocks), dim3(256), 0, st, x, n, amax);
   return hipGetLastError();
 }
