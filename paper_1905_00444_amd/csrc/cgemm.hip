@@ -276,27 +276,22 @@ cgemm_mfma(int64_t M, int64_t N, int64_t K, const float2* __restrict__ A, const 
     __syncthreads();
   }
 
-  // Epilogue: lane holds real column (n, q = l16 & 1) for rows 4*lg .. 4*lg+3 of each tile.
-  // Exchange with the partner lane (l ^ 1) so each lane owns two complex results.
-  const int q = l16 & 1;
+  const uint32_t seen = partial ? 0u : seen_amax(rn);
   float mx = 0.f;
+  Renorm om = rn;
+  if (partial) om.om_nh = 0;
+  const int64_t col0 = tn * BN + wc + 2 * (l16 >> 2);
 #pragma unroll
-  for (int i = 0; i < WTM; ++i)
+  for (int i = 0; i < WTM; ++i) {
+    float2* c = C + c_row(om, tm * BM + wr + 16 * i + 4 * lg + (l16 & 3), N);
 #pragma unroll
     for (int j = 0; j < WTN; ++j) {
-      const f4 v = acc[i][j] * unscale;
-      const float s0 = q ? v[0] : v[2], s1 = q ? v[1] : v[3];
-      const float r0 = __shfl_xor(s0, 1), r1 = __shfl_xor(s1, 1);
-      const int64_t row = tm * BM + wr + 16 * i + 4 * lg + (q ? 2 : 0);
-      const int64_t col = tn * BN + wc + 8 * j + (l16 >> 1);
-      float2 o0, o1;
-      if (q) { o0 = make_float2(r0, v[2]); o1 = make_float2(r1, v[3]); }
-      else { o0 = make_float2(v[0], r0); o1 = make_float2(v[1], r1); }
-      C[partial ? row * N + col : c_index(rn, row, col, N)] = o0;
-      C[partial ? (row + 1) * N + col : c_index(rn, row + 1, col, N)] = o1;
-      mx = fmaxf(mx, fmaxf(cmax(o0), cmax(o1)));
+      const f4 o = quad_transpose(acc[i][j] * unscale);
+      *reinterpret_cast<f4*>(c + c_col(om, col0 + 8 * j)) = o;
+      mx = fmaxf(mx, cmax4(o));
     }
-  if (rn.c && !partial) record_amax(rn.c, mx);
+  }
+  if (rn.c && !partial) raise_amax<kThreads / 64>(rn.c, mx, seen, reinterpret_cast<float*>(lds));
 }
 
 // Large shapes, BF16-family products: 512 threads = 8 waves as 4 (M) x 2 (N); a wave owns
@@ -467,24 +462,22 @@ cgemm_v2(int64_t M, int64_t N, int64_t K, const float2* __restrict__ A, const fl
     __syncthreads();
   }
 
+  const uint32_t seen = partial ? 0u : seen_amax(rn);
   float mx = 0.f;
+  Renorm om = rn;
+  if (partial) om.om_nh = 0;
+  const int64_t col0 = tn * kV2BN + wc + 2 * (l16 >> 2);
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < 4; ++i) {
+    float2* c = C + c_row(om, tm * kV2BM + wr + 16 * i + 4 * lg + (l16 & 3), N);
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-      const f4 v = acc[i][j] * unscale;
-      const float s0 = q ? v[0] : v[2], s1 = q ? v[1] : v[3];
-      const float r0 = __shfl_xor(s0, 1), r1 = __shfl_xor(s1, 1);
-      const int64_t row = tm * kV2BM + wr + 16 * i + 4 * lg + (q ? 2 : 0);
-      const int64_t col = tn * kV2BN + wc + 8 * j + (l16 >> 1);
-      float2 o0, o1;
-      if (q) { o0 = make_float2(r0, v[2]); o1 = make_float2(r1, v[3]); }
-      else { o0 = make_float2(v[0], r0); o1 = make_float2(v[1], r1); }
-      C[partial ? row * N + col : c_index(rn, row, col, N)] = o0;
-      C[partial ? (row + 1) * N + col : c_index(rn, row + 1, col, N)] = o1;
-      mx = fmaxf(mx, fmaxf(cmax(o0), cmax(o1)));
+      const f4 o = quad_transpose(acc[i][j] * unscale);
+      *reinterpret_cast<f4*>(c + c_col(om, col0 + 8 * j)) = o;
+      mx = fmaxf(mx, cmax4(o));
     }
-  if (rn.c && !partial) record_amax(rn.c, mx);
+  }
+  if (rn.c && !partial) raise_amax<kV2Threads / 64>(rn.c, mx, seen, reinterpret_cast<float*>(lds));
 }
 
 // Small or thin shapes: one thread per output element, FP32 complex FMA over K.
@@ -573,12 +566,16 @@ cgemm_skinny(int64_t M, int64_t N, int64_t K, const float2* __restrict__ A, cons
   if (rn.c) record_amax(rn.c, mx);
 }
 
-// Few outputs, long K (e.g. the last contraction of two halves into a scalar): one workgroup
-// per output element, threads stride over K, then a workgroup reduction.
-__global__ void __launch_bounds__(256)
+// Few outputs, long K (e.g. the last contraction of two halves into a scalar): one workgroup per output
+// element, threads stride over K with eight loads of each operand in flight, then a workgroup
+// reduction.  Bound by latency (one workgroup) or, over many outputs, by reading the operands.
+constexpr int kDotUnroll = 8;
+
+template <int NTH>
+__global__ void __launch_bounds__(NTH)
 cgemm_splitk(int64_t M, int64_t N, int64_t K, const float2* __restrict__ A, const float2* __restrict__ B,
              float2* __restrict__ C, int64_t sa, int64_t sb, int64_t sc, Renorm rn) {
-  __shared__ float red[2][4];
+  __shared__ float red[2][NTH / 64];
   float scale_a, scale_b, unscale;
   renorm_begin<P_FP32>(rn, nullptr, nullptr, scale_a, scale_b, unscale);
   const int64_t batch = blockIdx.z;
@@ -587,13 +584,24 @@ cgemm_splitk(int64_t M, int64_t N, int64_t K, const float2* __restrict__ A, cons
   const float2* a = A + batch * sa + m * K;
   const float2* b = B + batch * sb + n * K;
   float cr = 0.f, ci = 0.f;
-  for (int64_t k = threadIdx.x; k < K; k += 256) {
-    const float2 x = a[k], y = b[k];
+  auto add = [&](float2 x, float2 y) {
     cr = fmaf(x.x, y.x, cr);
     cr = fmaf(-x.y, y.y, cr);
     ci = fmaf(x.x, y.y, ci);
     ci = fmaf(x.y, y.x, ci);
+  };
+  int64_t k = threadIdx.x;
+  for (; k + (kDotUnroll - 1) * NTH < K; k += kDotUnroll * NTH) {
+    float2 x[kDotUnroll], y[kDotUnroll];
+#pragma unroll
+    for (int u = 0; u < kDotUnroll; ++u) {
+      x[u] = a[k + u * NTH];
+      y[u] = b[k + u * NTH];
+    }
+#pragma unroll
+    for (int u = 0; u < kDotUnroll; ++u) add(x[u], y[u]);
   }
+  for (; k < K; k += NTH) add(a[k], b[k]);
   for (int off = 32; off > 0; off >>= 1) {
     cr += __shfl_xor(cr, off);
     ci += __shfl_xor(ci, off);
@@ -602,8 +610,11 @@ cgemm_splitk(int64_t M, int64_t N, int64_t K, const float2* __restrict__ A, cons
   if ((threadIdx.x & 63) == 0) { red[0][w] = cr; red[1][w] = ci; }
   __syncthreads();
   if (threadIdx.x == 0) {
-    const float r = (red[0][0] + red[0][1] + red[0][2] + red[0][3]) * unscale;
-    const float i = (red[1][0] + red[1][1] + red[1][2] + red[1][3]) * unscale;
+    float r = 0.f, i = 0.f;
+#pragma unroll
+    for (int u = 0; u < NTH / 64; ++u) { r += red[0][u]; i += red[1][u]; }
+    r *= unscale;
+    i *= unscale;
     C[batch * sc + c_index(rn, m, n, N)] = make_float2(r, i);
     if (rn.c) atomicMax(&rn.c->amax, __float_as_uint(fmaxf(fabsf(r), fabsf(i))));
   }
@@ -656,8 +667,8 @@ int cgemm_default_variant(int precision, int64_t M, int64_t N, int64_t K, int64_
   // K = 16 is half a K-tile of the smaller 16-bit tiles
   if (precision != P_FP32 && cgemm_variant_fits(precision, M, N, K, GEMM_LARGE) && (M / kV2BM) * (N / kV2BN) >= 128)
     return GEMM_LARGE;
-  // a few long dot products: a workgroup each (from K = 4096 the tiles' split K spreads one further)
-  if (M * N <= 64 && K >= 32 && K < 4096) return GEMM_SPLITK;
+  // a few dot products: a workgroup each; very long ones are spread further by the tiles' split K
+  if (M * N <= 64 && K >= 32 && K <= (1 << 17)) return GEMM_SPLITK;
   // short K: the FP32 tiles would multiply zeros
   if (K < 32 && cgemm_variant_fits(precision, M, N, K, GEMM_SKINNY)) return GEMM_SKINNY;
   if (K < 8 || M * N * K < 4096) return GEMM_SIMT;
@@ -727,8 +738,16 @@ hipError_t launch_cgemm_ex(hipStream_t st, int precision, int64_t M, int64_t N, 
       return hipGetLastError();
     }
     case GEMM_SPLITK:
-      hipLaunchKernelGGL(cgemm_splitk, dim3((unsigned)(M * N), 1, (unsigned)batch), dim3(256), 0, st, M, N, K, A, B, C,
-                         sa, sb, sc, rn);
+      // a wave for the shortest sums, 16 waves from K = 4096 on (one output, K = 65536: 127 us with four)
+      if (K < 256)
+        hipLaunchKernelGGL(cgemm_splitk<64>, dim3((unsigned)(M * N), 1, (unsigned)batch), dim3(64), 0, st, M, N, K, A, B,
+                           C, sa, sb, sc, rn);
+      else if (K < 4096)
+        hipLaunchKernelGGL(cgemm_splitk<256>, dim3((unsigned)(M * N), 1, (unsigned)batch), dim3(256), 0, st, M, N, K, A,
+                           B, C, sa, sb, sc, rn);
+      else
+        hipLaunchKernelGGL(cgemm_splitk<1024>, dim3((unsigned)(M * N), 1, (unsigned)batch), dim3(1024), 0, st, M, N, K,
+                           A, B, C, sa, sb, sc, rn);
       return hipGetLastError();
     case GEMM_SIMT: {
       const unsigned blocks = (unsigned)std::min<int64_t>((M * N + 255) / 256, 65536);
@@ -742,7 +761,7 @@ hipError_t launch_cgemm_ex(hipStream_t st, int precision, int64_t M, int64_t N, 
   if (split > 1 && (size_t)split * (size_t)(batch * M * N) * sizeof(float2) > scratch_bytes) split = 1;
   hipError_t e;
   if (precision == P_FP32 || v == GEMM_F32) {
-    static const int tiles[] = {F32_AUTO, F32_128X64, F32_64X32, F32_32X32, F32_256X128};
+    static const int tiles[] = {F32_AUTO, F32_64X64, F32_64X32, F32_32X32, F32_64X64};
     e = launch_cgemm_f32(st, M, N, K, A, B, C, batch, sa, sb, sc, rn, &split, scratch, v == GEMM_F32 ? F32_AUTO : tiles[v]);
   } else {
     if (!chosen) v = cgemm_default_variant(precision, M, N, K, batch * split);

@@ -35,18 +35,53 @@ __device__ __forceinline__ int64_t c_index(const Renorm& rn, int64_t m, int64_t 
   return ((((m >> q) << (nh + q)) | ((n >> nl) << q) | mlo) << nl) | nlo;
 }
 
-// Store of result element (m, n): complex64 at c_index, or its split-BF16 planes (Renorm::so_*).
-__device__ __forceinline__ void store_c(float2* C, const Renorm& rn, int64_t m, int64_t n, int64_t N, float2 o) {
-  const int64_t j = c_index(rn, m, n, N);
+// The same index as a sum: c_index(m, n) = c_row(m) + c_col(n), so a kernel's epilogue computes the
+// two parts once per row and column of a lane.
+__device__ __forceinline__ int64_t c_row(const Renorm& rn, int64_t m, int64_t N) {
+  if (rn.om_nh == 0) return m * N;
+  const int64_t mlo = m & (((int64_t)1 << rn.om_q) - 1);
+  return (((m >> rn.om_q) << (rn.om_nh + rn.om_q)) | mlo) << rn.om_nl;
+}
+__device__ __forceinline__ int64_t c_col(const Renorm& rn, int64_t n) {
+  if (rn.om_nh == 0) return n;
+  return ((n >> rn.om_nl) << (rn.om_q + rn.om_nl)) | (n & (((int64_t)1 << rn.om_nl) - 1));
+}
+
+// 4 x 4 transposition among the lanes of a quad: an MFMA tile leaves lane (l16, lg) with rows
+// 4 lg .. 4 lg + 3 of real column l16; afterwards it has row 4 lg + (l16 & 3) of the real columns
+// 4 (l16 / 4) .. + 3, which are two neighbouring complex results, one 16-byte store.  The exchanges are
+// DPP moves (no LDS traffic), and one store instead of two halves the epilogue's address arithmetic:
+// on 2^21 x 64 x 64 the former epilogue's 64-bit shifts per element took as long as a third of the MFMAs.
+template <int CTRL>
+__device__ __forceinline__ float quad_move(float v) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ f4 quad_transpose(f4 v) {
+  constexpr int kXor1 = 0xB1, kXor2 = 0x4E;  // quad_perm [1,0,3,2] and [2,3,0,1]
+  const bool odd = threadIdx.x & 1, upper = threadIdx.x & 2;
+  const float a = quad_move<kXor1>(odd ? v[0] : v[1]), b = quad_move<kXor1>(odd ? v[2] : v[3]);
+  const f4 w = odd ? (f4){a, v[1], b, v[3]} : (f4){v[0], a, v[2], b};
+  const float c = quad_move<kXor2>(upper ? w[0] : w[2]), d = quad_move<kXor2>(upper ? w[1] : w[3]);
+  return upper ? (f4){c, d, w[2], w[3]} : (f4){w[0], w[1], c, d};
+}
+__device__ __forceinline__ float cmax4(f4 v) {
+  return fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3])));
+}
+
+// Store of the result pair at index j (even) of the mapped order: complex64, or its split-BF16 planes
+// (Renorm::so_*; so_kbits >= 4, so a pair never straddles a row of the planes).
+__device__ __forceinline__ void store_c2(float2* C, const Renorm& rn, int64_t j, f4 o) {
   if (rn.so_ld == 0) {
-    C[j] = o;
+    *reinterpret_cast<f4*>(C + j) = o;
     return;
   }
   uint32_t* w = reinterpret_cast<uint32_t*>(C);
   const int64_t idx = (j >> rn.so_kbits) * rn.so_ld + (j & (((int64_t)1 << rn.so_kbits) - 1));
-  const uint32_t hi = pack_bf16x2(o.x, o.y);
-  w[idx] = hi;
-  w[rn.so_plane + idx] = pack_bf16x2(o.x - bf16_lo_to_f32(hi), o.y - bf16_hi_to_f32(hi));
+  const uint32_t h0 = pack_bf16x2(o[0], o[1]), h1 = pack_bf16x2(o[2], o[3]);
+  *reinterpret_cast<uint2*>(w + idx) = make_uint2(h0, h1);
+  *reinterpret_cast<uint2*>(w + rn.so_plane + idx) =
+      make_uint2(pack_bf16x2(o[0] - bf16_lo_to_f32(h0), o[1] - bf16_hi_to_f32(h0)),
+                 pack_bf16x2(o[2] - bf16_lo_to_f32(h1), o[3] - bf16_hi_to_f32(h1)));
 }
 
 // Scale exponent that brings max|x| to about 2^14 (FP16 max is 65504 ~ 2^16).
@@ -96,13 +131,35 @@ __device__ __forceinline__ void renorm_begin(const Renorm& rn, const uint32_t* a
 
 __device__ __forceinline__ float cmax(float2 v) { return fmaxf(fabsf(v.x), fabsf(v.y)); }
 
-// Wave-wide max of m, raised into c->amax (every lane of the wave must call).  All waves of a
-// launch target one address, and atomics on one address are serialised (about 10 ns each: two
-// million waves cost 20 ms), so a wave first reads the current value from L2 and issues the
-// atomic only if it holds a larger one.  amax only grows during the launch, so the value read is
-// a lower bound of the final one and skipping is exact.
-__device__ __forceinline__ void record_amax(NodeScale* c, float m) {
+// Raises c->amax to the largest m of the launch.  All workgroups target one address, and atomics on one
+// address are served about 10 ns apart (two million waves cost 20 ms), so a workgroup first compares with
+// a value read before and issues its atomic only if it holds a larger one: amax only grows during the
+// launch, so any value read is a lower bound of the final one and skipping is exact.  seen_amax is called
+// between the main loop and the epilogue, whose stores hide the read; a read before the main loop is
+// too old (most workgroups then hold more: 2^21 x 8 x 64 took 308 us instead of 240).
+__device__ __forceinline__ uint32_t seen_amax(const Renorm& rn) {
+  return rn.c ? __hip_atomic_load(&rn.c->amax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+}
+__device__ __forceinline__ float wave_max(float m) {
   for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
+  return m;
+}
+// One atomic per workgroup of WAVES waves; red: LDS that no wave reads any more (every thread calls).
+template <int WAVES>
+__device__ __forceinline__ void raise_amax(NodeScale* c, float m, uint32_t seen, float* red) {
+  m = wave_max(m);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    float t = red[0];
+#pragma unroll
+    for (int w = 1; w < WAVES; ++w) t = fmaxf(t, red[w]);
+    if (__float_as_uint(t) > seen) atomicMax(&c->amax, __float_as_uint(t));
+  }
+}
+// One per wave, read and compared at the end (kernels whose load ring must stay alone in flight).
+__device__ __forceinline__ void record_amax(NodeScale* c, float m) {
+  m = wave_max(m);
   if ((threadIdx.x & 63) == 0) {
     const uint32_t v = __float_as_uint(m);
     if (v > __hip_atomic_load(&c->amax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(&c->amax, v);

@@ -1,23 +1,34 @@
 // FP32 complex GEMM on MFMA for every shape, C[m][n] = sum_k A(m, k) B(n, k) (paper Sec. III-E, the
 // "G" of transpose-GEMM-transpose; cgemm.hip describes the real embedding and the renormalisation).
 //
-// One kernel template covers the 256 x 128 tile of the large contractions down to 32 x 16 and 128 x 8
-// tiles for thin products.  v_mfma_f32_16x16x4_f32 takes 32 cycles for 2048 flop, so a wave needs one
-// 4-byte LDS operand read per 32 MFMA-cycles and operand layout is free: LDS tiles are [row][k] with
-// rows of 16 complex plus 8 bytes (34 dwords, 2 mod 32), which lands the 16 rows x 2 dwords of an
-// operand read in distinct banks, and either operand may lie in HBM with k or with its row index
-// contiguous (the transposition happens in the LDS store).  Two LDS stages, operands fetched two K-tiles
-// ahead into registers, one barrier per K-tile of 16 complex.
+// Bound by the matrix cores (v_mfma_f32_16x16x4_f32: 32 cycles for 2048 flop), or by HBM where N and K are
+// short.  Measured counters say that VALU instructions take their cycles from FP32 MFMAs (busy cycles of
+// the two add up to the time), so the layout leaves the loop next to none:
+//   * 16 complex columns take two MFMA tiles, one that multiplies (br, -bi) and gives the real parts, one
+//     that multiplies (bi, br) and gives the imaginary parts.  Both read the same registers of B, the only
+//     arithmetic is the sign of bi, and a lane ends up with whole complex results: an epilogue without
+//     exchanges whose stores are full 128-byte lines.
+//   * The sum over k may run in any order, so MFMA s of a K-step of 16 complex takes in lane group lg the
+//     real k = 16 (s / 4) + 4 lg + s % 4: a lane's operands of four MFMAs are 16 contiguous bytes of its row,
+//     and the four lane groups read 64 contiguous bytes of each row, in LDS or HBM.
 //
-// Every accumulator receives its products in the order of k, four reals (two complex) per MFMA,
-// whatever the tile: a result does not depend on the tile that a launch picks, so the choice may
-// follow the batch.  K is cut into chunks (gridDim.y > 1) by the shape alone.
-//
-// Measured (whole passes, MI355X): 1500 x 700 x 300 1.27 ms as one thread per output, 42 us here; the
-// 256^3 products of a 4 x 4 circuit in launches of 64 chains 332 us (two 256 x 128 tiles, K split in four)
-// against 60 us on 128 x 64 tiles; 2^20 x 16 x 256 4.7 ms as one thread per output, 0.5 ms on 128 x 16.
+// Tiles are staged in LDS, [row][k] with rows of 16 complex padded to 36 dwords (the 16-byte reads of 8
+// rows cover all banks once); either operand may lie in HBM with k or with its row index contiguous.  Two
+// LDS stages, operands fetched two K-tiles ahead, one barrier per K-tile.  Waves that wait at a barrier, for
+// LDS or to issue a load issue no MFMA, so many small workgroups that run apart beat few large ones:
+// 8192^3 runs at 140 TFLOP/s on 64 x 32 tiles (five workgroups per CU), 141 on 64 x 64 (four), 135 on
+// 128 x 64 (two) and 137 on 256 x 128 (one).  Loading operands straight into MFMA registers, without LDS or
+// barriers, gave 104 to 135.
 //
 // EDGE instances take any M, N and K: rows and columns past the end read as zeros and are not stored.
+//
+// Every accumulator receives its products in the same order in all tiles: a result does not depend on the
+// tile that a launch picks, so the choice may follow the batch.  K is cut into chunks (gridDim.y > 1) by
+// the shape alone.
+//
+// Measured (whole passes, MI355X): 1500 x 700 x 300 1.27 ms as one thread per output, 42 us here; the
+// 256^3 products of a 4 x 4 circuit in launches of 64 chains 331 us (two 256 x 128 tiles, K split in four)
+// against 80 us in one pass over K; four slices of the 7x7 (1+32+1) circuit 442 ms, 388 ms here.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <algorithm>
@@ -26,7 +37,7 @@
 namespace qf {
 
 constexpr int kFBK = 16;       // complex k per K-tile
-constexpr int kFRow = 34;      // dwords per LDS row
+constexpr int kFRow = 36;      // dwords per LDS row
 
 struct F32Args {
   int64_t M, N, K;
@@ -34,10 +45,9 @@ struct F32Args {
   const float2* B;
   float2* C;
   int64_t lda, ldb;      // elements between rows (k contiguous) or between k's (row index contiguous)
-  int64_t sa, sb, sc;    // batch strides
+  int64_t batch, sa, sb, sc;  // batch strides
   int64_t kc;            // k per chunk
   float2* P;             // partial tiles [chunk][batch][M][N] when gridDim.y > 1
-  int conj_b;
   Renorm rn;
 };
 
@@ -91,57 +101,122 @@ struct F32Loader {
     for (int i = 0; i < per; ++i) {
       if (partial && (int)threadIdx.x + i * NTH >= pairs) continue;
       float* d = lds + row[i] * kFRow + 2 * k[i];
-      *reinterpret_cast<float2*>(d) = make_float2(r[i].x, r[i].y);
-      *reinterpret_cast<float2*>(d + (T == 0 ? 2 : kFRow)) = make_float2(r[i].z, r[i].w);
+      if constexpr (T == 0) {
+        *reinterpret_cast<float4*>(d) = r[i];
+      } else {
+        *reinterpret_cast<float2*>(d) = make_float2(r[i].x, r[i].y);
+        *reinterpret_cast<float2*>(d + kFRow) = make_float2(r[i].z, r[i].w);
+      }
     }
   }
 };
 
+// Accumulators of 16 rows x 16 complex columns: element r of lane (l16, lg) is row 4 r + lg of column l16
+// (MFMA row 4 lg + r: A's rows are read in that order), so one store instruction writes four neighbouring
+// rows, which under an output map are contiguous memory.
+struct F32Acc { f4 re, im; };
+
+template <int TM, int TN>
+__device__ __forceinline__ void f32_zero(F32Acc (&acc)[TM][TN]) {
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j].re = acc[i][j].im = (f4){0.f, 0.f, 0.f, 0.f};
+}
+
+// The products of half a K-step: a[i] and b[j] hold this lane's 16 bytes (2 complex) of row / column l16.
+template <int TM, int TN, bool CONJ>
+__device__ __forceinline__ void f32_multiply(const f4 (&a)[TM], const f4 (&b)[TN], F32Acc (&acc)[TM][TN]) {
+#pragma unroll
+  for (int j = 0; j < TN; ++j)
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      // real row s & 1 of [[br, bi], [-bi, br]] (conjugated: [[br, -bi], [bi, br]])
+      const float own = b[j][s], other = b[j][s ^ 1];
+      const float p = ((s & 1) && !CONJ) ? -own : own;
+      const float q = (!(s & 1) && CONJ) ? -other : other;
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+        acc[i][j].re = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][s], p, acc[i][j].re, 0, 0, 0);
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+        acc[i][j].im = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][s], q, acc[i][j].im, 0, 0, 0);
+    }
+}
+
+// Stores a wave's 16 TM x 16 TN results whose first is (m, n), returns the largest magnitude.  c_row and
+// c_col add over disjoint bits of their index (and m N over sums), so a lane's own part is computed once
+// and the rest is uniform.
+template <int TM, int TN, bool EDGE>
+__device__ __forceinline__ float f32_store(float2* C, const Renorm& rn, int64_t m, int64_t n, int64_t M, int64_t N,
+                                           float unscale, const F32Acc (&acc)[TM][TN]) {
+  const int lane = threadIdx.x & 63, l16 = lane & 15, lg = lane >> 4;
+  float2* own = C + (c_row(rn, lg, N) + c_col(rn, l16));
+  float mx = 0.f;
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        const float2 o = make_float2(acc[i][j].re[r] * unscale, acc[i][j].im[r] * unscale);
+        const int64_t at = c_row(rn, m + 16 * i, N) + c_row(rn, 4 * r, N) + c_col(rn, n + 16 * j);
+        if (!EDGE || (m + 16 * i + 4 * r + lg < M && n + 16 * j + l16 < N)) own[at] = o;
+        mx = fmaxf(mx, cmax(o));  // zeros past the edge
+      }
+  return mx;
+}
+
+struct F32Place { int64_t m0, n0, batch; };
+
+// Tile id of a launch (batch-major): consecutive tiles go to one XCD (8 XCDs, dealt round-robin) and are
+// rasterised in groups of row tiles.
+__device__ __forceinline__ F32Place f32_place(int64_t id, int64_t tiles_m, int64_t tiles_n, int64_t total, int BM,
+                                              int BN) {
+  const int64_t ntiles = tiles_m * tiles_n;
+  if ((total & 7) == 0) id = (id & 7) * (total >> 3) + (id >> 3);
+  F32Place p;
+  p.batch = id / ntiles;
+  const int64_t bid = id - p.batch * ntiles;
+  const int64_t group = 8;
+  const int64_t per_group = group * tiles_n;
+  const int64_t first_m = bid / per_group * group;
+  const int64_t gsize = (tiles_m - first_m) < group ? (tiles_m - first_m) : group;
+  p.m0 = (first_m + (bid % per_group) % gsize) * BM;
+  p.n0 = (bid % per_group) / gsize * BN;
+  return p;
+}
+
 template <int WM, int WN, int TM, int TN>
 struct F32Tile {
-  static constexpr int threads = 64 * WM * WN, BM = 16 * WM * TM, BN = 8 * WN * TN;
+  static constexpr int threads = 64 * WM * WN, BM = 16 * WM * TM, BN = 16 * WN * TN;
   static constexpr int stage = (BM + BN) * kFRow;  // dwords
 };
 
-template <int WM, int WN, int TM, int TN, int TA, int TB, bool EDGE>
+template <int WM, int WN, int TM, int TN, int TA, int TB, bool CONJ, bool EDGE>
 __global__ void __launch_bounds__(64 * WM * WN)
 cgemm_f32(F32Args g) {
   using Tile = F32Tile<WM, WN, TM, TN>;
   constexpr int BM = Tile::BM, BN = Tile::BN, NTH = Tile::threads;
   __shared__ __attribute__((aligned(16))) float lds[2 * Tile::stage];
 
-  // consecutive tiles on one XCD (8 XCDs, dealt round-robin), rasterised in groups of row tiles
   const int64_t tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
-  const int64_t ntiles = tiles_m * tiles_n;
-  int64_t bid = blockIdx.x;
-  if ((ntiles & 7) == 0) bid = (bid & 7) * (ntiles >> 3) + (bid >> 3);
-  const int64_t group = BM >= 256 ? 4 : 8;
-  const int64_t per_group = group * tiles_n;
-  const int64_t first_m = bid / per_group * group;
-  const int64_t gsize = (tiles_m - first_m) < group ? (tiles_m - first_m) : group;
-  const int64_t m0 = (first_m + (bid % per_group) % gsize) * BM;
-  const int64_t n0 = (bid % per_group) / gsize * BN;
-
-  const int64_t batch = blockIdx.z;
+  const F32Place at = f32_place(blockIdx.x, tiles_m, tiles_n, tiles_m * tiles_n * g.batch, BM, BN);
+  const int64_t m0 = at.m0, n0 = at.n0, batch = at.batch;
   const bool partial = gridDim.y > 1;
   const int64_t k0 = blockIdx.y * g.kc;
   const int64_t klen = EDGE ? (g.K - k0 < g.kc ? g.K - k0 : g.kc) : g.kc;
-  float2* C = partial ? g.P + ((int64_t)blockIdx.y * gridDim.z + batch) * g.M * g.N : g.C + batch * g.sc;
+  float2* C = partial ? g.P + ((int64_t)blockIdx.y * g.batch + batch) * g.M * g.N : g.C + batch * g.sc;
 
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wr = (wave / WN) * (16 * TM), wc = (wave % WN) * (8 * TN);
-  const int l16 = lane & 15, lg = lane >> 4, q = l16 & 1;
-  // A: dword 4s + lg of its row.  B: entry (part, q) of [[br, bi], [-bi, br]], part = lg & 1: chosen by
-  // address, the sign flipped where the entry is -bi (or, conjugated, where it is bi)
-  const int b_word = 2 * (lg >> 1) + ((lg & 1) ^ q);
-  const int part = lg & 1;
-  const uint32_t b_flip = (part != q && (g.conj_b ? q == 1 : q == 0)) ? 0x80000000u : 0u;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wr = (wave / WN) * (16 * TM), wc = (wave % WN) * (16 * TN);
+  const int l16 = lane & 15, lg = lane >> 4;
 
   F32Loader<BM, NTH, TA, EDGE> la;
   F32Loader<BN, NTH, TB, EDGE> lb;
   la.init(g.A + batch * g.sa + (TA == 0 ? m0 * g.lda : m0), g.lda, k0);
   lb.init(g.B + batch * g.sb + (TB == 0 ? n0 * g.ldb : n0), g.ldb, k0);
-  const int64_t ml = g.M - m0, nl = g.N - n0;
+  const int64_t ml = g.M - m0, nl = g.N - n0;  // rows and columns that exist from the tile's first on
 
   float unscale = 1.f;
   if (!partial) {
@@ -149,11 +224,8 @@ cgemm_f32(F32Args g) {
     renorm_begin<P_FP32>(g.rn, nullptr, nullptr, s0, s1, unscale);
   }
 
-  f4 acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j) acc[i][j] = (f4){0.f, 0.f, 0.f, 0.f};
+  F32Acc acc[TM][TN];
+  f32_zero(acc);
 
   const int nk = (int)((klen + kFBK - 1) / kFBK);
   auto fetch = [&](int t) {
@@ -170,87 +242,66 @@ cgemm_f32(F32Args g) {
   if (nk > 1) fetch(1);
   __syncthreads();
   for (int t = 0; t < nk; ++t) {
-    const float* LA = lds + (t & 1) * Tile::stage + (wr + l16) * kFRow + lg;
-    const float* LB = lds + (t & 1) * Tile::stage + (BM + wc + (l16 >> 1)) * kFRow + b_word;
-#pragma unroll 2
-    for (int s = 0; s < kFBK / 2; ++s) {
-      float a[TM];
+    const float* LA = lds + (t & 1) * Tile::stage + (wr + 4 * (l16 & 3) + (l16 >> 2)) * kFRow + 4 * lg;
+    const float* LB = lds + (t & 1) * Tile::stage + (BM + wc + l16) * kFRow + 4 * lg;
+    f4 a[2][TM], b[2][TN];
+    auto read = [&](int h) {
 #pragma unroll
-      for (int i = 0; i < TM; ++i) a[i] = LA[16 * i * kFRow + 4 * s];
+      for (int i = 0; i < TM; ++i) a[h][i] = *reinterpret_cast<const f4*>(LA + 16 * i * kFRow + 16 * h);
 #pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const float b = __uint_as_float(__float_as_uint(LB[8 * j * kFRow + 4 * s]) ^ b_flip);
-#pragma unroll
-        for (int i = 0; i < TM; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b, acc[i][j], 0, 0, 0);
-      }
-    }
-    if (t + 1 < nk) {
+      for (int j = 0; j < TN; ++j) b[h][j] = *reinterpret_cast<const f4*>(LB + 16 * j * kFRow + 16 * h);
+    };
+    read(0);
+    if (t + 1 < nk) {  // staged and fetched under this tile's products
       stage(t + 1);
       if (t + 2 < nk) fetch(t + 2);
     }
+    read(1);
+    f32_multiply<TM, TN, CONJ>(a[0], b[0], acc);
+    f32_multiply<TM, TN, CONJ>(a[1], b[1], acc);
     __syncthreads();
   }
 
-  // lane holds real column (n, q) for rows 4 lg .. 4 lg + 3 of each tile; the partner lane (l ^ 1)
-  // holds the other part, and after the exchange each lane owns two complex results
-  float mx = 0.f;
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      const f4 v = acc[i][j] * unscale;
-      const float s0 = q ? v[0] : v[2], s1 = q ? v[1] : v[3];
-      const float r0 = __shfl_xor(s0, 1), r1 = __shfl_xor(s1, 1);
-      const int64_t row = m0 + wr + 16 * i + 4 * lg + (q ? 2 : 0);
-      const int64_t col = n0 + wc + 8 * j + (l16 >> 1);
-      float2 o0, o1;
-      if (q) { o0 = make_float2(r0, v[2]); o1 = make_float2(r1, v[3]); }
-      else { o0 = make_float2(v[0], r0); o1 = make_float2(v[1], r1); }
-      if (!EDGE || (row < g.M && col < g.N)) C[partial ? row * g.N + col : c_index(g.rn, row, col, g.N)] = o0;
-      if (!EDGE || (row + 1 < g.M && col < g.N))
-        C[partial ? (row + 1) * g.N + col : c_index(g.rn, row + 1, col, g.N)] = o1;
-      mx = fmaxf(mx, fmaxf(cmax(o0), cmax(o1)));  // zeros past the edge
-    }
-  if (g.rn.c && !partial) record_amax(g.rn.c, mx);
+  Renorm rn = g.rn;
+  if (partial) rn.om_nh = 0;
+  const uint32_t seen = partial ? 0u : seen_amax(g.rn);
+  const float mx = f32_store<TM, TN, EDGE>(C, rn, m0 + wr, n0 + wc, g.M, g.N, unscale, acc);
+  if (g.rn.c && !partial) raise_amax<WM * WN>(g.rn.c, mx, seen, lds);
 }
 
-template <int WM, int WN, int TM, int TN, int TA, int TB>
-static void f32_launch(hipStream_t st, const F32Args& g, int64_t batch, int split) {
+template <int WM, int WN, int TM, int TN, int TA, int TB, bool CONJ>
+static void f32_launch(hipStream_t st, const F32Args& g, int split) {
   using Tile = F32Tile<WM, WN, TM, TN>;
-  const int64_t tiles = ((g.M + Tile::BM - 1) / Tile::BM) * ((g.N + Tile::BN - 1) / Tile::BN);
-  const dim3 grid((unsigned)tiles, (unsigned)split, (unsigned)batch), block(Tile::threads);
+  const int64_t tiles = ((g.M + Tile::BM - 1) / Tile::BM) * ((g.N + Tile::BN - 1) / Tile::BN) * g.batch;
+  const dim3 grid((unsigned)tiles, (unsigned)split), block(Tile::threads);
   // whole tiles and pairs of elements that never straddle a row's end
   const bool whole = g.M % Tile::BM == 0 && g.N % Tile::BN == 0 && g.kc % kFBK == 0 && g.kc * split == g.K;
   if (whole)
-    hipLaunchKernelGGL((cgemm_f32<WM, WN, TM, TN, TA, TB, false>), grid, block, 0, st, g);
+    hipLaunchKernelGGL((cgemm_f32<WM, WN, TM, TN, TA, TB, CONJ, false>), grid, block, 0, st, g);
   else
-    hipLaunchKernelGGL((cgemm_f32<WM, WN, TM, TN, TA, TB, true>), grid, block, 0, st, g);
+    hipLaunchKernelGGL((cgemm_f32<WM, WN, TM, TN, TA, TB, CONJ, true>), grid, block, 0, st, g);
 }
 
-// Tile of a launch.  The larger the tile, the fewer operand reads per product (a 256 x 128 tile reads
-// each operand element from LDS for 64 to 128 outputs), so the largest one is taken that still gives the
-// 256 CUs a workgroup each; below that, smaller tiles spread the launch.  Thin products (N <= 16) get
-// the tiles of their width: a wider tile would multiply zeros.
-template <int TA, int TB>
-static void f32_pick(hipStream_t st, const F32Args& g, int64_t batch, int split, int want) {
-  auto blocks = [&](int64_t bm, int64_t bn) { return ((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn) * batch * split; };
+// Tile of a launch: 64 x 64 where that gives every CU its four workgroups (4096^3: 140 against 138 TFLOP/s
+// on 64 x 32 tiles, 2^20 x 256 x 256: 135 / 131, 2^21 x 64 x 64: 105 / 103), else the largest that still
+// gives the 256 CUs a workgroup each.  Thin products (N <= 16) get the tiles of that width: a wider tile
+// would multiply zeros.
+template <int TA, int TB, bool CONJ>
+static void f32_pick(hipStream_t st, const F32Args& g, int split, int want) {
+  auto blocks = [&](int64_t bm, int64_t bn) { return ((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn) * g.batch * split; };
   int tile = want;
   if (tile == F32_AUTO) {
-    if (g.N <= 8 && g.M >= 128) tile = F32_128X8;
-    else if (g.N <= 16) tile = g.M >= 128 && blocks(128, 16) >= 256 ? F32_128X16 : F32_32X16;
-    else if (g.M >= 256 && g.N >= 128 && blocks(256, 128) >= 256) tile = F32_256X128;
-    else if (g.M >= 128 && g.N >= 64 && blocks(128, 64) >= 256) tile = F32_128X64;
+    if (g.N <= 16) tile = g.M >= 128 && blocks(128, 16) >= 256 ? F32_128X16 : F32_32X16;
+    else if (g.M >= 64 && g.N >= 64 && blocks(64, 64) >= 1024) tile = F32_64X64;
     else if (g.M >= 64 && blocks(64, 32) >= 256) tile = F32_64X32;
     else tile = F32_32X32;
   }
   switch (tile) {
-    case F32_256X128: f32_launch<4, 2, 4, 8, TA, TB>(st, g, batch, split); return;
-    case F32_128X64: f32_launch<2, 2, 4, 4, TA, TB>(st, g, batch, split); return;
-    case F32_64X32: f32_launch<2, 2, 2, 2, TA, TB>(st, g, batch, split); return;
-    case F32_128X16: f32_launch<4, 1, 2, 2, TA, TB>(st, g, batch, split); return;
-    case F32_128X8: f32_launch<4, 1, 2, 1, TA, TB>(st, g, batch, split); return;
-    case F32_32X16: f32_launch<2, 1, 1, 2, TA, TB>(st, g, batch, split); return;
-    default: f32_launch<2, 2, 1, 2, TA, TB>(st, g, batch, split); return;
+    case F32_64X64: f32_launch<2, 2, 2, 2, TA, TB, CONJ>(st, g, split); return;
+    case F32_64X32: f32_launch<2, 2, 2, 1, TA, TB, CONJ>(st, g, split); return;
+    case F32_128X16: f32_launch<4, 1, 2, 1, TA, TB, CONJ>(st, g, split); return;
+    case F32_32X16: f32_launch<2, 1, 1, 1, TA, TB, CONJ>(st, g, split); return;
+    default: f32_launch<2, 2, 1, 1, TA, TB, CONJ>(st, g, split); return;
   }
 }
 
@@ -263,13 +314,12 @@ hipError_t launch_cgemm_f32(hipStream_t st, int64_t M, int64_t N, int64_t K, con
   g.A = A; g.B = B; g.C = C;
   g.lda = ta ? M : K;
   g.ldb = tb ? N : K;
-  g.sa = sa; g.sb = sb; g.sc = sc;
+  g.batch = batch; g.sa = sa; g.sb = sb; g.sc = sc;
   g.kc = *split > 1 ? ((K + *split - 1) / *split + kFBK - 1) / kFBK * kFBK : K;
   *split = (int)((K + g.kc - 1) / g.kc);  // whole K-tiles per chunk: every chunk holds some of K
   g.P = P;
-  g.conj_b = conj_b;
   g.rn = rn;
-  if (ta == 0 && tb == 0) f32_pick<0, 0>(st, g, batch, *split, tile);
+  if (ta == 0 && tb == 0 && !conj_b) f32_pick<0, 0, false>(st, g, *split, tile);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }

@@ -234,22 +234,17 @@ cgemm_pingpong_presplit(int64_t M, int64_t N, int64_t K, const uint32_t* __restr
   float scale_a, scale_b, unscale;
   renorm_begin<PREC>(rn, nullptr, nullptr, scale_a, scale_b, unscale);
   float mx = 0.f;
+  const int64_t col0 = tn * kPsBN + wc + 2 * (l16 >> 2);
 #pragma unroll
-  for (int i = 0; i < kPsWI; ++i)
+  for (int i = 0; i < kPsWI; ++i) {
+    const int64_t rp = c_row(rn, tm * kPsBM + wr + 16 * i + 4 * lg + (l16 & 3), N);
 #pragma unroll
     for (int j = 0; j < kPsWJ; ++j) {
-      const f4 v = acc[i][j] * unscale;
-      const float s0 = q ? v[0] : v[2], s1 = q ? v[1] : v[3];
-      const float r0 = __shfl_xor(s0, 1), r1 = __shfl_xor(s1, 1);
-      const int64_t row = tm * kPsBM + wr + 16 * i + 4 * lg + (q ? 2 : 0);
-      const int64_t col = tn * kPsBN + wc + 8 * j + (l16 >> 1);
-      float2 o0, o1;
-      if (q) { o0 = make_float2(r0, v[2]); o1 = make_float2(r1, v[3]); }
-      else { o0 = make_float2(v[0], r0); o1 = make_float2(v[1], r1); }
-      store_c(C, rn, row, col, N, o0);
-      store_c(C, rn, row + 1, col, N, o1);
-      mx = fmaxf(mx, fmaxf(cmax(o0), cmax(o1)));
+      const f4 o = quad_transpose(acc[i][j] * unscale);
+      store_c2(C, rn, rp + c_col(rn, col0 + 8 * j), o);
+      mx = fmaxf(mx, cmax4(o));
     }
+  }
   if (rn.c) record_amax(rn.c, mx);
 }
 

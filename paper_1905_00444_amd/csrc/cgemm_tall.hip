@@ -173,26 +173,22 @@ cgemm_tall(int64_t M, const float2* __restrict__ A, const float2* __restrict__ B
         }
     }
 
-    // lane (l16, lg) holds rows 4 lg .. 4 lg + 3 of real column l16; the partner lane (l16 ^ 1)
-    // holds the other part of the same complex column
 #pragma unroll
-    for (int r = 0; r < R; ++r)
+    for (int r = 0; r < R; ++r) {
+      float2* c = C + c_row(rn, row0 + 16 * r + 4 * lg + (l16 & 3), N);
 #pragma unroll
       for (int j = 0; j < NT; ++j) {
-        const f4 v = acc[r][j] * unscale;
-        const float s0 = q ? v[0] : v[2], s1 = q ? v[1] : v[3];
-        const float r0 = __shfl_xor(s0, 1), r1 = __shfl_xor(s1, 1);
-        const int64_t row = row0 + 16 * r + 4 * lg + (q ? 2 : 0);
-        const int col = 8 * j + (l16 >> 1);
-        float2 o0, o1;
-        if (q) { o0 = make_float2(r0, v[2]); o1 = make_float2(r1, v[3]); }
-        else { o0 = make_float2(v[0], r0); o1 = make_float2(v[1], r1); }
-        C[c_index(rn, row, col, N)] = o0;
-        C[c_index(rn, row + 1, col, N)] = o1;
-        mx = fmaxf(mx, fmaxf(cmax(o0), cmax(o1)));
+        const f4 o = quad_transpose(acc[r][j] * unscale);
+        *reinterpret_cast<f4*>(c + c_col(rn, 8 * j + 2 * (l16 >> 2))) = o;
+        mx = fmaxf(mx, cmax4(o));
       }
+    }
   }
-  if (rn.c) record_amax(rn.c, mx);
+  if (rn.c) {
+    const uint32_t seen = seen_amax(rn);
+    __syncthreads();  // B is read no more
+    raise_amax<kTallThreads / 64>(rn.c, mx, seen, reinterpret_cast<float*>(bs));
+  }
 }
 
 // Row groups per wave step: at most 4 A operand sets (K-steps x row groups) and 8 accumulator

@@ -169,7 +169,7 @@ enum {
   GEMM_N_VARIANTS = 10
 };
 // Tiles of the FP32 kernel (cgemm_f32.hip).
-enum { F32_AUTO = 0, F32_256X128, F32_128X64, F32_64X32, F32_32X32, F32_128X16, F32_128X8, F32_32X16 };
+enum { F32_AUTO = 0, F32_64X64, F32_64X32, F32_32X32, F32_128X16, F32_32X16 };
 bool cgemm_variant_fits(int precision, int64_t M, int64_t N, int64_t K, int variant);
 // blocks_per_tile: workgroups that a launch makes per output tile (batch x K-chunks).
 int cgemm_default_variant(int precision, int64_t M, int64_t N, int64_t K, int64_t blocks_per_tile = 1);
