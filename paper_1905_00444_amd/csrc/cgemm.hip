@@ -726,7 +726,7 @@ hipError_t launch_cgemm_ex(hipStream_t st, int precision, int64_t M, int64_t N, 
   if (precision != P_FP32 && precision != P_BF16X3 && precision != P_FP16) return hipErrorInvalidValue;
   const bool chosen = variant != GEMM_AUTO && cgemm_variant_fits(precision, M, N, K, variant);
   int v = chosen ? variant : cgemm_default_variant(precision, M, N, K);
-  if (rn.c) hipLaunchKernelGGL(renorm_reset, dim3(1), dim3(64), 0, st, rn.c);
+  if (rn.c && !rn.cleared) hipLaunchKernelGGL(renorm_reset, dim3(1), dim3(64), 0, st, rn.c);
   switch (v) {
     case GEMM_TALL:
       return launch_cgemm_tall(st, precision, M, N, K, A, B, C, batch, sa, sb, sc, amaxA, amaxB, rn);

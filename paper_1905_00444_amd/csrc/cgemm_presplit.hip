@@ -278,7 +278,7 @@ hipError_t launch_cgemm_presplit(hipStream_t st, int64_t M, int64_t N, int64_t K
   if (lda == 0) lda = K;
   if (ldb == 0) ldb = K;
   if (lda < K || ldb < K || (lda & 3) || (ldb & 3) || lda > kPsMaxLd || ldb > kPsMaxLd) return hipErrorInvalidValue;
-  if (rn.c) {
+  if (rn.c && !rn.cleared) {
     const hipError_t e = launch_renorm_reset(st, rn.c);
     if (e != hipSuccess) return e;
   }

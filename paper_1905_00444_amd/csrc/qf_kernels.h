@@ -32,6 +32,8 @@ struct Renorm {
   // words further (hi = bf16(x), lo = bf16(x - hi), as the splitting permute writes them).
   int so_kbits = 0;
   int64_t so_ld = 0, so_plane = 0;
+  // c->amax has been cleared already (the start of the chain does it for all steps in one launch)
+  bool cleared = false;
 };
 
 // One instruction of a qubit's world-line program.
@@ -126,20 +128,47 @@ struct LeafDesc {
   int32_t pos[kMaxLeafCut];      // bit position in the world-line
 };
 
-// Chain g (g < G) of the launch group that *chain0 names.  gpb == 0: chains c = *chain0 + g in
-// bitstring-major order, b = c / s_range, s = s_begin + c % s_range, idle past n_chains.  gpb > 0
-// (groups per bitstring): group q = *chain0 / G holds slices s_begin + (q mod gpb) G + g of
-// bitstring b = q / gpb, idle past s_begin + s_range.  base_table[g * n_leaves + l] = world-line
-// offset of leaf l's fixed bits; chain_b[g] = b (-1 for an idle chain).
-hipError_t launch_chain_setup(hipStream_t st, const int64_t* chain0, int G, int n_leaves, const LeafDesc* leaves,
-                              const uint8_t* bits, int n_qubits, int64_t s_begin, int64_t s_range, int64_t n_chains,
-                              int64_t gpb, int64_t* base_table, int32_t* chain_b);
+// Chains of a launch group.  gpb == 0: chain g is c = chain0 + g in bitstring-major order, b = c / s_range,
+// s = s_begin + c % s_range, idle past n_chains.  gpb > 0 (groups per bitstring): group q = chain0 / G
+// holds slices s_begin + (q mod gpb) G + g of bitstring b = q / gpb, idle past s_begin + s_range.
+struct ChainGroup {
+  int64_t chain0;
+  int32_t G, n_qubits;
+  const uint8_t* bits;  // device, n_qubits bytes per bitstring
+  int64_t s_begin, s_range, n_chains, gpb;
+};
+
+// One world-line operand that is gathered at the start of a chain (or launch group) rather than by a
+// permute of its own: element j of chain g's copy is src[base(g) + sum_i bit_i(j) << perm[i]], base from
+// the world-line's LeafDesc, written as complex64 or in the forms of PermuteArgs::split.
+constexpr int kGatherMaxBits = 14;
+struct GatherJob {
+  int64_t src;         // complex64 elements into the world-lines
+  int64_t dst;         // bytes into the workspace
+  int64_t dst_bstride; // complex64-sized elements between chains
+  int32_t leaf, step;  // LeafDesc index; step that reads the copy
+  int32_t batch;       // chains that have a copy of their own (1: shared)
+  int32_t nbits, split, split_kbits;
+  int64_t split_ld, split_plane;
+  int32_t scale_node;  // split == 2: the NodeScale that gives the fp16 scale, else -1
+  int8_t perm[kGatherMaxBits];
+};
+// A block of the launch: 1024 elements of one job from `first` on.
+struct GatherBlock { int32_t job, first; };
+constexpr int kGatherChunk = 1024;
+constexpr int kMaxChainSteps = 256;
+struct StepMask { uint64_t w[kMaxChainSteps / 64]; };
+
+// Start of a chain group, in one launch: base_table[g * n_leaves + l] = offset of leaf l's fixed bits and
+// chain_b[g] = bitstring (-1 for an idle chain) if base_table is given; scales[n_leaves + i].amax = 0 for the
+// steps i in `run` if scales is given; and the gathers of the jobs whose step is in `run`.
+hipError_t launch_chain_begin(hipStream_t st, const ChainGroup& grp, int n_leaves, const LeafDesc* leaves,
+                              int64_t* base_table, int32_t* chain_b, int n_steps, const StepMask& run, NodeScale* scales,
+                              const GatherJob* jobs, const GatherBlock* blocks, int n_blocks, const float2* wl, char* ws);
 // out[chain_b[g]][j] += root[g][sum_t bit_t(j) << pos[t]] for g = 0..G-1 in order (FP64).
 hipError_t launch_slice_accumulate_batched(hipStream_t st, const float2* root, int k, const int* pos, int G,
                                            const int32_t* chain_b, double2* out,
                                            const NodeScale* root_scale = nullptr);
-// *chain0 = value (add = 0) or *chain0 += value (add = 1), as a kernel (graph-capturable).
-hipError_t launch_chain_counter(hipStream_t st, int64_t* chain0, int64_t value, int add);
 
 // Split-BF16 GEMM on operands split by the permute (hi plane then lo plane per batch element), or
 // FP16 GEMM on operands scaled and converted by the permute (one plane); precision P_BF16X3 / P_FP16

@@ -35,6 +35,7 @@ using namespace qf;
 
 static const size_t kCtxScratch = 4096;  // start of the workspace reserved for small slots
 static const size_t kAlign = 256;
+static constexpr size_t kStaticScratchBytes = (size_t)64 << 20;  // qf_amplitudes_static's array
 
 static size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
@@ -91,6 +92,7 @@ struct Operand {
   int kbits = 0;          // contracted (lowest) bits, the GEMM's K
   int64_t ld = 0;         // split planes: words between rows (0: dense, 2^kbits)
   size_t buf = 0;         // arena offset of the permuted copy
+  bool early = false;     // small world-line slice: copied at the start of the chain, all in one launch
 };
 
 // Split operands with long rows get padded rows: rows 2^kbits words apart, a power of two of 32
@@ -179,6 +181,11 @@ struct qf_plan {
   std::vector<char> step_inv;
   std::vector<LeafDesc> leaf_desc;
   size_t off_leafdesc = 0, off_btable = 0, off_chainb = 0;
+  // gathers of small world-line operands at the start of a chain (group): jobs and the launch's blocks
+  std::vector<GatherJob> jobs;
+  std::vector<GatherBlock> job_blocks;
+  size_t off_jobs = 0, off_blocks = 0;
+  bool chain_begin = false;  // steps fit the launch's step mask
   hipGraphExec_t gexec = nullptr;
   hipGraph_t graph_obj = nullptr;
   std::vector<int64_t> graph_key;
@@ -397,6 +404,128 @@ static bool operand_invariant(const qf_plan* p, const Operand& op) {
   return p->ghoist && p->nodes[op.node].dep_cuts == 0;
 }
 static int operand_batch(const qf_plan* p, const Operand& op) { return operand_invariant(p, op) ? 1 : p->G; }
+
+// Offsets of everything a plan keeps in the workspace, and the gather jobs that use them.
+static void layout_arena(qf_plan* p, size_t n_ops) {
+  const int n = p->n;
+  size_t cur = kCtxScratch;
+  p->off_gates = cur;
+  cur = align_up(cur + n_ops * 4 * sizeof(float2));
+  p->off_wlq = cur;
+  cur = align_up(cur + p->wl_qubits.size() * sizeof(WlQubit));
+  p->off_prog = cur;
+  cur = align_up(cur + std::max<size_t>(1, p->wl_prog.size()) * sizeof(WlInstr));
+  p->off_wl = cur;
+  cur = align_up(cur + p->wl_elems * sizeof(float2));
+  std::vector<Buf> pers, trans;
+  const int S = (int)p->steps.size();
+  for (int i = 0; i < S; ++i) {
+    Node& nd = p->nodes[n + i];
+    const size_t G = (size_t)step_batch(p, i);
+    Step& st = p->steps[i];
+    const size_t bytes = align_up(G * sizeof(float2) * result_elems(st));
+    const size_t GA = (size_t)operand_batch(p, st.A), GB = (size_t)operand_batch(p, st.B);
+    if (p->backward) {
+      // every forward tensor is kept for the reverse sweep, next to its environment
+      pers.push_back({bytes, 0, S, &nd.offset});
+      pers.push_back({bytes, 0, S, &nd.env});
+      if (st.A.permute) pers.push_back({align_up(G * (sizeof(float2) << st.A.nbits)), 0, S, &st.A.buf});
+      if (st.B.permute) pers.push_back({align_up(G * (sizeof(float2) << st.B.nbits)), 0, S, &st.B.buf});
+      continue;
+    }
+    if (nd.persistent) pers.push_back({bytes, 0, S, &nd.offset});
+    else trans.push_back({bytes, i, (i == S - 1) ? S : nd.consumer, &nd.offset});
+    if (st.A.permute) trans.push_back({align_up(GA * sizeof(float2) * operand_elems(st.A)), st.A.early ? 0 : i, i, &st.A.buf});
+    if (st.B.permute) trans.push_back({align_up(GB * sizeof(float2) * operand_elems(st.B)), st.B.early ? 0 : i, i, &st.B.buf});
+  }
+  if (p->renorm) pers.push_back({align_up((n + S) * sizeof(NodeScale)), 0, S, &p->off_scales});
+  if (p->gscratch_bytes) pers.push_back({align_up(p->gscratch_bytes), 0, S, &p->off_gscratch});
+  pers.push_back({align_up(n * sizeof(LeafDesc)), 0, S, &p->off_leafdesc});
+  {
+    size_t n_jobs = 0, n_blocks = 0;
+    for (const Step& st : p->steps)
+      for (const Operand* op : {&st.A, &st.B})
+        if (op->early) {
+          ++n_jobs;
+          n_blocks += (size_t)std::max(1, (1 << op->nbits) / kGatherChunk);
+        }
+    pers.push_back({align_up(n_jobs * sizeof(GatherJob)), 0, S, &p->off_jobs});
+    pers.push_back({align_up(n_blocks * sizeof(GatherBlock)), 0, S, &p->off_blocks});
+  }
+  if (p->G > 1) {
+    pers.push_back({align_up((size_t)p->G * n * sizeof(int64_t)), 0, S, &p->off_btable});
+    pers.push_back({align_up((size_t)p->G * sizeof(int32_t)), 0, S, &p->off_chainb});
+  }
+  if (p->backward) {
+    size_t max_q = 0, max_c = 0, max_a = 0, max_b = 0;
+    for (int i = 0; i < S; ++i) {
+      const Step& st = p->steps[i];
+      const size_t va = sizeof(float2) << st.A.nbits, vb = sizeof(float2) << st.B.nbits;
+      max_q = std::max({max_q, va, vb});
+      max_c = std::max(max_c, sizeof(float2) << (st.m_bits + st.n_bits));
+      max_a = std::max(max_a, va);
+      max_b = std::max(max_b, vb);
+    }
+    const size_t G = (size_t)p->G;  // per chain in batched backward plans
+    pers.push_back({align_up(p->wl_elems * sizeof(float2)), 0, S, &p->off_envwl});
+    pers.push_back({align_up(G * max_q), 0, S, &p->off_bq});
+    pers.push_back({align_up(G * max_c), 0, S, &p->off_bp});
+    pers.push_back({align_up(G * max_a), 0, S, &p->off_bea});
+    pers.push_back({align_up(G * max_b), 0, S, &p->off_beb});
+  }
+  for (auto& b : pers) { *b.where = cur; cur = align_up(cur + b.bytes); }
+  const size_t tbase = cur;
+  // first fit by address among buffers with overlapping lifetimes, largest first
+  std::vector<int> idx(trans.size());
+  for (size_t i = 0; i < idx.size(); ++i) idx[i] = (int)i;
+  std::stable_sort(idx.begin(), idx.end(), [&](int a, int b) { return trans[a].bytes > trans[b].bytes; });
+  std::vector<std::pair<size_t, size_t>> placed_rng;  // (offset, end)
+  std::vector<int> placed_id;
+  size_t tend = tbase;
+  for (int id : idx) {
+    const Buf& b = trans[id];
+    std::vector<std::pair<size_t, size_t>> busy;
+    for (size_t j = 0; j < placed_id.size(); ++j) {
+      const Buf& o = trans[placed_id[j]];
+      if (o.start <= b.end && b.start <= o.end) busy.push_back(placed_rng[j]);
+    }
+    std::sort(busy.begin(), busy.end());
+    size_t at = tbase;
+    for (auto& r : busy) {
+      if (at + b.bytes <= r.first) break;
+      at = std::max(at, r.second);
+    }
+    *b.where = at;
+    placed_rng.push_back({at, at + b.bytes});
+    placed_id.push_back(id);
+    tend = std::max(tend, at + b.bytes);
+  }
+  p->arena_end = tend;
+  // the gather jobs of the early operands, in step order
+  p->jobs.clear();
+  p->job_blocks.clear();
+  for (int i = 0; i < S; ++i)
+    for (const Operand* op : {&p->steps[i].A, &p->steps[i].B}) {
+      if (!op->early) continue;
+      GatherJob j;
+      std::memset(&j, 0, sizeof(j));
+      j.src = p->wl_qubits[p->nodes[op->node].qubit].out_offset;
+      j.dst = (int64_t)op->buf;
+      j.dst_bstride = (int64_t)operand_elems(*op);
+      j.leaf = p->nodes[op->node].qubit;
+      j.step = i;
+      j.batch = operand_batch(p, *op);
+      j.nbits = op->nbits;
+      j.split = op->split ? (p->precision == QF_FP16 ? 2 : 1) : 0;
+      j.split_kbits = op->kbits;
+      j.split_ld = op->split ? op->ld : 0;
+      j.split_plane = j.split_ld ? (((int64_t)1 << (op->nbits - op->kbits)) * j.split_ld) : ((int64_t)1 << op->nbits);
+      j.scale_node = op->node;
+      for (int k = 0; k < op->nbits; ++k) j.perm[k] = (int8_t)op->perm[k];
+      for (int f = 0; f < (1 << op->nbits); f += kGatherChunk) p->job_blocks.push_back({(int)p->jobs.size(), f});
+      p->jobs.push_back(j);
+    }
+}
 
 qf_status qf_plan_create(qf_ctx* ctx, qf_circuit* circ, const qf_plan_desc* d, qf_plan** out) {
   if (!ctx || !circ || !d || !out) return fail(ctx, QF_ERR_ARG, "qf_plan_create: null argument");
@@ -747,93 +876,28 @@ qf_status qf_plan_create(qf_ctx* ctx, qf_circuit* circ, const qf_plan_desc* d, q
     }
   }
 
-  // ---- arena
-  size_t cur = kCtxScratch;
-  p->off_gates = cur;
-  cur = align_up(cur + circ->ops.size() * 4 * sizeof(float2));
-  p->off_wlq = cur;
-  cur = align_up(cur + p->wl_qubits.size() * sizeof(WlQubit));
-  p->off_prog = cur;
-  cur = align_up(cur + std::max<size_t>(1, p->wl_prog.size()) * sizeof(WlInstr));
-  p->off_wl = cur;
-  cur = align_up(cur + wl_elems * sizeof(float2));
-  std::vector<Buf> pers, trans;
-  const int S = (int)p->steps.size();
-  for (int i = 0; i < S; ++i) {
-    Node& nd = p->nodes[n + i];
-    const size_t G = (size_t)step_batch(p.get(), i);
-    Step& st = p->steps[i];
-    const size_t bytes = align_up(G * sizeof(float2) * result_elems(st));
-    const size_t GA = (size_t)operand_batch(p.get(), st.A), GB = (size_t)operand_batch(p.get(), st.B);
-    if (p->backward) {
-      // every forward tensor is kept for the reverse sweep, next to its environment
-      pers.push_back({bytes, 0, S, &nd.offset});
-      pers.push_back({bytes, 0, S, &nd.env});
-      if (st.A.permute) pers.push_back({align_up(G * (sizeof(float2) << st.A.nbits)), 0, S, &st.A.buf});
-      if (st.B.permute) pers.push_back({align_up(G * (sizeof(float2) << st.B.nbits)), 0, S, &st.B.buf});
-      continue;
+  // ---- world-line operands copied at the start of a chain.  Their buffers then live from the first step
+  // on; a plan that fits the library's static scratch only with shorter lifetimes keeps those
+  p->chain_begin = (int)p->steps.size() <= kMaxChainSteps;
+  for (Step& st : p->steps)
+    for (Operand* op : {&st.A, &st.B})
+      op->early = p->chain_begin && p->nodes[op->node].leaf && op->nbits <= kGatherMaxBits;
+  layout_arena(p.get(), circ->ops.size());
+  if (p->arena_end > kStaticScratchBytes) {
+    const size_t longer = p->arena_end;
+    for (Step& st : p->steps) st.A.early = st.B.early = false;
+    layout_arena(p.get(), circ->ops.size());
+    if (p->arena_end > kStaticScratchBytes && longer > kStaticScratchBytes) {
+      for (Step& st : p->steps)
+        for (Operand* op : {&st.A, &st.B})
+          op->early = p->chain_begin && p->nodes[op->node].leaf && op->nbits <= kGatherMaxBits;
+      layout_arena(p.get(), circ->ops.size());
     }
-    if (nd.persistent) pers.push_back({bytes, 0, S, &nd.offset});
-    else trans.push_back({bytes, i, (i == S - 1) ? S : nd.consumer, &nd.offset});
-    if (st.A.permute) trans.push_back({align_up(GA * sizeof(float2) * operand_elems(st.A)), i, i, &st.A.buf});
-    if (st.B.permute) trans.push_back({align_up(GB * sizeof(float2) * operand_elems(st.B)), i, i, &st.B.buf});
   }
-  if (p->renorm) pers.push_back({align_up((n + S) * sizeof(NodeScale)), 0, S, &p->off_scales});
-  if (p->gscratch_bytes) pers.push_back({align_up(p->gscratch_bytes), 0, S, &p->off_gscratch});
-  if (p->G > 1) {
-    pers.push_back({align_up(n * sizeof(LeafDesc)), 0, S, &p->off_leafdesc});
-    pers.push_back({align_up((size_t)p->G * n * sizeof(int64_t)), 0, S, &p->off_btable});
-    pers.push_back({align_up((size_t)p->G * sizeof(int32_t)), 0, S, &p->off_chainb});
-  }
-  if (p->backward) {
-    size_t max_q = 0, max_c = 0, max_a = 0, max_b = 0;
-    for (int i = 0; i < S; ++i) {
-      const Step& st = p->steps[i];
-      const size_t va = sizeof(float2) << st.A.nbits, vb = sizeof(float2) << st.B.nbits;
-      max_q = std::max({max_q, va, vb});
-      max_c = std::max(max_c, sizeof(float2) << (st.m_bits + st.n_bits));
-      max_a = std::max(max_a, va);
-      max_b = std::max(max_b, vb);
-    }
-    const size_t G = (size_t)p->G;  // per chain in batched backward plans
-    pers.push_back({align_up(wl_elems * sizeof(float2)), 0, S, &p->off_envwl});
-    pers.push_back({align_up(G * max_q), 0, S, &p->off_bq});
-    pers.push_back({align_up(G * max_c), 0, S, &p->off_bp});
-    pers.push_back({align_up(G * max_a), 0, S, &p->off_bea});
-    pers.push_back({align_up(G * max_b), 0, S, &p->off_beb});
-  }
-  for (auto& b : pers) { *b.where = cur; cur = align_up(cur + b.bytes); }
-  const size_t tbase = cur;
-  // first fit by address among buffers with overlapping lifetimes, largest first
-  std::vector<int> idx(trans.size());
-  for (size_t i = 0; i < idx.size(); ++i) idx[i] = (int)i;
-  std::stable_sort(idx.begin(), idx.end(), [&](int a, int b) { return trans[a].bytes > trans[b].bytes; });
-  std::vector<std::pair<size_t, size_t>> placed_rng;  // (offset, end)
-  std::vector<int> placed_id;
-  size_t tend = tbase;
-  for (int id : idx) {
-    const Buf& b = trans[id];
-    std::vector<std::pair<size_t, size_t>> busy;
-    for (size_t j = 0; j < placed_id.size(); ++j) {
-      const Buf& o = trans[placed_id[j]];
-      if (o.start <= b.end && b.start <= o.end) busy.push_back(placed_rng[j]);
-    }
-    std::sort(busy.begin(), busy.end());
-    size_t at = tbase;
-    for (auto& r : busy) {
-      if (at + b.bytes <= r.first) break;
-      at = std::max(at, r.second);
-    }
-    *b.where = at;
-    placed_rng.push_back({at, at + b.bytes});
-    placed_id.push_back(id);
-    tend = std::max(tend, at + b.bytes);
-  }
-  p->arena_end = tend;
   p->gates_host.resize(circ->ops.size() * 4);
   if (p->renorm) {
     // world-line entries are products of unitary gate entries and projectors: |x| <= 1
-    p->scale_init.assign(n + S, NodeScale{0, 0u});
+    p->scale_init.assign(n + (int)p->steps.size(), NodeScale{0, 0u});
     for (int q = 0; q < n; ++q) p->scale_init[q].amax = 0x3f800000u;  // 1.0f
   }
   ctx->plans.insert(p.get());
@@ -992,9 +1056,14 @@ static qf_status build_worldlines(qf_plan* p) {
   if (!p->wl_prog.empty())
     QF_HIP(c, hipMemcpyAsync(c->ws + p->off_prog, p->wl_prog.data(), p->wl_prog.size() * sizeof(WlInstr),
                              hipMemcpyHostToDevice, c->stream));
-  if (p->G > 1)
-    QF_HIP(c, hipMemcpyAsync(c->ws + p->off_leafdesc, p->leaf_desc.data(), p->leaf_desc.size() * sizeof(LeafDesc),
+  QF_HIP(c, hipMemcpyAsync(c->ws + p->off_leafdesc, p->leaf_desc.data(), p->leaf_desc.size() * sizeof(LeafDesc),
+                           hipMemcpyHostToDevice, c->stream));
+  if (!p->jobs.empty()) {
+    QF_HIP(c, hipMemcpyAsync(c->ws + p->off_jobs, p->jobs.data(), p->jobs.size() * sizeof(GatherJob),
                              hipMemcpyHostToDevice, c->stream));
+    QF_HIP(c, hipMemcpyAsync(c->ws + p->off_blocks, p->job_blocks.data(), p->job_blocks.size() * sizeof(GatherBlock),
+                             hipMemcpyHostToDevice, c->stream));
+  }
   if (p->renorm)
     QF_HIP(c, hipMemcpyAsync(c->ws + p->off_scales, p->scale_init.data(), p->scale_init.size() * sizeof(NodeScale),
                              hipMemcpyHostToDevice, c->stream));
@@ -1043,8 +1112,8 @@ static void set_split(qf_plan* p, const Operand& op, PermuteArgs* a) {
 static qf_status run_operand(qf_plan* p, const Operand& op, const uint8_t* bits_row, int64_t s, const float2** ptr) {
   qf_ctx* c = p->ctx;
   const Node& nd = p->nodes[op.node];
-  if (!op.permute) {
-    *ptr = wsp(c, nd.offset);
+  if (!op.permute || op.early) {
+    *ptr = wsp(c, op.early ? op.buf : nd.offset);
     return QF_OK;
   }
   PermuteArgs a;
@@ -1079,11 +1148,28 @@ static Renorm step_renorm(qf_plan* p, size_t i) {
     r.so_plane = ((int64_t)1 << (st.m_bits + st.n_bits - st.so_kbits)) * st.so_ld;
   }
   if (!p->renorm) return r;
+  r.cleared = p->chain_begin;
   r.a = node_scale(p, st.A.node);
   r.b = node_scale(p, st.B.node);
   r.c = node_scale(p, p->n + (int)i);
   return r;
 }
+
+// Start of a chain (group) for the steps in `run`: their running maxima are cleared and their small
+// world-line operands gathered, in one launch.  tables: also write the per-chain offsets of batched plans.
+static qf_status begin_chain(qf_plan* p, const ChainGroup& grp, const StepMask& run, bool tables) {
+  qf_ctx* c = p->ctx;
+  QF_HIP(c, launch_chain_begin(c->stream, grp, p->n, reinterpret_cast<const LeafDesc*>(c->ws + p->off_leafdesc),
+                               tables ? reinterpret_cast<int64_t*>(c->ws + p->off_btable) : nullptr,
+                               tables ? reinterpret_cast<int32_t*>(c->ws + p->off_chainb) : nullptr,
+                               (int)p->steps.size(), run, p->renorm && p->chain_begin ? node_scale(p, 0) : nullptr,
+                               reinterpret_cast<const GatherJob*>(c->ws + p->off_jobs),
+                               reinterpret_cast<const GatherBlock*>(c->ws + p->off_blocks), (int)p->job_blocks.size(),
+                               wsp(c, p->off_wl), c->ws));
+  return QF_OK;
+}
+
+static const StepMask kAllSteps = {{~0ull, ~0ull, ~0ull, ~0ull}};
 
 static const NodeScale* root_scale(qf_plan* p) {
   return p->renorm ? node_scale(p, (int)p->nodes.size() - 1) : nullptr;
@@ -1203,8 +1289,8 @@ static qf_status prepare(qf_plan* p) {
 static qf_status run_operand_batched(qf_plan* p, const Operand& op, const float2** ptr) {
   qf_ctx* c = p->ctx;
   const Node& nd = p->nodes[op.node];
-  if (!op.permute) {
-    *ptr = wsp(c, nd.offset);
+  if (!op.permute || op.early) {
+    *ptr = wsp(c, op.early ? op.buf : nd.offset);
     return QF_OK;
   }
   PermuteArgs a;
@@ -1232,15 +1318,14 @@ static qf_status run_operand_batched(qf_plan* p, const Operand& op, const float2
 }
 
 static qf_status enqueue_group(qf_plan* p, const uint8_t* bits_dev, int64_t s_begin, int64_t s_range,
-                               int64_t n_chains, double* out_dev, bool timed_ok) {
+                               int64_t chain0, int64_t n_chains, double* out_dev, bool timed_ok) {
   qf_ctx* c = p->ctx;
   const int n = p->n, G = p->G, k = (int)p->open.size();
-  int64_t* chain0 = reinterpret_cast<int64_t*>(c->ws + 8);
   int32_t* chain_b = reinterpret_cast<int32_t*>(c->ws + p->off_chainb);
   const int64_t gpb = p->ghoist ? (s_range + G - 1) / G : 0;  // launch groups per bitstring
-  QF_HIP(c, launch_chain_setup(c->stream, chain0, G, n, reinterpret_cast<const LeafDesc*>(c->ws + p->off_leafdesc),
-                               bits_dev, n, s_begin, s_range, n_chains, gpb,
-                               reinterpret_cast<int64_t*>(c->ws + p->off_btable), chain_b));
+  const ChainGroup grp = {chain0, G, n, bits_dev, s_begin, s_range, n_chains, gpb};
+  qf_status e0s = begin_chain(p, grp, kAllSteps, true);
+  if (e0s != QF_OK) return e0s;
   for (size_t i = 0; i < p->steps.size(); ++i) {
     const Step& st = p->steps[i];
     const int Gi = step_batch(p, i);
@@ -1280,12 +1365,10 @@ static qf_status enqueue_group(qf_plan* p, const uint8_t* bits_dev, int64_t s_be
   }
   QF_HIP(c, launch_slice_accumulate_batched(c->stream, wsp(c, p->nodes.back().offset), k, p->root_pos.data(), G,
                                             chain_b, reinterpret_cast<double2*>(out_dev), root_scale(p)));
-  QF_HIP(c, launch_chain_counter(c->stream, chain0, G, 1));
   return QF_OK;
 }
 
-// All groups of one call: the chain counter is reset, then every group runs the same launch
-// sequence (each reads the counter, runs its G chains and advances the counter on the device).
+// All groups of one call, the same launch sequence with another first chain each.
 static qf_status enqueue_call(qf_plan* p, int n_batch, const uint8_t* bits_dev, int64_t s_begin, int64_t s_end,
                               double* out_dev, bool timed_ok) {
   qf_ctx* c = p->ctx;
@@ -1294,15 +1377,14 @@ static qf_status enqueue_call(qf_plan* p, int n_batch, const uint8_t* bits_dev, 
   // group hoisting: each bitstring's slices in groups of G (the last one of a bitstring may be
   // partly idle); otherwise consecutive chains, bitstring-major, G per group
   const int64_t groups = p->ghoist ? n_batch * ((s_range + p->G - 1) / p->G) : (n_chains + p->G - 1) / p->G;
-  QF_HIP(c, launch_chain_counter(c->stream, reinterpret_cast<int64_t*>(c->ws + 8), 0, 0));
   for (int64_t g = 0; g < groups; ++g) {
-    qf_status e = enqueue_group(p, bits_dev, s_begin, s_range, n_chains, out_dev, timed_ok);
+    qf_status e = enqueue_group(p, bits_dev, s_begin, s_range, g * p->G, n_chains, out_dev, timed_ok);
     if (e != QF_OK) return e;
   }
   return QF_OK;
 }
 
-// Batched plans.  With QF_PLAN_GRAPH the whole call (counter reset and every group) is captured
+// Batched plans.  With QF_PLAN_GRAPH the whole call (every group) is captured
 // once into a hipGraph, keyed on the call's buffers, batch and slice range, and each call with
 // the same key is one hipGraphLaunch; otherwise the launches are enqueued directly.
 static qf_status amplitudes_batched(qf_plan* p, int n_batch, const uint8_t* bits_dev, int64_t s_begin, int64_t s_end,
@@ -1381,7 +1463,7 @@ extern "C" qf_status qf_amplitudes(qf_plan* p, int n_batch, const uint8_t* bits_
       if (fault_after >= 0 && done >= fault_after)
         return fail(c, QF_ERR_INJECTED, "fault injected after " + std::to_string(done) + " slices");
       const uint64_t changed = (s == s_begin) ? ~0ull : (uint64_t)(s ^ (s - 1));
-      for (size_t i = 0; i < p->steps.size(); ++i) {
+      auto runs = [&](size_t i) {
         const Node& nd = p->nodes[n + i];
         bool run = (s == s_begin) || (p->flags & QF_PLAN_NO_HOIST);
         if (!run)
@@ -1390,7 +1472,18 @@ extern "C" qf_status qf_amplitudes(qf_plan* p, int n_batch, const uint8_t* bits_
               const uint64_t mask = ((1ull << p->cuts[cc].nbits) - 1) << p->cut_offset[cc];
               if (changed & mask) run = true;
             }
-        if (!run) continue;
+        return run;
+      };
+      if (p->chain_begin) {
+        StepMask mask = {};
+        for (size_t i = 0; i < p->steps.size(); ++i)
+          if (runs(i)) mask.w[i >> 6] |= 1ull << (i & 63);
+        const ChainGroup grp = {0, 1, n, row, s, 1, 1, 0};  // the one chain (this bitstring, slice s)
+        e = begin_chain(p, grp, mask, false);
+        if (e != QF_OK) return e;
+      }
+      for (size_t i = 0; i < p->steps.size(); ++i) {
+        if (!runs(i)) continue;
         e = run_step(p, i, row, s);
         if (e != QF_OK) return e;
       }
@@ -1409,7 +1502,6 @@ extern "C" qf_status qf_amplitudes(qf_plan* p, int n_batch, const uint8_t* bits_
 // device holds its own copy of the array (loaded with the library's code object, held until the
 // process ends); its address on a device comes from hipGetSymbolAddress, taken once per device
 // with that device current.
-static constexpr size_t kStaticScratchBytes = (size_t)64 << 20;
 static __device__ __align__(256) char qf_static_scratch[kStaticScratchBytes];
 static constexpr int kMaxStaticDevices = 64;
 static std::mutex g_static_mu;
@@ -1540,14 +1632,13 @@ static qf_status route_env_batched(qf_plan* p, const Operand& op, const float2* 
 }
 
 static qf_status backward_group(qf_plan* p, const uint8_t* bits_dev, const double* cot_dev, int64_t s_begin,
-                                int64_t s_range, int64_t n_chains) {
+                                int64_t s_range, int64_t chain0, int64_t n_chains) {
   qf_ctx* c = p->ctx;
   const int n = p->n, G = p->G, k = (int)p->open.size();
-  int64_t* chain0 = reinterpret_cast<int64_t*>(c->ws + 8);
   int32_t* chain_b = reinterpret_cast<int32_t*>(c->ws + p->off_chainb);
-  QF_HIP(c, launch_chain_setup(c->stream, chain0, G, n, reinterpret_cast<const LeafDesc*>(c->ws + p->off_leafdesc),
-                               bits_dev, n, s_begin, s_range, n_chains, 0,
-                               reinterpret_cast<int64_t*>(c->ws + p->off_btable), chain_b));
+  const ChainGroup grp = {chain0, G, n, bits_dev, s_begin, s_range, n_chains, 0};
+  qf_status e0 = begin_chain(p, grp, kAllSteps, true);
+  if (e0 != QF_OK) return e0;
   // forward, every tensor of every chain kept
   for (size_t i = 0; i < p->steps.size(); ++i) {
     const Step& st = p->steps[i];
@@ -1589,7 +1680,6 @@ static qf_status backward_group(qf_plan* p, const uint8_t* bits_dev, const doubl
     e = route_env_batched(p, st.B, EB);
     if (e != QF_OK) return e;
   }
-  QF_HIP(c, launch_chain_counter(c->stream, chain0, G, 1));
   return QF_OK;
 }
 
@@ -1614,9 +1704,8 @@ extern "C" qf_status qf_backward(qf_plan* p, int n_batch, const uint8_t* bits_de
   if (p->G > 1) {
     const int64_t s_range = s_end - s_begin;
     const int64_t n_chains = (int64_t)n_batch * s_range;
-    QF_HIP(c, launch_chain_counter(c->stream, reinterpret_cast<int64_t*>(c->ws + 8), 0, 0));
     for (int64_t g = 0; g < (n_chains + p->G - 1) / p->G; ++g) {
-      e = backward_group(p, bits_dev, cot_dev, s_begin, s_range, n_chains);
+      e = backward_group(p, bits_dev, cot_dev, s_begin, s_range, g * p->G, n_chains);
       if (e != QF_OK) return e;
     }
     QF_HIP(c, launch_worldline_grad(c->stream, reinterpret_cast<const WlQubit*>(c->ws + p->off_wlq), n, p->max_nbond,
@@ -1632,6 +1721,11 @@ extern "C" qf_status qf_backward(qf_plan* p, int n_batch, const uint8_t* bits_de
   for (int b = 0; b < n_batch; ++b) {
     const uint8_t* row = bits_dev + (int64_t)b * n;
     for (int64_t s = s_begin; s < s_end; ++s) {
+      if (p->chain_begin) {
+        const ChainGroup grp = {0, 1, n, row, s, 1, 1, 0};
+        e = begin_chain(p, grp, kAllSteps, false);
+        if (e != QF_OK) return e;
+      }
       for (int i = 0; i < S_steps; ++i) {
         e = run_step(p, (size_t)i, row, s);
         if (e != QF_OK) return e;

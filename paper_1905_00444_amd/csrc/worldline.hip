@@ -9,7 +9,7 @@
 // T_q[0][bonds] and T_q[1][bonds].  Arithmetic is FP64, stored as complex64.
 #include <hip/hip_runtime.h>
 #include <algorithm>
-#include "qf_kernels.h"
+#include "cgemm_common.h"
 
 namespace qf {
 
@@ -329,43 +329,91 @@ hipError_t launch_zero(hipStream_t st, void* p, size_t bytes) {
 
 // ---------------------------------------------------------------------------------------------
 // Batched chains (bitstring x slice): per-chain leaf offsets and the ordered FP64 slice sum.
-__global__ void __launch_bounds__(256)
-chain_setup_kernel(const int64_t* __restrict__ chain0, int G, int n_leaves, const LeafDesc* __restrict__ leaves,
-                   const uint8_t* __restrict__ bits, int n_qubits, int64_t s_begin, int64_t s_range,
-                   int64_t n_chains, int64_t gpb, int64_t* __restrict__ base_table, int32_t* __restrict__ chain_b) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= G * n_leaves) return;
-  const int g = t / n_leaves, l = t - g * n_leaves;
-  int64_t bb, off;  // bitstring, slice offset in the range
-  if (gpb > 0) {
-    const int64_t q = *chain0 / G;
-    bb = q / gpb;
-    off = (q - bb * gpb) * G + g;
-    if (bb * s_range >= n_chains || off >= s_range) bb = -1;
+__device__ __forceinline__ void chain_of(const ChainGroup& c, int g, int64_t& b, int64_t& s) {
+  int64_t off;  // slice offset in the range
+  if (c.gpb > 0) {
+    const int64_t q = c.chain0 / c.G;
+    b = q / c.gpb;
+    off = (q - b * c.gpb) * c.G + g;
+    if (b * c.s_range >= c.n_chains || off >= c.s_range) b = -1;
   } else {
-    const int64_t c = *chain0 + g;
-    bb = c < n_chains ? c / s_range : -1;
-    off = c - bb * s_range;
+    const int64_t k = c.chain0 + g;
+    b = k < c.n_chains ? k / c.s_range : -1;
+    off = k - b * c.s_range;
   }
-  int64_t base = 0;
-  int32_t b = -1;
-  if (bb >= 0) {
-    b = (int32_t)bb;
-    const int64_t s = s_begin + off;
-    const LeafDesc& d = leaves[l];
-    for (int i = 0; i < d.n_cut; ++i) base |= ((s >> d.shift[i]) & 1) << d.pos[i];
-    if (d.xpos >= 0) base |= (int64_t)(bits[(int64_t)b * n_qubits + d.qubit] & 1) << d.xpos;
-  }
-  base_table[t] = base;
-  if (l == 0) chain_b[g] = b;
+  s = c.s_begin + off;
 }
 
-hipError_t launch_chain_setup(hipStream_t st, const int64_t* chain0, int G, int n_leaves, const LeafDesc* leaves,
-                              const uint8_t* bits, int n_qubits, int64_t s_begin, int64_t s_range, int64_t n_chains,
-                              int64_t gpb, int64_t* base_table, int32_t* chain_b) {
-  const int total = G * n_leaves;
-  hipLaunchKernelGGL(chain_setup_kernel, dim3((total + 255) / 256), dim3(256), 0, st, chain0, G, n_leaves, leaves,
-                     bits, n_qubits, s_begin, s_range, n_chains, gpb, base_table, chain_b);
+// World-line offset of the bits that chain (b, s) fixes; 0 for an idle chain.
+__device__ __forceinline__ int64_t leaf_base(const ChainGroup& c, const LeafDesc& d, int64_t b, int64_t s) {
+  if (b < 0) return 0;
+  int64_t base = 0;
+  for (int i = 0; i < d.n_cut; ++i) base |= ((s >> d.shift[i]) & 1) << d.pos[i];
+  if (d.xpos >= 0) base |= (int64_t)(c.bits[b * c.n_qubits + d.qubit] & 1) << d.xpos;
+  return base;
+}
+
+// Block 0: clears the running maxima of the steps; then setup_blocks blocks: per-chain offsets; then the
+// gathers, a GatherBlock each.  The gathered operands are small (at most 2^14 elements, whose world-line
+// slices sit in L2), so a launch each was all overhead: a chain of the 6x6 circuit made 75 of them.
+__global__ void __launch_bounds__(256)
+chain_begin_kernel(ChainGroup grp, int n_leaves, const LeafDesc* __restrict__ leaves, int64_t* __restrict__ base_table,
+                   int32_t* __restrict__ chain_b, int n_steps, StepMask run, NodeScale* __restrict__ scales,
+                   const GatherJob* __restrict__ jobs, const GatherBlock* __restrict__ blocks, int setup_blocks,
+                   const float2* __restrict__ wl, char* __restrict__ ws) {
+  const int tid = threadIdx.x, g = blockIdx.y;
+  int64_t b, s;
+  if ((int)blockIdx.x <= setup_blocks) {
+    if (g) return;
+    if (blockIdx.x == 0) {
+      if (scales && tid < n_steps && ((run.w[tid >> 6] >> (tid & 63)) & 1)) scales[n_leaves + tid].amax = 0u;
+      return;
+    }
+    const int t = ((int)blockIdx.x - 1) * 256 + tid;
+    if (t >= grp.G * n_leaves) return;
+    const int gg = t / n_leaves, l = t - gg * n_leaves;
+    chain_of(grp, gg, b, s);
+    base_table[t] = leaf_base(grp, leaves[l], b, s);
+    if (l == 0) chain_b[gg] = (int32_t)b;
+    return;
+  }
+  const GatherBlock blk = blocks[(int)blockIdx.x - 1 - setup_blocks];
+  const GatherJob& j = jobs[blk.job];
+  if (g >= j.batch || !((run.w[j.step >> 6] >> (j.step & 63)) & 1)) return;
+  chain_of(grp, g, b, s);
+  const float2* src = wl + j.src + leaf_base(grp, leaves[j.leaf], b, s);
+  float2* dst = reinterpret_cast<float2*>(ws + j.dst) + (int64_t)g * j.dst_bstride;
+  const int n = 1 << j.nbits;
+  const float f16s = (j.split == 2 && j.scale_node >= 0) ? ldexpf(1.f, 14 - renorm_exp(scales + j.scale_node)) : 1.f;
+#pragma unroll
+  for (int u = 0; u < kGatherChunk / 256; ++u) {
+    const int i = blk.first + u * 256 + tid;
+    if (i >= n) return;
+    int64_t off = 0;
+    for (int k = 0; k < j.nbits; ++k) off |= (int64_t)((i >> k) & 1) << j.perm[k];
+    const float2 x = src[off];
+    if (j.split == 0) {
+      dst[i] = x;
+      continue;
+    }
+    uint32_t* w = reinterpret_cast<uint32_t*>(dst);
+    const int64_t at = j.split_ld ? (int64_t)(i >> j.split_kbits) * j.split_ld + (i & ((1 << j.split_kbits) - 1)) : i;
+    if (j.split == 2) {
+      w[at] = pack_f16x2(x.x * f16s, x.y * f16s);
+    } else {
+      const uint32_t hi = pack_bf16x2(x.x, x.y);
+      w[at] = hi;
+      w[j.split_plane + at] = pack_bf16x2(x.x - bf16_lo_to_f32(hi), x.y - bf16_hi_to_f32(hi));
+    }
+  }
+}
+
+hipError_t launch_chain_begin(hipStream_t st, const ChainGroup& grp, int n_leaves, const LeafDesc* leaves,
+                              int64_t* base_table, int32_t* chain_b, int n_steps, const StepMask& run, NodeScale* scales,
+                              const GatherJob* jobs, const GatherBlock* blocks, int n_blocks, const float2* wl, char* ws) {
+  const int setup = base_table ? (grp.G * n_leaves + 255) / 256 : 0;
+  hipLaunchKernelGGL(chain_begin_kernel, dim3((unsigned)(1 + setup + n_blocks), n_blocks ? (unsigned)grp.G : 1u), dim3(256),
+                     0, st, grp, n_leaves, leaves, base_table, chain_b, n_steps, run, scales, jobs, blocks, setup, wl, ws);
   return hipGetLastError();
 }
 
@@ -399,15 +447,6 @@ hipError_t launch_slice_accumulate_batched(hipStream_t st, const float2* root, i
   if (blocks > 1024) blocks = 1024;
   hipLaunchKernelGGL(slice_accumulate_batched_kernel, dim3(blocks), dim3(256), 0, st, root, a, G, chain_b, out,
                      root_scale);
-  return hipGetLastError();
-}
-
-__global__ void chain_counter_kernel(int64_t* chain0, int64_t value, int add) {
-  if (threadIdx.x == 0) *chain0 = add ? *chain0 + value : value;
-}
-
-hipError_t launch_chain_counter(hipStream_t st, int64_t* chain0, int64_t value, int add) {
-  hipLaunchKernelGGL(chain_counter_kernel, dim3(1), dim3(64), 0, st, chain0, value, add);
   return hipGetLastError();
 }
 
