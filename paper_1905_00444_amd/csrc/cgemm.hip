@@ -45,7 +45,7 @@ constexpr int kBK = 32;          // complex k per K-tile
 constexpr int kThreads = 256;
 
 __global__ void renorm_reset(NodeScale* c) {
-  if (threadIdx.x == 0) c->amax = 0u;
+  if (threadIdx.x < kScaleSlots) c->slot[threadIdx.x].amax = 0u;
 }
 
 hipError_t launch_renorm_reset(hipStream_t st, NodeScale* c) {
@@ -616,7 +616,7 @@ cgemm_splitk(int64_t M, int64_t N, int64_t K, const float2* __restrict__ A, cons
     r *= unscale;
     i *= unscale;
     C[batch * sc + c_index(rn, m, n, N)] = make_float2(r, i);
-    if (rn.c) atomicMax(&rn.c->amax, __float_as_uint(fmaxf(fabsf(r), fabsf(i))));
+    if (rn.c) atomicMax(amax_slot(rn.c), __float_as_uint(fmaxf(fabsf(r), fabsf(i))));
   }
 }
 

@@ -97,7 +97,13 @@ __device__ __forceinline__ int fp16_shift(const uint32_t* amax) {
 // Binary exponent e of a stored tensor's max magnitude (amax = f 2^e, f in [0.5, 1)), clamped so
 // that the epilogue factor 2^-(e_A + e_B) stays a normal float; 0 for an all-zero tensor.
 __device__ __forceinline__ int renorm_exp(const NodeScale* n) {
-  const float m = __uint_as_float(n->amax);
+  uint32_t bits = 0;
+#pragma unroll
+  for (int i = 0; i < kScaleSlots; ++i) {
+    const uint32_t v = n->slot[i].amax;
+    bits = v > bits ? v : bits;
+  }
+  const float m = __uint_as_float(bits);
   if (!(m > 0.f) || !(m <= 3.0e38f)) return 0;
   int e;
   frexpf(m, &e);
@@ -119,7 +125,8 @@ __device__ __forceinline__ void renorm_begin(const Renorm& rn, const uint32_t* a
       s_a = 14 - ea;
       s_b = 14 - eb;
     }
-    if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x == 0) rn.c->e = rn.a->e + rn.b->e + e_ab;
+    if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x == 0)
+      rn.c->slot[0].e = rn.a->slot[0].e + rn.b->slot[0].e + e_ab;
   } else if constexpr (PREC == P_FP16) {
     s_a = fp16_shift(amaxA);
     s_b = fp16_shift(amaxB);
@@ -131,14 +138,17 @@ __device__ __forceinline__ void renorm_begin(const Renorm& rn, const uint32_t* a
 
 __device__ __forceinline__ float cmax(float2 v) { return fmaxf(fabsf(v.x), fabsf(v.y)); }
 
-// Raises c->amax to the largest m of the launch.  All workgroups target one address, and atomics on one
-// address are served about 10 ns apart (two million waves cost 20 ms), so a workgroup first compares with
-// a value read before and issues its atomic only if it holds a larger one: amax only grows during the
-// launch, so any value read is a lower bound of the final one and skipping is exact.  seen_amax is called
+// Raises the workgroup's slot of c's amax to its largest m.  The atomics on one slot are served about 12 ns
+// apart (two million waves on one slot cost 20 ms), so a workgroup first compares with a value read
+// before and issues its atomic only if it holds a larger one: amax only grows during the launch, so any
+// value read is a lower bound of the final one and skipping is exact.  seen_amax is called
 // between the main loop and the epilogue, whose stores hide the read; a read before the main loop is
 // too old (most workgroups then hold more: 2^21 x 8 x 64 took 308 us instead of 240).
+__device__ __forceinline__ uint32_t* amax_slot(NodeScale* c) {
+  return &c->slot[(blockIdx.x + blockIdx.z) % kScaleSlots].amax;
+}
 __device__ __forceinline__ uint32_t seen_amax(const Renorm& rn) {
-  return rn.c ? __hip_atomic_load(&rn.c->amax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+  return rn.c ? __hip_atomic_load(amax_slot(rn.c), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
 }
 __device__ __forceinline__ float wave_max(float m) {
   for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
@@ -154,7 +164,7 @@ __device__ __forceinline__ void raise_amax(NodeScale* c, float m, uint32_t seen,
     float t = red[0];
 #pragma unroll
     for (int w = 1; w < WAVES; ++w) t = fmaxf(t, red[w]);
-    if (__float_as_uint(t) > seen) atomicMax(&c->amax, __float_as_uint(t));
+    if (__float_as_uint(t) > seen) atomicMax(amax_slot(c), __float_as_uint(t));
   }
 }
 // One per wave, read and compared at the end (kernels whose load ring must stay alone in flight).
@@ -162,7 +172,7 @@ __device__ __forceinline__ void record_amax(NodeScale* c, float m) {
   m = wave_max(m);
   if ((threadIdx.x & 63) == 0) {
     const uint32_t v = __float_as_uint(m);
-    if (v > __hip_atomic_load(&c->amax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(&c->amax, v);
+    if (v > __hip_atomic_load(amax_slot(c), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(amax_slot(c), v);
   }
 }
 
@@ -178,7 +188,7 @@ struct BExpand {
   }
 };
 
-// Clears c->amax before a renormalised GEMM raises it (cgemm.hip).
+// Clears c's amax before a renormalised GEMM raises it (cgemm.hip).
 hipError_t launch_renorm_reset(hipStream_t st, NodeScale* c);
 
 } // namespace qf

@@ -6,17 +6,19 @@
 namespace qf {
 
 // Power-of-two renormalisation state of one stored tensor: its true values are the stored values
-// times 2^e; amax is the largest |re| or |im| among the stored values (float bits, which order
-// like the values since they are non-negative).
+// times 2^e; the largest |re| or |im| among the stored values is the largest of the slots' amax (float
+// bits, which order like the values since they are non-negative).  The workgroups of a launch raise
+// different slots, each in a 64-byte line of its own: atomics on one line are served 12 ns apart (1024
+// workgroups that end together: 13 us on one slot, not measurable on 16).
+constexpr int kScaleSlots = 16;
 struct NodeScale {
-  int32_t e;
-  uint32_t amax;
+  struct Slot { uint32_t amax; int32_t e; uint32_t pad[14]; } slot[kScaleSlots];  // e: slot 0 only
 };
 
 // Renormalised GEMM (all three null: off).  With e_A, e_B the binary exponents of the operands'
 // amax (amax = f 2^e, f in [0.5, 1)), the GEMM stores C * 2^-(e_A + e_B), writes
-// c->e = a->e + b->e + e_A + e_B from one thread, and raises c->amax to the stored result's
-// largest magnitude (c->amax is cleared by the launcher first).
+// c's e = a's + b's + e_A + e_B from one thread, and raises c's amax to the stored result's largest
+// magnitude (cleared by the launcher first).
 struct Renorm {
   const NodeScale* a = nullptr;
   const NodeScale* b = nullptr;

@@ -897,8 +897,8 @@ qf_status qf_plan_create(qf_ctx* ctx, qf_circuit* circ, const qf_plan_desc* d, q
   p->gates_host.resize(circ->ops.size() * 4);
   if (p->renorm) {
     // world-line entries are products of unitary gate entries and projectors: |x| <= 1
-    p->scale_init.assign(n + (int)p->steps.size(), NodeScale{0, 0u});
-    for (int q = 0; q < n; ++q) p->scale_init[q].amax = 0x3f800000u;  // 1.0f
+    p->scale_init.assign(n + (int)p->steps.size(), NodeScale{});
+    for (int q = 0; q < n; ++q) p->scale_init[q].slot[0].amax = 0x3f800000u;  // 1.0f
   }
   ctx->plans.insert(p.get());
   circ->plans.insert(p.get());

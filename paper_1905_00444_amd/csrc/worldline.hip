@@ -67,7 +67,7 @@ __global__ void __launch_bounds__(256)
 slice_accumulate_kernel(const float2* __restrict__ root, AccArgs a, double2* __restrict__ out,
                         const NodeScale* __restrict__ root_scale) {
   const int64_t n = (int64_t)1 << a.k;
-  const double f = root_scale ? ldexp(1.0, root_scale->e) : 1.0;  // exact power of two
+  const double f = root_scale ? ldexp(1.0, root_scale->slot[0].e) : 1.0;  // exact power of two
   for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < n; j += (int64_t)gridDim.x * blockDim.x) {
     int64_t src = 0;
     for (int t = 0; t < a.k; ++t) src |= ((j >> t) & 1) << a.pos[t];
@@ -366,7 +366,10 @@ chain_begin_kernel(ChainGroup grp, int n_leaves, const LeafDesc* __restrict__ le
   if ((int)blockIdx.x <= setup_blocks) {
     if (g) return;
     if (blockIdx.x == 0) {
-      if (scales && tid < n_steps && ((run.w[tid >> 6] >> (tid & 63)) & 1)) scales[n_leaves + tid].amax = 0u;
+      for (int t = tid; scales && t < n_steps * kScaleSlots; t += 256) {
+        const int i = t / kScaleSlots;
+        if ((run.w[i >> 6] >> (i & 63)) & 1) scales[n_leaves + i].slot[t % kScaleSlots].amax = 0u;
+      }
       return;
     }
     const int t = ((int)blockIdx.x - 1) * 256 + tid;
@@ -421,7 +424,7 @@ __global__ void __launch_bounds__(256)
 slice_accumulate_batched_kernel(const float2* __restrict__ root, AccArgs a, int G, const int32_t* __restrict__ chain_b,
                                 double2* __restrict__ out, const NodeScale* __restrict__ root_scale) {
   const int64_t n = (int64_t)1 << a.k;
-  const double f = root_scale ? ldexp(1.0, root_scale->e) : 1.0;
+  const double f = root_scale ? ldexp(1.0, root_scale->slot[0].e) : 1.0;
   for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < n; j += (int64_t)gridDim.x * blockDim.x) {
     int64_t src = 0;
     for (int t = 0; t < a.k; ++t) src |= ((j >> t) & 1) << a.pos[t];
