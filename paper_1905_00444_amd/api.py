@@ -202,6 +202,11 @@ class Plan:
         check(self.ctx.lib.qf_plan_flops(self.h, int(s_begin), int(s_end), C.byref(f)), self.ctx.h)
         return f.value
 
+    def _call_workspace(self, n_batch: int, n_slices: int) -> int:
+        n = C.c_size_t()
+        check(self.ctx.lib.qf_plan_call_workspace(self.h, int(n_batch), max(0, int(n_slices)), C.byref(n)), self.ctx.h)
+        return n.value
+
     def amplitudes(self, bits, s_begin: int = 0, s_end: Optional[int] = None, out=None):
         """Amplitudes (n_batch, 2^n_open) complex128 on the device, summed over slices
         [s_begin, s_end) and added into `out` if given.  Everything is enqueued on the
@@ -210,7 +215,7 @@ class Plan:
         info = self.info()
         if s_end is None:
             s_end = info["n_slices"]
-        self.ctx.ensure_workspace(info["workspace_bytes"])
+        self.ctx.ensure_workspace(self._call_workspace(len(bits), s_end - s_begin))
         with torch.cuda.stream(self.ctx.stream):
             if isinstance(bits, np.ndarray):
                 bits_t = torch.from_numpy(np.ascontiguousarray(bits, dtype=np.uint8)).to(self.ctx.device)
@@ -252,7 +257,7 @@ class Plan:
         info = self.info()
         if s_end is None:
             s_end = info["n_slices"]
-        self.ctx.ensure_workspace(info["workspace_bytes"])
+        self.ctx.ensure_workspace(self._call_workspace(len(bits), s_end - s_begin))
         with torch.cuda.stream(self.ctx.stream):
             if isinstance(bits, np.ndarray):
                 bits_t = torch.from_numpy(np.ascontiguousarray(bits, dtype=np.uint8)).to(self.ctx.device)

@@ -173,6 +173,7 @@ struct qf_plan {
   size_t off_gates = 0, off_wlq = 0, off_prog = 0, off_wl = 0, arena_end = 0;
   // batched plans: G chains per launch
   int G = 1;
+  int G_max = 1;  // chains that the workspace is laid out for (a batch form runs fewer if the call has fewer)
   bool graph = false;
   // batched forward plans with cuts: the chains of one launch group share one bitstring (groups
   // never straddle bitstrings), and every step whose result depends on no cut (step_inv) runs
@@ -202,6 +203,13 @@ struct qf_plan {
   bool renorm = false;
   size_t off_scales = 0;
   std::vector<NodeScale> scale_init;
+  bool no_hoist_asked = false;   // QF_PLAN_NO_HOIST in the description (flags gains it otherwise too)
+  // one-chain plans: the same steps laid out for G chains per launch, used for calls of several chains
+  // (batch_form below); built on the first such call
+  qf_plan* multi = nullptr;
+  bool multi_tried = false;
+  bool sequential_like = false;  // this plan is another's `multi`: roles and shapes of the one-chain form
+  std::vector<int32_t> desc_steps;
   // qf_plan_info_get's result: fixed once the plan is laid out, computed on the first call
   // (flops_next_slice simulates the reuse schedule over up to 4096 slices)
   mutable bool info_ready = false;
@@ -527,7 +535,7 @@ static void layout_arena(qf_plan* p, size_t n_ops) {
     }
 }
 
-qf_status qf_plan_create(qf_ctx* ctx, qf_circuit* circ, const qf_plan_desc* d, qf_plan** out) {
+static qf_status build_plan(qf_ctx* ctx, qf_circuit* circ, const qf_plan_desc* d, bool sequential_like, qf_plan** out) {
   if (!ctx || !circ || !d || !out) return fail(ctx, QF_ERR_ARG, "qf_plan_create: null argument");
   if (circ->ctx != ctx) return fail(ctx, QF_ERR_ARG, "qf_plan_create: the circuit belongs to another context");
   *out = nullptr;
@@ -540,14 +548,16 @@ qf_status qf_plan_create(qf_ctx* ctx, qf_circuit* circ, const qf_plan_desc* d, q
   p->precision = d->precision;
   p->flags = d->flags;
   p->backward = (d->flags & QF_PLAN_BACKWARD) != 0;
+  p->no_hoist_asked = (d->flags & QF_PLAN_NO_HOIST) != 0;
   if (p->backward) p->flags |= QF_PLAN_NO_HOIST;
-  p->G = d->batch > 1 ? d->batch : 1;
+  p->G = p->G_max = d->batch > 1 ? d->batch : 1;
   if (p->G & (p->G - 1)) return fail(ctx, QF_ERR_ARG, "batch must be a power of two");
   if (p->G > 1 && p->backward && (d->flags & QF_PLAN_GRAPH))
     return fail(ctx, QF_ERR_UNSUPPORTED, "backward plans are not captured in a graph");
   if (p->G > 1) p->flags |= QF_PLAN_NO_HOIST;
   p->graph = p->G > 1 && (d->flags & QF_PLAN_GRAPH);
   p->renorm = !p->backward && !(d->flags & QF_PLAN_NO_RENORM);
+  p->sequential_like = sequential_like;
 
   // ---- bonds: one bit per diagonal two-qubit gate, time order (ops are sorted by cycle)
   std::vector<std::vector<int>> edge_gate_bits;  // per edge: op indices
@@ -747,7 +757,7 @@ qf_status qf_plan_create(qf_ctx* ctx, qf_circuit* circ, const qf_plan_desc* d, q
     for (int lab : X->labels) if (contains(Y->labels, lab)) K.push_back(lab);
     int xf = (int)X->labels.size() - (int)K.size(), yf = (int)Y->labels.size() - (int)K.size();
     if (yf > xf) { std::swap(X, Y); std::swap(xid, yid); std::swap(xf, yf); }
-    if (group_hoist && X->dep_cuts == 0 && Y->dep_cuts != 0) { std::swap(X, Y); std::swap(xid, yid); std::swap(xf, yf); }
+    if (group_hoist && !sequential_like && X->dep_cuts == 0 && Y->dep_cuts != 0) { std::swap(X, Y); std::swap(xid, yid); std::swap(xf, yf); }
     // K order: keep an intermediate operand in place when its contracted bits already trail
     auto trailing = [&](const Node* nd) {
       if (nd->leaf) return false;
@@ -846,7 +856,7 @@ qf_status qf_plan_create(qf_ctx* ctx, qf_circuit* circ, const qf_plan_desc* d, q
     if (!p->ghoist) p->step_inv.clear();
     for (size_t i = 0; p->ghoist && i < p->steps.size(); ++i) {
       Step& st = p->steps[i];
-      st.fold = !p->step_inv[i] && !st.presplit && operand_invariant(p.get(), st.B) &&
+      st.fold = !sequential_like && !p->step_inv[i] && !st.presplit && operand_invariant(p.get(), st.B) &&
                 !operand_invariant(p.get(), st.A);
       if (st.fold)  // split-K partials of the folded shape (G M rows, one launch)
         p->gscratch_bytes = std::max(p->gscratch_bytes,
@@ -900,10 +910,15 @@ qf_status qf_plan_create(qf_ctx* ctx, qf_circuit* circ, const qf_plan_desc* d, q
     p->scale_init.assign(n + (int)p->steps.size(), NodeScale{});
     for (int q = 0; q < n; ++q) p->scale_init[q].slot[0].amax = 0x3f800000u;  // 1.0f
   }
+  p->desc_steps.assign(d->steps, d->steps + 2 * (size_t)d->n_steps);
   ctx->plans.insert(p.get());
   circ->plans.insert(p.get());
   *out = p.release();
   return QF_OK;
+}
+
+qf_status qf_plan_create(qf_ctx* ctx, qf_circuit* circ, const qf_plan_desc* d, qf_plan** out) {
+  return build_plan(ctx, circ, d, false, out);
 }
 
 // Destroys a plan's captured graph after the work queued on its stream has finished.
@@ -918,6 +933,7 @@ static void plan_release_graph(qf_plan* p) {
 
 void qf_plan_destroy(qf_plan* plan) {
   if (!plan) return;
+  qf_plan_destroy(plan->multi);
   plan_release_graph(plan);
   if (plan->ctx) {
     if (plan->ctx->last_built == plan) plan->ctx->last_built = nullptr;
@@ -962,6 +978,62 @@ static double schedule_flops(const qf_plan* p, int64_t s0, int64_t s1, bool firs
 qf_status qf_plan_flops(const qf_plan* p, int64_t s_begin, int64_t s_end, double* flops) {
   if (!p || !flops || s_begin < 0 || s_begin > s_end || s_end > ((int64_t)1 << p->total_cut_bits)) return QF_ERR_ARG;
   *flops = s_begin == s_end ? 0.0 : schedule_flops(p, s_begin, s_end, true);
+  return QF_OK;
+}
+
+// The form of a one-chain plan that runs a call of several chains (bitstrings x slices) with G chains per
+// launch, or null: the same steps, roles and GEMM shapes, so that every chain's values are those of the
+// one-chain path bit by bit (backward sums excepted: chains add atomically), but one launch per step and
+// group instead of one per step and chain.  A launch of a small step costs 2 to 5 us whatever it computes:
+// 48 chains of a 4x5 circuit took 9.8 ms one at a time, 1.0 ms in groups of 16 slices.
+// Not taken: FP16 (its operand scales come from a tensor's largest entry, which the chains of a launch
+// would share), and plans whose reuse of subtrees across slices saves more than launches cost (the group
+// form recomputes whatever depends on any cut).  G is bounded by the workspace it needs: chains of
+// large tensors fill the GPU by themselves.
+constexpr size_t kMultiBytes = (size_t)512 << 20;
+constexpr int kMultiChains = 64;
+
+static qf_plan* batch_form(qf_plan* p) {
+  if (p->multi || p->multi_tried) return p->multi;
+  p->multi_tried = true;
+  if (p->G != 1 || p->sequential_like || p->precision == QF_FP16) return nullptr;
+  const size_t shared = p->off_wl + p->wl_elems * sizeof(float2);
+  const size_t chain = p->arena_end > shared ? p->arena_end - shared : 1;
+  int G = 1;
+  while (G < kMultiChains && (size_t)(2 * G) * chain <= kMultiBytes) G *= 2;
+  if (G < 2) return nullptr;
+  qf_plan_desc d;
+  std::memset(&d, 0, sizeof(d));
+  d.n_steps = (int)p->steps.size();
+  d.steps = p->desc_steps.data();
+  d.n_cuts = (int)p->cuts.size();
+  d.cuts = p->cuts.data();
+  d.n_open = (int)p->open.size();
+  d.open = p->open.data();
+  d.precision = p->precision;
+  d.flags = (p->no_hoist_asked ? QF_PLAN_NO_HOIST : 0) | (p->backward ? QF_PLAN_BACKWARD : 0) |
+            (p->renorm || p->backward ? 0 : QF_PLAN_NO_RENORM);
+  d.batch = G;
+  qf_plan* q = nullptr;
+  if (build_plan(p->ctx, p->circ, &d, true, &q) != QF_OK) return nullptr;
+  // what the group form recomputes, at the rate of such steps, against the launches that it saves
+  const int64_t S = std::min<int64_t>((int64_t)1 << p->total_cut_bits, 4096);
+  const double more_s = (schedule_flops(q, 0, S, true) - schedule_flops(p, 0, S, true)) / 50e12;
+  if (more_s > 8e-6 * (double)p->steps.size() * (double)S * (1.0 - 1.0 / G)) {
+    qf_plan_destroy(q);
+    return nullptr;
+  }
+  p->multi = q;
+  return q;
+}
+
+// Workspace that a call of n_batch bitstrings over `slices` slices uses at most.
+qf_status qf_plan_call_workspace(qf_plan* p, int n_batch, int64_t slices, size_t* bytes) {
+  if (!p || !p->ctx || !p->circ || !bytes || n_batch < 0 || slices < 0) return QF_ERR_ARG;
+  *bytes = p->arena_end;
+  if ((int64_t)n_batch * slices < 2) return QF_OK;
+  const qf_plan* q = batch_form(p);
+  if (q) *bytes = std::max(*bytes, q->arena_end);
   return QF_OK;
 }
 
@@ -1439,6 +1511,28 @@ extern "C" qf_status qf_plan_graph_info(const qf_plan* p, int64_t* launches, int
   return QF_OK;
 }
 
+// The batch form of plan p if this call runs on it, with its chains per launch set for the call: calls of
+// several chains for which the workspace is there; and single chains while the workspace holds its
+// world-lines (another build of them costs more than it saves).  Not while a stream capture would record
+// the build.
+static qf_plan* multi_for_call(qf_plan* p, int n_batch, int64_t slices) {
+  qf_ctx* c = p->ctx;
+  if (p->G != 1 || p->sequential_like) return nullptr;
+  const bool several = (int64_t)n_batch * slices >= 2;
+  qf_plan* q = several ? batch_form(p) : p->multi;
+  if (!q || c->ws_bytes < q->arena_end) return nullptr;
+  const bool built = c->last_built == q && q->built_version == q->circ->version;
+  if (!built) {
+    if (!several || (q->ghoist && slices < 2)) return nullptr;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (c->stream && hipStreamIsCapturing(c->stream, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone) return nullptr;
+  }
+  const int64_t chains = q->ghoist ? slices : n_batch * slices;  // a group's chains share a bitstring if hoisted
+  q->G = 1;
+  while (q->G < q->G_max && q->G < chains) q->G *= 2;
+  return q;
+}
+
 extern "C" qf_status qf_amplitudes(qf_plan* p, int n_batch, const uint8_t* bits_dev, int64_t s_begin, int64_t s_end,
                                    double* out_dev) {
   if (!p || !p->ctx || !p->circ) return QF_ERR_ARG;
@@ -1449,11 +1543,18 @@ extern "C" qf_status qf_amplitudes(qf_plan* p, int n_batch, const uint8_t* bits_
   if (!c->ws || c->ws_bytes < p->arena_end)
     return fail(c, QF_ERR_WORKSPACE, "workspace too small: need " + std::to_string(p->arena_end) + " bytes");
   if (n_batch == 0 || s_begin == s_end) return QF_OK;
-  qf_status e = prepare(p);
+  qf_status e;
+  const char* fault = std::getenv("QFMI_FAULT_AFTER_SLICES");
+  if (qf_plan* q = (fault || trace_on()) ? nullptr : multi_for_call(p, n_batch, s_end - s_begin)) {
+    e = prepare(q);
+    if (e != QF_OK) return e;
+    return enqueue_call(q, n_batch, bits_dev, s_begin, s_end, out_dev, true);
+  }
+  e = prepare(p);
   if (e != QF_OK) return e;
   if (p->G > 1) return amplitudes_batched(p, n_batch, bits_dev, s_begin, s_end, out_dev);
   int64_t fault_after = -1;
-  if (const char* f = std::getenv("QFMI_FAULT_AFTER_SLICES")) fault_after = std::atoll(f);
+  if (fault) fault_after = std::atoll(fault);
   const int n = p->n;
   const int k = (int)p->open.size();
   int64_t done = 0;
@@ -1695,13 +1796,18 @@ extern "C" qf_status qf_backward(qf_plan* p, int n_batch, const uint8_t* bits_de
   if (!c->ws || c->ws_bytes < p->arena_end)
     return fail(c, QF_ERR_WORKSPACE, "workspace too small: need " + std::to_string(p->arena_end) + " bytes");
   if (n_batch == 0 || s_begin == s_end) return QF_OK;
+  bool batched = p->G > 1;
+  if (qf_plan* q = trace_on() ? nullptr : multi_for_call(p, n_batch, s_end - s_begin)) {
+    p = q;
+    batched = true;
+  }
   qf_status e = prepare(p);
   if (e != QF_OK) return e;
   QF_HIP(c, launch_zero(c->stream, c->ws + p->off_envwl, align_up(p->wl_elems * sizeof(float2))));
   const int n = p->n;
   const int k = (int)p->open.size();
   const int S_steps = (int)p->steps.size();
-  if (p->G > 1) {
+  if (batched) {
     const int64_t s_range = s_end - s_begin;
     const int64_t n_chains = (int64_t)n_batch * s_range;
     for (int64_t g = 0; g < (n_chains + p->G - 1) / p->G; ++g) {

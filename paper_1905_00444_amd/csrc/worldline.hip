@@ -420,23 +420,29 @@ hipError_t launch_chain_begin(hipStream_t st, const ChainGroup& grp, int n_leave
   return hipGetLastError();
 }
 
+// Chains of one bitstring add in order (g ascending) into one running FP64 value: block y = g starts such
+// a run, or has nothing to do if its bitstring is the previous chain's.
 __global__ void __launch_bounds__(256)
 slice_accumulate_batched_kernel(const float2* __restrict__ root, AccArgs a, int G, const int32_t* __restrict__ chain_b,
                                 double2* __restrict__ out, const NodeScale* __restrict__ root_scale) {
+  const int g0 = blockIdx.y;
+  const int32_t b = chain_b[g0];
+  if (b < 0 || (g0 > 0 && chain_b[g0 - 1] == b)) return;
+  int g1 = g0 + 1;
+  while (g1 < G && chain_b[g1] == b) ++g1;
   const int64_t n = (int64_t)1 << a.k;
   const double f = root_scale ? ldexp(1.0, root_scale->slot[0].e) : 1.0;
   for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < n; j += (int64_t)gridDim.x * blockDim.x) {
     int64_t src = 0;
     for (int t = 0; t < a.k; ++t) src |= ((j >> t) & 1) << a.pos[t];
-    for (int g = 0; g < G; ++g) {
-      const int32_t b = chain_b[g];
-      if (b < 0) continue;
+    double2 o = out[((int64_t)b << a.k) + j];
+#pragma unroll 8
+    for (int g = g0; g < g1; ++g) {
       const float2 v = root[(int64_t)g * n + src];
-      double2 o = out[((int64_t)b << a.k) + j];
       o.x += (double)v.x * f;
       o.y += (double)v.y * f;
-      out[((int64_t)b << a.k) + j] = o;
     }
+    out[((int64_t)b << a.k) + j] = o;
   }
 }
 
@@ -448,7 +454,7 @@ hipError_t launch_slice_accumulate_batched(hipStream_t st, const float2* root, i
   const int64_t n = (int64_t)1 << k;
   unsigned blocks = (unsigned)((n + 255) / 256);
   if (blocks > 1024) blocks = 1024;
-  hipLaunchKernelGGL(slice_accumulate_batched_kernel, dim3(blocks), dim3(256), 0, st, root, a, G, chain_b, out,
+  hipLaunchKernelGGL(slice_accumulate_batched_kernel, dim3(blocks, (unsigned)G), dim3(256), 0, st, root, a, G, chain_b, out,
                      root_scale);
   return hipGetLastError();
 }

@@ -221,6 +221,30 @@ def test_cgemm_variant_argument_checks_without_device():
     lib.qf_ctx_destroy(ctx)
 
 
+@pytest.mark.parametrize("precision,depth,batched", [(0, 16, True), (1, 16, True), (2, 16, False), (0, 40, False)])
+def test_call_workspace_of_one_chain_plans(precision, depth, batched):
+    """Calls of several chains may use more than workspace_bytes where chains run together: small tensors,
+    FP32 and split-BF16.  One chain never does."""
+    lib, ctx = _host_ctx()
+    c = generate(4, 4, 16, 0) if depth == 16 else generate(7, 7, depth, 0)
+    plan = sweep_plan(c) if depth == 16 else plan_7x7(c, depth)[0]
+    st, ch = _circuit(lib, ctx, c)
+    st, ph = _plan(lib, ctx, ch, plan, precision)
+    assert st == 0
+    inf = _lib.qf_plan_info()
+    assert lib.qf_plan_info_get(ph, C.byref(inf)) == 0
+    n = C.c_size_t()
+    for nb, ns, more in ((0, 1, False), (1, 1, False), (1, 2, batched), (3, 1, batched)):
+        assert lib.qf_plan_call_workspace(ph, nb, ns, C.byref(n)) == 0
+        assert (n.value > inf.workspace_bytes) == more
+        assert n.value >= inf.workspace_bytes
+    assert lib.qf_plan_call_workspace(ph, -1, 1, C.byref(n)) == _lib.QF_ERR_ARG
+    assert lib.qf_plan_call_workspace(ph, 1, 1, None) == _lib.QF_ERR_ARG
+    lib.qf_plan_destroy(ph)
+    lib.qf_circuit_destroy(ch)
+    lib.qf_ctx_destroy(ctx)
+
+
 def test_single_qubit_circuit_is_refused():
     """A one-qubit grid has no network to contract: the circuit is refused with a clear status."""
     lib, ctx = _host_ctx()

@@ -87,6 +87,36 @@ def test_group_hoisting_matches_sequential_and_state_vector(ctx, precision, G):
     assert bp.flops(0, S) < S * bp.info()["flops_per_slice"]
 
 
+@pytest.mark.parametrize("precision", ["fp32", "bf16x3"])
+@pytest.mark.parametrize("cuts,hoist,n,rng", [(True, True, 3, (0, 16)), (True, True, 1, (3, 10)), (True, False, 5, (2, 5)),
+                                              (False, True, 7, (0, 1)), (False, True, 70, (0, 1))])
+def test_call_of_several_chains_equals_single_chains_bitwise(precision, cuts, hoist, n, rng):
+    """A one-chain plan runs a call of several chains with several per launch: the same bits as one call
+    per bitstring and slice."""
+    import torch
+    from paper_1905_00444_amd import Context, Circuit, Plan
+    _say(f"several chains per call {precision} cuts {cuts} hoist {hoist} n {n} slices {rng}")
+    c, plan = _setup_4x5()
+    if not cuts:
+        c = generate(4, 5, 16, 2)
+        plan, _ = region_plan(c, 2, 2, [], [(3, 4), (2, 4)])
+    bits = random_bitstrings(n, 20, 8)
+    one = Context(0)
+    seq = Plan(one, Circuit(one, c.to_text()), plan, precision, hoist=hoist)
+    want = torch.zeros((n, 4), dtype=torch.complex128, device="cuda")
+    for b in range(n):
+        for s in range(*rng):
+            seq.amplitudes(bits[b:b + 1], s, s + 1, out=want[b:b + 1])
+    many = Context(0)
+    p = Plan(many, Circuit(many, c.to_text()), plan, precision, hoist=hoist)
+    got = p.amplitudes(bits, *rng)
+    again = p.amplitudes(bits[:1], *rng)  # fewer chains on the same layout
+    torch.cuda.synchronize()
+    assert many.ws.numel() > one.ws.numel()
+    assert np.array_equal(got.cpu().numpy(), want.cpu().numpy())
+    assert np.array_equal(again.cpu().numpy(), want[:1].cpu().numpy())
+
+
 def test_batched_tail_and_slice_subrange(ctx):
     """Chains that do not fill the last group are masked; slice sub-ranges compose.  Group
     hoisting puts each bitstring's slices in groups of their own (7 slices of 3 bitstrings in
