@@ -669,8 +669,8 @@ int cgemm_default_variant(int precision, int64_t M, int64_t N, int64_t K, int64_
     return GEMM_LARGE;
   // a few dot products: a workgroup each; very long ones are spread further by the tiles' split K
   if (M * N <= 64 && K >= 32 && K <= (1 << 17)) return GEMM_SPLITK;
-  // short K: the FP32 tiles would multiply zeros
-  if (K < 32 && cgemm_variant_fits(precision, M, N, K, GEMM_SKINNY)) return GEMM_SKINNY;
+  // short K or N: the FP32 tiles would multiply zeros
+  if ((K < 16 || (K < 32 && N < 32)) && cgemm_variant_fits(precision, M, N, K, GEMM_SKINNY)) return GEMM_SKINNY;
   if (K < 8 || M * N * K < 4096) return GEMM_SIMT;
   return GEMM_F32;
 }
@@ -715,6 +715,26 @@ size_t cgemm_split_scratch(int precision, int64_t M, int64_t N, int64_t K, int64
   if (variant == GEMM_AUTO) variant = cgemm_default_variant(precision, M, N, K);
   const int split = split_count(variant, M, N, K);
   return split > 1 ? (size_t)split * (size_t)(batch * M * N) * sizeof(float2) : 0;
+}
+
+size_t env_gemm_scratch(int side, int64_t M, int64_t N, int64_t K, int64_t batch) {
+  const int64_t rows = side ? N : M;
+  const int split = split_count(GEMM_F32, rows, K, side ? M : N);
+  return split > 1 ? (size_t)split * (size_t)(batch * rows * K) * sizeof(float2) : 0;
+}
+
+hipError_t launch_env_gemm(hipStream_t st, int side, int64_t M, int64_t N, int64_t K, const float2* env,
+                           const float2* other, float2* out, int64_t batch, const Renorm& map, float2* scratch,
+                           size_t scratch_bytes) {
+  const int64_t rows = side ? N : M;
+  int split = scratch ? split_count(GEMM_F32, rows, K, side ? M : N) : 1;
+  if (env_gemm_scratch(side, M, N, K, batch) > scratch_bytes) split = 1;
+  const hipError_t e = launch_cgemm_f32_env(st, side, M, N, K, env, other, out, batch, map, &split, scratch);
+  if (e != hipSuccess || split == 1) return e;
+  const unsigned blocks = (unsigned)std::min<int64_t>((batch * rows * K + kReduceOut - 1) / kReduceOut, 65536);
+  hipLaunchKernelGGL(cgemm_split_reduce, dim3(blocks), dim3(256), 0, st, scratch, split, batch, rows * K, K, rows * K,
+                     out, Renorm{});
+  return hipGetLastError();
 }
 
 hipError_t launch_cgemm_ex(hipStream_t st, int precision, int64_t M, int64_t N, int64_t K, const float2* A,

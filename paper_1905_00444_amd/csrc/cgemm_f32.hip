@@ -48,12 +48,15 @@ struct F32Args {
   int64_t batch, sa, sb, sc;  // batch strides
   int64_t kc;            // k per chunk
   float2* P;             // partial tiles [chunk][batch][M][N] when gridDim.y > 1
+  Renorm amap;           // MAPA: A is another product's result under its output map (om_*)
   Renorm rn;
 };
 
 // Loads of one operand tile (ROWS x 16 complex) into registers: pairs of neighbours along the
 // contiguous index.  T = 0: k contiguous, 8 threads per row; T = 1: rows contiguous.
-template <int ROWS, int NTH, int T, bool EDGE>
+// MAP: the operand is a result X[x][y] under an output map (or plain, om_nh = 0), read with its y along k
+// (T = 0) or along the rows (T = 1); the runs of y are at least 8 elements long, so a pair stays together.
+template <int ROWS, int NTH, int T, bool EDGE, bool MAP>
 struct F32Loader {
   static constexpr int pairs = ROWS * kFBK / 2;
   static constexpr int per = (pairs + NTH - 1) / NTH;
@@ -61,7 +64,15 @@ struct F32Loader {
   const float2* p[per];
   int row[per], k[per];   // of the pair's first element
   float4 r[per];
+  const float2* mbase;    // MAP: the operand's start, the tile's first row and k
+  int64_t mrow, mk;
 
+  __device__ __forceinline__ void init_map(const float2* base, int64_t row0, int64_t k0) {
+    mbase = base;
+    mrow = row0;
+    mk = k0;
+    init(base, 0, 0);
+  }
   __device__ __forceinline__ void init(const float2* base, int64_t ld, int64_t k0) {
 #pragma unroll
     for (int i = 0; i < per; ++i) {
@@ -78,11 +89,17 @@ struct F32Loader {
     }
   }
   // Tile at kt (k relative to the chunk); rows_left / k_left: elements that exist (EDGE).
-  __device__ __forceinline__ void load(int64_t kt, int64_t ld, int64_t rows_left, int64_t k_left) {
+  __device__ __forceinline__ void load(int64_t kt, int64_t ld, int64_t rows_left, int64_t k_left, const Renorm& map) {
 #pragma unroll
     for (int i = 0; i < per; ++i) {
       if (partial && (int)threadIdx.x + i * NTH >= pairs) continue;
-      const float2* q = p[i] + (T == 0 ? kt : kt * ld);
+      const float2* q;
+      if constexpr (MAP) {
+        const int64_t x = T == 0 ? mrow + row[i] : mk + kt + k[i], y = T == 0 ? mk + kt + k[i] : mrow + row[i];
+        q = mbase + (c_row(map, x, ld) + c_col(map, y));
+      } else {
+        q = p[i] + (T == 0 ? kt : kt * ld);
+      }
       if constexpr (!EDGE) {
         r[i] = *reinterpret_cast<const float4*>(q);
       } else {
@@ -212,9 +229,11 @@ cgemm_f32(F32Args g) {
   const int wr = (wave / WN) * (16 * TM), wc = (wave % WN) * (16 * TN);
   const int l16 = lane & 15, lg = lane >> 4;
 
-  F32Loader<BM, NTH, TA, EDGE> la;
-  F32Loader<BN, NTH, TB, EDGE> lb;
-  la.init(g.A + batch * g.sa + (TA == 0 ? m0 * g.lda : m0), g.lda, k0);
+  constexpr bool MAPA = TB == 1;
+  F32Loader<BM, NTH, TA, EDGE, MAPA> la;
+  F32Loader<BN, NTH, TB, EDGE, false> lb;
+  if constexpr (MAPA) la.init_map(g.A + batch * g.sa, m0, k0);
+  else la.init(g.A + batch * g.sa + (TA == 0 ? m0 * g.lda : m0), g.lda, k0);
   lb.init(g.B + batch * g.sb + (TB == 0 ? n0 * g.ldb : n0), g.ldb, k0);
   const int64_t ml = g.M - m0, nl = g.N - n0;  // rows and columns that exist from the tile's first on
 
@@ -229,8 +248,8 @@ cgemm_f32(F32Args g) {
 
   const int nk = (int)((klen + kFBK - 1) / kFBK);
   auto fetch = [&](int t) {
-    la.load((int64_t)t * kFBK, g.lda, ml, klen);
-    lb.load((int64_t)t * kFBK, g.ldb, nl, klen);
+    la.load((int64_t)t * kFBK, g.lda, ml, klen, g.amap);
+    lb.load((int64_t)t * kFBK, g.ldb, nl, klen, g.amap);
   };
   auto stage = [&](int t) {
     float* st = lds + (t & 1) * Tile::stage;
@@ -305,22 +324,44 @@ static void f32_pick(hipStream_t st, const F32Args& g, int split, int want) {
   }
 }
 
-hipError_t launch_cgemm_f32(hipStream_t st, int64_t M, int64_t N, int64_t K, const float2* A, const float2* B,
-                            float2* C, int64_t batch, int64_t sa, int64_t sb, int64_t sc, const Renorm& rn, int* split,
-                            float2* P, int tile, int ta, int tb, int conj_b) {
+static hipError_t f32_args(F32Args& g, int64_t M, int64_t N, int64_t K, const float2* A, const float2* B, float2* C,
+                           int64_t batch, int64_t sa, int64_t sb, int64_t sc, const Renorm& rn, int* split, float2* P) {
   if (M < 1 || N < 1 || K < 1 || batch < 1 || *split < 1) return hipErrorInvalidValue;
-  F32Args g;
   g.M = M; g.N = N; g.K = K;
   g.A = A; g.B = B; g.C = C;
-  g.lda = ta ? M : K;
-  g.ldb = tb ? N : K;
   g.batch = batch; g.sa = sa; g.sb = sb; g.sc = sc;
   g.kc = *split > 1 ? ((K + *split - 1) / *split + kFBK - 1) / kFBK * kFBK : K;
   *split = (int)((K + g.kc - 1) / g.kc);  // whole K-tiles per chunk: every chunk holds some of K
   g.P = P;
   g.rn = rn;
-  if (ta == 0 && tb == 0 && !conj_b) f32_pick<0, 0, false>(st, g, *split, tile);
-  else return hipErrorInvalidValue;
+  return hipSuccess;
+}
+
+hipError_t launch_cgemm_f32(hipStream_t st, int64_t M, int64_t N, int64_t K, const float2* A, const float2* B,
+                            float2* C, int64_t batch, int64_t sa, int64_t sb, int64_t sc, const Renorm& rn, int* split,
+                            float2* P, int tile) {
+  F32Args g;
+  const hipError_t e = f32_args(g, M, N, K, A, B, C, batch, sa, sb, sc, rn, split, P);
+  if (e != hipSuccess) return e;
+  g.lda = K;
+  g.ldb = K;
+  f32_pick<0, 0, false>(st, g, *split, tile);
+  return hipGetLastError();
+}
+
+hipError_t launch_cgemm_f32_env(hipStream_t st, int side, int64_t M, int64_t N, int64_t K, const float2* env,
+                                const float2* other, float2* out, int64_t batch, const Renorm& map, int* split,
+                                float2* P) {
+  // out[rows][K] = sum over the other index of env and conj(other): rows = M (side 0) or N (side 1)
+  F32Args g;
+  const int64_t rows = side ? N : M, sum = side ? M : N;
+  const hipError_t e = f32_args(g, rows, K, sum, env, other, out, batch, M * N, sum * K, rows * K, Renorm{}, split, P);
+  if (e != hipSuccess) return e;
+  g.lda = N;  // env's plain row pitch
+  g.ldb = K;
+  g.amap = map;
+  if (side) f32_pick<1, 1, true>(st, g, *split, F32_AUTO);
+  else f32_pick<0, 1, true>(st, g, *split, F32_AUTO);
   return hipGetLastError();
 }
 

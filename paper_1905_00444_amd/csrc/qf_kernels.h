@@ -212,11 +212,22 @@ hipError_t launch_cgemm_ex(hipStream_t st, int precision, int64_t M, int64_t N, 
                            const float2* B, float2* C, int64_t batch, int64_t sa, int64_t sb, int64_t sc,
                            const uint32_t* amaxA, const uint32_t* amaxB, const Renorm& rn = Renorm{},
                            int variant = GEMM_AUTO, float2* scratch = nullptr, size_t scratch_bytes = 0);
-// FP32 MFMA product of any shape (cgemm_f32.hip).  ta / tb: 0 if the operand lies [row][k], 1 if it lies
-// [k][row]; conj_b: conjugate B.  *split: K-chunks wanted, set to those used (partials in P).
+// FP32 MFMA product of any shape (cgemm_f32.hip).  *split: K-chunks wanted, set to those used (partials
+// in P, summed by launch_split_reduce).
 hipError_t launch_cgemm_f32(hipStream_t st, int64_t M, int64_t N, int64_t K, const float2* A, const float2* B,
                             float2* C, int64_t batch, int64_t sa, int64_t sb, int64_t sc, const Renorm& rn, int* split,
-                            float2* P, int tile = F32_AUTO, int ta = 0, int tb = 0, int conj_b = 0);
+                            float2* P, int tile = F32_AUTO);
+// Environments of a product C[M][N] = sum_K A[M][K] B[N][K] from that of C (env, under C's output map), in FP32
+// without transposed copies: side 0: out[M][K] = sum_n env[m][n] conj(other[n][k]) with other = B; side 1:
+// out[N][K] = sum_m env[m][n] conj(other[m][k]) with other = A.  Dense batch strides.
+hipError_t launch_cgemm_f32_env(hipStream_t st, int side, int64_t M, int64_t N, int64_t K, const float2* env,
+                                const float2* other, float2* out, int64_t batch, const Renorm& map, int* split,
+                                float2* P);
+// The same with the split of K that the shape asks for, given the scratch (cgemm.hip).
+hipError_t launch_env_gemm(hipStream_t st, int side, int64_t M, int64_t N, int64_t K, const float2* env,
+                           const float2* other, float2* out, int64_t batch, const Renorm& map, float2* scratch,
+                           size_t scratch_bytes);
+size_t env_gemm_scratch(int side, int64_t M, int64_t N, int64_t K, int64_t batch);
 // Tall-skinny kernel (cgemm_tall.hip): powers of two, 8 <= N <= 64, 16 <= K <= 64.
 bool cgemm_tall_fits(int precision, int64_t M, int64_t N, int64_t K);
 hipError_t launch_cgemm_tall(hipStream_t st, int precision, int64_t M, int64_t N, int64_t K, const float2* A,

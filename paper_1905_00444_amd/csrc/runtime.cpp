@@ -413,6 +413,12 @@ static bool operand_invariant(const qf_plan* p, const Operand& op) {
 }
 static int operand_batch(const qf_plan* p, const Operand& op) { return operand_invariant(p, op) ? 1 : p->G; }
 
+// FP32 backward plans: the environment of an operand that the step reads in place is that of its node, and
+// the environment GEMM writes it there.
+static bool env_direct(const qf_plan* p, const Operand& op) {
+  return p->precision == QF_FP32 && !op.permute && !p->nodes[op.node].leaf;
+}
+
 // Offsets of everything a plan keeps in the workspace, and the gather jobs that use them.
 static void layout_arena(qf_plan* p, size_t n_ops) {
   const int n = p->n;
@@ -469,10 +475,12 @@ static void layout_arena(qf_plan* p, size_t n_ops) {
     for (int i = 0; i < S; ++i) {
       const Step& st = p->steps[i];
       const size_t va = sizeof(float2) << st.A.nbits, vb = sizeof(float2) << st.B.nbits;
-      max_q = std::max({max_q, va, vb});
-      max_c = std::max(max_c, sizeof(float2) << (st.m_bits + st.n_bits));
-      max_a = std::max(max_a, va);
-      max_b = std::max(max_b, vb);
+      if (p->precision != QF_FP32) {  // transposed copies
+        max_q = std::max({max_q, va, vb});
+        max_c = std::max(max_c, sizeof(float2) << (st.m_bits + st.n_bits));
+      }
+      if (!env_direct(p, st.A)) max_a = std::max(max_a, va);
+      if (!env_direct(p, st.B)) max_b = std::max(max_b, vb);
     }
     const size_t G = (size_t)p->G;  // per chain in batched backward plans
     pers.push_back({align_up(p->wl_elems * sizeof(float2)), 0, S, &p->off_envwl});
@@ -774,7 +782,7 @@ static qf_status build_plan(qf_ctx* ctx, qf_circuit* circ, const qf_plan_desc* d
     for (int lab : Y->labels) if (!contains(K, lab)) ywant.push_back(lab);
     out_node.labels = xwant;
     out_node.labels.insert(out_node.labels.end(), ywant.begin(), ywant.end());
-    if (!p->backward) {
+    if (!p->backward || p->precision == QF_FP32) {
       // an intermediate whose contracted labels already trail in korder's order is read in place
       auto in_place = [&](const Node* nd) {
         return !nd->leaf && std::equal(nd->labels.end() - K.size(), nd->labels.end(), korder.begin());
@@ -837,7 +845,9 @@ static qf_status build_plan(qf_ctx* ctx, qf_circuit* circ, const qf_plan_desc* d
     for (const Step& st : p->steps) {
       const int64_t M = (int64_t)1 << st.m_bits, N = (int64_t)1 << st.n_bits, K = (int64_t)1 << st.k_bits;
       if (!st.presplit) need = std::max(need, cgemm_split_scratch(p->precision, M, N, K, p->G));
-      if (p->backward) {
+      if (p->backward && p->precision == QF_FP32) {
+        need = std::max({need, env_gemm_scratch(0, M, N, K, p->G), env_gemm_scratch(1, M, N, K, p->G)});
+      } else if (p->backward) {
         need = std::max(need, cgemm_split_scratch(p->precision, M, K, N, p->G));
         need = std::max(need, cgemm_split_scratch(p->precision, N, K, M, p->G));
       }
@@ -1732,6 +1742,23 @@ static qf_status route_env_batched(qf_plan* p, const Operand& op, const float2* 
   return QF_OK;
 }
 
+// Environments of step i's two operands from that of its result, FP32: both products read their operands as
+// they lie (the result's environment through its output map), and write the operand's node where the
+// step reads that in place; else to EA / EB, from where route_env carries them.
+static qf_status env_fp32(qf_plan* p, const Step& st, const float2* envC, const float2* Aop, const float2* Bop, int64_t G,
+                          float2* EA, float2* EB) {
+  qf_ctx* c = p->ctx;
+  const int64_t M = (int64_t)1 << st.m_bits, N = (int64_t)1 << st.n_bits, K = (int64_t)1 << st.k_bits;
+  Renorm map;
+  map.om_q = st.om_q;
+  map.om_nh = st.om_nh;
+  map.om_nl = st.n_bits - st.om_nh;
+  float2* scratch = p->gscratch_bytes ? wsp(c, p->off_gscratch) : nullptr;
+  QF_HIP(c, launch_env_gemm(c->stream, 0, M, N, K, envC, Bop, EA, G, map, scratch, p->gscratch_bytes));
+  QF_HIP(c, launch_env_gemm(c->stream, 1, M, N, K, envC, Aop, EB, G, map, scratch, p->gscratch_bytes));
+  return QF_OK;
+}
+
 static qf_status backward_group(qf_plan* p, const uint8_t* bits_dev, const double* cot_dev, int64_t s_begin,
                                 int64_t s_range, int64_t chain0, int64_t n_chains) {
   qf_ctx* c = p->ctx;
@@ -1749,7 +1776,7 @@ static qf_status backward_group(qf_plan* p, const uint8_t* bits_dev, const doubl
     e = run_operand_batched(p, st.B, &B);
     if (e != QF_OK) return e;
     const int64_t M = (int64_t)1 << st.m_bits, N = (int64_t)1 << st.n_bits, K = (int64_t)1 << st.k_bits;
-    e = plan_gemm(p, M, N, K, A, B, wsp(c, p->nodes[n + i].offset), G);
+    e = plan_gemm(p, M, N, K, A, B, wsp(c, p->nodes[n + i].offset), G, step_renorm(p, i));
     if (e != QF_OK) return e;
   }
   const Node& root = p->nodes.back();
@@ -1766,6 +1793,15 @@ static qf_status backward_group(qf_plan* p, const uint8_t* bits_dev, const doubl
     const float2* Bop = wsp(c, st.B.permute ? st.B.buf : p->nodes[st.B.node].offset);
     const int64_t M = (int64_t)1 << st.m_bits, N = (int64_t)1 << st.n_bits, K = (int64_t)1 << st.k_bits;
     // env(A)[m][k] = sum_n env(C)[m][n] conj(B[n][k]); env(B)[n][k] = sum_m env(C)[m][n] conj(A[m][k])
+    if (p->precision == QF_FP32) {
+      const bool da = env_direct(p, st.A), db = env_direct(p, st.B);
+      qf_status e = env_fp32(p, st, envC, Aop, Bop, G, da ? wsp(c, p->nodes[st.A.node].env) : EA,
+                             db ? wsp(c, p->nodes[st.B.node].env) : EB);
+      if (e == QF_OK && !da) e = route_env_batched(p, st.A, EA);
+      if (e == QF_OK && !db) e = route_env_batched(p, st.B, EB);
+      if (e != QF_OK) return e;
+      continue;
+    }
     qf_status e = batched_transpose(p, st.n_bits, st.k_bits, 1, Bop, Q);
     if (e != QF_OK) return e;
     e = plan_gemm(p, M, K, N, envC, Q, EA, G);
@@ -1845,6 +1881,15 @@ extern "C" qf_status qf_backward(qf_plan* p, int n_batch, const uint8_t* bits_de
         const float2* Aop = wsp(c, st.A.permute ? st.A.buf : p->nodes[st.A.node].offset);
         const float2* Bop = wsp(c, st.B.permute ? st.B.buf : p->nodes[st.B.node].offset);
         const int64_t M = (int64_t)1 << st.m_bits, N = (int64_t)1 << st.n_bits, K = (int64_t)1 << st.k_bits;
+        if (p->precision == QF_FP32) {
+          const bool da = env_direct(p, st.A), db = env_direct(p, st.B);
+          e = env_fp32(p, st, envC, Aop, Bop, 1, da ? wsp(c, p->nodes[st.A.node].env) : EA,
+                       db ? wsp(c, p->nodes[st.B.node].env) : EB);
+          if (e == QF_OK && !da) e = route_env(p, st.A, EA, row, s);
+          if (e == QF_OK && !db) e = route_env(p, st.B, EB, row, s);
+          if (e != QF_OK) return e;
+          continue;
+        }
         PermuteArgs a;
         // env(A)[m][k] = sum_n env(C)[m][n] conj(B[n][k])
         transpose_args(st.n_bits, st.k_bits, 1, &a);

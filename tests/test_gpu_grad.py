@@ -60,6 +60,26 @@ def test_grad_4x4_d16_norm_loss_vs_adjoint_oracle(ctx):
     assert rel_err(g.cpu().numpy(), ref) <= 1e-4
 
 
+@pytest.mark.parametrize("batch", [1, 4])
+@pytest.mark.parametrize("rows,cols,depth,n", [(3, 2, 9, 1), (3, 3, 12, 5), (2, 5, 24, 2), (4, 3, 31, 3), (4, 4, 24, 2)])
+def test_grad_small_grids_vs_adjoint_oracle(ctx, rows, cols, depth, n, batch):
+    """Sweeps whose environment products run from 1 x 2 x 2 up to 2^9 x 2^6 x 2^6, with results under output
+    maps: FP32 over at most 2 x 15 products of up to 2^6 terms, 30 x 8 x 2^-24 = 1.4e-5 norm-wise."""
+    import torch
+    from paper_1905_00444_amd import Circuit, Plan
+    _say(f"grad {rows}x{cols} d{depth} n {n} batch {batch}")
+    c = generate(rows, cols, depth, 3)
+    text = c.to_text()
+    bits = random_bitstrings(n, rows * cols, 11)
+    rng = np.random.default_rng(4)
+    cot = rng.normal(size=(n, 1)) + 1j * rng.normal(size=(n, 1))
+    p = Plan(ctx, Circuit(ctx, text), sweep_plan(c, by="row" if cols <= rows else "col"), "fp32", backward=True, batch=batch)
+    g = p.backward(bits, cot)
+    torch.cuda.synchronize()
+    ref = _oracle_grad(text, bits, cot[:, 0])
+    assert rel_err(g.cpu().numpy(), ref) <= 2e-5
+
+
 def test_grad_4x5_d32_cuts_open_random_cotangent(ctx):
     import torch
     from paper_1905_00444_amd import Circuit, Plan
