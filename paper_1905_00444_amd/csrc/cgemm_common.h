@@ -188,6 +188,31 @@ struct BExpand {
   }
 };
 
+// Bitstring b (-1: idle) and slice s of chain g.
+__device__ __forceinline__ void chain_of(const ChainGroup& c, int g, int64_t& b, int64_t& s) {
+  int64_t off;  // slice offset in the range
+  if (c.gpb > 0) {
+    const int64_t q = c.chain0 / c.G;
+    b = q / c.gpb;
+    off = (q - b * c.gpb) * c.G + g;
+    if (b * c.s_range >= c.n_chains || off >= c.s_range) b = -1;
+  } else {
+    const int64_t k = c.chain0 + g;
+    b = k < c.n_chains ? k / c.s_range : -1;
+    off = k - b * c.s_range;
+  }
+  s = c.s_begin + off;
+}
+
+// World-line offset of the bits that chain (b, s) fixes; 0 for an idle chain.
+__device__ __forceinline__ int64_t leaf_base(const ChainGroup& c, const LeafDesc& d, int64_t b, int64_t s) {
+  if (b < 0) return 0;
+  int64_t base = 0;
+  for (int i = 0; i < d.n_cut; ++i) base |= ((s >> d.shift[i]) & 1) << d.pos[i];
+  if (d.xpos >= 0) base |= (int64_t)(c.bits[b * c.n_qubits + d.qubit] & 1) << d.xpos;
+  return base;
+}
+
 // Clears c's amax before a renormalised GEMM raises it (cgemm.hip).
 hipError_t launch_renorm_reset(hipStream_t st, NodeScale* c);
 

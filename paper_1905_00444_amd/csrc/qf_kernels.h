@@ -167,10 +167,45 @@ struct StepMask { uint64_t w[kMaxChainSteps / 64]; };
 hipError_t launch_chain_begin(hipStream_t st, const ChainGroup& grp, int n_leaves, const LeafDesc* leaves,
                               int64_t* base_table, int32_t* chain_b, int n_steps, const StepMask& run, NodeScale* scales,
                               const GatherJob* jobs, const GatherBlock* blocks, int n_blocks, const float2* wl, char* ws);
-// out[chain_b[g]][j] += root[g][sum_t bit_t(j) << pos[t]] for g = 0..G-1 in order (FP64).
-hipError_t launch_slice_accumulate_batched(hipStream_t st, const float2* root, int k, const int* pos, int G,
-                                           const int32_t* chain_b, double2* out,
-                                           const NodeScale* root_scale = nullptr);
+// out[chain_b[g]][j] += root[g root_stride + sum_t bit_t(j) << pos[t]] for g = 0..G-1 in order (FP64), times 2^e
+// of root_scale, or of chain g's own exponent if chain_e is given.
+hipError_t launch_slice_accumulate_batched(hipStream_t st, const float2* root, int64_t root_stride, int k, const int* pos,
+                                           int G, const int32_t* chain_b, double2* out,
+                                           const NodeScale* root_scale = nullptr, const int32_t* chain_e = nullptr);
+
+// Whole chains of small tensors, a workgroup each (small_chain.hip).
+constexpr int kSmallMaxBits = 11;    // elements of any operand or result
+constexpr int kSmallMaxSteps = 128;
+// Bit i of an index goes to bit pos(i) < 32 of an address: up to 12 positions of 5 bits, and their number.
+struct SmallBits {
+  uint64_t v;
+  __host__ __device__ int n() const { return (int)(v >> 60); }
+  __host__ __device__ int pos(int i) const { return (int)(v >> (5 * i)) & 31; }
+  void push(int p) { v = (v | (uint64_t)p << (5 * n())) + ((uint64_t)1 << 60); }
+};
+struct SmallStep {
+  int64_t off[2], c;      // elements: A, B (into the world-lines for leaves, else the chain's scratch), C
+  int32_t leaf[2];        // world-line index of A, B, or -1
+  int32_t node[2];
+  SmallBits am, ak, bn, bk, cm, cn;
+};
+struct SmallArgs {
+  ChainGroup grp;
+  const SmallStep* steps;
+  int n_steps, n_leaves;
+  const LeafDesc* leaves;
+  const float2* wl;
+  float2* scratch;        // chain_elems per chain
+  int64_t chain_elems;
+  int renorm;
+  int32_t *chain_b, *chain_e;
+  // backward: cotangents, the root's output bits, environments (world-lines'; nodes' behind the tensors)
+  const double2* cot;
+  SmallBits root;
+  float2* env_wl;
+  int64_t env;
+};
+hipError_t launch_small_chain(hipStream_t st, const SmallArgs& a, bool backward);
 
 // Split-BF16 GEMM on operands split by the permute (hi plane then lo plane per batch element), or
 // FP16 GEMM on operands scaled and converted by the permute (one plane); precision P_BF16X3 / P_FP16

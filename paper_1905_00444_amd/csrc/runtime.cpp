@@ -36,6 +36,9 @@ using namespace qf;
 static const size_t kCtxScratch = 4096;  // start of the workspace reserved for small slots
 static const size_t kAlign = 256;
 static constexpr size_t kStaticScratchBytes = (size_t)64 << 20;  // qf_amplitudes_static's array
+// Plans of small tensors, a workgroup per chain: chains per launch and their tensors' bytes at most.
+static constexpr int kSmallChains = 512;
+static constexpr size_t kSmallBytes = (size_t)32 << 20;
 
 static size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
@@ -187,6 +190,11 @@ struct qf_plan {
   std::vector<GatherBlock> job_blocks;
   size_t off_jobs = 0, off_blocks = 0;
   bool chain_begin = false;  // steps fit the launch's step mask
+  // plans of small tensors: whole chains in one launch (small_chain.hip)
+  bool small = false;
+  std::vector<SmallStep> small_steps;
+  int64_t small_elems = 0;                  // scratch elements per chain
+  size_t off_small = 0, off_small_steps = 0, off_small_b = 0, off_small_e = 0;
   hipGraphExec_t gexec = nullptr;
   hipGraph_t graph_obj = nullptr;
   std::vector<int64_t> graph_key;
@@ -413,6 +421,63 @@ static bool operand_invariant(const qf_plan* p, const Operand& op) {
 }
 static int operand_batch(const qf_plan* p, const Operand& op) { return operand_invariant(p, op) ? 1 : p->G; }
 
+// Plans whose chains run whole in one workgroup each, and their step descriptions: all operands and results
+// fit its LDS buffers (2^11 elements, so that two workgroups share a CU).  At that size a step still takes
+// 3 us, less than the launches it replaces: a 4x4 chain of depth 18 68 us against 109, of depth 8 40
+// against 109, 1000 of them 95 against 2014.  With buffers of 2^12 elements, one workgroup a CU and
+// twice the work a step, single chains were slower than launches (3x4, depth 24: 131 against 78).
+static void plan_small(qf_plan* p) {
+  const int n = p->n, S = (int)p->steps.size();
+  if (S < 1 || S > kSmallMaxSteps) return;
+  for (const Step& st : p->steps)
+    if (std::max({st.m_bits + st.k_bits, st.n_bits + st.k_bits, st.m_bits + st.n_bits}) > kSmallMaxBits) return;
+  for (int q = 0; q < n; ++q)
+    if (p->wl_qubits[q].nbond > 28) return;
+  // scratch: every result, then (backward plans) every result's environment
+  std::vector<int64_t> at(n + S, 0);
+  int64_t elems = 0;
+  for (int i = 0; i < S; ++i) {
+    at[n + i] = elems;
+    elems += (int64_t)1 << p->nodes[n + i].labels.size();
+  }
+  p->small_elems = p->backward ? 2 * elems : elems;
+  p->small_steps.assign(S, SmallStep());
+  for (int i = 0; i < S; ++i) {
+    const Step& st = p->steps[i];
+    SmallStep& d = p->small_steps[i];
+    std::memset(&d, 0, sizeof(d));
+    const int ids[2] = {st.A.node, st.B.node};
+    // storage order of a tensor, most significant first: a world-line keeps its fixed bits
+    auto order = [&](int id) -> const std::vector<int>& {
+      return id < n ? p->leaf_full_labels[p->nodes[id].qubit] : p->nodes[id].labels;
+    };
+    auto bits = [&](const std::vector<int>& labels, const std::vector<int>& in) {  // labels, least significant first
+      SmallBits b = {0};
+      for (int lab : labels) b.push((int)(in.end() - std::find(in.begin(), in.end(), lab)) - 1);
+      return b;
+    };
+    std::vector<int> m, nn, k;
+    const Node &A = p->nodes[ids[0]], &B = p->nodes[ids[1]];
+    for (auto it = A.labels.rbegin(); it != A.labels.rend(); ++it) (contains(B.labels, *it) ? k : m).push_back(*it);
+    for (auto it = B.labels.rbegin(); it != B.labels.rend(); ++it)
+      if (!contains(A.labels, *it)) nn.push_back(*it);
+    d.am = bits(m, order(ids[0]));
+    d.ak = bits(k, order(ids[0]));
+    d.bn = bits(nn, order(ids[1]));
+    d.bk = bits(k, order(ids[1]));
+    d.cm = bits(m, p->nodes[n + i].labels);
+    d.cn = bits(nn, p->nodes[n + i].labels);
+    d.c = at[n + i];
+    for (int r = 0; r < 2; ++r) {
+      const bool leaf = ids[r] < n;
+      d.leaf[r] = leaf ? p->nodes[ids[r]].qubit : -1;
+      d.node[r] = ids[r];
+      d.off[r] = leaf ? p->wl_qubits[p->nodes[ids[r]].qubit].out_offset : at[ids[r]];
+    }
+  }
+  p->small = true;
+}
+
 // FP32 backward plans: the environment of an operand that the step reads in place is that of its node, and
 // the environment GEMM writes it there.
 static bool env_direct(const qf_plan* p, const Operand& op) {
@@ -465,6 +530,13 @@ static void layout_arena(qf_plan* p, size_t n_ops) {
         }
     pers.push_back({align_up(n_jobs * sizeof(GatherJob)), 0, S, &p->off_jobs});
     pers.push_back({align_up(n_blocks * sizeof(GatherBlock)), 0, S, &p->off_blocks});
+  }
+  if (p->small) {
+    // one chain; more of them behind the arena where a call's workspace has room (small_room)
+    pers.push_back({align_up(p->small_elems * sizeof(float2)), 0, S, &p->off_small});
+    pers.push_back({align_up(p->small_steps.size() * sizeof(SmallStep)), 0, S, &p->off_small_steps});
+    pers.push_back({align_up(kSmallChains * sizeof(int32_t)), 0, S, &p->off_small_b});
+    pers.push_back({align_up(kSmallChains * sizeof(int32_t)), 0, S, &p->off_small_e});
   }
   if (p->G > 1) {
     pers.push_back({align_up((size_t)p->G * n * sizeof(int64_t)), 0, S, &p->off_btable});
@@ -896,6 +968,8 @@ static qf_status build_plan(qf_ctx* ctx, qf_circuit* circ, const qf_plan_desc* d
     }
   }
 
+  plan_small(p.get());
+
   // ---- world-line operands copied at the start of a chain.  Their buffers then live from the first step
   // on; a plan that fits the library's static scratch only with shorter lifetimes keeps those
   p->chain_begin = (int)p->steps.size() <= kMaxChainSteps;
@@ -907,6 +981,10 @@ static qf_status build_plan(qf_ctx* ctx, qf_circuit* circ, const qf_plan_desc* d
     const size_t longer = p->arena_end;
     for (Step& st : p->steps) st.A.early = st.B.early = false;
     layout_arena(p.get(), circ->ops.size());
+    if (p->arena_end > kStaticScratchBytes && p->small) {
+      p->small = false;
+      layout_arena(p.get(), circ->ops.size());
+    }
     if (p->arena_end > kStaticScratchBytes && longer > kStaticScratchBytes) {
       for (Step& st : p->steps)
         for (Operand* op : {&st.A, &st.B})
@@ -991,6 +1069,13 @@ qf_status qf_plan_flops(const qf_plan* p, int64_t s_begin, int64_t s_end, double
   return QF_OK;
 }
 
+// Chains per launch of a call of `chains` chains on a plan of small tensors, as far as workspace goes: two
+// workgroups fit a CU's LDS, and 32 MiB keep the chains' tensors near the L2s.
+static size_t small_most(const qf_plan* p, int64_t chains) {
+  const size_t room = kSmallBytes / (p->small_elems * sizeof(float2));
+  return std::max<size_t>(1, std::min<size_t>({(size_t)kSmallChains, room, (size_t)chains}));
+}
+
 // The form of a one-chain plan that runs a call of several chains (bitstrings x slices) with G chains per
 // launch, or null: the same steps, roles and GEMM shapes, so that every chain's values are those of the
 // one-chain path bit by bit (backward sums excepted: chains add atomically), but one launch per step and
@@ -1006,7 +1091,7 @@ constexpr int kMultiChains = 64;
 static qf_plan* batch_form(qf_plan* p) {
   if (p->multi || p->multi_tried) return p->multi;
   p->multi_tried = true;
-  if (p->G != 1 || p->sequential_like || p->precision == QF_FP16) return nullptr;
+  if (p->G != 1 || p->sequential_like || p->precision == QF_FP16 || p->small) return nullptr;
   const size_t shared = p->off_wl + p->wl_elems * sizeof(float2);
   const size_t chain = p->arena_end > shared ? p->arena_end - shared : 1;
   int G = 1;
@@ -1042,6 +1127,10 @@ qf_status qf_plan_call_workspace(qf_plan* p, int n_batch, int64_t slices, size_t
   if (!p || !p->ctx || !p->circ || !bytes || n_batch < 0 || slices < 0) return QF_ERR_ARG;
   *bytes = p->arena_end;
   if ((int64_t)n_batch * slices < 2) return QF_OK;
+  if (p->small) {
+    if (p->precision != QF_FP16) *bytes += small_most(p, n_batch * slices) * (size_t)p->small_elems * sizeof(float2);
+    return QF_OK;
+  }
   const qf_plan* q = batch_form(p);
   if (q) *bytes = std::max(*bytes, q->arena_end);
   return QF_OK;
@@ -1126,6 +1215,8 @@ static hipEvent_t take_event(qf_ctx* c) {
   return e;
 }
 
+static bool trace_on();
+
 static qf_status build_worldlines(qf_plan* p) {
   qf_ctx* c = p->ctx;
   qf_circuit* circ = p->circ;
@@ -1140,6 +1231,9 @@ static qf_status build_worldlines(qf_plan* p) {
                              hipMemcpyHostToDevice, c->stream));
   QF_HIP(c, hipMemcpyAsync(c->ws + p->off_leafdesc, p->leaf_desc.data(), p->leaf_desc.size() * sizeof(LeafDesc),
                            hipMemcpyHostToDevice, c->stream));
+  if (p->small)
+    QF_HIP(c, hipMemcpyAsync(c->ws + p->off_small_steps, p->small_steps.data(), p->small_steps.size() * sizeof(SmallStep),
+                             hipMemcpyHostToDevice, c->stream));
   if (!p->jobs.empty()) {
     QF_HIP(c, hipMemcpyAsync(c->ws + p->off_jobs, p->jobs.data(), p->jobs.size() * sizeof(GatherJob),
                              hipMemcpyHostToDevice, c->stream));
@@ -1249,6 +1343,56 @@ static qf_status begin_chain(qf_plan* p, const ChainGroup& grp, const StepMask& 
                                reinterpret_cast<const GatherBlock*>(c->ws + p->off_blocks), (int)p->job_blocks.size(),
                                wsp(c, p->off_wl), c->ws));
   return QF_OK;
+}
+
+// Whole chains of a plan of small tensors; the event timing and tracing of single steps want the launches.
+static bool runs_small(const qf_plan* p) { return p->small && !p->ctx->profile && !trace_on(); }
+
+// Chains per launch that the workspace has room for.
+static int64_t small_room(const qf_plan* p, int64_t chains) {
+  const size_t behind = (p->ctx->ws_bytes - p->arena_end) / (p->small_elems * sizeof(float2));
+  return (int64_t)std::max<size_t>(1, std::min(behind, small_most(p, chains)));
+}
+
+// All chains of a call (bitstring-major) forward, or forward and in reverse.
+static qf_status small_call(qf_plan* p, int n_batch, const uint8_t* bits_dev, int64_t s_begin, int64_t s_end,
+                            double* out_dev, const double* cot_dev) {
+  qf_ctx* c = p->ctx;
+  const int64_t s_range = s_end - s_begin, chains = n_batch * s_range, G = small_room(p, chains);
+  SmallArgs a;
+  std::memset(&a, 0, sizeof(a));
+  a.steps = reinterpret_cast<const SmallStep*>(c->ws + p->off_small_steps);
+  a.n_steps = (int)p->small_steps.size();
+  a.n_leaves = p->n;
+  a.leaves = reinterpret_cast<const LeafDesc*>(c->ws + p->off_leafdesc);
+  a.wl = wsp(c, p->off_wl);
+  a.scratch = wsp(c, G > 1 ? p->arena_end : p->off_small);
+  a.chain_elems = p->small_elems;
+  a.renorm = p->renorm;
+  a.chain_b = reinterpret_cast<int32_t*>(c->ws + p->off_small_b);
+  a.chain_e = reinterpret_cast<int32_t*>(c->ws + p->off_small_e);
+  const int k = (int)p->open.size();
+  for (int t = 0; t < k; ++t) a.root.push(p->root_pos[t]);
+  a.cot = reinterpret_cast<const double2*>(cot_dev);
+  if (cot_dev) {
+    a.env_wl = wsp(c, p->off_envwl);
+    a.env = p->small_elems / 2;
+  }
+  for (int64_t g = 0; g < chains; g += G) {
+    a.grp = {g, (int)std::min(G, chains - g), p->n, bits_dev, s_begin, s_range, chains, 0};
+    QF_HIP(c, launch_small_chain(c->stream, a, cot_dev != nullptr));
+    if (cot_dev) continue;
+    QF_HIP(c, launch_slice_accumulate_batched(c->stream, a.scratch + p->small_steps.back().c, a.chain_elems, k,
+                                              p->root_pos.data(), a.grp.G, a.chain_b, reinterpret_cast<double2*>(out_dev),
+                                              nullptr, p->renorm ? a.chain_e : nullptr));
+  }
+  return QF_OK;
+}
+
+// Not where a single chain fits at a time and slices share the results of steps that no cut reaches.
+static bool call_runs_small(const qf_plan* p, int n_batch, int64_t slices) {
+  if (!runs_small(p)) return false;
+  return slices < 2 || (p->flags & QF_PLAN_NO_HOIST) || small_room(p, n_batch * slices) > 1;
 }
 
 static const StepMask kAllSteps = {{~0ull, ~0ull, ~0ull, ~0ull}};
@@ -1445,7 +1589,7 @@ static qf_status enqueue_group(qf_plan* p, const uint8_t* bits_dev, int64_t s_be
       ++c->prof_launches;
     }
   }
-  QF_HIP(c, launch_slice_accumulate_batched(c->stream, wsp(c, p->nodes.back().offset), k, p->root_pos.data(), G,
+  QF_HIP(c, launch_slice_accumulate_batched(c->stream, wsp(c, p->nodes.back().offset), (int64_t)1 << k, k, p->root_pos.data(), G,
                                             chain_b, reinterpret_cast<double2*>(out_dev), root_scale(p)));
   return QF_OK;
 }
@@ -1456,6 +1600,7 @@ static qf_status enqueue_call(qf_plan* p, int n_batch, const uint8_t* bits_dev, 
   qf_ctx* c = p->ctx;
   const int64_t s_range = s_end - s_begin;
   const int64_t n_chains = (int64_t)n_batch * s_range;
+  if (call_runs_small(p, n_batch, s_range)) return small_call(p, n_batch, bits_dev, s_begin, s_end, out_dev, nullptr);
   // group hoisting: each bitstring's slices in groups of G (the last one of a bitstring may be
   // partly idle); otherwise consecutive chains, bitstring-major, G per group
   const int64_t groups = p->ghoist ? n_batch * ((s_range + p->G - 1) / p->G) : (n_chains + p->G - 1) / p->G;
@@ -1475,7 +1620,7 @@ static qf_status amplitudes_batched(qf_plan* p, int n_batch, const uint8_t* bits
   if (!(p->graph && c->stream)) return enqueue_call(p, n_batch, bits_dev, s_begin, s_end, out_dev, true);
   const std::vector<int64_t> key = {(int64_t)(uintptr_t)c->ws, (int64_t)(uintptr_t)bits_dev,
                                     (int64_t)(uintptr_t)out_dev, n_batch, s_begin, s_end,
-                                    (int64_t)(uintptr_t)c->stream};
+                                    (int64_t)(uintptr_t)c->stream, (int64_t)c->ws_bytes};
   if (!p->gexec || key != p->graph_key) {
     if (p->gexec) {
       QF_HIP(c, hipStreamSynchronize(c->stream));
@@ -1568,11 +1713,19 @@ extern "C" qf_status qf_amplitudes(qf_plan* p, int n_batch, const uint8_t* bits_
   const int n = p->n;
   const int k = (int)p->open.size();
   int64_t done = 0;
+  const bool small = call_runs_small(p, n_batch, s_end - s_begin);
+  if (small && !fault) return small_call(p, n_batch, bits_dev, s_begin, s_end, out_dev, nullptr);
   for (int b = 0; b < n_batch; ++b) {
     const uint8_t* row = bits_dev + (int64_t)b * n;
     for (int64_t s = s_begin; s < s_end; ++s) {
       if (fault_after >= 0 && done >= fault_after)
         return fail(c, QF_ERR_INJECTED, "fault injected after " + std::to_string(done) + " slices");
+      if (small) {
+        e = small_call(p, 1, row, s, s + 1, out_dev + ((int64_t)2 * b << k), nullptr);
+        if (e != QF_OK) return e;
+        ++done;
+        continue;
+      }
       const uint64_t changed = (s == s_begin) ? ~0ull : (uint64_t)(s ^ (s - 1));
       auto runs = [&](size_t i) {
         const Node& nd = p->nodes[n + i];
@@ -1843,9 +1996,14 @@ extern "C" qf_status qf_backward(qf_plan* p, int n_batch, const uint8_t* bits_de
   const int n = p->n;
   const int k = (int)p->open.size();
   const int S_steps = (int)p->steps.size();
-  if (batched) {
+  const bool small = call_runs_small(p, n_batch, s_end - s_begin);
+  if (small) {
+    e = small_call(p, n_batch, bits_dev, s_begin, s_end, nullptr, cot_dev);
+    if (e != QF_OK) return e;
+  }
+  if (batched || small) {
     const int64_t s_range = s_end - s_begin;
-    const int64_t n_chains = (int64_t)n_batch * s_range;
+    const int64_t n_chains = small ? 0 : (int64_t)n_batch * s_range;  // left to run
     for (int64_t g = 0; g < (n_chains + p->G - 1) / p->G; ++g) {
       e = backward_group(p, bits_dev, cot_dev, s_begin, s_range, g * p->G, n_chains);
       if (e != QF_OK) return e;

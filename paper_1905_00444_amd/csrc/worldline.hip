@@ -338,30 +338,6 @@ hipError_t launch_zero(hipStream_t st, void* p, size_t bytes) {
 
 // ---------------------------------------------------------------------------------------------
 // Batched chains (bitstring x slice): per-chain leaf offsets and the ordered FP64 slice sum.
-__device__ __forceinline__ void chain_of(const ChainGroup& c, int g, int64_t& b, int64_t& s) {
-  int64_t off;  // slice offset in the range
-  if (c.gpb > 0) {
-    const int64_t q = c.chain0 / c.G;
-    b = q / c.gpb;
-    off = (q - b * c.gpb) * c.G + g;
-    if (b * c.s_range >= c.n_chains || off >= c.s_range) b = -1;
-  } else {
-    const int64_t k = c.chain0 + g;
-    b = k < c.n_chains ? k / c.s_range : -1;
-    off = k - b * c.s_range;
-  }
-  s = c.s_begin + off;
-}
-
-// World-line offset of the bits that chain (b, s) fixes; 0 for an idle chain.
-__device__ __forceinline__ int64_t leaf_base(const ChainGroup& c, const LeafDesc& d, int64_t b, int64_t s) {
-  if (b < 0) return 0;
-  int64_t base = 0;
-  for (int i = 0; i < d.n_cut; ++i) base |= ((s >> d.shift[i]) & 1) << d.pos[i];
-  if (d.xpos >= 0) base |= (int64_t)(c.bits[b * c.n_qubits + d.qubit] & 1) << d.xpos;
-  return base;
-}
-
 // Block 0: clears the running maxima of the steps; then setup_blocks blocks: per-chain offsets; then the
 // gathers, a GatherBlock each.  The gathered operands are small (at most 2^14 elements, whose world-line
 // slices sit in L2), so a launch each was all overhead: a chain of the 6x6 circuit made 75 of them.
@@ -432,7 +408,8 @@ hipError_t launch_chain_begin(hipStream_t st, const ChainGroup& grp, int n_leave
 // Chains of one bitstring add in order (g ascending) into one running FP64 value: block y = g starts such
 // a run, or has nothing to do if its bitstring is the previous chain's.
 __global__ void __launch_bounds__(256)
-slice_accumulate_batched_kernel(const float2* __restrict__ root, AccArgs a, int G, const int32_t* __restrict__ chain_b,
+slice_accumulate_batched_kernel(const float2* __restrict__ root, int64_t root_stride, AccArgs a, int G,
+                                const int32_t* __restrict__ chain_b, const int32_t* __restrict__ chain_e,
                                 double2* __restrict__ out, const NodeScale* __restrict__ root_scale) {
   const int g0 = blockIdx.y;
   const int32_t b = chain_b[g0];
@@ -447,24 +424,26 @@ slice_accumulate_batched_kernel(const float2* __restrict__ root, AccArgs a, int 
     double2 o = out[((int64_t)b << a.k) + j];
 #pragma unroll 8
     for (int g = g0; g < g1; ++g) {
-      const float2 v = root[(int64_t)g * n + src];
-      o.x += (double)v.x * f;
-      o.y += (double)v.y * f;
+      const float2 v = root[(int64_t)g * root_stride + src];
+      const double fg = chain_e ? ldexp(1.0, chain_e[g]) : f;
+      o.x += (double)v.x * fg;
+      o.y += (double)v.y * fg;
     }
     out[((int64_t)b << a.k) + j] = o;
   }
 }
 
-hipError_t launch_slice_accumulate_batched(hipStream_t st, const float2* root, int k, const int* pos, int G,
-                                           const int32_t* chain_b, double2* out, const NodeScale* root_scale) {
+hipError_t launch_slice_accumulate_batched(hipStream_t st, const float2* root, int64_t root_stride, int k, const int* pos,
+                                           int G, const int32_t* chain_b, double2* out, const NodeScale* root_scale,
+                                           const int32_t* chain_e) {
   AccArgs a;
   a.k = k;
   for (int t = 0; t < 32; ++t) a.pos[t] = t < k ? pos[t] : 0;
   const int64_t n = (int64_t)1 << k;
   unsigned blocks = (unsigned)((n + 255) / 256);
   if (blocks > 1024) blocks = 1024;
-  hipLaunchKernelGGL(slice_accumulate_batched_kernel, dim3(blocks, (unsigned)G), dim3(256), 0, st, root, a, G, chain_b, out,
-                     root_scale);
+  hipLaunchKernelGGL(slice_accumulate_batched_kernel, dim3(blocks, (unsigned)G), dim3(256), 0, st, root, root_stride, a, G,
+                     chain_b, chain_e, out, root_scale);
   return hipGetLastError();
 }
 

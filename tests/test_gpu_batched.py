@@ -8,7 +8,7 @@ from oracle import sv
 from oracle.metrics import rel_err
 from workloads.bitstrings import random_bitstrings
 from workloads.circuits import generate, identity_cz
-from workloads.plans import region_plan, plan_8x9, C5_REMOVED
+from workloads.plans import region_plan, sweep_plan, plan_8x9, C5_REMOVED
 
 pytestmark = pytest.mark.gpu
 
@@ -115,6 +115,29 @@ def test_call_of_several_chains_equals_single_chains_bitwise(precision, cuts, ho
     assert many.ws.numel() > one.ws.numel()
     assert np.array_equal(got.cpu().numpy(), want.cpu().numpy())
     assert np.array_equal(again.cpu().numpy(), want[:1].cpu().numpy())
+
+
+@pytest.mark.parametrize("rows,cols,depth,n_open,n,precision", [
+    (2, 1, 8, 0, 1, "fp32"), (1, 5, 23, 1, 3, "bf16x3"), (3, 3, 16, 2, 65, "fp32"), (3, 4, 20, 3, 7, "fp16"),
+    (4, 4, 8, 3, 600, "fp32"), (3, 1, 43, 0, 2, "bf16x3")])
+def test_plans_of_small_tensors_vs_state_vector(ctx, rows, cols, depth, n_open, n, precision):
+    """Plans whose chains run whole in a workgroup: FP32 products of at most 2^11 terms in at most 15 steps,
+    norm-wise 15 x 8 x 2^-24 = 7.2e-6; and one chain at a time (a workspace of one chain) the same bits as
+    all at once.  600 chains are more than a launch takes; tensors from 2 elements to 2^11."""
+    import torch
+    from paper_1905_00444_amd import Circuit, Plan
+    _say(f"small {rows}x{cols} d{depth} open {n_open} n {n} {precision}")
+    c = generate(rows, cols, depth, 5)
+    plan = sweep_plan(c, range(rows * cols - n_open, rows * cols), by="row" if cols <= rows else "col")
+    bits = random_bitstrings(n, rows * cols, 3)
+    p = Plan(ctx, Circuit(ctx, c.to_text()), plan, precision)
+    shapes = [(s["m_bits"], s["n_bits"], s["k_bits"]) for s in p.steps()]
+    assert max(max(M + K, N + K, M + N) for M, N, K in shapes) <= 11
+    got = p.amplitudes(bits)
+    one = torch.cat([p.amplitudes(bits[i:i + 1]) for i in range(min(n, 5))])
+    torch.cuda.synchronize()
+    assert rel_err(got.cpu().numpy(), sv.open_amplitudes(c.to_text(), bits, plan["open"])) <= 7.2e-6
+    assert np.array_equal(got[:5].cpu().numpy(), one.cpu().numpy())
 
 
 def test_batched_tail_and_slice_subrange(ctx):

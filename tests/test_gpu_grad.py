@@ -80,6 +80,29 @@ def test_grad_small_grids_vs_adjoint_oracle(ctx, rows, cols, depth, n, batch):
     assert rel_err(g.cpu().numpy(), ref) <= 2e-5
 
 
+@pytest.mark.parametrize("n,batch", [(1, 1), (70, 1), (3, 8)])
+def test_grad_of_small_regions_cuts_open_vs_adjoint_oracle(ctx, n, batch):
+    """Chains that run whole in a workgroup, with results that later steps than the next one read, 4 slices and
+    2 open qubits; the bound of the small grids."""
+    import torch
+    from paper_1905_00444_amd import Circuit, Plan
+    _say(f"grad small regions n {n} batch {batch}")
+    c = generate(4, 5, 20, 2)
+    text = c.to_text()
+    qid = c.qubit_of()
+    cuts = [[qid[(1, 3)], qid[(2, 3)], 0, 1], [qid[(3, 1)], qid[(3, 2)], 0, 1]]
+    plan, _ = region_plan(c, 2, 2, cuts, [(3, 4), (2, 4)])
+    bits = random_bitstrings(n, 20, 7)
+    rng = np.random.default_rng(3)
+    cot = rng.normal(size=(n, 4)) + 1j * rng.normal(size=(n, 4))
+    p = Plan(ctx, Circuit(ctx, text), plan, "fp32", backward=True, batch=batch)
+    assert max(max(s["m_bits"] + s["k_bits"], s["n_bits"] + s["k_bits"], s["m_bits"] + s["n_bits"]) for s in p.steps()) <= 11
+    g = p.backward(bits, cot)
+    torch.cuda.synchronize()
+    ref = _oracle_grad(text, *_expand_open(bits, plan["open"], cot))
+    assert rel_err(g.cpu().numpy(), ref) <= 2e-5
+
+
 def test_grad_4x5_d32_cuts_open_random_cotangent(ctx):
     import torch
     from paper_1905_00444_amd import Circuit, Plan
