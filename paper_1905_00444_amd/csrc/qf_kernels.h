@@ -187,7 +187,8 @@ struct SmallStep {
   int64_t off[2], c;      // elements: A, B (into the world-lines for leaves, else the chain's scratch), C
   int32_t leaf[2];        // world-line index of A, B, or -1
   int32_t node[2];
-  SmallBits am, ak, bn, bk, cm, cn;
+  int32_t mb, nb, kb, pad;
+  SmallBits a_km, a_mk, b_kn, b_nk, c_mn, c_nm;  // tensors as [k][m] (m the low bits), and so on
 };
 struct SmallArgs {
   ChainGroup grp;

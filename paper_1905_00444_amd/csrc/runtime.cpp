@@ -423,9 +423,9 @@ static int operand_batch(const qf_plan* p, const Operand& op) { return operand_i
 
 // Plans whose chains run whole in one workgroup each, and their step descriptions: all operands and results
 // fit its LDS buffers (2^11 elements, so that two workgroups share a CU).  At that size a step still takes
-// 3 us, less than the launches it replaces: a 4x4 chain of depth 18 68 us against 109, of depth 8 40
-// against 109, 1000 of them 95 against 2014.  With buffers of 2^12 elements, one workgroup a CU and
-// twice the work a step, single chains were slower than launches (3x4, depth 24: 131 against 78).
+// 2 to 3 us, less than the launches it replaces: a 4x4 chain of depth 18 47 us against 109, of depth 8 33
+// against 109, 1000 of them 83 against 2014.  With buffers of 2^12 elements, one workgroup a CU and
+// twice the work a step, single chains were slower than launches (3x4, depth 24, an early version: 131 against 78).
 static void plan_small(qf_plan* p) {
   const int n = p->n, S = (int)p->steps.size();
   if (S < 1 || S > kSmallMaxSteps) return;
@@ -451,9 +451,11 @@ static void plan_small(qf_plan* p) {
     auto order = [&](int id) -> const std::vector<int>& {
       return id < n ? p->leaf_full_labels[p->nodes[id].qubit] : p->nodes[id].labels;
     };
-    auto bits = [&](const std::vector<int>& labels, const std::vector<int>& in) {  // labels, least significant first
+    // labels, least significant first
+    auto bits = [&](const std::vector<int>& low, const std::vector<int>& high, const std::vector<int>& in) {
       SmallBits b = {0};
-      for (int lab : labels) b.push((int)(in.end() - std::find(in.begin(), in.end(), lab)) - 1);
+      for (const std::vector<int>* v : {&low, &high})
+        for (int lab : *v) b.push((int)(in.end() - std::find(in.begin(), in.end(), lab)) - 1);
       return b;
     };
     std::vector<int> m, nn, k;
@@ -461,12 +463,16 @@ static void plan_small(qf_plan* p) {
     for (auto it = A.labels.rbegin(); it != A.labels.rend(); ++it) (contains(B.labels, *it) ? k : m).push_back(*it);
     for (auto it = B.labels.rbegin(); it != B.labels.rend(); ++it)
       if (!contains(A.labels, *it)) nn.push_back(*it);
-    d.am = bits(m, order(ids[0]));
-    d.ak = bits(k, order(ids[0]));
-    d.bn = bits(nn, order(ids[1]));
-    d.bk = bits(k, order(ids[1]));
-    d.cm = bits(m, p->nodes[n + i].labels);
-    d.cn = bits(nn, p->nodes[n + i].labels);
+    const std::vector<int>& C = p->nodes[n + i].labels;
+    d.mb = (int)m.size();
+    d.nb = (int)nn.size();
+    d.kb = (int)k.size();
+    d.a_km = bits(m, k, order(ids[0]));
+    d.a_mk = bits(k, m, order(ids[0]));
+    d.b_kn = bits(nn, k, order(ids[1]));
+    d.b_nk = bits(k, nn, order(ids[1]));
+    d.c_mn = bits(nn, m, C);
+    d.c_nm = bits(m, nn, C);
     d.c = at[n + i];
     for (int r = 0; r < 2; ++r) {
       const bool leaf = ids[r] < n;

@@ -18,8 +18,9 @@
 // [l][j], a thread takes 1 x 1 to 2 x 2 outputs, and where there are fewer outputs than threads, l is cut
 // over the rest of them.  FP32 throughout, whatever precision the plan asks for.
 //
-// Measured (call to result): one 4x4 chain of depth 8, 15 steps, 109 -> 40 us (of depth 16, 2^10 elements,
-// 101 -> 50), with gradient 309 -> 99; 1000 chains 2014 -> 95, with gradient 5930 -> 246.
+// Measured (call to result): one 4x4 chain of depth 8, 15 steps, 109 us by launches, 33 here (of depth 16,
+// 2^10 elements, 101 and 38), with gradient 309 and 91; 1000 chains 2014 and 83, with gradient 5930 and 224.
+// Row and column scattered bit by bit in loops, and each step's scalars fetched on arrival: 40 (50), 99.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include "cgemm_common.h"
@@ -31,10 +32,12 @@ constexpr int kSmThreads = 1 << kSmLog;
 constexpr int kSmMax = 1 << kSmallMaxBits;
 constexpr int kSmRegs = kSmMax / kSmThreads;
 
+// Address of element i < 2^kSmallMaxBits: bits from b.n() on are zero in i.
+template <int BITS = kSmallMaxBits>
 __device__ __forceinline__ int scatter_bits(int i, SmallBits b) {
   int off = 0;
-  const int n = b.n();
-  for (int k = 0; k < n; ++k) off |= ((i >> k) & 1) << b.pos(k);
+#pragma unroll
+  for (int k = 0; k < BITS; ++k) off |= ((i >> k) & 1) << b.pos(k);
   return off;
 }
 
@@ -55,14 +58,14 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// This thread's elements of the operand p as [row][col].
-__device__ __forceinline__ void fetch(float2 (&r)[kSmRegs], const float2* p, SmallBits row, SmallBits col) {
-  const int cb = col.n(), size = 1 << (row.n() + cb);
+// This thread's elements of the operand p in the order of b.
+__device__ __forceinline__ void fetch(float2 (&r)[kSmRegs], const float2* p, SmallBits b) {
+  static_assert(kSmRegs == 4, "two bits above the thread's");
+  const int at = scatter_bits<kSmLog>(threadIdx.x, b), size = 1 << b.n();
+  const int hi[4] = {0, 1 << b.pos(kSmLog), 1 << b.pos(kSmLog + 1), 1 << b.pos(kSmLog) | 1 << b.pos(kSmLog + 1)};
 #pragma unroll
-  for (int q = 0; q < kSmRegs; ++q) {
-    const int t = threadIdx.x + q * kSmThreads;
-    if (t < size) r[q] = p[scatter_bits(t >> cb, row) | scatter_bits(t & ((1 << cb) - 1), col)];
-  }
+  for (int q = 0; q < kSmRegs; ++q)
+    if ((int)threadIdx.x + q * kSmThreads < size) r[q] = p[at | hi[q]];
 }
 
 __device__ __forceinline__ void stash(float2* dst, const float2 (&r)[kSmRegs], int bits, bool conj) {
@@ -105,10 +108,10 @@ __device__ __forceinline__ void small_tile(const SmallLds& s, int ib, int jb, in
 #pragma unroll
   for (int u = 0; u < TI; ++u)
 #pragma unroll
-    for (int w = 0; w < TJ; ++w) out(i0 + (u << gi), j0 + (w << gj), acc[u][w]);
+    for (int w = 0; w < TJ; ++w) out(((i0 + (u << gi)) << jb) + j0 + (w << gj), acc[u][w]);
 }
 
-// out(i, j, value) of all 2^(ib+jb) <= kSmMax outputs, from X and Y in LDS.
+// out(i 2^jb + j, value) of all 2^(ib+jb) <= kSmMax outputs, from X and Y in LDS.
 template <class Out>
 __device__ __forceinline__ void small_product(SmallLds& s, int ib, int jb, int lb, Out&& out) {
   static_assert(kSmallMaxBits == kSmLog + 2, "tiles cover the outputs");
@@ -121,7 +124,7 @@ __device__ __forceinline__ void small_product(SmallLds& s, int ib, int jb, int l
       float2 acc = make_float2(0.f, 0.f);
 #pragma unroll 4
       for (int l = 0; l < L; ++l) cfma(acc, s.x[(l << ib) + i], s.y[(l << jb) + j]);
-      out(i, j, acc);
+      out(t, acc);
     }
     return;
   }
@@ -132,7 +135,7 @@ __device__ __forceinline__ void small_product(SmallLds& s, int ib, int jb, int l
 #pragma unroll 4
     for (int l = tid & (seg - 1); l < L; l += seg) cfma(acc, s.x[(l << ib) + i], s.y[(l << jb) + j]);
     if (sb == 0)
-      out(i, j, acc);
+      out(o, acc);
     else
       s.red[tid] = acc;
   }
@@ -145,7 +148,7 @@ __device__ __forceinline__ void small_product(SmallLds& s, int ib, int jb, int l
         v.x += r.x;
         v.y += r.y;
       }
-      out(tid >> jb, tid & ((1 << jb) - 1), v);
+      out(tid, v);
     }
   }
 }
@@ -156,6 +159,17 @@ __device__ __forceinline__ int small_exp(uint32_t bits) {
   int e;
   frexpf(m, &e);
   return e < -62 ? -62 : (e > 62 ? 62 : e);
+}
+
+// Bits of the largest m >= 0 of the wave: rows of 16 by DPP, then the four rows.
+__device__ __forceinline__ uint32_t wave_max_bits(float m) {
+  int v = __float_as_int(m);  // the order of non-negative floats
+  v = max(v, __builtin_amdgcn_mov_dpp(v, 0xb1, 0xf, 0xf, true));   // lane ^ 1
+  v = max(v, __builtin_amdgcn_mov_dpp(v, 0x4e, 0xf, 0xf, true));   // lane ^ 2
+  v = max(v, __builtin_amdgcn_mov_dpp(v, 0x141, 0xf, 0xf, true));  // mirrored in 8
+  v = max(v, __builtin_amdgcn_mov_dpp(v, 0x140, 0xf, 0xf, true));  // mirrored in 16
+  const int a = max(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16));
+  return (uint32_t)max(a, max(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
 }
 
 template <bool BACKWARD>
@@ -174,6 +188,10 @@ small_chain_kernel(SmallArgs a, const SmallStep* __restrict__ steps) {
     s.e[t] = 0;
     if (t < n) s.base[t] = (int)leaf_base(a.grp, a.leaves[t], b, sl);
   }
+  int warm = 0;  // the steps' lines into the scalar cache, together instead of one by one
+#pragma unroll 8
+  for (int i = 0; i < S; ++i) warm |= steps[i].mb;
+  asm volatile("" ::"s"(warm));
   lds_barrier();
   // where operand r of a step lies in memory
   auto place = [&](const SmallStep& st, int r) -> const float2* {
@@ -181,8 +199,8 @@ small_chain_kernel(SmallArgs a, const SmallStep* __restrict__ steps) {
   };
   float2 ra[kSmRegs], rb[kSmRegs], re[kSmRegs];
   SmallStep st = steps[0];
-  if (st.leaf[0] >= 0) fetch(ra, place(st, 0), st.ak, st.am);
-  if (st.leaf[1] >= 0) fetch(rb, place(st, 1), st.bk, st.bn);
+  if (st.leaf[0] >= 0) fetch(ra, place(st, 0), st.a_km);
+  if (st.leaf[1] >= 0) fetch(rb, place(st, 1), st.b_kn);
   for (int i = 0; i < S; ++i) {
     const SmallStep nx = steps[i + 1 < S ? i + 1 : i];
     const bool lds0 = i > 0 && st.node[0] == n + i - 1, lds1 = i > 0 && st.node[1] == n + i - 1;
@@ -190,16 +208,16 @@ small_chain_kernel(SmallArgs a, const SmallStep* __restrict__ steps) {
       __syncthreads();  // an earlier step's result in memory
     else
       lds_barrier();    // the previous step's result and magnitude
-    if (lds0) fetch(ra, s.c, st.ak, st.am);
-    else if (st.leaf[0] < 0) fetch(ra, place(st, 0), st.ak, st.am);
-    if (lds1) fetch(rb, s.c, st.bk, st.bn);
-    else if (st.leaf[1] < 0) fetch(rb, place(st, 1), st.bk, st.bn);
-    const int mb = st.am.n(), nb = st.bn.n(), kb = st.ak.n();
+    if (lds0) fetch(ra, s.c, st.a_km);
+    else if (st.leaf[0] < 0) fetch(ra, place(st, 0), st.a_km);
+    if (lds1) fetch(rb, s.c, st.b_kn);
+    else if (st.leaf[1] < 0) fetch(rb, place(st, 1), st.b_kn);
+    const int mb = st.mb, nb = st.nb, kb = st.kb;
     stash(s.x, ra, mb + kb, false);
     stash(s.y, rb, nb + kb, false);
     if (i + 1 < S) {
-      if (nx.leaf[0] >= 0) fetch(ra, place(nx, 0), nx.ak, nx.am);
-      if (nx.leaf[1] >= 0) fetch(rb, place(nx, 1), nx.bk, nx.bn);
+      if (nx.leaf[0] >= 0) fetch(ra, place(nx, 0), nx.a_km);
+      if (nx.leaf[1] >= 0) fetch(rb, place(nx, 1), nx.b_kn);
     }
     float unscale = 1.f;
     int e_ab = 0;
@@ -212,16 +230,16 @@ small_chain_kernel(SmallArgs a, const SmallStep* __restrict__ steps) {
     const bool next = i + 1 < S && (nx.node[0] == n + i || nx.node[1] == n + i);
     float2* C = mine + st.c;
     float mx = 0.f;
-    small_product(s, mb, nb, kb, [&](int m, int j, float2 v) {
+    small_product(s, mb, nb, kb, [&](int o, float2 v) {
       v = make_float2(v.x * unscale, v.y * unscale);
-      const int at = scatter_bits(m, st.cm) | scatter_bits(j, st.cn);
+      const int at = scatter_bits(o, st.c_mn);
       if (next) s.c[at] = v;
       if (BACKWARD || !next) C[at] = v;
       mx = fmaxf(mx, cmax(v));
     });
     if (a.renorm) {
-      mx = wave_max(mx);
-      if ((tid & 63) == 0) atomicMax(&s.amax[n + i], __float_as_uint(mx));
+      const uint32_t top = wave_max_bits(mx);
+      if ((tid & 63) == 0) atomicMax(&s.amax[n + i], top);
     }
     st = nx;
   }
@@ -235,12 +253,12 @@ small_chain_kernel(SmallArgs a, const SmallStep* __restrict__ steps) {
     const double2 c = a.cot[(b << a.root.n()) + j];
     s.c[scatter_bits(j, a.root)] = make_float2((float)c.x, (float)c.y);
   }
-  fetch(ra, place(st, 0), st.am, st.ak);
-  fetch(rb, place(st, 1), st.bn, st.bk);
+  fetch(ra, place(st, 0), st.a_mk);
+  fetch(rb, place(st, 1), st.b_nk);
   bool in_lds = true;  // the environment of the step's result
   for (int i = S - 1; i >= 0; --i) {
     const SmallStep nx = steps[i > 0 ? i - 1 : 0];
-    const int mb = st.am.n(), nb = st.bn.n(), kb = st.ak.n();
+    const int mb = st.mb, nb = st.nb, kb = st.kb;
     const float2* E = mine + a.env + st.c;
     // the environment that the next step reads comes second, over that of this step's result
     const bool next0 = i > 0 && st.node[0] == n + i - 1, next1 = i > 0 && st.node[1] == n + i - 1;
@@ -249,27 +267,27 @@ small_chain_kernel(SmallArgs a, const SmallStep* __restrict__ steps) {
     else
       __syncthreads();  // written by an earlier step of this pass
     auto product = [&](bool of_a, bool last) {
-      const SmallBits row = of_a ? st.cn : st.cm, col = of_a ? st.cm : st.cn;
+      const SmallBits order = of_a ? st.c_nm : st.c_mn;
       if (in_lds)
-        fetch(re, s.c, row, col);
+        fetch(re, s.c, order);
       else
-        fetch(re, E, row, col);
+        fetch(re, E, order);
       stash(s.x, re, mb + nb, false);
       if (of_a)
         stash(s.y, rb, nb + kb, true);
       else
         stash(s.y, ra, mb + kb, true);
       if (last && i > 0) {
-        fetch(ra, place(nx, 0), nx.am, nx.ak);
-        fetch(rb, place(nx, 1), nx.bn, nx.bk);
+        fetch(ra, place(nx, 0), nx.a_mk);
+        fetch(rb, place(nx, 1), nx.b_nk);
       }
       lds_barrier();
       const int r = of_a ? 0 : 1, leaf = st.leaf[r];
-      const SmallBits oi = of_a ? st.am : st.bn, ok = of_a ? st.ak : st.bk;
+      const SmallBits to_order = of_a ? st.a_mk : st.b_nk;
       const bool next = of_a ? next0 : next1;
       float2* to = leaf >= 0 ? a.env_wl + st.off[r] + s.base[leaf] : mine + a.env + st.off[r];
-      small_product(s, of_a ? mb : nb, kb, of_a ? nb : mb, [&](int m, int k, float2 v) {
-        const int at = scatter_bits(m, oi) | scatter_bits(k, ok);
+      small_product(s, of_a ? mb : nb, kb, of_a ? nb : mb, [&](int o, float2 v) {
+        const int at = scatter_bits(o, to_order);
         if (next) {
           s.c[at] = v;
         } else if (leaf >= 0) {  // gathers from all chains that fixed the same bits
