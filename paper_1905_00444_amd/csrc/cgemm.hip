@@ -177,7 +177,7 @@ template <int PREC, int WTM, int WTN>
 __global__ void __launch_bounds__(kThreads)
 cgemm_mfma(int64_t M, int64_t N, int64_t K, const float2* __restrict__ A, const float2* __restrict__ B,
            float2* __restrict__ C, int64_t sa, int64_t sb, int64_t sc, const uint32_t* amaxA,
-           const uint32_t* amaxB, Renorm rn, int64_t kc, float2* __restrict__ P) {
+           const uint32_t* amaxB, Renorm rn, int64_t kc, float2* __restrict__ P, int64_t nbatch) {
   constexpr int BM = 32 * WTM, BN = 16 * WTN;
   using LA = TileLds<PREC, BM>;
   using LB = TileLds<PREC, BN>;
@@ -185,11 +185,14 @@ cgemm_mfma(int64_t M, int64_t N, int64_t K, const float2* __restrict__ A, const 
   char* ldsA = lds;
   char* ldsB = lds + LA::bytes;
 
-  // tile mapping: XCD-contiguous remap, then grouped rasterisation over row tiles
+  // tile mapping: XCD-contiguous remap over the whole launch (an XCD's L2 then holds its own chains'
+  // operands), then grouped rasterisation over row tiles
   const int64_t tiles_m = M / BM, tiles_n = N / BN;
-  const int64_t ntiles = tiles_m * tiles_n;
+  const int64_t ntiles = tiles_m * tiles_n, total = ntiles * nbatch;
   int64_t bid = blockIdx.x;
-  if ((ntiles & 7) == 0) bid = (bid & 7) * (ntiles >> 3) + (bid >> 3);
+  if ((total & 7) == 0) bid = (bid & 7) * (total >> 3) + (bid >> 3);
+  const int64_t batch = bid / ntiles;
+  bid -= batch * ntiles;
   const int64_t group = 8;
   const int64_t per_group = group * tiles_n;
   const int64_t gidx = bid / per_group;
@@ -198,12 +201,11 @@ cgemm_mfma(int64_t M, int64_t N, int64_t K, const float2* __restrict__ A, const 
   const int64_t tm = first_m + (bid % per_group) % gsize;
   const int64_t tn = (bid % per_group) / gsize;
 
-  const int64_t batch = blockIdx.z;
   const bool partial = gridDim.y > 1;
   A += batch * sa + tm * BM * K + blockIdx.y * kc;
   B += batch * sb + tn * BN * K + blockIdx.y * kc;
   if (partial) {
-    C = P + ((int64_t)blockIdx.y * gridDim.z + batch) * M * N;
+    C = P + ((int64_t)blockIdx.y * nbatch + batch) * M * N;
   } else {
     C += batch * sc;
   }
@@ -626,8 +628,8 @@ static void launch_tiled(hipStream_t st, int64_t M, int64_t N, int64_t K, const 
                          const uint32_t* amaxB, const Renorm& rn, int split, float2* P) {
   constexpr int BM = 32 * WTM, BN = 16 * WTN;
   const int64_t tiles = (M / BM) * (N / BN);
-  hipLaunchKernelGGL((cgemm_mfma<PREC, WTM, WTN>), dim3((unsigned)tiles, (unsigned)split, (unsigned)batch),
-                     dim3(kThreads), 0, st, M, N, K, A, B, C, sa, sb, sc, amaxA, amaxB, rn, K / split, P);
+  hipLaunchKernelGGL((cgemm_mfma<PREC, WTM, WTN>), dim3((unsigned)(tiles * batch), (unsigned)split), dim3(kThreads), 0, st,
+                     M, N, K, A, B, C, sa, sb, sc, amaxA, amaxB, rn, K / split, P, batch);
 }
 
 static bool pow2(int64_t x) { return x > 0 && (x & (x - 1)) == 0; }
