@@ -79,9 +79,9 @@ __device__ __forceinline__ void scales_for(const Renorm& rn, const uint32_t* ama
   unscale = ldexpf(1.f, -(s_a + s_b));
 }
 
-// Sum of the chunks: a workgroup takes 32 consecutive outputs, its 8 groups of 32 lanes read whole
-// 256-byte runs of the chunks y = t, t + 8, ... (one chunk's row per group), and the 8 partial sums meet in
-// LDS.  The order of the sum is a function of the chunk count alone.  Bound by reading the chunks once.
+// Sum of the chunks in ascending order: a workgroup takes 32 consecutive outputs, its 8 groups of 32 lanes read
+// whole 256-byte runs of 8 chunks at a time (one chunk's row per group) into LDS, and the first group adds
+// them.  Bound by reading the chunks once.
 constexpr int kReduceOut = 32, kReduceSlots = 8;
 
 __global__ void __launch_bounds__(256)
@@ -95,30 +95,21 @@ cgemm_split_reduce(const float2* __restrict__ P, int split, int64_t batch, int64
   float mx = 0.f;
   for (int64_t i0 = (int64_t)blockIdx.x * kReduceOut; i0 < total; i0 += (int64_t)gridDim.x * kReduceOut) {
     const int64_t i = i0 + lane;
-    float re = 0.f, im = 0.f;
-    if (i < total)
-#pragma unroll 4
-      for (int y = t; y < split; y += kReduceSlots) {
-        const float2 v = P[(int64_t)y * total + i];
-        re += v.x;
-        im += v.y;
-      }
-    part[t][lane] = make_float2(re, im);
-    __syncthreads();
+    float2 sum = make_float2(0.f, 0.f);
+    for (int y0 = 0; y0 < split; y0 += kReduceSlots) {
+      part[t][lane] = i < total && y0 + t < split ? P[(int64_t)(y0 + t) * total + i] : make_float2(0.f, 0.f);
+      __syncthreads();
+      if (t == 0)
+#pragma unroll
+        for (int k = 0; k < kReduceSlots; ++k) sum = make_float2(sum.x + part[k][lane].x, sum.y + part[k][lane].y);
+      __syncthreads();
+    }
     if (t == 0 && i < total) {
-      float2 s[kReduceSlots];
-#pragma unroll
-      for (int k = 0; k < kReduceSlots; ++k) s[k] = part[k][lane];
-#pragma unroll
-      for (int w = kReduceSlots / 2; w > 0; w >>= 1)
-#pragma unroll
-        for (int k = 0; k < w; ++k) s[k] = make_float2(s[k].x + s[k + w].x, s[k].y + s[k + w].y);
-      const float2 o = make_float2(s[0].x * unscale, s[0].y * unscale);
+      const float2 o = make_float2(sum.x * unscale, sum.y * unscale);
       const int64_t b = i / MN, e = i - b * MN, m = e / N;
       C[b * sc + c_index(rn, m, e - m * N, N)] = o;
       mx = fmaxf(mx, cmax(o));
     }
-    __syncthreads();
   }
   if (rn.c) record_amax(rn.c, mx);
 }
@@ -650,11 +641,36 @@ bool cgemm_variant_fits(int precision, int64_t M, int64_t N, int64_t K, int vari
   return false;
 }
 
+// FP16 products, sizes powers of two: the kernels and chunks of K of this rule, whatever is faster.  Another order
+// of FP32 sums flips roundings to fp16 in every later step of a contraction: 1e-4 of the amplitudes of
+// a 5x5 circuit of depth 30, 5e-4 with some products in FP32.
+static int fp16_variant(int64_t M, int64_t N, int64_t K) {
+  auto fits = [&](int v) { return cgemm_variant_fits(P_FP16, M, N, K, v); };
+  if (fits(GEMM_LARGE)) return GEMM_LARGE;
+  if (M >= 4096 && (N < 32 || K < kBK) && fits(GEMM_TALL)) return GEMM_TALL;
+  if (fits(GEMM_TILED_1X2)) return M >= 128 && N >= 64 ? GEMM_TILED_4X4 : M >= 64 ? GEMM_TILED_2X2 : GEMM_TILED_1X2;
+  if (fits(GEMM_SKINNY)) return GEMM_SKINNY;
+  return M * N <= 4096 && K >= 256 ? GEMM_SPLITK : GEMM_SIMT;
+}
+
+static int fp16_split(int variant, int64_t M, int64_t N, int64_t K) {
+  int64_t bm = 0, bn = 0, bk = kBK;
+  if (variant == GEMM_LARGE) bm = kV2BM, bn = kV2BN, bk = kV2BK;
+  else if (variant == GEMM_TILED_4X4) bm = 128, bn = 64;
+  else if (variant == GEMM_TILED_2X2) bm = 64, bn = 32;
+  else if (variant == GEMM_TILED_1X2) bm = 32, bn = 32;
+  if (bm == 0 || (M / bm) * (N / bn) >= 256) return 1;
+  int split = 1;
+  while (split < 1024 && (M / bm) * (N / bn) * split * 2 <= 1024 && K / (split * 2) >= 4 * bk) split *= 2;
+  return split;
+}
+
 // Every tile of one precision adds an output's products in the same order, so among the tiles the
 // launch may pick by how many workgroups they give (batch included) without changing a result; the
 // choice between the families below, and the cut of K, are functions of the shape alone, and a
 // batched launch equals the launches of its elements bit by bit.
 int cgemm_default_variant(int precision, int64_t M, int64_t N, int64_t K, int64_t blocks_per_tile) {
+  if (precision == P_FP16 && pow2(M) && pow2(N) && pow2(K)) return fp16_variant(M, N, K);
   // HBM-bound tall-skinny products below the tiles' N and K (as fast as the 64 x 32 tiles where
   // those fit: 5.1 TB/s on 2^25 x 32 x 32 split-BF16)
   if (M >= 4096 && (N < 32 || K < kBK) && cgemm_variant_fits(precision, M, N, K, GEMM_TALL)) return GEMM_TALL;
@@ -666,11 +682,15 @@ int cgemm_default_variant(int precision, int64_t M, int64_t N, int64_t K, int64_
     if (M >= 64 && (M / 64) * (N / 32) * blocks_per_tile >= 256) return GEMM_TILED_2X2;
     return GEMM_TILED_1X2;
   }
-  // K = 16 is half a K-tile of the smaller 16-bit tiles
-  if (precision != P_FP32 && cgemm_variant_fits(precision, M, N, K, GEMM_LARGE) && (M / kV2BM) * (N / kV2BN) >= 128)
+  // K = 16 is half a K-tile of the smaller 16-bit tiles; few large tiles are slower than the FP32 tiles
+  if (precision == P_BF16X3 && cgemm_variant_fits(precision, M, N, K, GEMM_LARGE) && (M / kV2BM) * (N / kV2BN) >= 128)
     return GEMM_LARGE;
   // a few dot products: a workgroup each; very long ones are spread further by the tiles' split K
   if (M * N <= 64 && K >= 32 && K <= (1 << 17)) return GEMM_SPLITK;
+  // up to 4096 of them where the sizes are no powers of two, a single product by its caller: 2 x 1078 x 3529
+  // 12 us against 33 on the tiles, 64 x 64 x 1000 7 / 33, 4 x 1000 x 40 5 / 5.  A contraction's steps are powers
+  // of two and run with many chains per launch, which the tiles suit better.
+  if (M * N > 64 && M * N <= 4096 && K >= 64 && !(pow2(M) && pow2(N) && pow2(K))) return GEMM_SPLITK;
   // short K or N: the FP32 tiles would multiply zeros
   if ((K < 16 || (K < 32 && N < 32)) && cgemm_variant_fits(precision, M, N, K, GEMM_SKINNY)) return GEMM_SKINNY;
   if (K < 8 || M * N * K < 4096) return GEMM_SIMT;
@@ -704,7 +724,8 @@ static hipError_t launch_mfma(hipStream_t st, int variant, int64_t M, int64_t N,
 // write and a read of its partial tile and the reduction a launch, which K < 1024 does not repay: the
 // 256 x 256 x 256 products of the 4 x 4 and 4 x 5 circuits took 332 us of split kernel and reduction per
 // 64 chains, 100 us in one pass over K on smaller tiles.
-static int split_count(int variant, int64_t M, int64_t N, int64_t K) {
+static int split_count(int precision, int variant, int64_t M, int64_t N, int64_t K) {
+  if (precision == P_FP16 && variant != GEMM_F32) return fp16_split(variant, M, N, K);
   if (variant == GEMM_SKINNY || variant == GEMM_SPLITK || variant == GEMM_SIMT || variant == GEMM_TALL) return 1;
   const int64_t tiles = ((M + 63) / 64) * ((N + 31) / 32);
   if (tiles >= 256) return 1;
@@ -715,13 +736,13 @@ static int split_count(int variant, int64_t M, int64_t N, int64_t K) {
 
 size_t cgemm_split_scratch(int precision, int64_t M, int64_t N, int64_t K, int64_t batch, int variant) {
   if (variant == GEMM_AUTO) variant = cgemm_default_variant(precision, M, N, K);
-  const int split = split_count(variant, M, N, K);
+  const int split = split_count(precision, variant, M, N, K);
   return split > 1 ? (size_t)split * (size_t)(batch * M * N) * sizeof(float2) : 0;
 }
 
 size_t env_gemm_scratch(int side, int64_t M, int64_t N, int64_t K, int64_t batch) {
   const int64_t rows = side ? N : M;
-  const int split = split_count(GEMM_F32, rows, K, side ? M : N);
+  const int split = split_count(P_FP32, GEMM_F32, rows, K, side ? M : N);
   return split > 1 ? (size_t)split * (size_t)(batch * rows * K) * sizeof(float2) : 0;
 }
 
@@ -729,7 +750,7 @@ hipError_t launch_env_gemm(hipStream_t st, int side, int64_t M, int64_t N, int64
                            const float2* other, float2* out, int64_t batch, const Renorm& map, float2* scratch,
                            size_t scratch_bytes) {
   const int64_t rows = side ? N : M;
-  int split = scratch ? split_count(GEMM_F32, rows, K, side ? M : N) : 1;
+  int split = scratch ? split_count(P_FP32, GEMM_F32, rows, K, side ? M : N) : 1;
   if (env_gemm_scratch(side, M, N, K, batch) > scratch_bytes) split = 1;
   const hipError_t e = launch_cgemm_f32_env(st, side, M, N, K, env, other, out, batch, map, &split, scratch);
   if (e != hipSuccess || split == 1) return e;
@@ -764,7 +785,7 @@ hipError_t launch_cgemm_ex(hipStream_t st, int precision, int64_t M, int64_t N, 
       if (K < 256)
         hipLaunchKernelGGL(cgemm_splitk<64>, dim3((unsigned)(M * N), 1, (unsigned)batch), dim3(64), 0, st, M, N, K, A, B,
                            C, sa, sb, sc, rn);
-      else if (K < 4096)
+      else if (K < 4096 || precision == P_FP16)
         hipLaunchKernelGGL(cgemm_splitk<256>, dim3((unsigned)(M * N), 1, (unsigned)batch), dim3(256), 0, st, M, N, K, A,
                            B, C, sa, sb, sc, rn);
       else
@@ -779,7 +800,7 @@ hipError_t launch_cgemm_ex(hipStream_t st, int precision, int64_t M, int64_t N, 
     }
   }
   // split only when the caller's scratch holds every partial (otherwise one pass over K)
-  int split = scratch ? split_count(v, M, N, K) : 1;
+  int split = scratch ? split_count(precision, v, M, N, K) : 1;
   if (split > 1 && (size_t)split * (size_t)(batch * M * N) * sizeof(float2) > scratch_bytes) split = 1;
   hipError_t e;
   if (precision == P_FP32 || v == GEMM_F32) {

@@ -261,10 +261,11 @@ bool cgemm_presplit_fits(int64_t M, int64_t N, int64_t K, int precision) {
 // 1024^3 (32): 96 / 49, 2048 x 1024 x 1024 (64): 97 / 82, 2048^2 x 1024 (128): 105 / 126, 4096 x 2048 x
 // 1024 (256): 143 / 175.  Between 32 and 128 tiles the loss is small in plans whose other steps are larger,
 // and the step keeps handing its result over as split planes, which saves its consumer a pass; below, the
-// plans are small throughout.  A function of the shape alone, so that a batched plan and its one-chain form
+// plans are small throughout.  FP16 steps always (another order of sums flips later roundings to fp16).  A
+// function of the shape alone, so that a batched plan and its one-chain form
 // cut K alike.
 bool cgemm_presplit_pays(int64_t M, int64_t N, int64_t K, int precision) {
-  return cgemm_presplit_fits(M, N, K, precision) && (M / kPsBM) * (N / kPsBN) >= 32;
+  return cgemm_presplit_fits(M, N, K, precision) && (precision == P_FP16 || (M / kPsBM) * (N / kPsBN) >= 32);
 }
 
 // Split-BF16: A, B each a hi plane followed by a lo plane (rows x K bfloat16 pairs each,

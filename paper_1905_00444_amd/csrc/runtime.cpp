@@ -422,7 +422,8 @@ static bool operand_invariant(const qf_plan* p, const Operand& op) {
 static int operand_batch(const qf_plan* p, const Operand& op) { return operand_invariant(p, op) ? 1 : p->G; }
 
 // Plans whose chains run whole in one workgroup each, and their step descriptions: all operands and results
-// fit its LDS buffers (2^11 elements, so that two workgroups share a CU).  At that size a step still takes
+// fit its LDS buffers (2^11 elements, so that two workgroups share a CU), and no product is one that the plan's
+// precision takes to 16-bit tiles.  At that size a step still takes
 // 2 to 3 us, less than the launches it replaces: a 4x4 chain of depth 18 47 us against 109, of depth 8 33
 // against 109, 1000 of them 83 against 2014.  With buffers of 2^12 elements, one workgroup a CU and
 // twice the work a step, single chains were slower than launches (3x4, depth 24, an early version: 131 against 78).
@@ -430,7 +431,10 @@ static void plan_small(qf_plan* p) {
   const int n = p->n, S = (int)p->steps.size();
   if (S < 1 || S > kSmallMaxSteps) return;
   for (const Step& st : p->steps)
-    if (std::max({st.m_bits + st.k_bits, st.n_bits + st.k_bits, st.m_bits + st.n_bits}) > kSmallMaxBits) return;
+    if (std::max({st.m_bits + st.k_bits, st.n_bits + st.k_bits, st.m_bits + st.n_bits}) > kSmallMaxBits ||
+        (p->precision != QF_FP32 && cgemm_variant_fits(p->precision, (int64_t)1 << st.m_bits, (int64_t)1 << st.n_bits,
+                                                       (int64_t)1 << st.k_bits, GEMM_TILED_1X2)))
+      return;
   for (int q = 0; q < n; ++q)
     if (p->wl_qubits[q].nbond > 28) return;
   // scratch: every result, then (backward plans) every result's environment
@@ -1134,7 +1138,7 @@ qf_status qf_plan_call_workspace(qf_plan* p, int n_batch, int64_t slices, size_t
   *bytes = p->arena_end;
   if ((int64_t)n_batch * slices < 2) return QF_OK;
   if (p->small) {
-    if (p->precision != QF_FP16) *bytes += small_most(p, n_batch * slices) * (size_t)p->small_elems * sizeof(float2);
+    if (p->precision != QF_FP16 || p->G > 1) *bytes += small_most(p, n_batch * slices) * (size_t)p->small_elems * sizeof(float2);
     return QF_OK;
   }
   const qf_plan* q = batch_form(p);
@@ -1395,10 +1399,13 @@ static qf_status small_call(qf_plan* p, int n_batch, const uint8_t* bits_dev, in
   return QF_OK;
 }
 
-// Not where a single chain fits at a time and slices share the results of steps that no cut reaches.
+// Not where the workspace holds fewer chains than the launches of a group would run, or one at a time where slices
+// share the results of steps that no cut reaches.
 static bool call_runs_small(const qf_plan* p, int n_batch, int64_t slices) {
   if (!runs_small(p)) return false;
-  return slices < 2 || (p->flags & QF_PLAN_NO_HOIST) || small_room(p, n_batch * slices) > 1;
+  const int64_t chains = n_batch * slices, room = small_room(p, chains);
+  return room >= std::min<int64_t>(p->G, chains) &&
+         (room > 1 || slices < 2 || (p->flags & QF_PLAN_NO_HOIST));
 }
 
 static const StepMask kAllSteps = {{~0ull, ~0ull, ~0ull, ~0ull}};

@@ -118,7 +118,7 @@ def test_call_of_several_chains_equals_single_chains_bitwise(precision, cuts, ho
 
 
 @pytest.mark.parametrize("rows,cols,depth,n_open,n,precision", [
-    (2, 1, 8, 0, 1, "fp32"), (1, 5, 23, 1, 3, "bf16x3"), (3, 3, 16, 2, 65, "fp32"), (3, 4, 20, 3, 7, "fp16"),
+    (2, 1, 8, 0, 1, "fp32"), (1, 5, 23, 1, 3, "bf16x3"), (3, 3, 16, 2, 65, "fp16"), (3, 4, 20, 3, 7, "fp32"),
     (4, 4, 8, 3, 600, "fp32"), (3, 1, 43, 0, 2, "bf16x3")])
 def test_plans_of_small_tensors_vs_state_vector(ctx, rows, cols, depth, n_open, n, precision):
     """Plans whose chains run whole in a workgroup: FP32 products of at most 2^11 terms in at most 15 steps,
