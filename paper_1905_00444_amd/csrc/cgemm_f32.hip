@@ -32,106 +32,33 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <algorithm>
-#include "cgemm_common.h"
+#include "cgemm_f32.h"
 
 namespace qf {
 
-constexpr int kFBK = 16;       // complex k per K-tile
 constexpr int kFRow = 36;      // dwords per LDS row
 
-struct F32Args {
-  int64_t M, N, K;
-  const float2* A;
-  const float2* B;
-  float2* C;
-  int64_t lda, ldb;      // elements between rows (k contiguous) or between k's (row index contiguous)
-  int64_t batch, sa, sb, sc;  // batch strides
-  int64_t kc;            // k per chunk
-  float2* P;             // partial tiles [chunk][batch][M][N] when gridDim.y > 1
-  Renorm amap;           // MAPA: A is another product's result under its output map (om_*)
-  Renorm rn;
-};
-
-// Loads of one operand tile (ROWS x 16 complex) into registers: pairs of neighbours along the
-// contiguous index.  T = 0: k contiguous, 8 threads per row; T = 1: rows contiguous.
-// MAP: the operand is a result X[x][y] under an output map (or plain, om_nh = 0), read with its y along k
-// (T = 0) or along the rows (T = 1); the runs of y are at least 8 elements long, so a pair stays together.
-template <int ROWS, int NTH, int T, bool EDGE, bool MAP>
-struct F32Loader {
-  static constexpr int pairs = ROWS * kFBK / 2;
-  static constexpr int per = (pairs + NTH - 1) / NTH;
-  static constexpr bool partial = pairs % NTH != 0;
-  const float2* p[per];
-  int row[per], k[per];   // of the pair's first element
-  float4 r[per];
-  const float2* mbase;    // MAP: the operand's start, the tile's first row and k
-  int64_t mrow, mk;
-
-  __device__ __forceinline__ void init_map(const float2* base, int64_t row0, int64_t k0) {
-    mbase = base;
-    mrow = row0;
-    mk = k0;
-    init(base, 0, 0);
-  }
-  __device__ __forceinline__ void init(const float2* base, int64_t ld, int64_t k0) {
-#pragma unroll
-    for (int i = 0; i < per; ++i) {
-      const int id = (int)threadIdx.x + i * NTH;
-      if constexpr (T == 0) {
-        row[i] = id >> 3;
-        k[i] = 2 * (id & 7);
-        p[i] = base + row[i] * ld + k0 + k[i];
-      } else {
-        row[i] = 2 * (id % (ROWS / 2));
-        k[i] = id / (ROWS / 2);
-        p[i] = base + (k0 + k[i]) * ld + row[i];
-      }
+// A thread's pairs into a tile of [row][k].
+template <int T, class Loader>
+__device__ __forceinline__ void f32_stage(float* lds, const Loader& l) {
+  l.each([&](int row, int k, float4 v) {
+    float* d = lds + row * kFRow + 2 * k;
+    if constexpr (T == 0) {
+      *reinterpret_cast<float4*>(d) = v;
+    } else {
+      *reinterpret_cast<float2*>(d) = make_float2(v.x, v.y);
+      *reinterpret_cast<float2*>(d + kFRow) = make_float2(v.z, v.w);
     }
-  }
-  // Tile at kt (k relative to the chunk); rows_left / k_left: elements that exist (EDGE).
-  __device__ __forceinline__ void load(int64_t kt, int64_t ld, int64_t rows_left, int64_t k_left, const Renorm& map) {
-#pragma unroll
-    for (int i = 0; i < per; ++i) {
-      if (partial && (int)threadIdx.x + i * NTH >= pairs) continue;
-      const float2* q;
-      if constexpr (MAP) {
-        const int64_t x = T == 0 ? mrow + row[i] : mk + kt + k[i], y = T == 0 ? mk + kt + k[i] : mrow + row[i];
-        q = mbase + (c_row(map, x, ld) + c_col(map, y));
-      } else {
-        q = p[i] + (T == 0 ? kt : kt * ld);
-      }
-      if constexpr (!EDGE) {
-        r[i] = *reinterpret_cast<const float4*>(q);
-      } else {
-        const int64_t kk = kt + k[i];
-        const bool first = row[i] < rows_left && kk < k_left;
-        const bool second = T == 0 ? row[i] < rows_left && kk + 1 < k_left : row[i] + 1 < rows_left && kk < k_left;
-        float2 a = make_float2(0.f, 0.f), b = a;
-        if (first) a = q[0];
-        if (second) b = q[1];
-        r[i] = make_float4(a.x, a.y, b.x, b.y);
-      }
-    }
-  }
-  __device__ __forceinline__ void store(float* lds) const {
-#pragma unroll
-    for (int i = 0; i < per; ++i) {
-      if (partial && (int)threadIdx.x + i * NTH >= pairs) continue;
-      float* d = lds + row[i] * kFRow + 2 * k[i];
-      if constexpr (T == 0) {
-        *reinterpret_cast<float4*>(d) = r[i];
-      } else {
-        *reinterpret_cast<float2*>(d) = make_float2(r[i].x, r[i].y);
-        *reinterpret_cast<float2*>(d + kFRow) = make_float2(r[i].z, r[i].w);
-      }
-    }
-  }
-};
+  });
+}
 
 // Accumulators of 16 rows x 16 complex columns: element r of lane (l16, lg) is row 4 r + lg of column l16
 // (MFMA row 4 lg + r: A's rows are read in that order), so one store instruction writes four neighbouring
 // rows, which under an output map are contiguous memory.
-struct F32Acc { f4 re, im; };
+struct F32Acc {
+  f4 re, im;
+  __device__ __forceinline__ float2 at(int r) const { return make_float2(re[r], im[r]); }
+};
 
 template <int TM, int TN>
 __device__ __forceinline__ void f32_zero(F32Acc (&acc)[TM][TN]) {
@@ -161,49 +88,6 @@ __device__ __forceinline__ void f32_multiply(const f4 (&a)[TM], const f4 (&b)[TN
     }
 }
 
-// Stores a wave's 16 TM x 16 TN results whose first is (m, n), returns the largest magnitude.  c_row and
-// c_col add over disjoint bits of their index (and m N over sums), so a lane's own part is computed once
-// and the rest is uniform.
-template <int TM, int TN, bool EDGE>
-__device__ __forceinline__ float f32_store(float2* C, const Renorm& rn, int64_t m, int64_t n, int64_t M, int64_t N,
-                                           float unscale, const F32Acc (&acc)[TM][TN]) {
-  const int lane = threadIdx.x & 63, l16 = lane & 15, lg = lane >> 4;
-  float2* own = C + (c_row(rn, lg, N) + c_col(rn, l16));
-  float mx = 0.f;
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const float2 o = make_float2(acc[i][j].re[r] * unscale, acc[i][j].im[r] * unscale);
-        const int64_t at = c_row(rn, m + 16 * i, N) + c_row(rn, 4 * r, N) + c_col(rn, n + 16 * j);
-        if (!EDGE || (m + 16 * i + 4 * r + lg < M && n + 16 * j + l16 < N)) own[at] = o;
-        mx = fmaxf(mx, cmax(o));  // zeros past the edge
-      }
-  return mx;
-}
-
-struct F32Place { int64_t m0, n0, batch; };
-
-// Tile id of a launch (batch-major): consecutive tiles go to one XCD (8 XCDs, dealt round-robin) and are
-// rasterised in groups of row tiles.
-__device__ __forceinline__ F32Place f32_place(int64_t id, int64_t tiles_m, int64_t tiles_n, int64_t total, int BM,
-                                              int BN) {
-  const int64_t ntiles = tiles_m * tiles_n;
-  if ((total & 7) == 0) id = (id & 7) * (total >> 3) + (id >> 3);
-  F32Place p;
-  p.batch = id / ntiles;
-  const int64_t bid = id - p.batch * ntiles;
-  const int64_t group = 8;
-  const int64_t per_group = group * tiles_n;
-  const int64_t first_m = bid / per_group * group;
-  const int64_t gsize = (tiles_m - first_m) < group ? (tiles_m - first_m) : group;
-  p.m0 = (first_m + (bid % per_group) % gsize) * BM;
-  p.n0 = (bid % per_group) / gsize * BN;
-  return p;
-}
-
 template <int WM, int WN, int TM, int TN>
 struct F32Tile {
   static constexpr int threads = 64 * WM * WN, BM = 16 * WM * TM, BN = 16 * WN * TN;
@@ -218,7 +102,7 @@ cgemm_f32(F32Args g) {
   __shared__ __attribute__((aligned(16))) float lds[2 * Tile::stage];
 
   const int64_t tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
-  const F32Place at = f32_place(blockIdx.x, tiles_m, tiles_n, tiles_m * tiles_n * g.batch, BM, BN);
+  const F32Place at = f32_place(blockIdx.x, (uint32_t)tiles_m, (uint32_t)tiles_n, gridDim.x, BM, BN);
   const int64_t m0 = at.m0, n0 = at.n0, batch = at.batch;
   const bool partial = gridDim.y > 1;
   const int64_t k0 = blockIdx.y * g.kc;
@@ -253,8 +137,8 @@ cgemm_f32(F32Args g) {
   };
   auto stage = [&](int t) {
     float* st = lds + (t & 1) * Tile::stage;
-    la.store(st);
-    lb.store(st + BM * kFRow);
+    f32_stage<TA>(st, la);
+    f32_stage<TB>(st + BM * kFRow, lb);
   };
   fetch(0);
   stage(0);
@@ -345,7 +229,8 @@ hipError_t launch_cgemm_f32(hipStream_t st, int64_t M, int64_t N, int64_t K, con
   if (e != hipSuccess) return e;
   g.lda = K;
   g.ldb = K;
-  f32_pick<0, 0, false>(st, g, *split, tile);
+  if (tile == F32_AUTO && f32s_takes(M, N, K)) launch_f32s(st, g, *split, false, false);
+  else f32_pick<0, 0, false>(st, g, *split, tile);
   return hipGetLastError();
 }
 
@@ -360,7 +245,8 @@ hipError_t launch_cgemm_f32_env(hipStream_t st, int side, int64_t M, int64_t N, 
   g.lda = N;  // env's plain row pitch
   g.ldb = K;
   g.amap = map;
-  if (side) f32_pick<1, 1, true>(st, g, *split, F32_AUTO);
+  if (f32s_takes(g.M, g.N, g.K)) launch_f32s(st, g, *split, true, side);
+  else if (side) f32_pick<1, 1, true>(st, g, *split, F32_AUTO);
   else f32_pick<0, 1, true>(st, g, *split, F32_AUTO);
   return hipGetLastError();
 }

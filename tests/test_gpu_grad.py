@@ -80,6 +80,24 @@ def test_grad_small_grids_vs_adjoint_oracle(ctx, rows, cols, depth, n, batch):
     assert rel_err(g.cpu().numpy(), ref) <= 2e-5
 
 
+def test_grad_4x4_d32_large_products_vs_adjoint_oracle(ctx):
+    """Environments of 2^12 x 2^8 x 2^8 products, plain and under output maps, on the bfloat16 matrix cores: the
+    small grids' bound."""
+    import torch
+    from paper_1905_00444_amd import Circuit, Plan
+    _say("grad 4x4 d32")
+    c = generate(4, 4, 32, 3)
+    text = c.to_text()
+    bits = random_bitstrings(2, 16, 11)
+    rng = np.random.default_rng(4)
+    cot = rng.normal(size=(2, 1)) + 1j * rng.normal(size=(2, 1))
+    p = Plan(ctx, Circuit(ctx, text), sweep_plan(c), "fp32", backward=True)
+    assert max(s["m_bits"] + s["n_bits"] + s["k_bits"] for s in p.steps()) >= 24
+    g = p.backward(bits, cot)
+    torch.cuda.synchronize()
+    assert rel_err(g.cpu().numpy(), _oracle_grad(text, bits, cot[:, 0])) <= 2e-5
+
+
 @pytest.mark.parametrize("n,batch", [(1, 1), (70, 1), (3, 8)])
 def test_grad_of_small_regions_cuts_open_vs_adjoint_oracle(ctx, n, batch):
     """Chains that run whole in a workgroup, with results that later steps than the next one read, 4 slices and

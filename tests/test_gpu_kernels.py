@@ -119,7 +119,7 @@ def test_cgemm_matches_numpy(ctx, precision, M, N, K):
 # into chunks that do not divide it
 RAGGED_SHAPES = [(129, 65, 33), (31, 33, 17), (257, 129, 48), (300, 1, 50), (1, 300, 50), (130, 16, 49), (129, 17, 15),
                  (2049, 7, 40), (1000, 600, 300), (4097, 129, 31), (100, 9, 5000), (33, 70, 2049), (1, 2, 9001),
-                 (1 << 15, 16, 256)]
+                 (1 << 15, 16, 256), (70, 60, 2049), (2050, 3, 2049)]
 
 
 @pytest.mark.parametrize("precision", ["fp32", "bf16x3", "fp16"])
@@ -142,6 +142,59 @@ def test_cgemm_any_size_is_fp32_exact(split_ctx, precision, M, N, K):
     err = np.max(np.abs(C.cpu().numpy().astype(np.complex128) - ref) / bound)
     assert err <= TOL["fp32"], err
     assert bool((guard[M * N:] == 7.0).all())
+
+
+# Products on six bfloat16 products: each tile whole and with remainders in M, N and K, and K in chunks
+SIX_SHAPES = [(4096, 1024, 128), (4097, 1025, 131), (16384, 64, 128), (16385, 65, 129), (4096, 128, 128),
+              (4095, 127, 143), (64, 64, 4096), (65, 70, 4100), (256, 256, 256)]
+
+
+@pytest.mark.parametrize("M,N,K", SIX_SHAPES)
+def test_cgemm_fp32_on_bfloat16_products(split_ctx, M, N, K):
+    """Norm-wise per element: 2^-26 of each product is left out, and each step of 16 k, its small sums and the
+    chunks round the sum, 2^-23 (K / 16 + 8) of sum |a| |b|.  One row of A and one of B are near the smallest
+    normal number, where the products' own rounding is 2^-149."""
+    import torch
+    from paper_1905_00444_amd import cgemm
+    _say(f"cgemm six products {M}x{N}x{K}")
+    rng = np.random.default_rng(M * 5 + N * 3 + K)
+    A, B = _rand_c64(rng, (M, K)), _rand_c64(rng, (N, K))
+    A[M // 2] *= np.float32(1e-36)
+    B[N - 1] *= np.float32(1e-30)
+    ref = A.astype(np.complex128) @ B.astype(np.complex128).T
+    bound = np.abs(A).astype(np.float64) @ np.abs(B).astype(np.float64).T
+    guard = torch.full((M * N + 64,), 7.0 + 0j, dtype=torch.complex64, device="cuda")
+    C = cgemm(split_ctx, torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda(), "fp32", out=guard[:M * N].view(M, N))
+    torch.cuda.synchronize()
+    err = np.max(np.abs(C.cpu().numpy().astype(np.complex128) - ref) / (bound * 2.0 ** -23 * (K / 16 + 8) + 4 * K * 2.0 ** -149))
+    assert err <= 1.0, err
+    assert bool((guard[M * N:] == 7.0).all())
+
+
+@pytest.mark.parametrize("M,N,K", [(4096, 1024, 128), (16385, 65, 129), (64, 64, 4096)])
+def test_cgemm_fp32_on_bfloat16_products_keeps_infinities(split_ctx, M, N, K):
+    """Rows with an infinity, a NaN or a number beyond bfloat16's range come out as FP32 sums do; no other row
+    changes."""
+    import torch
+    from paper_1905_00444_amd import cgemm
+    _say(f"cgemm six products, not finite {M}x{N}x{K}")
+    rng = np.random.default_rng(K)
+    A, B = _rand_c64(rng, (M, K)), _rand_c64(rng, (N, K))
+    A[M - 1] = 0
+    B[:, 4] = np.clip(B[:, 4].real, -0.9, 0.9) + 1j * np.clip(B[:, 4].imag, -0.9, 0.9)
+    run = lambda: cgemm(split_ctx, torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda()).cpu().numpy()
+    finite = run()
+    A[1, 2] = complex(np.inf, 0.0)
+    A[20, 3] = complex(np.nan, 0.0)
+    A[M - 1, 4] = 3.4e38
+    C = run()
+    assert np.array_equal(C[1].real, np.copysign(np.inf, B[:, 2].real))
+    assert np.array_equal(C[1].imag, np.copysign(np.inf, B[:, 2].imag))
+    assert np.isnan(C[20]).all()
+    assert np.allclose(C[M - 1].astype(np.complex128), 3.4e38 * B[:, 4].astype(np.complex128), rtol=2.0 ** -22, atol=0)
+    rest = np.setdiff1d(np.arange(M), [1, 20, M - 1])
+    bound = np.abs(A[rest]).astype(np.float64) @ np.abs(B).astype(np.float64).T
+    assert np.max(np.abs(C[rest] - finite[rest]) / bound) <= 2.0 ** -22 * (K / 16 + 8)
 
 
 SPLIT_SHAPES = [(128, 64, 65536), (64, 32, 131072), (32, 32, 16384), (512, 512, 16384), (256, 128, 32768)]
