@@ -128,14 +128,22 @@ struct TileLds {
 };
 
 // Stage ROWS x 32 complex (held as float4 = 2 complex per register) into LDS with conversion.
+// Row of a thread's pair i and the pair's place in the row: pairs run along k, or (rows) along the rows.
+template <int ROWS>
+__device__ __forceinline__ void pair_of(int i, bool rows, int& row, int& c4) {
+  const int idx = threadIdx.x + i * kThreads;
+  row = rows ? idx % ROWS : idx >> 4;
+  c4 = rows ? idx / ROWS : idx & 15;
+}
+
 template <int PREC, int ROWS>
-__device__ __forceinline__ void stage_tile(char* lds, const float4 (&r)[ROWS * 16 / kThreads], float scale) {
+__device__ __forceinline__ void stage_tile(char* lds, const float4 (&r)[ROWS * 16 / kThreads], float scale,
+                                           bool rows = false) {
   constexpr int per = ROWS * 16 / kThreads;
-  const int tid = threadIdx.x;
 #pragma unroll
   for (int i = 0; i < per; ++i) {
-    const int idx = tid + i * kThreads;
-    const int row = idx >> 4, c4 = idx & 15;  // c4: pair of complex k = 2*c4, 2*c4+1
+    int row, c4;  // c4: pair of complex k = 2*c4, 2*c4+1
+    pair_of<ROWS>(i, rows, row, c4);
     const float4 v = r[i];
     if constexpr (PREC == P_BF16X3) {
       const uint32_t h0 = pack_bf16x2(v.x, v.y), h1 = pack_bf16x2(v.z, v.w);
@@ -164,11 +172,34 @@ __device__ __forceinline__ void load_tile(float4 (&r)[ROWS * 16 / kThreads], con
   }
 }
 
-template <int PREC, int WTM, int WTN>
+// The loads of an operand that is read through an OpMap (see F32Gather): p is its element (tile's first row, k = 0).
+template <int ROWS>
+__device__ __forceinline__ void gather_tile(float4 (&r)[ROWS * 16 / kThreads], const float2* __restrict__ p,
+                                            const OpMap& m, const uint32_t (&at)[ROWS * 16 / kThreads], uint32_t k0) {
+  const uint32_t off = map_bits<12>(k0, m.k), second = 1u << (m.k & 31);
+#pragma unroll
+  for (int i = 0; i < ROWS * 16 / kThreads; ++i) {
+    const float2* q = p + (at[i] | off);
+    const float2 a = q[0], b = q[second];
+    r[i] = make_float4(a.x, a.y, b.x, b.y);
+  }
+}
+template <int ROWS>
+__device__ __forceinline__ void gather_places(uint32_t (&at)[ROWS * 16 / kThreads], const OpMap& m, int64_t row0) {
+  const uint32_t r0 = map_row(m, (uint32_t)row0);
+#pragma unroll
+  for (int i = 0; i < ROWS * 16 / kThreads; ++i) {
+    int row, c4;
+    pair_of<ROWS>(i, m.row_fast, row, c4);
+    at[i] = r0 | map_bits<7>(row, m.row[0]) | map_bits<5>(2 * c4, m.k);
+  }
+}
+
+template <int PREC, int WTM, int WTN, bool GA, bool GB>
 __global__ void __launch_bounds__(kThreads)
 cgemm_mfma(int64_t M, int64_t N, int64_t K, const float2* __restrict__ A, const float2* __restrict__ B,
            float2* __restrict__ C, int64_t sa, int64_t sb, int64_t sc, const uint32_t* amaxA,
-           const uint32_t* amaxB, Renorm rn, int64_t kc, float2* __restrict__ P, int64_t nbatch) {
+           const uint32_t* amaxB, Renorm rn, int64_t kc, float2* __restrict__ P, int64_t nbatch, OpMap ma, OpMap mb) {
   constexpr int BM = 32 * WTM, BN = 16 * WTN;
   using LA = TileLds<PREC, BM>;
   using LB = TileLds<PREC, BN>;
@@ -193,8 +224,20 @@ cgemm_mfma(int64_t M, int64_t N, int64_t K, const float2* __restrict__ A, const 
   const int64_t tn = (bid % per_group) / gsize;
 
   const bool partial = gridDim.y > 1;
-  A += batch * sa + tm * BM * K + blockIdx.y * kc;
-  B += batch * sb + tn * BN * K + blockIdx.y * kc;
+  const uint32_t k0 = blockIdx.y * (uint32_t)kc;
+  uint32_t pa[GA ? BM * 16 / kThreads : 1], pb[GB ? BN * 16 / kThreads : 1];
+  if constexpr (GA) {
+    A += map_base(ma, batch, sa);
+    gather_places<BM>(pa, ma, tm * BM);
+  } else {
+    A += batch * sa + tm * BM * K + blockIdx.y * kc;
+  }
+  if constexpr (GB) {
+    B += map_base(mb, batch, sb);
+    gather_places<BN>(pb, mb, tn * BN);
+  } else {
+    B += batch * sb + tn * BN * K + blockIdx.y * kc;
+  }
   if (partial) {
     C = P + ((int64_t)blockIdx.y * nbatch + batch) * M * N;
   } else {
@@ -216,17 +259,19 @@ cgemm_mfma(int64_t M, int64_t N, int64_t K, const float2* __restrict__ A, const 
     for (int j = 0; j < WTN; ++j) acc[i][j] = (f4){0.f, 0.f, 0.f, 0.f};
 
   float4 ra[BM * 16 / kThreads], rb[BN * 16 / kThreads];
-  load_tile<BM>(ra, A, K, 0);
-  load_tile<BN>(rb, B, K, 0);
+  auto fetch = [&](int64_t kt) {
+    if constexpr (GA) gather_tile<BM>(ra, A, ma, pa, k0 + (uint32_t)(kt * kBK));
+    else load_tile<BM>(ra, A, K, kt * kBK);
+    if constexpr (GB) gather_tile<BN>(rb, B, mb, pb, k0 + (uint32_t)(kt * kBK));
+    else load_tile<BN>(rb, B, K, kt * kBK);
+  };
+  fetch(0);
   const int64_t nk = kc / kBK;
   for (int64_t kt = 0; kt < nk; ++kt) {
-    stage_tile<PREC, BM>(ldsA, ra, scale_a);
-    stage_tile<PREC, BN>(ldsB, rb, scale_b);
+    stage_tile<PREC, BM>(ldsA, ra, scale_a, GA && ma.row_fast);
+    stage_tile<PREC, BN>(ldsB, rb, scale_b, GB && mb.row_fast);
     __syncthreads();
-    if (kt + 1 < nk) {
-      load_tile<BM>(ra, A, K, (kt + 1) * kBK);
-      load_tile<BN>(rb, B, K, (kt + 1) * kBK);
-    }
+    if (kt + 1 < nk) fetch(kt + 1);
     // 2 chunks of 16 complex k; lane group lg holds complex k 4*lg .. 4*lg+3 (8 real k)
     const BExpand bx(l16 & 1);
 #pragma unroll
@@ -616,11 +661,20 @@ cgemm_splitk(int64_t M, int64_t N, int64_t K, const float2* __restrict__ A, cons
 template <int PREC, int WTM, int WTN>
 static void launch_tiled(hipStream_t st, int64_t M, int64_t N, int64_t K, const float2* A, const float2* B, float2* C,
                          int64_t batch, int64_t sa, int64_t sb, int64_t sc, const uint32_t* amaxA,
-                         const uint32_t* amaxB, const Renorm& rn, int split, float2* P) {
+                         const uint32_t* amaxB, const Renorm& rn, int split, float2* P, const OpMap& ma,
+                         const OpMap& mb) {
   constexpr int BM = 32 * WTM, BN = 16 * WTN;
   const int64_t tiles = (M / BM) * (N / BN);
-  hipLaunchKernelGGL((cgemm_mfma<PREC, WTM, WTN>), dim3((unsigned)(tiles * batch), (unsigned)split), dim3(kThreads), 0, st,
-                     M, N, K, A, B, C, sa, sb, sc, amaxA, amaxB, rn, K / split, P, batch);
+  auto run = [&](auto* kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(tiles * batch), (unsigned)split), dim3(kThreads), 0, st, M, N, K, A, B, C,
+                       sa, sb, sc, amaxA, amaxB, rn, K / split, P, batch, ma, mb);
+  };
+  if constexpr (PREC == P_BF16X3) {
+    if (ma.on && mb.on) return run(cgemm_mfma<PREC, WTM, WTN, true, true>);
+    if (ma.on) return run(cgemm_mfma<PREC, WTM, WTN, true, false>);
+    if (mb.on) return run(cgemm_mfma<PREC, WTM, WTN, false, true>);
+  }
+  run(cgemm_mfma<PREC, WTM, WTN, false, false>);
 }
 
 static bool pow2(int64_t x) { return x > 0 && (x & (x - 1)) == 0; }
@@ -701,20 +755,20 @@ template <int PREC>
 static hipError_t launch_mfma(hipStream_t st, int variant, int64_t M, int64_t N, int64_t K, const float2* A,
                               const float2* B, float2* C, int64_t batch, int64_t sa, int64_t sb, int64_t sc,
                               const uint32_t* amaxA, const uint32_t* amaxB, const Renorm& rn, int split,
-                              float2* P) {
+                              float2* P, const OpMap& ma, const OpMap& mb) {
   switch (variant) {
     case GEMM_LARGE:
       hipLaunchKernelGGL((cgemm_v2<PREC>), dim3((unsigned)((M / kV2BM) * (N / kV2BN)), (unsigned)split, (unsigned)batch),
                          dim3(kV2Threads), 0, st, M, N, K, A, B, C, sa, sb, sc, amaxA, amaxB, rn, K / split, P);
       break;
     case GEMM_TILED_4X4:
-      launch_tiled<PREC, 4, 4>(st, M, N, K, A, B, C, batch, sa, sb, sc, amaxA, amaxB, rn, split, P);
+      launch_tiled<PREC, 4, 4>(st, M, N, K, A, B, C, batch, sa, sb, sc, amaxA, amaxB, rn, split, P, ma, mb);
       break;
     case GEMM_TILED_2X2:
-      launch_tiled<PREC, 2, 2>(st, M, N, K, A, B, C, batch, sa, sb, sc, amaxA, amaxB, rn, split, P);
+      launch_tiled<PREC, 2, 2>(st, M, N, K, A, B, C, batch, sa, sb, sc, amaxA, amaxB, rn, split, P, ma, mb);
       break;
     default:
-      launch_tiled<PREC, 1, 2>(st, M, N, K, A, B, C, batch, sa, sb, sc, amaxA, amaxB, rn, split, P);
+      launch_tiled<PREC, 1, 2>(st, M, N, K, A, B, C, batch, sa, sb, sc, amaxA, amaxB, rn, split, P, ma, mb);
   }
   return hipGetLastError();
 }
@@ -763,10 +817,11 @@ hipError_t launch_env_gemm(hipStream_t st, int side, int64_t M, int64_t N, int64
 hipError_t launch_cgemm_ex(hipStream_t st, int precision, int64_t M, int64_t N, int64_t K, const float2* A,
                            const float2* B, float2* C, int64_t batch, int64_t sa, int64_t sb, int64_t sc,
                            const uint32_t* amaxA, const uint32_t* amaxB, const Renorm& rn, int variant,
-                           float2* scratch, size_t scratch_bytes) {
+                           float2* scratch, size_t scratch_bytes, const OpMap* ma, const OpMap* mb) {
   if (rn.c && (!rn.a || !rn.b)) return hipErrorInvalidValue;
   if (M < 1 || N < 1 || K < 1 || batch < 1) return hipErrorInvalidValue;
   if (precision != P_FP32 && precision != P_BF16X3 && precision != P_FP16) return hipErrorInvalidValue;
+  if ((ma || mb) && (variant != GEMM_AUTO || !cgemm_reads_maps(precision, M, N, K, batch))) return hipErrorInvalidValue;
   const bool chosen = variant != GEMM_AUTO && cgemm_variant_fits(precision, M, N, K, variant);
   int v = chosen ? variant : cgemm_default_variant(precision, M, N, K);
   if (rn.c && !rn.cleared) hipLaunchKernelGGL(renorm_reset, dim3(1), dim3(64), 0, st, rn.c);
@@ -805,17 +860,28 @@ hipError_t launch_cgemm_ex(hipStream_t st, int precision, int64_t M, int64_t N, 
   hipError_t e;
   if (precision == P_FP32 || v == GEMM_F32) {
     static const int tiles[] = {F32_AUTO, F32_64X64, F32_64X32, F32_32X32, F32_64X64};
-    e = launch_cgemm_f32(st, M, N, K, A, B, C, batch, sa, sb, sc, rn, &split, scratch, v == GEMM_F32 ? F32_AUTO : tiles[v]);
+    e = launch_cgemm_f32(st, M, N, K, A, B, C, batch, sa, sb, sc, rn, &split, scratch,
+                         v == GEMM_F32 ? F32_AUTO : tiles[v], ma, mb);
   } else {
     if (!chosen) v = cgemm_default_variant(precision, M, N, K, batch * split);
+    const OpMap a = ma ? *ma : OpMap{}, b = mb ? *mb : OpMap{};
     e = precision == P_BF16X3
-            ? launch_mfma<P_BF16X3>(st, v, M, N, K, A, B, C, batch, sa, sb, sc, amaxA, amaxB, rn, split, scratch)
-            : launch_mfma<P_FP16>(st, v, M, N, K, A, B, C, batch, sa, sb, sc, amaxA, amaxB, rn, split, scratch);
+            ? launch_mfma<P_BF16X3>(st, v, M, N, K, A, B, C, batch, sa, sb, sc, amaxA, amaxB, rn, split, scratch, a, b)
+            : launch_mfma<P_FP16>(st, v, M, N, K, A, B, C, batch, sa, sb, sc, amaxA, amaxB, rn, split, scratch, a, b);
   }
   if (e != hipSuccess || split == 1) return e;
   const unsigned blocks = (unsigned)std::min<int64_t>((batch * M * N + kReduceOut - 1) / kReduceOut, 65536);
   hipLaunchKernelGGL(cgemm_split_reduce, dim3(blocks), dim3(256), 0, st, scratch, split, batch, M * N, N, sc, C, rn);
   return hipGetLastError();
+}
+
+// The FP32 tiles where they are whole, and the 16-bit tiles below the largest; FP16 keeps its copies.
+bool cgemm_reads_maps(int precision, int64_t M, int64_t N, int64_t K, int64_t batch) {
+  if (precision == P_FP16 || !pow2(M) || !pow2(N) || !pow2(K)) return false;
+  int v = cgemm_default_variant(precision, M, N, K);
+  if (v == GEMM_F32) return M >= 32 && (N >= 32 || N == 16) && K >= 16;
+  if (precision == P_FP32 || v == GEMM_TALL || v == GEMM_SKINNY || v == GEMM_SPLITK || v == GEMM_SIMT) return false;
+  return cgemm_default_variant(precision, M, N, K, batch * split_count(precision, v, M, N, K)) != GEMM_LARGE;
 }
 
 hipError_t launch_cgemm(hipStream_t st, int precision, int64_t M, int64_t N, int64_t K, const float2* A,

@@ -191,6 +191,23 @@ struct BExpand {
   }
 };
 
+// Bits of i scattered to N packed positions (OpMap).
+template <int N>
+__device__ __forceinline__ uint32_t map_bits(uint32_t i, uint64_t v) {
+  uint32_t off = 0;
+#pragma unroll
+  for (int b = 0; b < N; ++b) off |= ((i >> b) & 1) << ((v >> (5 * b)) & 31);
+  return off;
+}
+__device__ __forceinline__ uint32_t map_row(const OpMap& m, uint32_t row) {
+  return map_bits<12>(row & 0xfff, m.row[0]) | map_bits<12>(row >> 12, m.row[1]);
+}
+__device__ __forceinline__ int64_t map_base(const OpMap& m, int64_t batch, int64_t stride) {
+  int64_t at = m.src_base + (m.base_table ? m.base_table[batch * m.base_stride] : batch * stride);
+  if (m.dyn_bits) at += (int64_t)(*m.dyn_bits & 1) * m.dyn_stride;
+  return at;
+}
+
 // Bitstring b (-1: idle) and slice s of chain g.
 __device__ __forceinline__ void chain_of(const ChainGroup& c, int g, int64_t& b, int64_t& s) {
   int64_t off;  // slice offset in the range

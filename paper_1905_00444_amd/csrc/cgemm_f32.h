@@ -18,6 +18,7 @@ struct F32Args {
   float2* P;             // partial tiles [chunk][batch][M][N] when gridDim.y > 1
   Renorm amap;           // MAPA: A is another product's result under its output map (om_*)
   Renorm rn;
+  OpMap ma, mb;          // gathered operands (whole tiles only)
 };
 
 // cgemm_f32s.hip: products that it takes instead (by shape alone: a result does not depend on the batch), and
@@ -87,6 +88,52 @@ struct F32Loader {
     }
   }
   // put(row, k, pair) for the thread's pairs.
+  template <class Put>
+  __device__ __forceinline__ void each(Put&& put) const {
+#pragma unroll
+    for (int i = 0; i < per; ++i)
+      if (!partial || (int)threadIdx.x + i * NTH < pairs) put(row[i], k[i], r[i]);
+  }
+};
+
+// The same loads of an operand that is read through an OpMap: two elements of one row each, from where the row
+// and k are scattered to.  Rows or k's run over the lanes, whichever has the lower address bits; the plan
+// checks that the lowest address bits belong to a tile's own rows and k's, so that lines are used whole.
+// Twice the load instructions, but no launch and no pass to copy the operand: 16 chains of 256^3 split-BF16
+// products 17.0 us with copies made, 6.7 us each, before; 20 us gathered.  The 4x5 path sum 938 -> 772 us, 4x4
+// sampling 3.01 -> 2.63 ms.
+template <int ROWS, int NTH>
+struct F32Gather {
+  static constexpr int pairs = ROWS * kFBK / 2;
+  static constexpr int per = (pairs + NTH - 1) / NTH;
+  static constexpr bool partial = pairs % NTH != 0;
+  const float2* p[per];
+  int row[per], k[per];
+  float4 r[per];
+  uint32_t second, kc0;
+
+  __device__ __forceinline__ void init_gather(const float2* base, const OpMap& m, int64_t row0, int64_t k0) {
+    const uint32_t r0 = map_row(m, (uint32_t)row0);
+    second = 1u << (m.k & 31);
+    kc0 = (uint32_t)k0;
+#pragma unroll
+    for (int i = 0; i < per; ++i) {
+      const int id = (int)threadIdx.x + i * NTH;
+      row[i] = m.row_fast ? id % ROWS : id / (kFBK / 2);
+      k[i] = 2 * (m.row_fast ? id / ROWS : id % (kFBK / 2));
+      p[i] = base + (r0 | map_bits<7>(row[i], m.row[0]) | map_bits<4>(k[i], m.k));
+    }
+  }
+  __device__ __forceinline__ void load_gather(int64_t kt, const OpMap& m) {
+    const uint32_t off = map_bits<12>(kc0 + (uint32_t)kt, m.k);
+#pragma unroll
+    for (int i = 0; i < per; ++i) {
+      if (partial && (int)threadIdx.x + i * NTH >= pairs) continue;
+      const float2* q = p[i] + off;
+      const float2 a = q[0], b = q[second];
+      r[i] = make_float4(a.x, a.y, b.x, b.y);
+    }
+  }
   template <class Put>
   __device__ __forceinline__ void each(Put&& put) const {
 #pragma unroll

@@ -32,6 +32,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <algorithm>
+#include <type_traits>
 #include "cgemm_f32.h"
 
 namespace qf {
@@ -94,7 +95,7 @@ struct F32Tile {
   static constexpr int stage = (BM + BN) * kFRow;  // dwords
 };
 
-template <int WM, int WN, int TM, int TN, int TA, int TB, bool CONJ, bool EDGE>
+template <int WM, int WN, int TM, int TN, int TA, int TB, bool CONJ, bool EDGE, bool GA, bool GB>
 __global__ void __launch_bounds__(64 * WM * WN)
 cgemm_f32(F32Args g) {
   using Tile = F32Tile<WM, WN, TM, TN>;
@@ -114,11 +115,13 @@ cgemm_f32(F32Args g) {
   const int l16 = lane & 15, lg = lane >> 4;
 
   constexpr bool MAPA = TB == 1;
-  F32Loader<BM, NTH, TA, EDGE, MAPA> la;
-  F32Loader<BN, NTH, TB, EDGE, false> lb;
-  if constexpr (MAPA) la.init_map(g.A + batch * g.sa, m0, k0);
-  else la.init(g.A + batch * g.sa + (TA == 0 ? m0 * g.lda : m0), g.lda, k0);
-  lb.init(g.B + batch * g.sb + (TB == 0 ? n0 * g.ldb : n0), g.ldb, k0);
+  std::conditional_t<GA, F32Gather<BM, NTH>, F32Loader<BM, NTH, TA, EDGE, MAPA>> la;
+  std::conditional_t<GB, F32Gather<BN, NTH>, F32Loader<BN, NTH, TB, EDGE, false>> lb;
+  if constexpr (GA) la.init_gather(g.A + map_base(g.ma, batch, g.sa), g.ma, m0, k0);
+  else if constexpr (MAPA) la.init_map((g.A + batch * g.sa), m0, k0);
+  else la.init((g.A + batch * g.sa) + (TA == 0 ? m0 * g.lda : m0), g.lda, k0);
+  if constexpr (GB) lb.init_gather(g.B + map_base(g.mb, batch, g.sb), g.mb, n0, k0);
+  else lb.init((g.B + batch * g.sb) + (TB == 0 ? n0 * g.ldb : n0), g.ldb, k0);
   const int64_t ml = g.M - m0, nl = g.N - n0;  // rows and columns that exist from the tile's first on
 
   float unscale = 1.f;
@@ -132,8 +135,10 @@ cgemm_f32(F32Args g) {
 
   const int nk = (int)((klen + kFBK - 1) / kFBK);
   auto fetch = [&](int t) {
-    la.load((int64_t)t * kFBK, g.lda, ml, klen, g.amap);
-    lb.load((int64_t)t * kFBK, g.ldb, nl, klen, g.amap);
+    if constexpr (GA) la.load_gather((int64_t)t * kFBK, g.ma);
+    else la.load((int64_t)t * kFBK, g.lda, ml, klen, g.amap);
+    if constexpr (GB) lb.load_gather((int64_t)t * kFBK, g.mb);
+    else lb.load((int64_t)t * kFBK, g.ldb, nl, klen, g.amap);
   };
   auto stage = [&](int t) {
     float* st = lds + (t & 1) * Tile::stage;
@@ -179,10 +184,14 @@ static void f32_launch(hipStream_t st, const F32Args& g, int split) {
   const dim3 grid((unsigned)tiles, (unsigned)split), block(Tile::threads);
   // whole tiles and pairs of elements that never straddle a row's end
   const bool whole = g.M % Tile::BM == 0 && g.N % Tile::BN == 0 && g.kc % kFBK == 0 && g.kc * split == g.K;
-  if (whole)
-    hipLaunchKernelGGL((cgemm_f32<WM, WN, TM, TN, TA, TB, CONJ, false>), grid, block, 0, st, g);
-  else
-    hipLaunchKernelGGL((cgemm_f32<WM, WN, TM, TN, TA, TB, CONJ, true>), grid, block, 0, st, g);
+  auto run = [&](auto* kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, st, g); };
+  if constexpr (TA == 0 && TB == 0 && !CONJ) {
+    if (g.ma.on && g.mb.on) return run(cgemm_f32<WM, WN, TM, TN, 0, 0, false, false, true, true>);
+    if (g.ma.on) return run(cgemm_f32<WM, WN, TM, TN, 0, 0, false, false, true, false>);
+    if (g.mb.on) return run(cgemm_f32<WM, WN, TM, TN, 0, 0, false, false, false, true>);
+  }
+  if (whole) run(cgemm_f32<WM, WN, TM, TN, TA, TB, CONJ, false, false, false>);
+  else run(cgemm_f32<WM, WN, TM, TN, TA, TB, CONJ, true, false, false>);
 }
 
 // Tile of a launch: 64 x 64 where that gives every CU its four workgroups (4096^3: 140 against 138 TFLOP/s
@@ -223,8 +232,10 @@ static hipError_t f32_args(F32Args& g, int64_t M, int64_t N, int64_t K, const fl
 
 hipError_t launch_cgemm_f32(hipStream_t st, int64_t M, int64_t N, int64_t K, const float2* A, const float2* B,
                             float2* C, int64_t batch, int64_t sa, int64_t sb, int64_t sc, const Renorm& rn, int* split,
-                            float2* P, int tile) {
+                            float2* P, int tile, const OpMap* ma, const OpMap* mb) {
   F32Args g;
+  if (ma) g.ma = *ma;
+  if (mb) g.mb = *mb;
   const hipError_t e = f32_args(g, M, N, K, A, B, C, batch, sa, sb, sc, rn, split, P);
   if (e != hipSuccess) return e;
   g.lda = K;

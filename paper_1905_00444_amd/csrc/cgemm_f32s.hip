@@ -28,6 +28,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <algorithm>
+#include <type_traits>
 #include "cgemm_f32.h"
 
 namespace qf {
@@ -124,7 +125,7 @@ __device__ __forceinline__ bool f32s_out_of_range(const F32sAcc (&acc)[TM][TN]) 
 }
 
 // The wave's results as plain FP32 sums over k0 .. k0 + klen - 1.
-template <int TM, int TN, int TA, int TB, bool CONJ, bool MAPA>
+template <int TM, int TN, int TA, int TB, bool CONJ, bool MAPA, bool GA, bool GB>
 __device__ __forceinline__ float f32s_plain(const F32Args& g, const float2* A, const float2* B, float2* C,
                                             const Renorm& rn, int64_t m, int64_t n, int64_t k0, int64_t klen,
                                             float unscale) {
@@ -137,8 +138,11 @@ __device__ __forceinline__ float f32s_plain(const F32Args& g, const float2* A, c
     float2 c = make_float2(0.f, 0.f);
 #pragma unroll 1
     for (int64_t k = k0; k < k0 + klen; ++k) {
-      float2 a, b = TB == 0 ? B[y * g.ldb + k] : B[k * g.ldb + y];
-      if constexpr (MAPA) a = A[c_row(g.amap, TA == 0 ? x : k, g.lda) + c_col(g.amap, TA == 0 ? k : x)];
+      float2 a, b;
+      if constexpr (GB) b = B[map_row(g.mb, (uint32_t)y) | map_bits<12>((uint32_t)k, g.mb.k)];
+      else b = TB == 0 ? B[y * g.ldb + k] : B[k * g.ldb + y];
+      if constexpr (GA) a = A[map_row(g.ma, (uint32_t)x) | map_bits<12>((uint32_t)k, g.ma.k)];
+      else if constexpr (MAPA) a = A[c_row(g.amap, TA == 0 ? x : k, g.lda) + c_col(g.amap, TA == 0 ? k : x)];
       else a = TA == 0 ? A[x * g.lda + k] : A[k * g.lda + x];
       if (CONJ) b.y = -b.y;
       c.x = fmaf(a.x, b.x, c.x);
@@ -159,7 +163,7 @@ struct F32sTile {
   static constexpr int dwords = 3 * (BM + BN) * kSRow;
 };
 
-template <int WM, int WN, int TM, int TN, int TA, int TB, bool CONJ, bool EDGE>
+template <int WM, int WN, int TM, int TN, int TA, int TB, bool CONJ, bool EDGE, bool GA, bool GB>
 __global__ void __launch_bounds__(64 * WM * WN)
 cgemm_f32s(F32Args g) {
   using Tile = F32sTile<WM, WN, TM, TN>;
@@ -180,11 +184,13 @@ cgemm_f32s(F32Args g) {
   const int l16 = lane & 15, lg = lane >> 4;
 
   constexpr bool MAPA = TB == 1;
-  F32Loader<BM, NTH, TA, EDGE, MAPA> la;
-  F32Loader<BN, NTH, TB, EDGE, false> lb;
-  if constexpr (MAPA) la.init_map(A, m0, k0);
+  std::conditional_t<GA, F32Gather<BM, NTH>, F32Loader<BM, NTH, TA, EDGE, MAPA>> la;
+  std::conditional_t<GB, F32Gather<BN, NTH>, F32Loader<BN, NTH, TB, EDGE, false>> lb;
+  if constexpr (GA) la.init_gather(g.A + map_base(g.ma, at.batch, g.sa), g.ma, m0, k0);
+  else if constexpr (MAPA) la.init_map(A, m0, k0);
   else la.init(A + (TA == 0 ? m0 * g.lda : m0), g.lda, k0);
-  lb.init(B + (TB == 0 ? n0 * g.ldb : n0), g.ldb, k0);
+  if constexpr (GB) lb.init_gather(g.B + map_base(g.mb, at.batch, g.sb), g.mb, n0, k0);
+  else lb.init(B + (TB == 0 ? n0 * g.ldb : n0), g.ldb, k0);
   const int64_t ml = g.M - m0, nl = g.N - n0;  // rows and columns that exist from the tile's first on
 
   float unscale = 1.f;
@@ -202,8 +208,10 @@ cgemm_f32s(F32Args g) {
 
   const int nk = (int)((klen + kFBK - 1) / kFBK);
   auto fetch = [&](int t) {
-    la.load((int64_t)t * kFBK, g.lda, ml, klen, g.amap);
-    lb.load((int64_t)t * kFBK, g.ldb, nl, klen, g.amap);
+    if constexpr (GA) la.load_gather((int64_t)t * kFBK, g.ma);
+    else la.load((int64_t)t * kFBK, g.lda, ml, klen, g.amap);
+    if constexpr (GB) lb.load_gather((int64_t)t * kFBK, g.mb);
+    else lb.load((int64_t)t * kFBK, g.ldb, nl, klen, g.amap);
   };
   fetch(0);
   for (int t = 0; t < nk; ++t) {
@@ -221,7 +229,8 @@ cgemm_f32s(F32Args g) {
   const uint32_t seen = partial ? 0u : seen_amax(g.rn);
   float mx;
   if (f32s_out_of_range<TM, TN>(acc))
-    mx = f32s_plain<TM, TN, TA, TB, CONJ, MAPA>(g, A, B, C, rn, m0 + wr, n0 + wc, k0, klen, unscale);
+    mx = f32s_plain<TM, TN, TA, TB, CONJ, MAPA, GA, GB>(g, GA ? g.A + map_base(g.ma, at.batch, g.sa) : A,
+                                                        GB ? g.B + map_base(g.mb, at.batch, g.sb) : B, C, rn, m0 + wr, n0 + wc, k0, klen, unscale);
   else
     mx = f32_store<TM, TN, EDGE>(C, rn, m0 + wr, n0 + wc, g.M, g.N, unscale, acc);
   if (g.rn.c && !partial) raise_amax<WM * WN>(g.rn.c, mx, seen, reinterpret_cast<float*>(lds));
@@ -233,10 +242,14 @@ static void f32s_launch(hipStream_t st, const F32Args& g, int split) {
   const int64_t tiles = ((g.M + Tile::BM - 1) / Tile::BM) * ((g.N + Tile::BN - 1) / Tile::BN) * g.batch;
   const dim3 grid((unsigned)tiles, (unsigned)split), block(Tile::threads);
   const bool whole = g.M % Tile::BM == 0 && g.N % Tile::BN == 0 && g.kc % kFBK == 0 && g.kc * split == g.K;
-  if (whole)
-    hipLaunchKernelGGL((cgemm_f32s<WM, WN, TM, TN, TA, TB, CONJ, false>), grid, block, 0, st, g);
-  else
-    hipLaunchKernelGGL((cgemm_f32s<WM, WN, TM, TN, TA, TB, CONJ, true>), grid, block, 0, st, g);
+  auto run = [&](auto* kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, st, g); };
+  if constexpr (TA == 0 && TB == 0 && !CONJ) {
+    if (g.ma.on && g.mb.on) return run(cgemm_f32s<WM, WN, TM, TN, 0, 0, false, false, true, true>);
+    if (g.ma.on) return run(cgemm_f32s<WM, WN, TM, TN, 0, 0, false, false, true, false>);
+    if (g.mb.on) return run(cgemm_f32s<WM, WN, TM, TN, 0, 0, false, false, false, true>);
+  }
+  if (whole) run(cgemm_f32s<WM, WN, TM, TN, TA, TB, CONJ, false, false, false>);
+  else run(cgemm_f32s<WM, WN, TM, TN, TA, TB, CONJ, true, false, false>);
 }
 
 // The largest tile that gives each of the 256 CUs a workgroup: 128 x 128 against 64 x 64 on 4096^3 2.38 / 2.67 ms,

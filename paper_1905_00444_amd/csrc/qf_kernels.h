@@ -241,18 +241,36 @@ bool cgemm_variant_fits(int precision, int64_t M, int64_t N, int64_t K, int vari
 // blocks_per_tile: workgroups that a launch makes per output tile (batch x K-chunks).
 int cgemm_default_variant(int precision, int64_t M, int64_t N, int64_t K, int64_t blocks_per_tile = 1);
 
+// An operand that a product reads in another order than [row][k]: element (row, k) lies where the row's and k's
+// bits are scattered to (5 bits per position, 12 to a word), from src_base + the dynamic output bit's
+// offset + the chain's table entry (world-lines) or the chain's stride on.
+struct OpMap {
+  int on = 0;
+  int row_fast = 0;        // the row's lowest bit is the lower one in memory
+  uint64_t k = 0, row[2] = {0, 0};
+  int64_t src_base = 0;
+  const uint8_t* dyn_bits = nullptr;
+  int64_t dyn_stride = 0;
+  const int64_t* base_table = nullptr;
+  int64_t base_stride = 0;
+};
+constexpr int kMapKBits = 12, kMapRowBits = 24;
+
 // Same, with optional operand max magnitudes for FP16 scaling (ignored when rn is on: then the
 // FP16 operands are scaled from rn.a / rn.b), optional renormalisation, and a kernel variant
 // (one that does not fit the shape falls back to GEMM_AUTO).
 hipError_t launch_cgemm_ex(hipStream_t st, int precision, int64_t M, int64_t N, int64_t K, const float2* A,
                            const float2* B, float2* C, int64_t batch, int64_t sa, int64_t sb, int64_t sc,
                            const uint32_t* amaxA, const uint32_t* amaxB, const Renorm& rn = Renorm{},
-                           int variant = GEMM_AUTO, float2* scratch = nullptr, size_t scratch_bytes = 0);
+                           int variant = GEMM_AUTO, float2* scratch = nullptr, size_t scratch_bytes = 0,
+                           const OpMap* ma = nullptr, const OpMap* mb = nullptr);
+// Whether that call (GEMM_AUTO) reads operands through maps.
+bool cgemm_reads_maps(int precision, int64_t M, int64_t N, int64_t K, int64_t batch);
 // FP32 MFMA product of any shape (cgemm_f32.hip).  *split: K-chunks wanted, set to those used (partials
 // in P, summed by launch_split_reduce).
 hipError_t launch_cgemm_f32(hipStream_t st, int64_t M, int64_t N, int64_t K, const float2* A, const float2* B,
                             float2* C, int64_t batch, int64_t sa, int64_t sb, int64_t sc, const Renorm& rn, int* split,
-                            float2* P, int tile = F32_AUTO);
+                            float2* P, int tile = F32_AUTO, const OpMap* ma = nullptr, const OpMap* mb = nullptr);
 // Environments of a product C[M][N] = sum_K A[M][K] B[N][K] from that of C (env, under C's output map), in FP32
 // without transposed copies: side 0: out[M][K] = sum_n env[m][n] conj(other[n][k]) with other = B; side 1:
 // out[N][K] = sum_m env[m][n] conj(other[m][k]) with other = A.  Dense batch strides.

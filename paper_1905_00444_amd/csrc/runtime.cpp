@@ -96,6 +96,8 @@ struct Operand {
   int64_t ld = 0;         // split planes: words between rows (0: dense, 2^kbits)
   size_t buf = 0;         // arena offset of the permuted copy
   bool early = false;     // small world-line slice: copied at the start of the chain, all in one launch
+  bool gather = false;    // a product that reads maps takes it where it lies, without a copy
+  OpMap map;              // ... then its bit positions
 };
 
 // Split operands with long rows get padded rows: rows 2^kbits words apart, a power of two of 32
@@ -420,6 +422,26 @@ static bool operand_invariant(const qf_plan* p, const Operand& op) {
   return p->ghoist && p->nodes[op.node].dep_cuts == 0;
 }
 static int operand_batch(const qf_plan* p, const Operand& op) { return operand_invariant(p, op) ? 1 : p->G; }
+
+// Operands that products may read where they lie.  A tile takes the 16 lowest rows and k's together (more, mostly),
+// so the lowest three address bits have to be among those: 64-byte pieces of memory are then used whole by
+// the tile that fetches them.
+static void plan_gather(const qf_plan* p, const Step& st, Operand& op) {
+  const int kb = st.k_bits, rb = op.nbits - kb;
+  if (p->backward || p->precision == QF_FP16 || st.presplit || st.fold || !op.permute || op.split) return;
+  if (kb < 1 || rb < 1 || kb > kMapKBits || rb > kMapRowBits) return;
+  int low = 0;  // of address bits 0, 1, 2
+  for (int i = 0; i < op.nbits; ++i) {
+    const int pos = op.perm[i], at = i < kb ? i : i - kb;
+    if (pos > 30) return;
+    if (pos < 3 && at < 4) ++low;
+    if (i < kb) op.map.k |= (uint64_t)pos << (5 * i);
+    else op.map.row[at / 12] |= (uint64_t)pos << (5 * (at % 12));
+    if (pos == 0) op.map.row_fast = i >= kb;
+  }
+  op.map.on = 1;
+  op.gather = low == 3;
+}
 
 // Plans whose chains run whole in one workgroup each, and their step descriptions: all operands and results
 // fit its LDS buffers (2^11 elements, so that two workgroups share a CU), and no product is one that the plan's
@@ -979,6 +1001,8 @@ static qf_status build_plan(qf_ctx* ctx, qf_circuit* circ, const qf_plan_desc* d
   }
 
   plan_small(p.get());
+  for (Step& st : p->steps)
+    for (Operand* op : {&st.A, &st.B}) plan_gather(p.get(), st, *op);
 
   // ---- world-line operands copied at the start of a chain.  Their buffers then live from the first step
   // on; a plan that fits the library's static scratch only with shorter lifetimes keeps those
@@ -1295,7 +1319,9 @@ static void set_split(qf_plan* p, const Operand& op, PermuteArgs* a) {
   a->f16_scale = (op.split && p->precision == QF_FP16) ? node_scale(p, op.node) : nullptr;
 }
 
-static qf_status run_operand(qf_plan* p, const Operand& op, const uint8_t* bits_row, int64_t s, const float2** ptr) {
+// map: not null where the product reads maps; filled if it takes this operand where it lies
+static qf_status run_operand(qf_plan* p, const Operand& op, const uint8_t* bits_row, int64_t s, const float2** ptr,
+                             OpMap* map = nullptr) {
   qf_ctx* c = p->ctx;
   const Node& nd = p->nodes[op.node];
   if (!op.permute || op.early) {
@@ -1303,6 +1329,18 @@ static qf_status run_operand(qf_plan* p, const Operand& op, const uint8_t* bits_
     return QF_OK;
   }
   PermuteArgs a;
+  if (map && op.gather) {
+    *map = op.map;
+    *ptr = wsp(c, nd.offset);
+    if (nd.leaf) {
+      leaf_args(p, nd, op, bits_row, s, &a);
+      map->src_base = a.src_base;
+      map->dyn_bits = a.dyn_bits;
+      map->dyn_stride = a.dyn_stride;
+      *ptr = wsp(c, p->off_wl) + p->wl_qubits[nd.qubit].out_offset;
+    }
+    return QF_OK;
+  }
   const float2* src;
   if (nd.leaf) {
     leaf_args(p, nd, op, bits_row, s, &a);
@@ -1417,7 +1455,8 @@ static const NodeScale* root_scale(qf_plan* p) {
 // One GEMM of the plan's precision (FP16 without renormalisation takes the operands' max
 // magnitudes first).
 static qf_status plan_gemm(qf_plan* p, int64_t M, int64_t N, int64_t K, const float2* A, const float2* B, float2* C,
-                           int64_t batch = 1, const Renorm& rn = Renorm{}, int64_t sa = -1, int64_t sb = -1) {
+                           int64_t batch = 1, const Renorm& rn = Renorm{}, int64_t sa = -1, int64_t sb = -1,
+                           const OpMap& ma = OpMap{}, const OpMap& mb = OpMap{}) {
   qf_ctx* c = p->ctx;
   if (sa < 0) sa = M * K;  // batch strides: dense per chain, or 0 for an operand shared by the batch
   if (sb < 0) sb = N * K;
@@ -1436,8 +1475,16 @@ static qf_status plan_gemm(qf_plan* p, int64_t M, int64_t N, int64_t K, const fl
   }
   float2* scratch = p->gscratch_bytes ? wsp(c, p->off_gscratch) : nullptr;
   QF_HIP(c, launch_cgemm_ex(c->stream, p->precision, M, N, K, A, B, C, batch, sa, sb, M * N, amA, amB, rn,
-                            variant, scratch, p->gscratch_bytes));
+                            variant, scratch, p->gscratch_bytes, ma.on ? &ma : nullptr, mb.on ? &mb : nullptr));
   return QF_OK;
+}
+
+// Whether plan_gemm's product of step st reads maps: by the default rule, not a tuned variant.
+static bool step_reads_maps(const qf_plan* p, const Step& st, int64_t batch) {
+  if (!(st.A.gather || st.B.gather) || trace_on()) return false;
+  const int64_t M = (int64_t)1 << st.m_bits, N = (int64_t)1 << st.n_bits, K = (int64_t)1 << st.k_bits;
+  if (!p->ctx->tune.empty() && p->ctx->tune.count({(int64_t)p->precision, M, N, K, batch})) return false;
+  return cgemm_reads_maps(p->precision, M, N, K, batch);
 }
 
 // QFMI_TRACE=1: after every executed step, synchronise and print the step's shape and the largest
@@ -1478,9 +1525,11 @@ static qf_status run_step(qf_plan* p, size_t i, const uint8_t* row, int64_t s) {
   const Step& st = p->steps[i];
   const Node& nd = p->nodes[p->n + i];
   const float2 *A, *B;
-  qf_status e = run_operand(p, st.A, row, s, &A);
+  OpMap ma, mb;
+  const bool maps = step_reads_maps(p, st, 1);
+  qf_status e = run_operand(p, st.A, row, s, &A, maps ? &ma : nullptr);
   if (e != QF_OK) return e;
-  e = run_operand(p, st.B, row, s, &B);
+  e = run_operand(p, st.B, row, s, &B, maps ? &mb : nullptr);
   if (e != QF_OK) return e;
   float2* C = wsp(c, nd.offset);
   const int64_t M = (int64_t)1 << st.m_bits, N = (int64_t)1 << st.n_bits, K = (int64_t)1 << st.k_bits;
@@ -1497,7 +1546,7 @@ static qf_status run_step(qf_plan* p, size_t i, const uint8_t* row, int64_t s) {
     QF_HIP(c, launch_cgemm_presplit(c->stream, M, N, K, A, B, C, 1, M * lda, N * ldb, (int64_t)result_elems(st), rn,
                                     lda, ldb, p->precision));
   } else {
-    e = plan_gemm(p, M, N, K, A, B, C, 1, rn);
+    e = plan_gemm(p, M, N, K, A, B, C, 1, rn, -1, -1, ma, mb);
     if (e != QF_OK) return e;
   }
   if (timed && e0 && e1) {
@@ -1525,11 +1574,21 @@ static qf_status prepare(qf_plan* p) {
 }
 
 // ---- batched chains: every step runs G chains (bitstring x slice pairs) as one launch --------
-static qf_status run_operand_batched(qf_plan* p, const Operand& op, const float2** ptr) {
+static qf_status run_operand_batched(qf_plan* p, const Operand& op, const float2** ptr, OpMap* map = nullptr) {
   qf_ctx* c = p->ctx;
   const Node& nd = p->nodes[op.node];
   if (!op.permute || op.early) {
     *ptr = wsp(c, op.early ? op.buf : nd.offset);
+    return QF_OK;
+  }
+  if (map && op.gather) {
+    *map = op.map;
+    *ptr = wsp(c, nd.offset);
+    if (nd.leaf) {
+      map->base_table = reinterpret_cast<const int64_t*>(c->ws + p->off_btable) + nd.qubit;
+      map->base_stride = operand_batch(p, op) > 1 ? p->n : 0;
+      *ptr = wsp(c, p->off_wl) + p->wl_qubits[nd.qubit].out_offset;
+    }
     return QF_OK;
   }
   PermuteArgs a;
@@ -1569,9 +1628,11 @@ static qf_status enqueue_group(qf_plan* p, const uint8_t* bits_dev, int64_t s_be
     const Step& st = p->steps[i];
     const int Gi = step_batch(p, i);
     const float2 *A, *B;
-    qf_status e = run_operand_batched(p, st.A, &A);
+    OpMap ma, mb;
+    const bool maps = step_reads_maps(p, st, Gi);
+    qf_status e = run_operand_batched(p, st.A, &A, maps ? &ma : nullptr);
     if (e != QF_OK) return e;
-    e = run_operand_batched(p, st.B, &B);
+    e = run_operand_batched(p, st.B, &B, maps ? &mb : nullptr);
     if (e != QF_OK) return e;
     float2* C = wsp(c, p->nodes[n + i].offset);
     const int64_t M = (int64_t)1 << st.m_bits, N = (int64_t)1 << st.n_bits, K = (int64_t)1 << st.k_bits;
@@ -1592,7 +1653,7 @@ static qf_status enqueue_group(qf_plan* p, const uint8_t* bits_dev, int64_t s_be
       // folded: the group's per-chain A matrices are consecutive, so with B shared they form one
       // A of G M rows and the product's rows are the chains' results in order
       e = st.fold ? plan_gemm(p, Gi * M, N, K, A, B, C, 1, rn)
-                  : plan_gemm(p, M, N, K, A, B, C, Gi, rn, shared_a ? 0 : M * K, shared_b ? 0 : N * K);
+                  : plan_gemm(p, M, N, K, A, B, C, Gi, rn, shared_a ? 0 : M * K, shared_b ? 0 : N * K, ma, mb);
       if (e != QF_OK) return e;
     }
     if (timed && e0 && e1) {

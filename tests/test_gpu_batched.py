@@ -140,6 +140,27 @@ def test_plans_of_small_tensors_vs_state_vector(ctx, rows, cols, depth, n_open, 
     assert np.array_equal(got[:5].cpu().numpy(), one.cpu().numpy())
 
 
+@pytest.mark.parametrize("precision", ["fp32", "bf16x3"])
+@pytest.mark.parametrize("depth,cut_bits,n,batch", [(16, 0, 1, 1), (20, 1, 3, 1), (24, 0, 40, 64), (27, 2, 2, 4), (32, 0, 2, 1),
+                                                    (32, 2, 5, 16)])
+def test_products_that_read_reordered_operands_in_place(ctx, precision, depth, cut_bits, n, batch):
+    """Regions whose joins read one or both results in another order than they lie in, through every tile that
+    depths 16 to 32 give (bonds of 2 to 4 bits), single chains and groups.  15 steps, the plan tests' bounds."""
+    import torch
+    from paper_1905_00444_amd import Circuit, Plan
+    _say(f"reordered operands d{depth} cut {cut_bits} n {n} batch {batch} {precision}")
+    c = generate(4, 4, depth, 6)
+    qid = c.qubit_of()
+    plan, _ = region_plan(c, 2, 2, [[qid[(1, 3)], qid[(2, 3)], 0, cut_bits]] if cut_bits else [], [(3, 3)])
+    bits = random_bitstrings(n, 16, 5)
+    p = Plan(ctx, Circuit(ctx, c.to_text()), plan, precision, batch=batch)
+    nodes = [(s["a_node"], s["a_reordered"]) for s in p.steps()] + [(s["b_node"], s["b_reordered"]) for s in p.steps()]
+    assert any(node >= 16 and reordered for node, reordered in nodes)
+    got = p.amplitudes(bits)
+    torch.cuda.synchronize()
+    assert rel_err(got.cpu().numpy(), sv.open_amplitudes(c.to_text(), bits, plan["open"])) <= {"fp32": 1e-5, "bf16x3": 1e-4}[precision]
+
+
 def test_batched_tail_and_slice_subrange(ctx):
     """Chains that do not fill the last group are masked; slice sub-ranges compose.  Group
     hoisting puts each bitstring's slices in groups of their own (7 slices of 3 bitstrings in
