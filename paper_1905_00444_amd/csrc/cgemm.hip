@@ -230,13 +230,13 @@ cgemm_mfma(int64_t M, int64_t N, int64_t K, const float2* __restrict__ A, const 
     A += map_base(ma, batch, sa);
     gather_places<BM>(pa, ma, tm * BM);
   } else {
-    A += batch * sa + tm * BM * K + blockIdx.y * kc;
+    A += (ma.on ? map_base(ma, batch, sa) : batch * sa) + tm * BM * K + blockIdx.y * kc;
   }
   if constexpr (GB) {
     B += map_base(mb, batch, sb);
     gather_places<BN>(pb, mb, tn * BN);
   } else {
-    B += batch * sb + tn * BN * K + blockIdx.y * kc;
+    B += (mb.on ? map_base(mb, batch, sb) : batch * sb) + tn * BN * K + blockIdx.y * kc;
   }
   if (partial) {
     C = P + ((int64_t)blockIdx.y * nbatch + batch) * M * N;
@@ -670,9 +670,9 @@ static void launch_tiled(hipStream_t st, int64_t M, int64_t N, int64_t K, const 
                        sa, sb, sc, amaxA, amaxB, rn, K / split, P, batch, ma, mb);
   };
   if constexpr (PREC == P_BF16X3) {
-    if (ma.on && mb.on) return run(cgemm_mfma<PREC, WTM, WTN, true, true>);
-    if (ma.on) return run(cgemm_mfma<PREC, WTM, WTN, true, false>);
-    if (mb.on) return run(cgemm_mfma<PREC, WTM, WTN, false, true>);
+    if (ma.on == 1 && mb.on == 1) return run(cgemm_mfma<PREC, WTM, WTN, true, true>);
+    if (ma.on == 1) return run(cgemm_mfma<PREC, WTM, WTN, true, false>);
+    if (mb.on == 1) return run(cgemm_mfma<PREC, WTM, WTN, false, true>);
   }
   run(cgemm_mfma<PREC, WTM, WTN, false, false>);
 }

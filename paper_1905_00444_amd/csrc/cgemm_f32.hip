@@ -114,14 +114,16 @@ cgemm_f32(F32Args g) {
   const int wr = (wave / WN) * (16 * TM), wc = (wave % WN) * (16 * TN);
   const int l16 = lane & 15, lg = lane >> 4;
 
+  const float2* A = g.A + (g.ma.on ? map_base(g.ma, batch, g.sa) : batch * g.sa);
+  const float2* B = g.B + (g.mb.on ? map_base(g.mb, batch, g.sb) : batch * g.sb);
   constexpr bool MAPA = TB == 1;
   std::conditional_t<GA, F32Gather<BM, NTH>, F32Loader<BM, NTH, TA, EDGE, MAPA>> la;
   std::conditional_t<GB, F32Gather<BN, NTH>, F32Loader<BN, NTH, TB, EDGE, false>> lb;
-  if constexpr (GA) la.init_gather(g.A + map_base(g.ma, batch, g.sa), g.ma, m0, k0);
-  else if constexpr (MAPA) la.init_map((g.A + batch * g.sa), m0, k0);
-  else la.init((g.A + batch * g.sa) + (TA == 0 ? m0 * g.lda : m0), g.lda, k0);
-  if constexpr (GB) lb.init_gather(g.B + map_base(g.mb, batch, g.sb), g.mb, n0, k0);
-  else lb.init((g.B + batch * g.sb) + (TB == 0 ? n0 * g.ldb : n0), g.ldb, k0);
+  if constexpr (GA) la.init_gather(A, g.ma, m0, k0);
+  else if constexpr (MAPA) la.init_map(A, m0, k0);
+  else la.init(A + (TA == 0 ? m0 * g.lda : m0), g.lda, k0);
+  if constexpr (GB) lb.init_gather(B, g.mb, n0, k0);
+  else lb.init(B + (TB == 0 ? n0 * g.ldb : n0), g.ldb, k0);
   const int64_t ml = g.M - m0, nl = g.N - n0;  // rows and columns that exist from the tile's first on
 
   float unscale = 1.f;
@@ -186,9 +188,9 @@ static void f32_launch(hipStream_t st, const F32Args& g, int split) {
   const bool whole = g.M % Tile::BM == 0 && g.N % Tile::BN == 0 && g.kc % kFBK == 0 && g.kc * split == g.K;
   auto run = [&](auto* kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, st, g); };
   if constexpr (TA == 0 && TB == 0 && !CONJ) {
-    if (g.ma.on && g.mb.on) return run(cgemm_f32<WM, WN, TM, TN, 0, 0, false, false, true, true>);
-    if (g.ma.on) return run(cgemm_f32<WM, WN, TM, TN, 0, 0, false, false, true, false>);
-    if (g.mb.on) return run(cgemm_f32<WM, WN, TM, TN, 0, 0, false, false, false, true>);
+    if (g.ma.on == 1 && g.mb.on == 1) return run(cgemm_f32<WM, WN, TM, TN, 0, 0, false, false, true, true>);
+    if (g.ma.on == 1) return run(cgemm_f32<WM, WN, TM, TN, 0, 0, false, false, true, false>);
+    if (g.mb.on == 1) return run(cgemm_f32<WM, WN, TM, TN, 0, 0, false, false, false, true>);
   }
   if (whole) run(cgemm_f32<WM, WN, TM, TN, TA, TB, CONJ, false, false, false>);
   else run(cgemm_f32<WM, WN, TM, TN, TA, TB, CONJ, true, false, false>);

@@ -176,7 +176,8 @@ cgemm_f32s(F32Args g) {
   const bool partial = gridDim.y > 1;
   const int64_t k0 = blockIdx.y * g.kc;
   const int64_t klen = EDGE ? (g.K - k0 < g.kc ? g.K - k0 : g.kc) : g.kc;
-  const float2 *A = g.A + at.batch * g.sa, *B = g.B + at.batch * g.sb;
+  const float2* A = g.A + (g.ma.on ? map_base(g.ma, at.batch, g.sa) : at.batch * g.sa);
+  const float2* B = g.B + (g.mb.on ? map_base(g.mb, at.batch, g.sb) : at.batch * g.sb);
   float2* C = partial ? g.P + ((int64_t)blockIdx.y * g.batch + at.batch) * g.M * g.N : g.C + at.batch * g.sc;
 
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -186,10 +187,10 @@ cgemm_f32s(F32Args g) {
   constexpr bool MAPA = TB == 1;
   std::conditional_t<GA, F32Gather<BM, NTH>, F32Loader<BM, NTH, TA, EDGE, MAPA>> la;
   std::conditional_t<GB, F32Gather<BN, NTH>, F32Loader<BN, NTH, TB, EDGE, false>> lb;
-  if constexpr (GA) la.init_gather(g.A + map_base(g.ma, at.batch, g.sa), g.ma, m0, k0);
+  if constexpr (GA) la.init_gather(A, g.ma, m0, k0);
   else if constexpr (MAPA) la.init_map(A, m0, k0);
   else la.init(A + (TA == 0 ? m0 * g.lda : m0), g.lda, k0);
-  if constexpr (GB) lb.init_gather(g.B + map_base(g.mb, at.batch, g.sb), g.mb, n0, k0);
+  if constexpr (GB) lb.init_gather(B, g.mb, n0, k0);
   else lb.init(B + (TB == 0 ? n0 * g.ldb : n0), g.ldb, k0);
   const int64_t ml = g.M - m0, nl = g.N - n0;  // rows and columns that exist from the tile's first on
 
@@ -229,8 +230,7 @@ cgemm_f32s(F32Args g) {
   const uint32_t seen = partial ? 0u : seen_amax(g.rn);
   float mx;
   if (f32s_out_of_range<TM, TN>(acc))
-    mx = f32s_plain<TM, TN, TA, TB, CONJ, MAPA, GA, GB>(g, GA ? g.A + map_base(g.ma, at.batch, g.sa) : A,
-                                                        GB ? g.B + map_base(g.mb, at.batch, g.sb) : B, C, rn, m0 + wr, n0 + wc, k0, klen, unscale);
+    mx = f32s_plain<TM, TN, TA, TB, CONJ, MAPA, GA, GB>(g, A, B, C, rn, m0 + wr, n0 + wc, k0, klen, unscale);
   else
     mx = f32_store<TM, TN, EDGE>(C, rn, m0 + wr, n0 + wc, g.M, g.N, unscale, acc);
   if (g.rn.c && !partial) raise_amax<WM * WN>(g.rn.c, mx, seen, reinterpret_cast<float*>(lds));
@@ -244,9 +244,9 @@ static void f32s_launch(hipStream_t st, const F32Args& g, int split) {
   const bool whole = g.M % Tile::BM == 0 && g.N % Tile::BN == 0 && g.kc % kFBK == 0 && g.kc * split == g.K;
   auto run = [&](auto* kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, st, g); };
   if constexpr (TA == 0 && TB == 0 && !CONJ) {
-    if (g.ma.on && g.mb.on) return run(cgemm_f32s<WM, WN, TM, TN, 0, 0, false, false, true, true>);
-    if (g.ma.on) return run(cgemm_f32s<WM, WN, TM, TN, 0, 0, false, false, true, false>);
-    if (g.mb.on) return run(cgemm_f32s<WM, WN, TM, TN, 0, 0, false, false, false, true>);
+    if (g.ma.on == 1 && g.mb.on == 1) return run(cgemm_f32s<WM, WN, TM, TN, 0, 0, false, false, true, true>);
+    if (g.ma.on == 1) return run(cgemm_f32s<WM, WN, TM, TN, 0, 0, false, false, true, false>);
+    if (g.mb.on == 1) return run(cgemm_f32s<WM, WN, TM, TN, 0, 0, false, false, false, true>);
   }
   if (whole) run(cgemm_f32s<WM, WN, TM, TN, TA, TB, CONJ, false, false, false>);
   else run(cgemm_f32s<WM, WN, TM, TN, TA, TB, CONJ, true, false, false>);

@@ -245,7 +245,7 @@ int cgemm_default_variant(int precision, int64_t M, int64_t N, int64_t K, int64_
 // bits are scattered to (5 bits per position, 12 to a word), from src_base + the dynamic output bit's
 // offset + the chain's table entry (world-lines) or the chain's stride on.
 struct OpMap {
-  int on = 0;
+  int on = 0;              // 2: [row][k] as it is, only elsewhere
   int row_fast = 0;        // the row's lowest bit is the lower one in memory
   uint64_t k = 0, row[2] = {0, 0};
   int64_t src_base = 0;

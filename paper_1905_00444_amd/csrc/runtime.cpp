@@ -423,6 +423,50 @@ static bool operand_invariant(const qf_plan* p, const Operand& op) {
 }
 static int operand_batch(const qf_plan* p, const Operand& op) { return operand_invariant(p, op) ? 1 : p->G; }
 
+// Bond bits of the world-lines in the order in which their steps read them, cut bits on top: a chain's slice is then
+// a contiguous block in the order of the product's operand (where an open output bit does not come between).
+// In time order every slice was a bit-permuted gather.  Sets the fixed bits' places.
+static void order_leaves(qf_plan* p) {
+  for (Step& st : p->steps)
+    for (Operand* op : {&st.A, &st.B}) {
+      if (!p->nodes[op->node].leaf) continue;
+      const int q = p->nodes[op->node].qubit;
+      std::vector<int>& full = p->leaf_full_labels[q];
+      const std::vector<int> time = full;
+      const int hb = (int)full.size();
+      std::vector<int> want(op->nbits);  // most significant first
+      for (int i = 0; i < op->nbits; ++i) want[op->nbits - 1 - i] = time[hb - 1 - op->perm[i]];
+      full.assign(1, time[0]);
+      for (int j = 1; j < hb; ++j)
+        if (p->label_cut[time[j]] >= 0) full.push_back(time[j]);
+      for (int lab : want)
+        if (lab != time[0]) full.push_back(lab);
+      op->perm = make_perm(full, want);
+      auto place = [&](int lab) { return hb - 1 - (int)(std::find(full.begin(), full.end(), lab) - full.begin()); };
+      const WlQubit& wq = p->wl_qubits[q];
+      for (int t = 0; t < wq.count; ++t) {
+        WlInstr& in = p->wl_prog[wq.first + t];
+        if (in.kind != 1) in.bitpos = place(time[hb - 1 - in.bitpos]);
+      }
+    }
+  p->leaf_desc.assign(p->n, LeafDesc());
+  for (int q = 0; q < p->n; ++q) {
+    LeafDesc& ld = p->leaf_desc[q];
+    std::memset(&ld, 0, sizeof(ld));
+    const std::vector<int>& full = p->leaf_full_labels[q];
+    const int hb = (int)full.size();
+    ld.qubit = q;
+    ld.xpos = contains(p->open, q) ? -1 : hb - 1;
+    for (int j = 1; j < hb; ++j) {
+      const int lab = full[j];
+      if (p->label_cut[lab] < 0) continue;
+      ld.shift[ld.n_cut] = p->label_cut_shift[lab];
+      ld.pos[ld.n_cut] = hb - 1 - j;
+      ++ld.n_cut;
+    }
+  }
+}
+
 // Operands that products may read where they lie.  A tile takes the 16 lowest rows and k's together (more, mostly),
 // so the lowest three address bits have to be among those: 64-byte pieces of memory are then used whole by
 // the tile that fetches them.
@@ -439,8 +483,10 @@ static void plan_gather(const qf_plan* p, const Step& st, Operand& op) {
     else op.map.row[at / 12] |= (uint64_t)pos << (5 * (at % 12));
     if (pos == 0) op.map.row_fast = i >= kb;
   }
-  op.map.on = 1;
-  op.gather = low == 3;
+  bool dense = kb >= 1;
+  for (int i = 0; i < op.nbits; ++i) dense = dense && op.perm[i] == i;
+  op.map.on = dense ? 2 : 1;
+  op.gather = dense || low == 3;
 }
 
 // Plans whose chains run whole in one workgroup each, and their step descriptions: all operands and results
@@ -789,23 +835,10 @@ static qf_status build_plan(qf_ctx* ctx, qf_circuit* circ, const qf_plan_desc* d
       else nd.labels.push_back(lab);
     }
   }
-  // per-leaf fixed bits (batched chains compute their offsets on the device)
-  p->leaf_desc.assign(n, LeafDesc());
   for (int q = 0; q < n; ++q) {
-    LeafDesc& ld = p->leaf_desc[q];
-    std::memset(&ld, 0, sizeof(ld));
-    const auto& full = p->leaf_full_labels[q];
-    const int hb = (int)full.size();
-    ld.qubit = q;
-    ld.xpos = contains(p->open, q) ? -1 : hb - 1;
-    for (int j = 1; j < hb; ++j) {
-      const int lab = full[j];
-      if (p->label_cut[lab] < 0) continue;
-      if (ld.n_cut >= kMaxLeafCut) return fail(ctx, QF_ERR_UNSUPPORTED, "too many cut bits on one world-line");
-      ld.shift[ld.n_cut] = p->label_cut_shift[lab];
-      ld.pos[ld.n_cut] = hb - 1 - j;
-      ++ld.n_cut;
-    }
+    int n_cut = 0;
+    for (size_t j = 1; j < p->leaf_full_labels[q].size(); ++j) n_cut += p->label_cut[p->leaf_full_labels[q][j]] >= 0;
+    if (n_cut > kMaxLeafCut) return fail(ctx, QF_ERR_UNSUPPORTED, "too many cut bits on one world-line");
   }
   if (d->n_steps != n - 1 || !d->steps) return fail(ctx, QF_ERR_PLAN, "a plan over n tensors needs exactly n-1 steps");
   std::vector<char> used(2 * n, 0);
@@ -1000,6 +1033,7 @@ static qf_status build_plan(qf_ctx* ctx, qf_circuit* circ, const qf_plan_desc* d
     }
   }
 
+  order_leaves(p.get());
   plan_small(p.get());
   for (Step& st : p->steps)
     for (Operand* op : {&st.A, &st.B}) plan_gather(p.get(), st, *op);
