@@ -560,19 +560,19 @@ constexpr int kSkinnyMaxB = 4096;  // complex elements of B held in LDS
 // and write consecutive complex numbers of C (coalesced).  Each output sums k in ascending order.
 __global__ void __launch_bounds__(256)
 cgemm_skinny(int64_t M, int64_t N, int64_t K, const float2* __restrict__ A, const float2* __restrict__ B,
-             float2* __restrict__ C, int64_t sa, int64_t sb, int64_t sc, Renorm rn) {
+             float2* __restrict__ C, int64_t sa, int64_t sb, int64_t sc, Renorm rn, OpMap ma, OpMap mb) {
   __shared__ float2 Bs[kSkinnyMaxB];
   float scale_a, scale_b, unscale;
   renorm_begin<P_FP32>(rn, nullptr, nullptr, scale_a, scale_b, unscale);
   float mx = 0.f;
   const int64_t batch = blockIdx.z;
-  A += batch * sa;
-  B += batch * sb;
+  A += ma.on ? map_base(ma, batch, sa) : batch * sa;
+  B += mb.on ? map_base(mb, batch, sb) : batch * sb;
   C += batch * sc;
   const int n_ = (int)N, k_ = (int)K;
   for (int i = threadIdx.x; i < n_ * k_; i += 256) {
     const int n = i / k_, k = i - n * k_;
-    Bs[k * n_ + n] = B[i];
+    Bs[k * n_ + n] = B[mb.on == 1 ? map_row(mb, n) | map_bits<6>(k, mb.k) : (uint32_t)i];
   }
   __syncthreads();
   const int Q = n_ / 4;
@@ -580,10 +580,10 @@ cgemm_skinny(int64_t M, int64_t N, int64_t K, const float2* __restrict__ A, cons
   for (int64_t o = (int64_t)blockIdx.x * 256 + threadIdx.x; o < total; o += (int64_t)gridDim.x * 256) {
     const int64_t m = o / Q;
     const int g = (int)(o - m * Q);
-    const float2* a = A + m * K;
+    const float2* a = A + (ma.on == 1 ? (int64_t)map_row(ma, (uint32_t)m) : m * K);
     float cr[4] = {0.f, 0.f, 0.f, 0.f}, ci[4] = {0.f, 0.f, 0.f, 0.f};
     for (int k = 0; k < k_; ++k) {
-      const float2 x = a[k];
+      const float2 x = a[ma.on == 1 ? map_bits<6>(k, ma.k) : (uint32_t)k];
       const float2* brow = Bs + k * n_ + g;
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
@@ -822,17 +822,18 @@ hipError_t launch_cgemm_ex(hipStream_t st, int precision, int64_t M, int64_t N, 
   if (M < 1 || N < 1 || K < 1 || batch < 1) return hipErrorInvalidValue;
   if (precision != P_FP32 && precision != P_BF16X3 && precision != P_FP16) return hipErrorInvalidValue;
   if ((ma || mb) && (variant != GEMM_AUTO || !cgemm_reads_maps(precision, M, N, K, batch))) return hipErrorInvalidValue;
+  const OpMap a = ma ? *ma : OpMap{}, b = mb ? *mb : OpMap{};
   const bool chosen = variant != GEMM_AUTO && cgemm_variant_fits(precision, M, N, K, variant);
   int v = chosen ? variant : cgemm_default_variant(precision, M, N, K);
   if (rn.c && !rn.cleared) hipLaunchKernelGGL(renorm_reset, dim3(1), dim3(64), 0, st, rn.c);
   switch (v) {
     case GEMM_TALL:
-      return launch_cgemm_tall(st, precision, M, N, K, A, B, C, batch, sa, sb, sc, amaxA, amaxB, rn);
+      return launch_cgemm_tall(st, precision, M, N, K, A, B, C, batch, sa, sb, sc, amaxA, amaxB, rn, a, b);
     case GEMM_SKINNY: {
       const int64_t total = M * (N / 4);
       const unsigned blocks = (unsigned)std::min<int64_t>((total + 255) / 256, 65536);
       hipLaunchKernelGGL(cgemm_skinny, dim3(blocks, 1, (unsigned)batch), dim3(256), 0, st, M, N, K, A, B, C, sa, sb,
-                         sc, rn);
+                         sc, rn, a, b);
       return hipGetLastError();
     }
     case GEMM_SPLITK:
@@ -864,7 +865,6 @@ hipError_t launch_cgemm_ex(hipStream_t st, int precision, int64_t M, int64_t N, 
                          v == GEMM_F32 ? F32_AUTO : tiles[v], ma, mb);
   } else {
     if (!chosen) v = cgemm_default_variant(precision, M, N, K, batch * split);
-    const OpMap a = ma ? *ma : OpMap{}, b = mb ? *mb : OpMap{};
     e = precision == P_BF16X3
             ? launch_mfma<P_BF16X3>(st, v, M, N, K, A, B, C, batch, sa, sb, sc, amaxA, amaxB, rn, split, scratch, a, b)
             : launch_mfma<P_FP16>(st, v, M, N, K, A, B, C, batch, sa, sb, sc, amaxA, amaxB, rn, split, scratch, a, b);
@@ -875,12 +875,14 @@ hipError_t launch_cgemm_ex(hipStream_t st, int precision, int64_t M, int64_t N, 
   return hipGetLastError();
 }
 
-// The FP32 tiles where they are whole, and the 16-bit tiles below the largest; FP16 keeps its copies.
+// The kernels of short sums, the FP32 tiles where they are whole, and the 16-bit tiles below the largest; FP16 keeps
+// its copies.
 bool cgemm_reads_maps(int precision, int64_t M, int64_t N, int64_t K, int64_t batch) {
   if (precision == P_FP16 || !pow2(M) || !pow2(N) || !pow2(K)) return false;
   int v = cgemm_default_variant(precision, M, N, K);
+  if (v == GEMM_TALL || v == GEMM_SKINNY) return true;
   if (v == GEMM_F32) return M >= 32 && (N >= 32 || N == 16) && K >= 16;
-  if (precision == P_FP32 || v == GEMM_TALL || v == GEMM_SKINNY || v == GEMM_SPLITK || v == GEMM_SIMT) return false;
+  if (precision == P_FP32 || v == GEMM_SPLITK || v == GEMM_SIMT) return false;
   return cgemm_default_variant(precision, M, N, K, batch * split_count(precision, v, M, N, K)) != GEMM_LARGE;
 }
 

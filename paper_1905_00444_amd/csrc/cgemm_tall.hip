@@ -39,10 +39,14 @@ __device__ __forceinline__ float tall_b32(const f8& b, int t, int q) {
   return q ? bi : br;
 }
 
-template <int PREC, int NT, int KS, int R>
+// GA: A is read through ma, 8 bytes at a time.  The 16 rows of a lane group's loads and the K-step's k's cover the
+// lowest address bits, so lines are used whole: as fast as the copies alone were (2^21 x 64 x 8, 2^27
+// elements).
+template <int PREC, int NT, int KS, int R, bool GA>
 __global__ void __launch_bounds__(kTallThreads)
 cgemm_tall(int64_t M, const float2* __restrict__ A, const float2* __restrict__ B, float2* __restrict__ C,
-           int64_t sa, int64_t sb, int64_t sc, const uint32_t* amaxA, const uint32_t* amaxB, Renorm rn) {
+           int64_t sa, int64_t sb, int64_t sc, const uint32_t* amaxA, const uint32_t* amaxB, Renorm rn, OpMap ma,
+           OpMap mb) {
   constexpr int N = 8 * NT, K = KS ? 16 * KS : 8, KSN = KS ? KS : 1;  // K-steps of 16 complex
   constexpr bool HALF = KS == 0;
   // B in LDS: packed 16-bit pairs (hi plane, then lo plane for split-BF16) or FP32 complex,
@@ -54,13 +58,13 @@ cgemm_tall(int64_t M, const float2* __restrict__ A, const float2* __restrict__ B
   float scale_a, scale_b, unscale;
   renorm_begin<PREC>(rn, amaxA, amaxB, scale_a, scale_b, unscale);
   const int64_t batch = blockIdx.z;
-  A += batch * sa;
-  B += batch * sb;
+  A += ma.on ? map_base(ma, batch, sa) : batch * sa;
+  B += mb.on ? map_base(mb, batch, sb) : batch * sb;
   C += batch * sc;
 
   for (int i = threadIdx.x; i < N * K; i += kTallThreads) {
     const int n = i / K, k = i % K;
-    const float2 b = B[i];
+    const float2 b = B[mb.on == 1 ? map_bits<6>(n, mb.row[0]) | map_bits<6>(k, mb.k) : (uint32_t)i];
     const float re = b.x * scale_b, im = b.y * scale_b;
     if constexpr (PREC == P_FP32) {
       bs[n * LDW + 2 * k] = __float_as_uint(re);
@@ -79,10 +83,21 @@ cgemm_tall(int64_t M, const float2* __restrict__ A, const float2* __restrict__ B
   const int l16 = lane & 15, lg = lane >> 4, q = l16 & 1;
   const BExpand bx(q);
   float mx = 0.f;
+  uint32_t arow[GA ? R : 1], ak[GA ? KSN : 1][4];  // this lane's rows and k's
+  if constexpr (GA) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) arow[r] = map_bits<6>(16 * r + l16, ma.row[0]);
+#pragma unroll
+    for (int s = 0; s < KSN; ++s)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) ak[s][e] = map_bits<6>((16 * s + 4 * lg + e) & (K - 1), ma.k);
+  }
   const int64_t groups = M / (16 * R);
   constexpr int64_t kWaves = kTallThreads / 64;
   for (int64_t g = (int64_t)blockIdx.x * kWaves + wave; g < groups; g += (int64_t)gridDim.x * kWaves) {
     const int64_t row0 = g * 16 * R;
+    uint32_t at0 = 0;
+    if constexpr (GA) at0 = map_row(ma, (uint32_t)__builtin_amdgcn_readfirstlane((int)row0));
     // this lane's 4 complex of A per (row group, K-step)
     f8 a[R][KSN];
 #pragma unroll
@@ -93,8 +108,17 @@ cgemm_tall(int64_t M, const float2* __restrict__ A, const float2* __restrict__ B
           a[r][s] = (f8){0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
           continue;
         }
-        const f4* p = reinterpret_cast<const f4*>(A + (row0 + 16 * r + l16) * K + 16 * s + 4 * lg);
-        const f4 x0 = p[0], x1 = p[1];
+        f4 x0, x1;
+        if constexpr (GA) {
+          const float2* p = A + (at0 | arow[r]);
+          const float2 y0 = p[ak[s][0]], y1 = p[ak[s][1]], y2 = p[ak[s][2]], y3 = p[ak[s][3]];
+          x0 = (f4){y0.x, y0.y, y1.x, y1.y};
+          x1 = (f4){y2.x, y2.y, y3.x, y3.y};
+        } else {
+          const f4* p = reinterpret_cast<const f4*>(A + (row0 + 16 * r + l16) * K + 16 * s + 4 * lg);
+          x0 = p[0];
+          x1 = p[1];
+        }
         a[r][s] = (f8){x0[0], x0[1], x0[2], x0[3], x1[0], x1[1], x1[2], x1[3]} * scale_a;
       }
     f4 acc[R][NT];
@@ -209,25 +233,30 @@ bool cgemm_tall_fits(int precision, int64_t M, int64_t N, int64_t K) {
 template <int PREC, int NT, int KS>
 static void tall_launch(hipStream_t st, int64_t M, const float2* A, const float2* B, float2* C, int64_t batch,
                         int64_t sa, int64_t sb, int64_t sc, const uint32_t* amaxA, const uint32_t* amaxB,
-                        const Renorm& rn) {
+                        const Renorm& rn, const OpMap& ma, const OpMap& mb) {
   constexpr int R = tall_rows(NT, KS);
   const int64_t groups = M / (16 * R);
   const int64_t want = (groups + kTallThreads / 64 - 1) / (kTallThreads / 64);
   // enough workgroups to fill the GPU several times over; each wave then strides over groups
   const int64_t cap = std::max<int64_t>(64, 4096 / std::max<int64_t>(1, batch));
   const unsigned gx = (unsigned)std::min(want, cap);
-  hipLaunchKernelGGL((cgemm_tall<PREC, NT, KS, R>), dim3(gx, 1, (unsigned)batch), dim3(kTallThreads), 0, st, M, A, B,
-                     C, sa, sb, sc, amaxA, amaxB, rn);
+  auto run = [&](auto* kernel) {
+    hipLaunchKernelGGL(kernel, dim3(gx, 1, (unsigned)batch), dim3(kTallThreads), 0, st, M, A, B, C, sa, sb, sc, amaxA,
+                       amaxB, rn, ma, mb);
+  };
+  if constexpr (PREC != P_FP16)
+    if (ma.on == 1) return run(cgemm_tall<PREC, NT, KS, R, true>);
+  run(cgemm_tall<PREC, NT, KS, R, false>);
 }
 
 template <int PREC>
 static hipError_t tall_dispatch(hipStream_t st, int64_t M, int64_t N, int64_t K, const float2* A, const float2* B,
                                 float2* C, int64_t batch, int64_t sa, int64_t sb, int64_t sc, const uint32_t* amaxA,
-                                const uint32_t* amaxB, const Renorm& rn) {
+                                const uint32_t* amaxB, const Renorm& rn, const OpMap& ma, const OpMap& mb) {
   const int nt = (int)(N / 8), ks = (int)(K / 16);
 #define QF_TALL(NT_, KS_)                                                                    \
   if (nt == NT_ && ks == KS_) {                                                              \
-    tall_launch<PREC, NT_, KS_>(st, M, A, B, C, batch, sa, sb, sc, amaxA, amaxB, rn);        \
+    tall_launch<PREC, NT_, KS_>(st, M, A, B, C, batch, sa, sb, sc, amaxA, amaxB, rn, ma, mb); \
     return hipGetLastError();                                                                \
   }
   QF_TALL(1, 0) QF_TALL(2, 0) QF_TALL(4, 0) QF_TALL(8, 0)
@@ -241,12 +270,13 @@ static hipError_t tall_dispatch(hipStream_t st, int64_t M, int64_t N, int64_t K,
 
 hipError_t launch_cgemm_tall(hipStream_t st, int precision, int64_t M, int64_t N, int64_t K, const float2* A,
                              const float2* B, float2* C, int64_t batch, int64_t sa, int64_t sb, int64_t sc,
-                             const uint32_t* amaxA, const uint32_t* amaxB, const Renorm& rn) {
+                             const uint32_t* amaxA, const uint32_t* amaxB, const Renorm& rn, const OpMap& ma,
+                             const OpMap& mb) {
   if (!cgemm_tall_fits(precision, M, N, K) || batch < 1) return hipErrorInvalidValue;
   switch (precision) {
-    case P_FP32: return tall_dispatch<P_FP32>(st, M, N, K, A, B, C, batch, sa, sb, sc, amaxA, amaxB, rn);
-    case P_BF16X3: return tall_dispatch<P_BF16X3>(st, M, N, K, A, B, C, batch, sa, sb, sc, amaxA, amaxB, rn);
-    default: return tall_dispatch<P_FP16>(st, M, N, K, A, B, C, batch, sa, sb, sc, amaxA, amaxB, rn);
+    case P_FP32: return tall_dispatch<P_FP32>(st, M, N, K, A, B, C, batch, sa, sb, sc, amaxA, amaxB, rn, ma, mb);
+    case P_BF16X3: return tall_dispatch<P_BF16X3>(st, M, N, K, A, B, C, batch, sa, sb, sc, amaxA, amaxB, rn, ma, mb);
+    default: return tall_dispatch<P_FP16>(st, M, N, K, A, B, C, batch, sa, sb, sc, amaxA, amaxB, rn, ma, mb);
   }
 }
 

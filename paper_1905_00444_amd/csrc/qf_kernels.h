@@ -286,7 +286,8 @@ size_t env_gemm_scratch(int side, int64_t M, int64_t N, int64_t K, int64_t batch
 bool cgemm_tall_fits(int precision, int64_t M, int64_t N, int64_t K);
 hipError_t launch_cgemm_tall(hipStream_t st, int precision, int64_t M, int64_t N, int64_t K, const float2* A,
                              const float2* B, float2* C, int64_t batch, int64_t sa, int64_t sb, int64_t sc,
-                             const uint32_t* amaxA, const uint32_t* amaxB, const Renorm& rn);
+                             const uint32_t* amaxA, const uint32_t* amaxB, const Renorm& rn,
+                             const OpMap& ma = OpMap{}, const OpMap& mb = OpMap{});
 // Bytes of scratch that lets an MFMA launch of this shape split K over more workgroups (0: the
 // launch fills the GPU without splitting, or its variant cannot split).
 size_t cgemm_split_scratch(int precision, int64_t M, int64_t N, int64_t K, int64_t batch, int variant = GEMM_AUTO);
