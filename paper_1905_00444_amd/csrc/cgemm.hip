@@ -578,7 +578,7 @@ cgemm_skinny(int64_t M, int64_t N, int64_t K, const float2* __restrict__ A, cons
   const int Q = n_ / 4;
   const int64_t total = M * Q;
   for (int64_t o = (int64_t)blockIdx.x * 256 + threadIdx.x; o < total; o += (int64_t)gridDim.x * 256) {
-    const int64_t m = o / Q;
+    int64_t m = o / Q;
     const int g = (int)(o - m * Q);
     const float2* a = A + (ma.on == 1 ? (int64_t)map_row(ma, (uint32_t)m) : m * K);
     float cr[4] = {0.f, 0.f, 0.f, 0.f}, ci[4] = {0.f, 0.f, 0.f, 0.f};
@@ -594,6 +594,7 @@ cgemm_skinny(int64_t M, int64_t N, int64_t K, const float2* __restrict__ A, cons
         ci[t] = fmaf(x.y, y.x, ci[t]);
       }
     }
+    if (rn.rp_on) m = map_bits<12>((uint32_t)m & 0xfff, rn.rp[0]) | map_bits<12>((uint32_t)m >> 12, rn.rp[1]);
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
       const float2 v = make_float2(cr[t] * unscale, ci[t] * unscale);
@@ -884,6 +885,12 @@ bool cgemm_reads_maps(int precision, int64_t M, int64_t N, int64_t K, int64_t ba
   if (v == GEMM_F32) return M >= 32 && (N >= 32 || N == 16) && K >= 16;
   if (precision == P_FP32 || v == GEMM_SPLITK || v == GEMM_SIMT) return false;
   return cgemm_default_variant(precision, M, N, K, batch * split_count(precision, v, M, N, K)) != GEMM_LARGE;
+}
+
+// The tall kernel could too, but its scattered rows of results cost what the copy did (2^21 x 64 x 8).
+bool cgemm_takes_row_order(int precision, int64_t M, int64_t N, int64_t K) {
+  return precision != P_FP16 && pow2(M) && pow2(N) && pow2(K) &&
+         cgemm_default_variant(precision, M, N, K) == GEMM_SKINNY;
 }
 
 hipError_t launch_cgemm(hipStream_t st, int precision, int64_t M, int64_t N, int64_t K, const float2* A,

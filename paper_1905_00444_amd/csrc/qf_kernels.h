@@ -36,6 +36,10 @@ struct Renorm {
   int64_t so_ld = 0, so_plane = 0;
   // c->amax has been cleared already (the start of the chain does it for all steps in one launch)
   bool cleared = false;
+  // rows taken in another order (skinny products that read A through a map): bit i of a row is bit rp[i]
+  // of the result's row, 5 bits per position, 12 to a word
+  int rp_on = 0;
+  uint64_t rp[2] = {0, 0};
 };
 
 // One instruction of a qubit's world-line program.
@@ -266,6 +270,8 @@ hipError_t launch_cgemm_ex(hipStream_t st, int precision, int64_t M, int64_t N, 
                            const OpMap* ma = nullptr, const OpMap* mb = nullptr);
 // Whether that call (GEMM_AUTO) reads operands through maps.
 bool cgemm_reads_maps(int precision, int64_t M, int64_t N, int64_t K, int64_t batch);
+// ... and takes A's rows in any order (by shape alone).
+bool cgemm_takes_row_order(int precision, int64_t M, int64_t N, int64_t K);
 // FP32 MFMA product of any shape (cgemm_f32.hip).  *split: K-chunks wanted, set to those used (partials
 // in P, summed by launch_split_reduce).
 hipError_t launch_cgemm_f32(hipStream_t st, int64_t M, int64_t N, int64_t K, const float2* A, const float2* B,

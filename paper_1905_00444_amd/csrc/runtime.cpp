@@ -126,6 +126,8 @@ struct Step {
   bool split_out = false;  // the result is written as its pre-split consumer's split-BF16 operand
   int so_kbits = 0;        // ... with that operand's K bits and row pitch (words)
   int64_t so_ld = 0;
+  bool row_order = false; // a mapped A is read with its rows in memory order, which the epilogue undoes
+  uint64_t rp[2] = {0, 0};
   double flops = 0.0;
   size_t out = 0;         // arena offset of the result
 };
@@ -470,23 +472,41 @@ static void order_leaves(qf_plan* p) {
 // Operands that products may read where they lie.  A tile takes the 16 lowest rows and k's together (more, mostly),
 // so the lowest three address bits have to be among those: 64-byte pieces of memory are then used whole by
 // the tile that fetches them.
-static void plan_gather(const qf_plan* p, const Step& st, Operand& op) {
+// Where A's rows are not in memory order (their lowest address bits may be the top bits of a row), products
+// that can take rows in any order read them in that order.
+static void plan_gather(const qf_plan* p, Step& st, Operand& op) {
   const int kb = st.k_bits, rb = op.nbits - kb;
   if (p->backward || p->precision == QF_FP16 || st.presplit || st.fold || !op.permute || op.split) return;
   if (kb < 1 || rb < 1 || kb > kMapKBits || rb > kMapRowBits) return;
-  int low = 0;  // of address bits 0, 1, 2
+  bool dense = true;
   for (int i = 0; i < op.nbits; ++i) {
-    const int pos = op.perm[i], at = i < kb ? i : i - kb;
-    if (pos > 30) return;
-    if (pos < 3 && at < 4) ++low;
-    if (i < kb) op.map.k |= (uint64_t)pos << (5 * i);
-    else op.map.row[at / 12] |= (uint64_t)pos << (5 * (at % 12));
-    if (pos == 0) op.map.row_fast = i >= kb;
+    if (op.perm[i] > 30) return;
+    dense = dense && op.perm[i] == i;
   }
-  bool dense = kb >= 1;
-  for (int i = 0; i < op.nbits; ++i) dense = dense && op.perm[i] == i;
+  std::vector<int> row(rb), pos(rb);  // bit i of a row as read: bit row[i] of the operand's row, address bit pos[i]
+  auto lowest = [&] {                 // of address bits 0, 1, 2
+    int low = 0;
+    for (int i = 0; i < std::min(kb, 4); ++i) low += op.perm[i] < 3;
+    for (int i = 0; i < std::min(rb, 4); ++i) low += pos[i] < 3;
+    return low;
+  };
+  auto set = [&] {
+    for (int i = 0; i < rb; ++i) pos[i] = op.perm[kb + row[i]];
+  };
+  for (int i = 0; i < rb; ++i) row[i] = i;
+  set();
+  if (!dense && lowest() < 3 && &op == &st.A &&
+      cgemm_takes_row_order(p->precision, (int64_t)1 << st.m_bits, (int64_t)1 << st.n_bits, (int64_t)1 << kb)) {
+    std::sort(row.begin(), row.end(), [&](int a, int b) { return op.perm[kb + a] < op.perm[kb + b]; });
+    set();
+    st.row_order = true;
+    for (int i = 0; i < rb; ++i) st.rp[i / 12] |= (uint64_t)row[i] << (5 * (i % 12));
+  }
+  for (int i = 0; i < kb; ++i) op.map.k |= (uint64_t)op.perm[i] << (5 * i);
+  for (int i = 0; i < rb; ++i) op.map.row[i / 12] |= (uint64_t)pos[i] << (5 * (i % 12));
+  op.map.row_fast = std::find(pos.begin(), pos.end(), 0) != pos.end();
   op.map.on = dense ? 2 : 1;
-  op.gather = dense || low == 3;
+  op.gather = dense || lowest() == 3;
 }
 
 // Plans whose chains run whole in one workgroup each, and their step descriptions: all operands and results
@@ -1394,9 +1414,14 @@ static qf_status run_operand(qf_plan* p, const Operand& op, const uint8_t* bits_
 }
 
 // Renormalisation slots of step i's operands and result (all null when the plan stores true scales).
-static Renorm step_renorm(qf_plan* p, size_t i) {
+static Renorm step_renorm(qf_plan* p, size_t i, bool mapped_a = false) {
   Renorm r;
   const Step& st = p->steps[i];
+  if (mapped_a && st.row_order) {
+    r.rp_on = 1;
+    r.rp[0] = st.rp[0];
+    r.rp[1] = st.rp[1];
+  }
   r.om_q = st.om_q;
   r.om_nh = st.om_nh;
   r.om_nl = st.n_bits - st.om_nh;
@@ -1574,7 +1599,7 @@ static qf_status run_step(qf_plan* p, size_t i, const uint8_t* row, int64_t s) {
     e1 = take_event(c);
     if (e0 && e1) QF_HIP(c, hipEventRecord(e0, c->stream));
   }
-  const Renorm rn = step_renorm(p, i);
+  const Renorm rn = step_renorm(p, i, ma.on == 1);
   if (st.presplit) {
     const int64_t lda = split_ld(st.A), ldb = split_ld(st.B);
     QF_HIP(c, launch_cgemm_presplit(c->stream, M, N, K, A, B, C, 1, M * lda, N * ldb, (int64_t)result_elems(st), rn,
@@ -1678,7 +1703,7 @@ static qf_status enqueue_group(qf_plan* p, const uint8_t* bits_dev, int64_t s_be
       e1 = take_event(c);
       if (e0 && e1) QF_HIP(c, hipEventRecord(e0, c->stream));
     }
-    const Renorm rn = step_renorm(p, i);
+    const Renorm rn = step_renorm(p, i, ma.on == 1);
     if (st.presplit) {
       const int64_t lda = split_ld(st.A), ldb = split_ld(st.B);
       QF_HIP(c, launch_cgemm_presplit(c->stream, M, N, K, A, B, C, Gi, shared_a ? 0 : M * lda, shared_b ? 0 : N * ldb,
