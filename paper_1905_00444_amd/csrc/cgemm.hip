@@ -10,7 +10,8 @@
 // count 8 M N K of the paper's formula F = 8 sqrt(v0 v1 v2) equals the real MFMA work.
 //
 // Precisions (the operand conversion happens when a K-tile is staged into LDS):
-//   FP32   : v_mfma_f32_16x16x4_f32 on the FP32 operands (cgemm_f32.hip).
+//   FP32   : v_mfma_f32_16x16x4_f32 on the FP32 operands (cgemm_f32.hip); large products as six bfloat16
+//            products (cgemm_f32s.hip).
 //   BF16X3 : x = hi + lo with hi = bf16(x), lo = bf16(x - hi); C += hi*hi + hi*lo + lo*hi on
 //            v_mfma_f32_16x16x32_bf16 with FP32 accumulation (the lo*lo term, about 2^-16
 //            relative, is dropped).
@@ -23,15 +24,16 @@
 // (true values = stored * 2^E_X) and the max magnitude of its stored values.  A renormalised
 // GEMM stores C * 2^-(e_A + e_B), e_X the binary exponent of X's max magnitude, so stored
 // values stay near 1 whatever the true scale; E_C = E_A + E_B + e_A + e_B is written by one
-// thread, C's max magnitude is gathered in the epilogue (one atomic max per wave), and the FP64
+// thread, C's max magnitude is gathered in the epilogue (one atomic max per workgroup), and the FP64
 // slice sum applies 2^E of the root.
 //
 // Tiling: 256 threads = 4 waves as 2 x 2; a wave owns WTM x WTN MFMA tiles of 16 rows x 16 real
 // columns (8 complex); block tile BM = 32 WTM rows x BN = 16 WTN complex columns; K-tiles of
 // 32 complex.  Global loads for the next K-tile are issued into registers before the current
 // tile's MFMAs, then converted and stored to LDS.  Rows are padded by 16 bytes in LDS.
-// Workgroups are remapped so consecutive tiles share an XCD (8 XCDs, round-robin dispatch)
-// and rasterised in groups of row-tiles for L2 reuse.
+// Workgroups are remapped so consecutive tiles of the launch share an XCD (8 XCDs, round-robin dispatch)
+// and rasterised in groups of row-tiles for L2 reuse: 16 split-BF16 products of 256^3 take 16.2 us, 18.0 with
+// each chain's tiles dealt to all XCDs.  K-tiles fetched three ahead instead of one: 17.0.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <stdlib.h>

@@ -26,9 +26,10 @@
 // tile that a launch picks, so the choice may follow the batch.  K is cut into chunks (gridDim.y > 1) by
 // the shape alone.
 //
-// Measured (whole passes, MI355X): 1500 x 700 x 300 1.27 ms as one thread per output, 42 us here; the
-// 256^3 products of a 4 x 4 circuit in launches of 64 chains 331 us (two 256 x 128 tiles, K split in four)
-// against 80 us in one pass over K; four slices of the 7x7 (1+32+1) circuit 442 ms, 388 ms here.
+// Measured (MI355X, before / here): 1500 x 700 x 300 1.27 ms as one thread per output, 42 us; 256^3 products of a
+// 4 x 4 circuit in launches of 64 chains 331 us (two 256 x 128 tiles, K split in four), 70 us in one pass over
+// K; 64 products of 2^15 x 64 x 64 785 us on 128 x 64 tiles, 619 (111 TFLOP/s, 3.5 TB/s); four slices of the
+// 7x7 (1+32+1) circuit 442 and 388 ms.  The large ones (K >= 128) have since gone to cgemm_f32s.hip.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <algorithm>
