@@ -22,9 +22,9 @@
 // 2^108 on, infinities and NaNs, and results from 2^88 on, leave sums that are not finite: a wave that sees
 // one computes its results again as plain FP32 sums.
 //
-// Measured (MI355X, FP32 MFMAs / here): 4096^3 140 / 230 TFLOP/s, 2^18 x 256 x 256 134 / 193, 64 products of
-// 256^3 123 / 191, 16 of them 97 / 112, one 8.7 / 9.3 us; 1500 x 700 x 300 38.9 / 32 us, the 7x7 slices
-// 388 / 224 ms, 4x4 sampling 3.98 / 3.01 ms.
+// Measured (MI355X, FP32 MFMAs / here): 4096^3 140 / 234 TFLOP/s, 2^18 x 256 x 256 134 / 201, 64 products of
+// 256^3 123 / 192, 16 of them 97 / 112, one 8.7 / 9.3 us; 1500 x 700 x 300 38.9 / 32 us, the 7x7 slices
+// 388 / 206 ms.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <algorithm>
@@ -161,6 +161,9 @@ template <int WM, int WN, int TM, int TN>
 struct F32sTile {
   static constexpr int threads = 64 * WM * WN, BM = 16 * WM * TM, BN = 16 * WN * TN;
   static constexpr int dwords = 3 * (BM + BN) * kSRow;
+  // Two LDS stages and one barrier per K-tile where few workgroups fit a CU anyway: 128 x 128 tiles on 2^18 x 256 x
+  // 256 718 -> 682 us, 4096^3 2.41 -> 2.34 ms; 64 x 64 tiles lose an overlapping workgroup by it (1024^3 61 -> 63 us).
+  static constexpr int stages = BM * BN >= 128 * 128 ? 2 : 1;
 };
 
 template <int WM, int WN, int TM, int TN, int TA, int TB, bool CONJ, bool EDGE, bool GA, bool GB>
@@ -168,7 +171,7 @@ __global__ void __launch_bounds__(64 * WM * WN)
 cgemm_f32s(F32Args g) {
   using Tile = F32sTile<WM, WN, TM, TN>;
   constexpr int BM = Tile::BM, BN = Tile::BN, NTH = Tile::threads;
-  __shared__ __attribute__((aligned(16))) uint32_t lds[Tile::dwords];
+  __shared__ __attribute__((aligned(16))) uint32_t lds[Tile::stages * Tile::dwords];
 
   const uint32_t tiles_m = (uint32_t)((g.M + BM - 1) / BM), tiles_n = (uint32_t)((g.N + BN - 1) / BN);
   const F32Place at = f32_place(blockIdx.x, tiles_m, tiles_n, gridDim.x, BM, BN);
@@ -214,14 +217,29 @@ cgemm_f32s(F32Args g) {
     if constexpr (GB) lb.load_gather((int64_t)t * kFBK, g.mb);
     else lb.load((int64_t)t * kFBK, g.ldb, nl, klen, g.amap);
   };
+  auto stage_of = [&](int t) { return lds + (Tile::stages == 2 ? (t & 1) * Tile::dwords : 0); };
+  auto stage = [&](int t) {
+    f32s_stage<TA, BM>(stage_of(t), la);
+    f32s_stage<TB, BN>(stage_of(t) + 3 * BM * kSRow, lb);
+  };
   fetch(0);
-  for (int t = 0; t < nk; ++t) {
-    f32s_stage<TA, BM>(lds, la);
-    f32s_stage<TB, BN>(lds + 3 * BM * kSRow, lb);
+  if constexpr (Tile::stages == 2) {
+    stage(0);
+    if (nk > 1) fetch(1);
     __syncthreads();
-    if (t + 1 < nk) fetch(t + 1);
-    f32s_multiply<TM, TN, BM, BN, CONJ>(lds + (wr + 4 * (l16 & 3) + (l16 >> 2)) * kSRow + 4 * lg,
-                                        lds + (3 * BM + wc + l16) * kSRow + 4 * lg, acc);
+  }
+  for (int t = 0; t < nk; ++t) {
+    if constexpr (Tile::stages == 1) {
+      stage(t);
+      __syncthreads();
+      if (t + 1 < nk) fetch(t + 1);
+    } else if (t + 1 < nk) {
+      stage(t + 1);
+      if (t + 2 < nk) fetch(t + 2);
+    }
+    const uint32_t* st = stage_of(t);
+    f32s_multiply<TM, TN, BM, BN, CONJ>(st + (wr + 4 * (l16 & 3) + (l16 >> 2)) * kSRow + 4 * lg,
+                                        st + (3 * BM + wc + l16) * kSRow + 4 * lg, acc);
     __syncthreads();
   }
 
@@ -252,8 +270,8 @@ static void f32s_launch(hipStream_t st, const F32Args& g, int split) {
   else run(cgemm_f32s<WM, WN, TM, TN, TA, TB, CONJ, true, false, false>);
 }
 
-// The largest tile that gives each of the 256 CUs a workgroup: 128 x 128 against 64 x 64 on 4096^3 2.38 / 2.67 ms,
-// on 64 products of 256^3 45 / 50 us.  A result does not depend on the tile.
+// The largest tile that gives each of the 256 CUs a workgroup: 128 x 128 against 64 x 64 on 4096^3 2.34 / 2.67 ms,
+// on 64 products of 256^3 44 / 50 us.  A result does not depend on the tile.
 template <int TA, int TB, bool CONJ>
 static void f32s_pick(hipStream_t st, const F32Args& g, int split) {
   auto blocks = [&](int64_t bm, int64_t bn) { return ((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn) * g.batch * split; };
