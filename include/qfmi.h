@@ -217,8 +217,8 @@ qf_status qf_plan_graph_info(const qf_plan* plan, int64_t* launches, int64_t* no
 /* Workspace that a call of n_batch bitstrings over n_slices slices can use (host only; housekeeping, no
  * counterpart in the paper).  A one-chain plan (batch <= 1) of small tensors runs calls of several chains
  * with several chains per launch when the context's workspace has room for it, with the same results as
- * one chain at a time (plans of tensors up to 2^11 elements: up to rounding); *bytes then exceeds qf_plan_info.workspace_bytes, which remains enough for every
- * call.  Errors: QF_ERR_ARG. */
+ * one chain at a time (plans of tensors up to 2^11 elements: up to rounding); *bytes then exceeds
+ * qf_plan_info.workspace_bytes, which remains enough for every call.  Errors: QF_ERR_ARG. */
 qf_status qf_plan_call_workspace(qf_plan* plan, int n_batch, int64_t n_slices, size_t* bytes);
 /* Description of step i (0 <= i < n_steps) of a laid-out plan: its TTGT roles and shapes
  * (Sec. III-E) (host only).  Errors: QF_ERR_ARG. */

@@ -1530,7 +1530,7 @@ static qf_status plan_gemm(qf_plan* p, int64_t M, int64_t N, int64_t K, const fl
   int variant = GEMM_AUTO;
   if (!c->tune.empty()) {
     auto it = c->tune.find({(int64_t)p->precision, M, N, K, batch});
-    if (it != c->tune.end()) variant = it->second;
+    if (it != c->tune.end() && !ma.on && !mb.on) variant = it->second;
   }
   float2* scratch = p->gscratch_bytes ? wsp(c, p->off_gscratch) : nullptr;
   QF_HIP(c, launch_cgemm_ex(c->stream, p->precision, M, N, K, A, B, C, batch, sa, sb, M * N, amA, amB, rn,
@@ -1538,11 +1538,14 @@ static qf_status plan_gemm(qf_plan* p, int64_t M, int64_t N, int64_t K, const fl
   return QF_OK;
 }
 
-// Whether plan_gemm's product of step st reads maps: by the default rule, not a tuned variant.
+// Whether plan_gemm's product of step st reads maps: by the default rule, unless another variant was tuned.
 static bool step_reads_maps(const qf_plan* p, const Step& st, int64_t batch) {
   if (!(st.A.gather || st.B.gather) || trace_on()) return false;
   const int64_t M = (int64_t)1 << st.m_bits, N = (int64_t)1 << st.n_bits, K = (int64_t)1 << st.k_bits;
-  if (!p->ctx->tune.empty() && p->ctx->tune.count({(int64_t)p->precision, M, N, K, batch})) return false;
+  if (!p->ctx->tune.empty()) {
+    auto it = p->ctx->tune.find({(int64_t)p->precision, M, N, K, batch});
+    if (it != p->ctx->tune.end() && it->second != cgemm_default_variant(p->precision, M, N, K, batch)) return false;
+  }
   return cgemm_reads_maps(p->precision, M, N, K, batch);
 }
 
@@ -2608,6 +2611,7 @@ extern "C" qf_status qf_autotune(qf_ctx* c, const qf_plan* pc, const char* path)
     QF_HIP(c, launch_fill_random(c->stream, B, GB * N * K, seed++));
     const int64_t sa = (GA > 1 && !st.fold) ? M * K : 0, sb = GB > 1 ? N * K : 0;
     int best = GEMM_AUTO;
+    const int rule = cgemm_default_variant(p->precision, M, N, K, G);
     float best_ms = 0.f;
     std::string times = "{";
     for (int v : tune_candidates(p->precision, M, N, K, G)) {
@@ -2617,6 +2621,9 @@ extern "C" qf_status qf_autotune(qf_ctx* c, const qf_plan* pc, const char* path)
       char buf[64];
       std::snprintf(buf, sizeof buf, "%s\"%s\": %.2f", times.size() > 1 ? ", " : "", kVariantName[v], 1e3 * ms);
       times += buf;
+      // the rule's own variant reads reordered operands in place, another one needs copies: it has to be faster
+      // by more than timings of short launches differ
+      if (v == rule) ms *= 0.9f;
       if (best == GEMM_AUTO || ms < best_ms) {
         best = v;
         best_ms = ms;
