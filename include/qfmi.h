@@ -284,7 +284,9 @@ qf_status qf_permute(qf_ctx* ctx, const void* src, void* dst, int nbits, const i
  * Batch strides are in complex elements.  M, N, K >= 1.  precision: qf_precision.
  * Launches whose output tiles cannot fill the GPU split K over more workgroups when the context
  * workspace, past its first 4 KiB, holds the partial tiles (split x batch x M x N complex64);
- * the chunks are then summed in a fixed order.  Without such a workspace K is not split. */
+ * the chunks are then summed in a fixed order.  Without such a workspace K is not split.  The partial tiles
+ * overwrite what a plan keeps in the workspace; its next call builds that again (a caller's own captured
+ * graph of a plan's call does not: run such products on another context). */
 qf_status qf_cgemm(qf_ctx* ctx, int precision, int64_t M, int64_t N, int64_t K, const void* A,
                    const void* B, void* C, int64_t batch, int64_t stride_a, int64_t stride_b,
                    int64_t stride_c);

@@ -2260,12 +2260,15 @@ qf_status qf_cgemm_variant(qf_ctx* c, int precision, int variant, int64_t M, int
     amA = slots;
     amB = slots + 1;
   }
-  // the context workspace beyond its slots holds split-K partials when it is large enough
+  // the context workspace beyond its slots holds split-K partials when it is large enough.  A plan's tables and
+  // world-lines begin there: the partials take their place, and the plan's next call builds them again
   float2* scratch = nullptr;
-  size_t scratch_bytes = 0;
-  if (c->ws && c->ws_bytes > kCtxScratch) {
+  size_t scratch_bytes = cgemm_split_scratch(precision, M, N, K, batch, variant);
+  if (scratch_bytes > 0 && c->ws && c->ws_bytes > kCtxScratch && c->ws_bytes - kCtxScratch >= scratch_bytes) {
     scratch = reinterpret_cast<float2*>(c->ws + kCtxScratch);
-    scratch_bytes = c->ws_bytes - kCtxScratch;
+    c->last_built = nullptr;
+  } else {
+    scratch_bytes = 0;
   }
   QF_HIP(c, launch_cgemm_ex(c->stream, precision, M, N, K, reinterpret_cast<const float2*>(A),
                             reinterpret_cast<const float2*>(B), reinterpret_cast<float2*>(C), batch, sa, sb, sc, amA, amB,
