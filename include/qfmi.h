@@ -162,6 +162,11 @@ qf_status qf_ctx_create(int device, void* hip_stream, void* workspace, size_t ws
  * housekeeping, no counterpart in the paper).  Errors: QF_ERR_ARG. */
 qf_status qf_ctx_set_workspace(qf_ctx* ctx, void* workspace, size_t ws_bytes);
 qf_status qf_ctx_set_stream(qf_ctx* ctx, void* hip_stream);
+/* A second buffer (same rules) for what calls of several chains use beyond qf_plan_info.workspace_bytes
+ * (qf_plan_call_workspace minus that), where the workspace has no room for it; NULL/0 for none.  Unlike the
+ * workspace it may be replaced without disturbing captured graphs of a plan's calls, as long as the buffers
+ * that they were captured with stay allocated (housekeeping, no counterpart in the paper).  Errors: QF_ERR_ARG. */
+qf_status qf_ctx_set_call_workspace(qf_ctx* ctx, void* workspace, size_t ws_bytes);
 /* Destroys the context (housekeeping, no counterpart in the paper).  Circuits and plans still
  * alive are detached, not freed: destroy them as usual later; every other call on them then
  * fails with QF_ERR_ARG.  Destroying a circuit likewise detaches the plans built on it. */
@@ -216,9 +221,11 @@ qf_status qf_plan_flops(const qf_plan* plan, int64_t s_begin, int64_t s_end, dou
 qf_status qf_plan_graph_info(const qf_plan* plan, int64_t* launches, int64_t* nodes);
 /* Workspace that a call of n_batch bitstrings over n_slices slices can use (host only; housekeeping, no
  * counterpart in the paper).  A one-chain plan (batch <= 1) of small tensors runs calls of several chains
- * with several chains per launch when the context's workspace has room for it, with the same results as
- * one chain at a time (plans of tensors up to 2^11 elements: up to rounding); *bytes then exceeds
- * qf_plan_info.workspace_bytes, which remains enough for every call.  Errors: QF_ERR_ARG. */
+ * with several chains per launch where there is room for it, behind qf_plan_info.workspace_bytes in the
+ * context's workspace or in the buffer of qf_ctx_set_call_workspace, with the same results as
+ * one chain at a time (plans of tensors up to 2^11 elements, and the sums over chains of qf_backward: up to
+ * rounding).  *bytes is the same for all calls of several chains, and qf_plan_info.workspace_bytes
+ * remains enough for every call.  Errors: QF_ERR_ARG. */
 qf_status qf_plan_call_workspace(qf_plan* plan, int n_batch, int64_t n_slices, size_t* bytes);
 /* Description of step i (0 <= i < n_steps) of a laid-out plan: its TTGT roles and shapes
  * (Sec. III-E) (host only).  Errors: QF_ERR_ARG. */

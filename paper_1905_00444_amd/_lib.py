@@ -58,6 +58,7 @@ class qf_step_info(C.Structure):
 EXPORTS = {
     "qf_ctx_create": (C.c_int, [C.c_int, C.c_void_p, C.c_void_p, C.c_size_t, C.POINTER(C.c_void_p)]),
     "qf_ctx_set_workspace": (C.c_int, [C.c_void_p, C.c_void_p, C.c_size_t]),
+    "qf_ctx_set_call_workspace": (C.c_int, [C.c_void_p, C.c_void_p, C.c_size_t]),
     "qf_ctx_set_stream": (C.c_int, [C.c_void_p, C.c_void_p]),
     "qf_ctx_destroy": (None, [C.c_void_p]),
     "qf_last_error": (C.c_char_p, [C.c_void_p]),

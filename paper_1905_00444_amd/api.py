@@ -35,20 +35,48 @@ class Context:
         check(self.lib.qf_ctx_create(device, C.c_void_p(self.stream.cuda_stream), None, 0, C.byref(h)))
         self.h = h
         self.ws = None
+        self._call_ws = None
+        self._outgrown = []
+        self._refused = float("inf")  # bytes that could not be had
 
-    def ensure_workspace(self, nbytes: int) -> None:
+    def ensure_workspace(self, nbytes: int, more: int = 0) -> None:
         """Grow the workspace to at least nbytes.  The old buffer may still be in use by work
         queued on the context's stream: it is released only after that work (the stream is
         synchronised first), and the new one is allocated on the context's stream so that the
-        caching allocator orders its reuse after the library's kernels."""
+        caching allocator orders its reuse after the library's kernels.
+        more: bytes that make the call faster, where they are to be had: in the workspace if it has to grow
+        anyway, else in a second buffer, since captured graphs of earlier calls work in the first
+        (and in outgrown second ones, which are kept until the workspace grows).  Neither grows for
+        their sake during a stream capture."""
         torch = _torch()
         nbytes = max(int(nbytes), 4096)
-        if self.ws is None or self.ws.numel() < nbytes:
-            if self.ws is not None:
+        have = 0 if self.ws is None else self.ws.numel()
+        room = 0 if self._call_ws is None else self._call_ws.numel()
+        if have >= max(nbytes, int(more)) or (have >= nbytes and room >= int(more) - nbytes):
+            return
+        with torch.cuda.stream(self.stream):
+            extra = max(int(more) - nbytes, 0)
+            if extra >= self._refused or torch.cuda.is_current_stream_capturing():
+                extra = 0
+            if have < nbytes and self.ws is not None:
                 self.stream.synchronize()
+                self._outgrown.clear()
                 self.ws = None
-            with torch.cuda.stream(self.stream):
+            if extra:
+                try:
+                    buf = torch.empty(extra + (nbytes if have < nbytes else 0), dtype=torch.uint8, device=self.device)
+                except torch.cuda.OutOfMemoryError:
+                    self._refused = extra
+                else:
+                    if have < nbytes:
+                        self.ws = buf
+                    else:
+                        self._outgrown.append(self._call_ws)
+                        self._call_ws = buf
+                        check(self.lib.qf_ctx_set_call_workspace(self.h, C.c_void_p(buf.data_ptr()), buf.numel()), self.h)
+            if self.ws is None:
                 self.ws = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
+        if have < nbytes:
             check(self.lib.qf_ctx_set_workspace(self.h, C.c_void_p(self.ws.data_ptr()), self.ws.numel()), self.h)
 
     def synchronize(self) -> None:
@@ -215,7 +243,7 @@ class Plan:
         info = self.info()
         if s_end is None:
             s_end = info["n_slices"]
-        self.ctx.ensure_workspace(self._call_workspace(len(bits), s_end - s_begin))
+        self.ctx.ensure_workspace(info["workspace_bytes"], self._call_workspace(len(bits), s_end - s_begin))
         with torch.cuda.stream(self.ctx.stream):
             if isinstance(bits, np.ndarray):
                 bits_t = torch.from_numpy(np.ascontiguousarray(bits, dtype=np.uint8)).to(self.ctx.device)
@@ -257,7 +285,7 @@ class Plan:
         info = self.info()
         if s_end is None:
             s_end = info["n_slices"]
-        self.ctx.ensure_workspace(self._call_workspace(len(bits), s_end - s_begin))
+        self.ctx.ensure_workspace(info["workspace_bytes"], self._call_workspace(len(bits), s_end - s_begin))
         with torch.cuda.stream(self.ctx.stream):
             if isinstance(bits, np.ndarray):
                 bits_t = torch.from_numpy(np.ascontiguousarray(bits, dtype=np.uint8)).to(self.ctx.device)

@@ -47,8 +47,14 @@ struct qf_ctx {
   hipStream_t stream = nullptr;
   char* ws = nullptr;
   size_t ws_bytes = 0;
+  char* call_ws = nullptr;  // more room for calls of several chains (qf_ctx_set_call_workspace)
+  size_t call_ws_bytes = 0;
+  char* base = nullptr;     // where offset 0 of the running plan's arena is: ws, or such that a form lies in call_ws
   std::string err;
+  // what the workspace holds the tables and world-lines of: a plan, at its start, and that plan's form for calls
+  // of several chains (qf_plan::multi), behind the plan's arena or in call_ws
   const qf_plan* last_built = nullptr;
+  const qf_plan* multi_built = nullptr;
   // profiling of the dominant GEMM class
   bool profile = false;
   std::vector<hipEvent_t> ev_pool;
@@ -220,7 +226,7 @@ struct qf_plan {
   // (batch_form below); built on the first such call
   qf_plan* multi = nullptr;
   bool multi_tried = false;
-  bool sequential_like = false;  // this plan is another's `multi`: roles and shapes of the one-chain form
+  qf_plan* form_of = nullptr;    // this plan is that one's `multi`: roles and shapes of the one-chain form
   std::vector<int32_t> desc_steps;
   // qf_plan_info_get's result: fixed once the plan is laid out, computed on the first call
   // (flops_next_slice simulates the reuse schedule over up to 4096 slices)
@@ -233,6 +239,9 @@ static qf_status fail(qf_ctx* ctx, qf_status st, const std::string& msg) {
   if (ctx) ctx->err = msg;
   return st;
 }
+
+// Nothing of a plan is left in the workspace.
+static void forget_built(qf_ctx* c) { c->last_built = c->multi_built = nullptr; }
 
 static qf_status hip_fail(qf_ctx* ctx, hipError_t e, const char* what) {
   return fail(ctx, QF_ERR_HIP, std::string(what) + ": " + hipGetErrorString(e));
@@ -313,7 +322,16 @@ qf_status qf_ctx_set_workspace(qf_ctx* ctx, void* workspace, size_t ws_bytes) {
   if ((reinterpret_cast<uintptr_t>(workspace) % kAlign) != 0) return fail(ctx, QF_ERR_ARG, "workspace must be 256-byte aligned");
   ctx->ws = reinterpret_cast<char*>(workspace);
   ctx->ws_bytes = workspace ? ws_bytes : 0;
-  ctx->last_built = nullptr;
+  forget_built(ctx);
+  return QF_OK;
+}
+
+qf_status qf_ctx_set_call_workspace(qf_ctx* ctx, void* workspace, size_t ws_bytes) {
+  if (!ctx) return QF_ERR_ARG;
+  if ((reinterpret_cast<uintptr_t>(workspace) % kAlign) != 0) return fail(ctx, QF_ERR_ARG, "workspace must be 256-byte aligned");
+  ctx->call_ws = reinterpret_cast<char*>(workspace);
+  ctx->call_ws_bytes = workspace ? ws_bytes : 0;
+  ctx->multi_built = nullptr;
   return QF_OK;
 }
 
@@ -517,7 +535,7 @@ static void plan_gather(const qf_plan* p, Step& st, Operand& op) {
 // twice the work a step, single chains were slower than launches (3x4, depth 24, an early version: 131 against 78).
 static void plan_small(qf_plan* p) {
   const int n = p->n, S = (int)p->steps.size();
-  if (S < 1 || S > kSmallMaxSteps) return;
+  if (S < 1 || S > kSmallMaxSteps || p->form_of) return;
   for (const Step& st : p->steps)
     if (std::max({st.m_bits + st.k_bits, st.n_bits + st.k_bits, st.m_bits + st.n_bits}) > kSmallMaxBits ||
         (p->precision != QF_FP32 && cgemm_variant_fits(p->precision, (int64_t)1 << st.m_bits, (int64_t)1 << st.n_bits,
@@ -582,7 +600,10 @@ static bool env_direct(const qf_plan* p, const Operand& op) {
   return p->precision == QF_FP32 && !op.permute && !p->nodes[op.node].leaf;
 }
 
-// Offsets of everything a plan keeps in the workspace, and the gather jobs that use them.
+// Offsets of everything a plan keeps in the workspace, and the gather jobs that use them.  A form for several
+// chains reads its plan's world-lines and has an arena behind the plan's: a captured graph of a call reads tables and
+// world-lines that were built before it, so calls of other sizes between its replays have to leave them there,
+// and a call after a change of the gates has to bring them up to date.
 static void layout_arena(qf_plan* p, size_t n_ops) {
   const int n = p->n;
   size_t cur = kCtxScratch;
@@ -594,6 +615,7 @@ static void layout_arena(qf_plan* p, size_t n_ops) {
   cur = align_up(cur + std::max<size_t>(1, p->wl_prog.size()) * sizeof(WlInstr));
   p->off_wl = cur;
   cur = align_up(cur + p->wl_elems * sizeof(float2));
+  if (p->form_of) cur = align_up(p->form_of->arena_end);
   std::vector<Buf> pers, trans;
   const int S = (int)p->steps.size();
   for (int i = 0; i < S; ++i) {
@@ -713,7 +735,7 @@ static void layout_arena(qf_plan* p, size_t n_ops) {
     }
 }
 
-static qf_status build_plan(qf_ctx* ctx, qf_circuit* circ, const qf_plan_desc* d, bool sequential_like, qf_plan** out) {
+static qf_status build_plan(qf_ctx* ctx, qf_circuit* circ, const qf_plan_desc* d, qf_plan* form_of, qf_plan** out) {
   if (!ctx || !circ || !d || !out) return fail(ctx, QF_ERR_ARG, "qf_plan_create: null argument");
   if (circ->ctx != ctx) return fail(ctx, QF_ERR_ARG, "qf_plan_create: the circuit belongs to another context");
   *out = nullptr;
@@ -735,7 +757,7 @@ static qf_status build_plan(qf_ctx* ctx, qf_circuit* circ, const qf_plan_desc* d
   if (p->G > 1) p->flags |= QF_PLAN_NO_HOIST;
   p->graph = p->G > 1 && (d->flags & QF_PLAN_GRAPH);
   p->renorm = !p->backward && !(d->flags & QF_PLAN_NO_RENORM);
-  p->sequential_like = sequential_like;
+  p->form_of = form_of;
 
   // ---- bonds: one bit per diagonal two-qubit gate, time order (ops are sorted by cycle)
   std::vector<std::vector<int>> edge_gate_bits;  // per edge: op indices
@@ -922,7 +944,7 @@ static qf_status build_plan(qf_ctx* ctx, qf_circuit* circ, const qf_plan_desc* d
     for (int lab : X->labels) if (contains(Y->labels, lab)) K.push_back(lab);
     int xf = (int)X->labels.size() - (int)K.size(), yf = (int)Y->labels.size() - (int)K.size();
     if (yf > xf) { std::swap(X, Y); std::swap(xid, yid); std::swap(xf, yf); }
-    if (group_hoist && !sequential_like && X->dep_cuts == 0 && Y->dep_cuts != 0) { std::swap(X, Y); std::swap(xid, yid); std::swap(xf, yf); }
+    if (group_hoist && !form_of && X->dep_cuts == 0 && Y->dep_cuts != 0) { std::swap(X, Y); std::swap(xid, yid); std::swap(xf, yf); }
     // K order: keep an intermediate operand in place when its contracted bits already trail
     auto trailing = [&](const Node* nd) {
       if (nd->leaf) return false;
@@ -1023,7 +1045,7 @@ static qf_status build_plan(qf_ctx* ctx, qf_circuit* circ, const qf_plan_desc* d
     if (!p->ghoist) p->step_inv.clear();
     for (size_t i = 0; p->ghoist && i < p->steps.size(); ++i) {
       Step& st = p->steps[i];
-      st.fold = !sequential_like && !p->step_inv[i] && !st.presplit && operand_invariant(p.get(), st.B) &&
+      st.fold = !form_of && !p->step_inv[i] && !st.presplit && operand_invariant(p.get(), st.B) &&
                 !operand_invariant(p.get(), st.A);
       if (st.fold)  // split-K partials of the folded shape (G M rows, one launch)
         p->gscratch_bytes = std::max(p->gscratch_bytes,
@@ -1094,7 +1116,7 @@ static qf_status build_plan(qf_ctx* ctx, qf_circuit* circ, const qf_plan_desc* d
 }
 
 qf_status qf_plan_create(qf_ctx* ctx, qf_circuit* circ, const qf_plan_desc* d, qf_plan** out) {
-  return build_plan(ctx, circ, d, false, out);
+  return build_plan(ctx, circ, d, nullptr, out);
 }
 
 // Destroys a plan's captured graph after the work queued on its stream has finished.
@@ -1113,6 +1135,7 @@ void qf_plan_destroy(qf_plan* plan) {
   plan_release_graph(plan);
   if (plan->ctx) {
     if (plan->ctx->last_built == plan) plan->ctx->last_built = nullptr;
+    if (plan->ctx->multi_built == plan) plan->ctx->multi_built = nullptr;
     plan->ctx->plans.erase(plan);
   }
   if (plan->circ) plan->circ->plans.erase(plan);
@@ -1179,7 +1202,7 @@ constexpr int kMultiChains = 64;
 static qf_plan* batch_form(qf_plan* p) {
   if (p->multi || p->multi_tried) return p->multi;
   p->multi_tried = true;
-  if (p->G != 1 || p->sequential_like || p->precision == QF_FP16 || p->small) return nullptr;
+  if (p->G != 1 || p->form_of || p->precision == QF_FP16 || p->small) return nullptr;
   const size_t shared = p->off_wl + p->wl_elems * sizeof(float2);
   const size_t chain = p->arena_end > shared ? p->arena_end - shared : 1;
   int G = 1;
@@ -1198,11 +1221,18 @@ static qf_plan* batch_form(qf_plan* p) {
             (p->renorm || p->backward ? 0 : QF_PLAN_NO_RENORM);
   d.batch = G;
   qf_plan* q = nullptr;
-  if (build_plan(p->ctx, p->circ, &d, true, &q) != QF_OK) return nullptr;
+  try {
+    if (build_plan(p->ctx, p->circ, &d, p, &q) != QF_OK) return nullptr;
+  } catch (const std::bad_alloc&) {  // the chains then run one at a time
+    return nullptr;
+  }
+  // its leaves are stored as the plan's (the order follows from the steps' roles, which are the same)
+  bool same = q->off_wl == p->off_wl && q->leaf_full_labels == p->leaf_full_labels;
+  for (size_t i = 0; same && i < q->wl_prog.size(); ++i) same = q->wl_prog[i].bitpos == p->wl_prog[i].bitpos;
   // what the group form recomputes, at the rate of such steps, against the launches that it saves
   const int64_t S = std::min<int64_t>((int64_t)1 << p->total_cut_bits, 4096);
   const double more_s = (schedule_flops(q, 0, S, true) - schedule_flops(p, 0, S, true)) / 50e12;
-  if (more_s > 8e-6 * (double)p->steps.size() * (double)S * (1.0 - 1.0 / G)) {
+  if (!same || more_s > 8e-6 * (double)p->steps.size() * (double)S * (1.0 - 1.0 / G)) {
     qf_plan_destroy(q);
     return nullptr;
   }
@@ -1214,13 +1244,14 @@ static qf_plan* batch_form(qf_plan* p) {
 qf_status qf_plan_call_workspace(qf_plan* p, int n_batch, int64_t slices, size_t* bytes) {
   if (!p || !p->ctx || !p->circ || !bytes || n_batch < 0 || slices < 0) return QF_ERR_ARG;
   *bytes = p->arena_end;
-  if ((int64_t)n_batch * slices < 2) return QF_OK;
+  if (n_batch < 1 || slices < 1 || (n_batch < 2 && slices < 2)) return QF_OK;
+  // the same for every such call, so that a workspace once large enough stays where it is
   if (p->small) {
-    if (p->precision != QF_FP16 || p->G > 1) *bytes += small_most(p, n_batch * slices) * (size_t)p->small_elems * sizeof(float2);
+    if (p->precision != QF_FP16 || p->G > 1) *bytes += small_most(p, kSmallChains) * (size_t)p->small_elems * sizeof(float2);
     return QF_OK;
   }
   const qf_plan* q = batch_form(p);
-  if (q) *bytes = std::max(*bytes, q->arena_end);
+  if (q) *bytes = q->arena_end;  // behind the plan's own
   return QF_OK;
 }
 
@@ -1290,7 +1321,8 @@ qf_status qf_plan_info_get(const qf_plan* p, qf_plan_info* out) {
 }  // extern "C"
 
 // ---------------------------------------------------------------------------------------------
-static float2* wsp(qf_ctx* c, size_t off) { return reinterpret_cast<float2*>(c->ws + off); }
+static float2* wsp(qf_ctx* c, size_t off) { return reinterpret_cast<float2*>(c->base + off); }
+static float2* wl_of(const qf_plan* p) { return reinterpret_cast<float2*>(p->ctx->ws + p->off_wl); }
 
 static hipEvent_t take_event(qf_ctx* c) {
   if (!c->ev_pool.empty()) {
@@ -1305,6 +1337,26 @@ static hipEvent_t take_event(qf_ctx* c) {
 
 static bool trace_on();
 
+// The plan's own tables into its arena.
+static qf_status upload_tables(qf_plan* p) {
+  qf_ctx* c = p->ctx;
+  QF_HIP(c, hipMemcpyAsync(c->base + p->off_leafdesc, p->leaf_desc.data(), p->leaf_desc.size() * sizeof(LeafDesc),
+                           hipMemcpyHostToDevice, c->stream));
+  if (p->small)
+    QF_HIP(c, hipMemcpyAsync(c->base + p->off_small_steps, p->small_steps.data(), p->small_steps.size() * sizeof(SmallStep),
+                             hipMemcpyHostToDevice, c->stream));
+  if (!p->jobs.empty()) {
+    QF_HIP(c, hipMemcpyAsync(c->base + p->off_jobs, p->jobs.data(), p->jobs.size() * sizeof(GatherJob),
+                             hipMemcpyHostToDevice, c->stream));
+    QF_HIP(c, hipMemcpyAsync(c->base + p->off_blocks, p->job_blocks.data(), p->job_blocks.size() * sizeof(GatherBlock),
+                             hipMemcpyHostToDevice, c->stream));
+  }
+  if (p->renorm)
+    QF_HIP(c, hipMemcpyAsync(c->base + p->off_scales, p->scale_init.data(), p->scale_init.size() * sizeof(NodeScale),
+                             hipMemcpyHostToDevice, c->stream));
+  return QF_OK;
+}
+
 static qf_status build_worldlines(qf_plan* p) {
   qf_ctx* c = p->ctx;
   qf_circuit* circ = p->circ;
@@ -1317,23 +1369,9 @@ static qf_status build_worldlines(qf_plan* p) {
   if (!p->wl_prog.empty())
     QF_HIP(c, hipMemcpyAsync(c->ws + p->off_prog, p->wl_prog.data(), p->wl_prog.size() * sizeof(WlInstr),
                              hipMemcpyHostToDevice, c->stream));
-  QF_HIP(c, hipMemcpyAsync(c->ws + p->off_leafdesc, p->leaf_desc.data(), p->leaf_desc.size() * sizeof(LeafDesc),
-                           hipMemcpyHostToDevice, c->stream));
-  if (p->small)
-    QF_HIP(c, hipMemcpyAsync(c->ws + p->off_small_steps, p->small_steps.data(), p->small_steps.size() * sizeof(SmallStep),
-                             hipMemcpyHostToDevice, c->stream));
-  if (!p->jobs.empty()) {
-    QF_HIP(c, hipMemcpyAsync(c->ws + p->off_jobs, p->jobs.data(), p->jobs.size() * sizeof(GatherJob),
-                             hipMemcpyHostToDevice, c->stream));
-    QF_HIP(c, hipMemcpyAsync(c->ws + p->off_blocks, p->job_blocks.data(), p->job_blocks.size() * sizeof(GatherBlock),
-                             hipMemcpyHostToDevice, c->stream));
-  }
-  if (p->renorm)
-    QF_HIP(c, hipMemcpyAsync(c->ws + p->off_scales, p->scale_init.data(), p->scale_init.size() * sizeof(NodeScale),
-                             hipMemcpyHostToDevice, c->stream));
   QF_HIP(c, launch_worldlines(c->stream, reinterpret_cast<const WlQubit*>(c->ws + p->off_wlq), p->n, p->max_nbond,
                               reinterpret_cast<const WlInstr*>(c->ws + p->off_prog),
-                              reinterpret_cast<const float2*>(c->ws + p->off_gates), wsp(c, p->off_wl)));
+                              reinterpret_cast<const float2*>(c->ws + p->off_gates), wl_of(p)));
   return QF_OK;
 }
 
@@ -1361,7 +1399,7 @@ static void leaf_args(const qf_plan* p, const Node& nd, const Operand& op, const
 }
 
 static NodeScale* node_scale(qf_plan* p, int node) {
-  return reinterpret_cast<NodeScale*>(p->ctx->ws + p->off_scales) + node;
+  return reinterpret_cast<NodeScale*>(p->ctx->base + p->off_scales) + node;
 }
 
 // Conversion that an operand's permute applies for a pre-split GEMM: bfloat16 hi and lo planes
@@ -1391,14 +1429,14 @@ static qf_status run_operand(qf_plan* p, const Operand& op, const uint8_t* bits_
       map->src_base = a.src_base;
       map->dyn_bits = a.dyn_bits;
       map->dyn_stride = a.dyn_stride;
-      *ptr = wsp(c, p->off_wl) + p->wl_qubits[nd.qubit].out_offset;
+      *ptr = wl_of(p) + p->wl_qubits[nd.qubit].out_offset;
     }
     return QF_OK;
   }
   const float2* src;
   if (nd.leaf) {
     leaf_args(p, nd, op, bits_row, s, &a);
-    src = wsp(c, p->off_wl) + p->wl_qubits[nd.qubit].out_offset;
+    src = wl_of(p) + p->wl_qubits[nd.qubit].out_offset;
   } else {
     std::memset(&a, 0, sizeof(a));
     a.nbits = op.nbits;
@@ -1442,13 +1480,13 @@ static Renorm step_renorm(qf_plan* p, size_t i, bool mapped_a = false) {
 // world-line operands gathered, in one launch.  tables: also write the per-chain offsets of batched plans.
 static qf_status begin_chain(qf_plan* p, const ChainGroup& grp, const StepMask& run, bool tables) {
   qf_ctx* c = p->ctx;
-  QF_HIP(c, launch_chain_begin(c->stream, grp, p->n, reinterpret_cast<const LeafDesc*>(c->ws + p->off_leafdesc),
-                               tables ? reinterpret_cast<int64_t*>(c->ws + p->off_btable) : nullptr,
-                               tables ? reinterpret_cast<int32_t*>(c->ws + p->off_chainb) : nullptr,
+  QF_HIP(c, launch_chain_begin(c->stream, grp, p->n, reinterpret_cast<const LeafDesc*>(c->base + p->off_leafdesc),
+                               tables ? reinterpret_cast<int64_t*>(c->base + p->off_btable) : nullptr,
+                               tables ? reinterpret_cast<int32_t*>(c->base + p->off_chainb) : nullptr,
                                (int)p->steps.size(), run, p->renorm && p->chain_begin ? node_scale(p, 0) : nullptr,
-                               reinterpret_cast<const GatherJob*>(c->ws + p->off_jobs),
-                               reinterpret_cast<const GatherBlock*>(c->ws + p->off_blocks), (int)p->job_blocks.size(),
-                               wsp(c, p->off_wl), c->ws));
+                               reinterpret_cast<const GatherJob*>(c->base + p->off_jobs),
+                               reinterpret_cast<const GatherBlock*>(c->base + p->off_blocks), (int)p->job_blocks.size(),
+                               wl_of(p), c->base));
   return QF_OK;
 }
 
@@ -1457,8 +1495,8 @@ static bool runs_small(const qf_plan* p) { return p->small && !p->ctx->profile &
 
 // Chains per launch that the workspace has room for.
 static int64_t small_room(const qf_plan* p, int64_t chains) {
-  const size_t behind = (p->ctx->ws_bytes - p->arena_end) / (p->small_elems * sizeof(float2));
-  return (int64_t)std::max<size_t>(1, std::min(behind, small_most(p, chains)));
+  const size_t room = std::max(p->ctx->ws_bytes - p->arena_end, p->ctx->call_ws_bytes) / (p->small_elems * sizeof(float2));
+  return (int64_t)std::max<size_t>(1, std::min(room, small_most(p, chains)));
 }
 
 // All chains of a call (bitstring-major) forward, or forward and in reverse.
@@ -1468,16 +1506,18 @@ static qf_status small_call(qf_plan* p, int n_batch, const uint8_t* bits_dev, in
   const int64_t s_range = s_end - s_begin, chains = n_batch * s_range, G = small_room(p, chains);
   SmallArgs a;
   std::memset(&a, 0, sizeof(a));
-  a.steps = reinterpret_cast<const SmallStep*>(c->ws + p->off_small_steps);
+  a.steps = reinterpret_cast<const SmallStep*>(c->base + p->off_small_steps);
   a.n_steps = (int)p->small_steps.size();
   a.n_leaves = p->n;
-  a.leaves = reinterpret_cast<const LeafDesc*>(c->ws + p->off_leafdesc);
-  a.wl = wsp(c, p->off_wl);
-  a.scratch = wsp(c, G > 1 ? p->arena_end : p->off_small);
+  a.leaves = reinterpret_cast<const LeafDesc*>(c->base + p->off_leafdesc);
+  a.wl = wl_of(p);
+  a.scratch = wsp(c, p->off_small);
+  if (G > 1)
+    a.scratch = c->ws_bytes - p->arena_end >= c->call_ws_bytes ? wsp(c, p->arena_end) : reinterpret_cast<float2*>(c->call_ws);
   a.chain_elems = p->small_elems;
   a.renorm = p->renorm;
-  a.chain_b = reinterpret_cast<int32_t*>(c->ws + p->off_small_b);
-  a.chain_e = reinterpret_cast<int32_t*>(c->ws + p->off_small_e);
+  a.chain_b = reinterpret_cast<int32_t*>(c->base + p->off_small_b);
+  a.chain_e = reinterpret_cast<int32_t*>(c->base + p->off_small_e);
   const int k = (int)p->open.size();
   for (int t = 0; t < k; ++t) a.root.push(p->root_pos[t]);
   a.cot = reinterpret_cast<const double2*>(cot_dev);
@@ -1621,13 +1661,35 @@ static qf_status run_step(qf_plan* p, size_t i, const uint8_t* row, int64_t s) {
   return QF_OK;
 }
 
+// Where offset 0 of the arena of form q is (null: no room for q): behind its plan's in the workspace, else in the
+// calls' own.
+static char* form_base(const qf_ctx* c, const qf_plan* q) {
+  const size_t start = align_up(q->form_of->arena_end);
+  if (c->ws_bytes >= q->arena_end) return c->ws;
+  if (c->call_ws_bytes < q->arena_end - start) return nullptr;
+  return reinterpret_cast<char*>(reinterpret_cast<uintptr_t>(c->call_ws) - start);
+}
+
 static qf_status prepare(qf_plan* p) {
   qf_ctx* c = p->ctx;
+  if (p->form_of) {  // the plan's world-lines, and tables of its own
+    qf_status st = prepare(p->form_of);
+    if (st != QF_OK) return st;
+    c->base = form_base(c, p);
+    if (!c->base) return fail(c, QF_ERR_WORKSPACE, "no room for calls of several chains");
+    if (c->multi_built == p) return QF_OK;
+    st = upload_tables(p);
+    if (st == QF_OK) c->multi_built = p;
+    return st;
+  }
   if (!c->ws || c->ws_bytes < p->arena_end)
     return fail(c, QF_ERR_WORKSPACE, "workspace too small: need " + std::to_string(p->arena_end) + " bytes");
   QF_HIP(c, hipSetDevice(c->device));
+  c->base = c->ws;
   if (c->last_built != p || p->built_version != p->circ->version) {
+    if (c->last_built != p) forget_built(c);
     qf_status st = build_worldlines(p);
+    if (st == QF_OK && c->last_built != p) st = upload_tables(p);
     if (st != QF_OK) return st;
     c->last_built = p;
     p->built_version = p->circ->version;
@@ -1647,9 +1709,9 @@ static qf_status run_operand_batched(qf_plan* p, const Operand& op, const float2
     *map = op.map;
     *ptr = wsp(c, nd.offset);
     if (nd.leaf) {
-      map->base_table = reinterpret_cast<const int64_t*>(c->ws + p->off_btable) + nd.qubit;
+      map->base_table = reinterpret_cast<const int64_t*>(c->base + p->off_btable) + nd.qubit;
       map->base_stride = operand_batch(p, op) > 1 ? p->n : 0;
-      *ptr = wsp(c, p->off_wl) + p->wl_qubits[nd.qubit].out_offset;
+      *ptr = wl_of(p) + p->wl_qubits[nd.qubit].out_offset;
     }
     return QF_OK;
   }
@@ -1662,9 +1724,9 @@ static qf_status run_operand_batched(qf_plan* p, const Operand& op, const float2
   a.dst_bstride = (int64_t)operand_elems(op);
   const float2* src;
   if (nd.leaf) {
-    src = wsp(c, p->off_wl) + p->wl_qubits[nd.qubit].out_offset;
+    src = wl_of(p) + p->wl_qubits[nd.qubit].out_offset;
     a.src_bstride = 0;
-    a.base_table = reinterpret_cast<const int64_t*>(c->ws + p->off_btable) + nd.qubit;
+    a.base_table = reinterpret_cast<const int64_t*>(c->base + p->off_btable) + nd.qubit;
     a.base_stride = p->n;
   } else {
     src = wsp(c, nd.offset);
@@ -1681,7 +1743,7 @@ static qf_status enqueue_group(qf_plan* p, const uint8_t* bits_dev, int64_t s_be
                                int64_t chain0, int64_t n_chains, double* out_dev, bool timed_ok) {
   qf_ctx* c = p->ctx;
   const int n = p->n, G = p->G, k = (int)p->open.size();
-  int32_t* chain_b = reinterpret_cast<int32_t*>(c->ws + p->off_chainb);
+  int32_t* chain_b = reinterpret_cast<int32_t*>(c->base + p->off_chainb);
   const int64_t gpb = p->ghoist ? (s_range + G - 1) / G : 0;  // launch groups per bitstring
   const ChainGroup grp = {chain0, G, n, bits_dev, s_begin, s_range, n_chains, gpb};
   qf_status e0s = begin_chain(p, grp, kAllSteps, true);
@@ -1756,7 +1818,8 @@ static qf_status amplitudes_batched(qf_plan* p, int n_batch, const uint8_t* bits
   if (!(p->graph && c->stream)) return enqueue_call(p, n_batch, bits_dev, s_begin, s_end, out_dev, true);
   const std::vector<int64_t> key = {(int64_t)(uintptr_t)c->ws, (int64_t)(uintptr_t)bits_dev,
                                     (int64_t)(uintptr_t)out_dev, n_batch, s_begin, s_end,
-                                    (int64_t)(uintptr_t)c->stream, (int64_t)c->ws_bytes};
+                                    (int64_t)(uintptr_t)c->stream, (int64_t)c->ws_bytes,
+                                    (int64_t)(uintptr_t)c->call_ws, (int64_t)c->call_ws_bytes};
   if (!p->gexec || key != p->graph_key) {
     if (p->gexec) {
       QF_HIP(c, hipStreamSynchronize(c->stream));
@@ -1803,18 +1866,14 @@ extern "C" qf_status qf_plan_graph_info(const qf_plan* p, int64_t* launches, int
 }
 
 // The batch form of plan p if this call runs on it, with its chains per launch set for the call: calls of
-// several chains for which the workspace is there; and single chains while the workspace holds its
-// world-lines (another build of them costs more than it saves).  Not while a stream capture would record
-// the build.
+// several chains for which the workspace is there.  Not while a stream capture would record the build.
 static qf_plan* multi_for_call(qf_plan* p, int n_batch, int64_t slices) {
   qf_ctx* c = p->ctx;
-  if (p->G != 1 || p->sequential_like) return nullptr;
-  const bool several = (int64_t)n_batch * slices >= 2;
-  qf_plan* q = several ? batch_form(p) : p->multi;
-  if (!q || c->ws_bytes < q->arena_end) return nullptr;
-  const bool built = c->last_built == q && q->built_version == q->circ->version;
-  if (!built) {
-    if (!several || (q->ghoist && slices < 2)) return nullptr;
+  if (p->G != 1 || p->form_of) return nullptr;
+  if (n_batch < 2 && slices < 2) return nullptr;
+  qf_plan* q = batch_form(p);
+  if (!q || !form_base(c, q) || (q->ghoist && slices < 2)) return nullptr;
+  if (c->multi_built != q || c->last_built != p || p->built_version != p->circ->version) {
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (c->stream && hipStreamIsCapturing(c->stream, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone) return nullptr;
   }
@@ -1945,18 +2004,20 @@ extern "C" qf_status qf_amplitudes_static(qf_plan* p, int n_batch, const uint8_t
   // run on the static array: the world-lines are rebuilt in it (every region that must start at a
   // known value, the chain counter, the scale table and the max-magnitude slots, is written by
   // the call itself before it is read), profiling (which may create events) is off
-  char* ws = c->ws;
-  const size_t ws_bytes = c->ws_bytes;
+  char* const ws = c->ws;
+  const size_t ws_bytes = c->ws_bytes, call_ws_bytes = c->call_ws_bytes;
   const bool prof = c->profile;
   c->ws = ptr;
   c->ws_bytes = kStaticScratchBytes;
+  c->call_ws_bytes = 0;
   c->profile = false;
-  c->last_built = nullptr;
+  forget_built(c);
   st = qf_amplitudes(p, n_batch, bits_dev, s_begin, s_end, out_dev);
   c->ws = ws;
   c->ws_bytes = ws_bytes;
+  c->call_ws_bytes = call_ws_bytes;
   c->profile = prof;
-  c->last_built = nullptr;  // the caller's workspace is rebuilt on its next use
+  forget_built(c);  // the caller's workspace is rebuilt on its next use
   return st;
 }
 
@@ -2008,7 +2069,7 @@ static qf_status batched_transpose(qf_plan* p, int xb, int yb, int conj, const f
 static qf_status route_env_batched(qf_plan* p, const Operand& op, const float2* E) {
   qf_ctx* c = p->ctx;
   const Node& nd = p->nodes[op.node];
-  const int32_t* chain_b = reinterpret_cast<const int32_t*>(c->ws + p->off_chainb);
+  const int32_t* chain_b = reinterpret_cast<const int32_t*>(c->base + p->off_chainb);
   PermuteArgs a;
   std::memset(&a, 0, sizeof(a));
   a.nbits = op.nbits;
@@ -2016,7 +2077,7 @@ static qf_status route_env_batched(qf_plan* p, const Operand& op, const float2* 
   if (nd.leaf) {
     for (int i = 0; i < op.nbits; ++i) a.perm[i] = op.perm[i];
     float2* dst = wsp(c, p->off_envwl) + p->wl_qubits[nd.qubit].out_offset;
-    const int64_t* btab = reinterpret_cast<const int64_t*>(c->ws + p->off_btable) + nd.qubit;
+    const int64_t* btab = reinterpret_cast<const int64_t*>(c->base + p->off_btable) + nd.qubit;
     QF_HIP(c, launch_scatter_add_batched(c->stream, E, dst, a, p->G, btab, p->n, (int64_t)1 << op.nbits, chain_b));
     return QF_OK;
   }
@@ -2052,7 +2113,7 @@ static qf_status backward_group(qf_plan* p, const uint8_t* bits_dev, const doubl
                                 int64_t s_range, int64_t chain0, int64_t n_chains) {
   qf_ctx* c = p->ctx;
   const int n = p->n, G = p->G, k = (int)p->open.size();
-  int32_t* chain_b = reinterpret_cast<int32_t*>(c->ws + p->off_chainb);
+  int32_t* chain_b = reinterpret_cast<int32_t*>(c->base + p->off_chainb);
   const ChainGroup grp = {chain0, G, n, bits_dev, s_begin, s_range, n_chains, 0};
   qf_status e0 = begin_chain(p, grp, kAllSteps, true);
   if (e0 != QF_OK) return e0;
@@ -2128,7 +2189,7 @@ extern "C" qf_status qf_backward(qf_plan* p, int n_batch, const uint8_t* bits_de
   }
   qf_status e = prepare(p);
   if (e != QF_OK) return e;
-  QF_HIP(c, launch_zero(c->stream, c->ws + p->off_envwl, align_up(p->wl_elems * sizeof(float2))));
+  QF_HIP(c, launch_zero(c->stream, c->base + p->off_envwl, align_up(p->wl_elems * sizeof(float2))));
   const int n = p->n;
   const int k = (int)p->open.size();
   const int S_steps = (int)p->steps.size();
@@ -2266,7 +2327,7 @@ qf_status qf_cgemm_variant(qf_ctx* c, int precision, int variant, int64_t M, int
   size_t scratch_bytes = cgemm_split_scratch(precision, M, N, K, batch, variant);
   if (scratch_bytes > 0 && c->ws && c->ws_bytes > kCtxScratch && c->ws_bytes - kCtxScratch >= scratch_bytes) {
     scratch = reinterpret_cast<float2*>(c->ws + kCtxScratch);
-    c->last_built = nullptr;
+    forget_built(c);
   } else {
     scratch_bytes = 0;
   }
@@ -2523,7 +2584,7 @@ static qf_status time_variant(qf_ctx* c, const qf_plan* p, int variant, int64_t 
                               int64_t G, const float2* A, const float2* B, float2* C, float give_up_ms, float* ms,
                               int64_t sa, int64_t sb) {
   const int prec = p->precision;
-  float2* scratch = p->gscratch_bytes ? reinterpret_cast<float2*>(c->ws + p->off_gscratch) : nullptr;
+  float2* scratch = p->gscratch_bytes ? reinterpret_cast<float2*>(c->base + p->off_gscratch) : nullptr;
   hipEvent_t e0 = take_event(c), e1 = take_event(c);
   if (!e0 || !e1) return fail(c, QF_ERR_HIP, "hipEventCreate failed");
   auto launch = [&]() {
@@ -2581,6 +2642,7 @@ extern "C" qf_status qf_autotune(qf_ctx* c, const qf_plan* pc, const char* path)
   if (!c->ws || c->ws_bytes < p->arena_end)
     return fail(c, QF_ERR_WORKSPACE, "workspace too small: need " + std::to_string(p->arena_end) + " bytes");
   QF_HIP(c, hipSetDevice(c->device));
+  c->base = c->ws;
   const std::string dev = device_tag(c->device);
   std::map<std::array<int64_t, 5>, TuneEntry> file;
   if (path) {
@@ -2639,7 +2701,7 @@ extern "C" qf_status qf_autotune(qf_ctx* c, const qf_plan* pc, const char* path)
     }
   }
   QF_HIP(c, hipStreamSynchronize(c->stream));
-  c->last_built = nullptr;  // nothing of the plan's intermediate state survives
+  forget_built(c);  // nothing of the plan's intermediate state survives
   if (!path) return QF_OK;
   // rewrite the file: entries of the file (other shapes, same device) plus the context's table
   for (const auto& kv : c->tune) {

@@ -46,3 +46,84 @@ def test_split_products_between_a_plans_calls(kind, M, N, K):
     got = p.amplitudes(bits)
     torch.cuda.synchronize()
     assert np.array_equal(got.cpu().numpy(), want.cpu().numpy())
+
+
+@pytest.mark.parametrize("kind", ["small", "one chain"])
+@pytest.mark.parametrize("roomy", [True, False])
+def test_captured_call_survives_calls_of_other_sizes(kind, roomy):
+    """A caller's own graph of a one-chain call, with calls of one and of several chains and a change of the
+    gates between its replays: every replay gives what an eager call gives.  roomy: the workspace holds
+    the largest of these calls from the start; else they get a buffer of their own."""
+    import torch
+    from paper_1905_00444_amd import Context
+    _say(f"captured call among others: {kind}, roomy {roomy}")
+    ctx = Context(0, stream=torch.cuda.Stream())
+    if roomy:
+        ctx.ensure_workspace(128 << 20)
+    p, n = _plan(ctx, kind)
+    bits = torch.from_numpy(random_bitstrings(40, n, 1)).cuda()
+    torch.cuda.synchronize()
+    one = bits[:1]
+
+    def eager(b):
+        got = p.amplitudes(b)
+        ctx.synchronize()
+        return got.cpu().numpy()
+
+    want = eager(one)
+    out = torch.zeros((1, 4), dtype=torch.complex128, device="cuda")
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=ctx.stream):
+        out.zero_()
+        p.amplitudes(one, out=out)
+
+    def replay():
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        return out.cpu().numpy()
+
+    assert np.array_equal(replay(), want)
+    many = eager(bits)
+    assert np.array_equal(many[:1], want)
+    litter = [torch.full((1 << 20,), 255, dtype=torch.uint8, device="cuda") for _ in range(32)]  # what was given back
+    assert np.array_equal(replay(), want)
+    values = p.circuit.values
+    p.circuit.set_values(values * np.complex64(0.5))
+    half = eager(one)
+    assert not np.array_equal(half, want)
+    assert np.array_equal(replay(), half)
+    p.circuit.set_values(values)
+    assert np.array_equal(eager(bits), many)
+    assert np.array_equal(replay(), want)
+    assert litter[0][0] == 255
+
+
+def test_captured_call_of_several_chains():
+    """Captured after an eager call of one chain only: the workspace does not move under the capture."""
+    import torch
+    from paper_1905_00444_amd import Context
+    _say("captured call of several chains")
+    for kind in ("small", "one chain"):
+        ctx = Context(0, stream=torch.cuda.Stream())
+        p, n = _plan(ctx, kind)
+        bits = torch.from_numpy(random_bitstrings(3, n, 1)).cuda()
+        torch.cuda.synchronize()
+        want = [p.amplitudes(bits[i:i + 1]) for i in range(3)]
+        ctx.synchronize()
+        want = torch.cat(want)
+        out = torch.zeros((3, 4), dtype=torch.complex128, device="cuda")
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=ctx.stream):
+            p.amplitudes(bits, out=out)
+        for _ in range(2):
+            with torch.cuda.stream(ctx.stream):
+                out.zero_()
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert np.array_equal(out.cpu().numpy(), want.cpu().numpy())
+            p.amplitudes(bits)
+            ctx.synchronize()
