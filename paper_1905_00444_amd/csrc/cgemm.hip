@@ -47,11 +47,11 @@ constexpr int kBK = 32;          // complex k per K-tile
 constexpr int kThreads = 256;
 
 __global__ void renorm_reset(NodeScale* c) {
-  if (threadIdx.x < kScaleSlots) c->slot[threadIdx.x].amax = 0u;
+  if (threadIdx.x < kScaleSlots) c[blockIdx.x].slot[threadIdx.x].amax = 0u;
 }
 
-hipError_t launch_renorm_reset(hipStream_t st, NodeScale* c) {
-  hipLaunchKernelGGL(renorm_reset, dim3(1), dim3(64), 0, st, c);
+hipError_t launch_renorm_reset(hipStream_t st, const Renorm& rn, int64_t batch) {
+  hipLaunchKernelGGL(renorm_reset, dim3(rn.c_step ? (unsigned)batch : 1u), dim3(64), 0, st, rn.c);
   return hipGetLastError();
 }
 
@@ -61,9 +61,9 @@ hipError_t launch_renorm_reset(hipStream_t st, NodeScale* c) {
 // (undone here); the renormalisation exponent is applied by the reduction.
 template <int PREC>
 __device__ __forceinline__ void scales_for(const Renorm& rn, const uint32_t* amaxA, const uint32_t* amaxB,
-                                           bool partial, float& scale_a, float& scale_b, float& unscale) {
+                                           bool partial, bool first, float& scale_a, float& scale_b, float& unscale) {
   if (!partial) {
-    renorm_begin<PREC>(rn, amaxA, amaxB, scale_a, scale_b, unscale);
+    renorm_begin<PREC>(rn, amaxA, amaxB, first, scale_a, scale_b, unscale);
     return;
   }
   int s_a = 0, s_b = 0;
@@ -86,12 +86,20 @@ __device__ __forceinline__ void scales_for(const Renorm& rn, const uint32_t* ama
 // them.  Bound by reading the chunks once.
 constexpr int kReduceOut = 32, kReduceSlots = 8;
 
+// A grid's z (the batch elements of P_z, C) where the elements keep scales of their own, else one z for all.
 __global__ void __launch_bounds__(256)
 cgemm_split_reduce(const float2* __restrict__ P, int split, int64_t batch, int64_t MN, int64_t N, int64_t sc,
                    float2* __restrict__ C, Renorm rn) {
   __shared__ float2 part[kReduceSlots][kReduceOut];
   float sa_, sb_, unscale;
-  renorm_begin<P_FP32>(rn, nullptr, nullptr, sa_, sb_, unscale);
+  const int64_t chunk = batch * MN;
+  if (rn.c_step) {
+    rn = renorm_of(rn, blockIdx.z);
+    P += blockIdx.z * MN;
+    C += blockIdx.z * sc;
+    batch = 1;
+  }
+  renorm_begin<P_FP32>(rn, nullptr, nullptr, blockIdx.x == 0, sa_, sb_, unscale);
   const int64_t total = batch * MN;
   const int lane = threadIdx.x % kReduceOut, t = threadIdx.x / kReduceOut;
   float mx = 0.f;
@@ -99,7 +107,7 @@ cgemm_split_reduce(const float2* __restrict__ P, int split, int64_t batch, int64
     const int64_t i = i0 + lane;
     float2 sum = make_float2(0.f, 0.f);
     for (int y0 = 0; y0 < split; y0 += kReduceSlots) {
-      part[t][lane] = i < total && y0 + t < split ? P[(int64_t)(y0 + t) * total + i] : make_float2(0.f, 0.f);
+      part[t][lane] = i < total && y0 + t < split ? P[(int64_t)(y0 + t) * chunk + i] : make_float2(0.f, 0.f);
       __syncthreads();
       if (t == 0)
 #pragma unroll
@@ -252,7 +260,8 @@ cgemm_mfma(int64_t M, int64_t N, int64_t K, const float2* __restrict__ A, const 
   const int l16 = lane & 15, lg = lane >> 4;
 
   float scale_a, scale_b, unscale;
-  scales_for<PREC>(rn, amaxA, amaxB, partial, scale_a, scale_b, unscale);
+  rn = renorm_of(rn, batch);
+  scales_for<PREC>(rn, amaxA, amaxB, partial, tm == 0 && tn == 0, scale_a, scale_b, unscale);
 
   f4 acc[WTM][WTN];
 #pragma unroll
@@ -443,7 +452,8 @@ cgemm_v2(int64_t M, int64_t N, int64_t K, const float2* __restrict__ A, const fl
   const BExpand bx(q);
 
   float scale_a, scale_b, unscale;
-  scales_for<PREC>(rn, amaxA, amaxB, partial, scale_a, scale_b, unscale);
+  rn = renorm_of(rn, batch);
+  scales_for<PREC>(rn, amaxA, amaxB, partial, tm == 0 && tn == 0, scale_a, scale_b, unscale);
 
   f4 acc[4][8];
 #pragma unroll
@@ -525,9 +535,10 @@ __global__ void __launch_bounds__(256)
 cgemm_simt(int64_t M, int64_t N, int64_t K, const float2* __restrict__ A, const float2* __restrict__ B,
            float2* __restrict__ C, int64_t sa, int64_t sb, int64_t sc, Renorm rn) {
   float scale_a, scale_b, unscale;
-  renorm_begin<P_FP32>(rn, nullptr, nullptr, scale_a, scale_b, unscale);
-  float mx = 0.f;
   const int64_t batch = blockIdx.z;
+  rn = renorm_of(rn, batch);
+  renorm_begin<P_FP32>(rn, nullptr, nullptr, blockIdx.x == 0, scale_a, scale_b, unscale);
+  float mx = 0.f;
   A += batch * sa;
   B += batch * sb;
   C += batch * sc;
@@ -565,9 +576,10 @@ cgemm_skinny(int64_t M, int64_t N, int64_t K, const float2* __restrict__ A, cons
              float2* __restrict__ C, int64_t sa, int64_t sb, int64_t sc, Renorm rn, OpMap ma, OpMap mb) {
   __shared__ float2 Bs[kSkinnyMaxB];
   float scale_a, scale_b, unscale;
-  renorm_begin<P_FP32>(rn, nullptr, nullptr, scale_a, scale_b, unscale);
-  float mx = 0.f;
   const int64_t batch = blockIdx.z;
+  rn = renorm_of(rn, batch);
+  renorm_begin<P_FP32>(rn, nullptr, nullptr, blockIdx.x == 0, scale_a, scale_b, unscale);
+  float mx = 0.f;
   A += ma.on ? map_base(ma, batch, sa) : batch * sa;
   B += mb.on ? map_base(mb, batch, sb) : batch * sb;
   C += batch * sc;
@@ -618,8 +630,9 @@ cgemm_splitk(int64_t M, int64_t N, int64_t K, const float2* __restrict__ A, cons
              float2* __restrict__ C, int64_t sa, int64_t sb, int64_t sc, Renorm rn) {
   __shared__ float red[2][NTH / 64];
   float scale_a, scale_b, unscale;
-  renorm_begin<P_FP32>(rn, nullptr, nullptr, scale_a, scale_b, unscale);
   const int64_t batch = blockIdx.z;
+  rn = renorm_of(rn, batch);
+  renorm_begin<P_FP32>(rn, nullptr, nullptr, blockIdx.x == 0, scale_a, scale_b, unscale);
   const int64_t out = blockIdx.x;  // m * N + n
   const int64_t m = out / N, n = out - m * N;
   const float2* a = A + batch * sa + m * K;
@@ -828,7 +841,10 @@ hipError_t launch_cgemm_ex(hipStream_t st, int precision, int64_t M, int64_t N, 
   const OpMap a = ma ? *ma : OpMap{}, b = mb ? *mb : OpMap{};
   const bool chosen = variant != GEMM_AUTO && cgemm_variant_fits(precision, M, N, K, variant);
   int v = chosen ? variant : cgemm_default_variant(precision, M, N, K);
-  if (rn.c && !rn.cleared) hipLaunchKernelGGL(renorm_reset, dim3(1), dim3(64), 0, st, rn.c);
+  if (rn.c && !rn.cleared) {
+    const hipError_t e = launch_renorm_reset(st, rn, batch);
+    if (e != hipSuccess) return e;
+  }
   switch (v) {
     case GEMM_TALL:
       return launch_cgemm_tall(st, precision, M, N, K, A, B, C, batch, sa, sb, sc, amaxA, amaxB, rn, a, b);
@@ -873,8 +889,10 @@ hipError_t launch_cgemm_ex(hipStream_t st, int precision, int64_t M, int64_t N, 
             : launch_mfma<P_FP16>(st, v, M, N, K, A, B, C, batch, sa, sb, sc, amaxA, amaxB, rn, split, scratch, a, b);
   }
   if (e != hipSuccess || split == 1) return e;
-  const unsigned blocks = (unsigned)std::min<int64_t>((batch * M * N + kReduceOut - 1) / kReduceOut, 65536);
-  hipLaunchKernelGGL(cgemm_split_reduce, dim3(blocks), dim3(256), 0, st, scratch, split, batch, M * N, N, sc, C, rn);
+  const unsigned apart = rn.c_step ? (unsigned)batch : 1u;
+  const unsigned blocks = (unsigned)std::min<int64_t>((batch / apart * M * N + kReduceOut - 1) / kReduceOut, 65536);
+  hipLaunchKernelGGL(cgemm_split_reduce, dim3(blocks, 1, apart), dim3(256), 0, st, scratch, split, batch, M * N, N, sc, C,
+                     rn);
   return hipGetLastError();
 }
 

@@ -113,13 +113,23 @@ __device__ __forceinline__ int renorm_exp(const NodeScale* n) {
   return e < -62 ? -62 : (e > 62 ? 62 : e);
 }
 
+// The scales of one batch element.
+__device__ __forceinline__ Renorm renorm_of(Renorm rn, int64_t batch) {
+  if (rn.c) {
+    rn.a += batch * rn.a_step;
+    rn.b += batch * rn.b_step;
+    rn.c += batch * rn.c_step;
+  }
+  return rn;
+}
+
 // Operand scales for staging (FP16 only) and the epilogue factor.  Renormalised: FP16 operands are
 // brought to max ~2^14 from their exponents, the result is stored times 2^-(e_A + e_B), and
-// thread 0 of the first workgroup writes the result's exponent.  Otherwise FP16 scales from the
-// given max magnitudes and undoes them in the epilogue; FP32 / BF16 use no scaling.
+// thread 0 of a batch element's first workgroup writes the result's exponent.  Otherwise FP16 scales from
+// the given max magnitudes and undoes them in the epilogue; FP32 / BF16 use no scaling.
 template <int PREC>
 __device__ __forceinline__ void renorm_begin(const Renorm& rn, const uint32_t* amaxA, const uint32_t* amaxB,
-                                             float& scale_a, float& scale_b, float& unscale) {
+                                             bool first, float& scale_a, float& scale_b, float& unscale) {
   int s_a = 0, s_b = 0, e_ab = 0;
   if (rn.c) {
     const int ea = renorm_exp(rn.a), eb = renorm_exp(rn.b);
@@ -128,7 +138,7 @@ __device__ __forceinline__ void renorm_begin(const Renorm& rn, const uint32_t* a
       s_a = 14 - ea;
       s_b = 14 - eb;
     }
-    if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x == 0)
+    if (first && threadIdx.x == 0)
       rn.c->slot[0].e = rn.a->slot[0].e + rn.b->slot[0].e + e_ab;
   } else if constexpr (PREC == P_FP16) {
     s_a = fp16_shift(amaxA);
@@ -233,7 +243,7 @@ __device__ __forceinline__ int64_t leaf_base(const ChainGroup& c, const LeafDesc
   return base;
 }
 
-// Clears c's amax before a renormalised GEMM raises it (cgemm.hip).
-hipError_t launch_renorm_reset(hipStream_t st, NodeScale* c);
+// Clears the results' amax before a renormalised GEMM raises them (cgemm.hip).
+hipError_t launch_renorm_reset(hipStream_t st, const Renorm& rn, int64_t batch);
 
 } // namespace qf

@@ -128,9 +128,10 @@ cgemm_f32(F32Args g) {
   const int64_t ml = g.M - m0, nl = g.N - n0;  // rows and columns that exist from the tile's first on
 
   float unscale = 1.f;
+  Renorm rn = renorm_of(g.rn, batch);
   if (!partial) {
     float s0, s1;
-    renorm_begin<P_FP32>(g.rn, nullptr, nullptr, s0, s1, unscale);
+    renorm_begin<P_FP32>(rn, nullptr, nullptr, m0 == 0 && n0 == 0, s0, s1, unscale);
   }
 
   F32Acc acc[TM][TN];
@@ -173,11 +174,10 @@ cgemm_f32(F32Args g) {
     __syncthreads();
   }
 
-  Renorm rn = g.rn;
   if (partial) rn.om_nh = 0;
-  const uint32_t seen = partial ? 0u : seen_amax(g.rn);
+  const uint32_t seen = partial ? 0u : seen_amax(rn);
   const float mx = f32_store<TM, TN, EDGE>(C, rn, m0 + wr, n0 + wc, g.M, g.N, unscale, acc);
-  if (g.rn.c && !partial) raise_amax<WM * WN>(g.rn.c, mx, seen, lds);
+  if (rn.c && !partial) raise_amax<WM * WN>(rn.c, mx, seen, lds);
 }
 
 template <int WM, int WN, int TM, int TN, int TA, int TB, bool CONJ>

@@ -232,7 +232,8 @@ cgemm_pingpong_presplit(int64_t M, int64_t N, int64_t K, const uint32_t* __restr
 
   // renormalisation is read only now, so that nothing else is in flight during the load ring
   float scale_a, scale_b, unscale;
-  renorm_begin<PREC>(rn, nullptr, nullptr, scale_a, scale_b, unscale);
+  rn = renorm_of(rn, batch);
+  renorm_begin<PREC>(rn, nullptr, nullptr, tm == 0 && tn == 0, scale_a, scale_b, unscale);
   float mx = 0.f;
   const int64_t col0 = tn * kPsBN + wc + 2 * (l16 >> 2);
 #pragma unroll
@@ -280,7 +281,7 @@ hipError_t launch_cgemm_presplit(hipStream_t st, int64_t M, int64_t N, int64_t K
   if (ldb == 0) ldb = K;
   if (lda < K || ldb < K || (lda & 3) || (ldb & 3) || lda > kPsMaxLd || ldb > kPsMaxLd) return hipErrorInvalidValue;
   if (rn.c && !rn.cleared) {
-    const hipError_t e = launch_renorm_reset(st, rn.c);
+    const hipError_t e = launch_renorm_reset(st, rn, batch);
     if (e != hipSuccess) return e;
   }
   const uint32_t* a = reinterpret_cast<const uint32_t*>(A);

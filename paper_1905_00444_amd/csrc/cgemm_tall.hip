@@ -55,8 +55,9 @@ cgemm_tall(int64_t M, const float2* __restrict__ A, const float2* __restrict__ B
   __shared__ __attribute__((aligned(16))) uint32_t bs[PLANES * N * LDW];
 
   float scale_a, scale_b, unscale;
-  renorm_begin<PREC>(rn, amaxA, amaxB, scale_a, scale_b, unscale);
   const int64_t batch = blockIdx.z;
+  rn = renorm_of(rn, batch);
+  renorm_begin<PREC>(rn, amaxA, amaxB, blockIdx.x == 0, scale_a, scale_b, unscale);
   A += ma.on ? map_base(ma, batch, sa) : batch * sa;
   B += mb.on ? map_base(mb, batch, sb) : batch * sb;
   C += batch * sc;

@@ -23,6 +23,8 @@ struct Renorm {
   const NodeScale* a = nullptr;
   const NodeScale* b = nullptr;
   NodeScale* c = nullptr;
+  // from one batch element's scale to the next one's: 0 where they share it, 1 where each keeps its own
+  int a_step = 0, b_step = 0, c_step = 0;
   // Output map of the epilogue: with om_nh > 0, C[m][n] goes to index
   // ((m >> om_q) << (om_nh + om_q) | (n >> om_nl) << om_q | (m mod 2^om_q)) << om_nl | (n mod 2^om_nl),
   // i.e. the top om_nh bits of n sit above the low om_q bits of m (om_nl = log2 N - om_nh);
@@ -166,16 +168,18 @@ constexpr int kMaxChainSteps = 256;
 struct StepMask { uint64_t w[kMaxChainSteps / 64]; };
 
 // Start of a chain group, in one launch: base_table[g * n_leaves + l] = offset of leaf l's fixed bits and
-// chain_b[g] = bitstring (-1 for an idle chain) if base_table is given; scales[n_leaves + i].amax = 0 for the
-// steps i in `run` if scales is given; and the gathers of the jobs whose step is in `run`.
+// chain_b[g] = bitstring (-1 for an idle chain) if base_table is given; the maxima of the steps i in `run`
+// cleared if scales is given (steps' scales behind the leaves', chain_scales of them per step: 1, or the chains
+// that the layout has room for); and the gathers of the jobs whose step is in `run`.
 hipError_t launch_chain_begin(hipStream_t st, const ChainGroup& grp, int n_leaves, const LeafDesc* leaves,
-                              int64_t* base_table, int32_t* chain_b, int n_steps, const StepMask& run, NodeScale* scales,
+                              int64_t* base_table, int32_t* chain_b, int n_steps, const StepMask& run, NodeScale* scales, int chain_scales,
                               const GatherJob* jobs, const GatherBlock* blocks, int n_blocks, const float2* wl, char* ws);
 // out[chain_b[g]][j] += root[g root_stride + sum_t bit_t(j) << pos[t]] for g = 0..G-1 in order (FP64), times 2^e
-// of root_scale, or of chain g's own exponent if chain_e is given.
+// of root_scale[g root_scale_step], or of chain g's own exponent if chain_e is given.
 hipError_t launch_slice_accumulate_batched(hipStream_t st, const float2* root, int64_t root_stride, int k, const int* pos,
                                            int G, const int32_t* chain_b, double2* out,
-                                           const NodeScale* root_scale = nullptr, const int32_t* chain_e = nullptr);
+                                           const NodeScale* root_scale = nullptr, int root_scale_step = 0,
+                                           const int32_t* chain_e = nullptr);
 
 // Whole chains of small tensors, a workgroup each (small_chain.hip).
 constexpr int kSmallMaxBits = 11;    // elements of any operand or result

@@ -443,6 +443,9 @@ static bool operand_invariant(const qf_plan* p, const Operand& op) {
 }
 static int operand_batch(const qf_plan* p, const Operand& op) { return operand_invariant(p, op) ? 1 : p->G; }
 
+// Scales per step: one, which the chains of a launch share, or (forms) one per chain, as if it ran alone.
+static int chain_scales(const qf_plan* p) { return p->form_of ? p->G_max : 1; }
+
 // Bond bits of the world-lines in the order in which their steps read them, cut bits on top: a chain's slice is then
 // a contiguous block in the order of the product's operand (where an open output bit does not come between).
 // In time order every slice was a bit-permuted gather.  Sets the fixed bits' places.
@@ -637,7 +640,7 @@ static void layout_arena(qf_plan* p, size_t n_ops) {
     if (st.A.permute) trans.push_back({align_up(GA * sizeof(float2) * operand_elems(st.A)), st.A.early ? 0 : i, i, &st.A.buf});
     if (st.B.permute) trans.push_back({align_up(GB * sizeof(float2) * operand_elems(st.B)), st.B.early ? 0 : i, i, &st.B.buf});
   }
-  if (p->renorm) pers.push_back({align_up((n + S) * sizeof(NodeScale)), 0, S, &p->off_scales});
+  if (p->renorm) pers.push_back({align_up((n + (size_t)S * chain_scales(p)) * sizeof(NodeScale)), 0, S, &p->off_scales});
   if (p->gscratch_bytes) pers.push_back({align_up(p->gscratch_bytes), 0, S, &p->off_gscratch});
   pers.push_back({align_up(n * sizeof(LeafDesc)), 0, S, &p->off_leafdesc});
   {
@@ -1105,7 +1108,7 @@ static qf_status build_plan(qf_ctx* ctx, qf_circuit* circ, const qf_plan_desc* d
   p->gates_host.resize(circ->ops.size() * 4);
   if (p->renorm) {
     // world-line entries are products of unitary gate entries and projectors: |x| <= 1
-    p->scale_init.assign(n + (int)p->steps.size(), NodeScale{});
+    p->scale_init.assign(n, NodeScale{});  // a step's are written when it runs
     for (int q = 0; q < n; ++q) p->scale_init[q].slot[0].amax = 0x3f800000u;  // 1.0f
   }
   p->desc_steps.assign(d->steps, d->steps + 2 * (size_t)d->n_steps);
@@ -1399,7 +1402,13 @@ static void leaf_args(const qf_plan* p, const Node& nd, const Operand& op, const
 }
 
 static NodeScale* node_scale(qf_plan* p, int node) {
-  return reinterpret_cast<NodeScale*>(p->ctx->base + p->off_scales) + node;
+  const int at = node < p->n ? node : p->n + (node - p->n) * chain_scales(p);
+  return reinterpret_cast<NodeScale*>(p->ctx->base + p->off_scales) + at;
+}
+
+// From one chain's scale of a node to the next one's: leaves and what is computed once for all chains have one.
+static int scale_step(const qf_plan* p, int node) {
+  return p->form_of && node >= p->n && !(p->ghoist && p->step_inv[node - p->n]);
 }
 
 // Conversion that an operand's permute applies for a pre-split GEMM: bfloat16 hi and lo planes
@@ -1473,6 +1482,9 @@ static Renorm step_renorm(qf_plan* p, size_t i, bool mapped_a = false) {
   r.a = node_scale(p, st.A.node);
   r.b = node_scale(p, st.B.node);
   r.c = node_scale(p, p->n + (int)i);
+  r.a_step = scale_step(p, st.A.node);
+  r.b_step = scale_step(p, st.B.node);
+  r.c_step = scale_step(p, p->n + (int)i);
   return r;
 }
 
@@ -1483,7 +1495,7 @@ static qf_status begin_chain(qf_plan* p, const ChainGroup& grp, const StepMask& 
   QF_HIP(c, launch_chain_begin(c->stream, grp, p->n, reinterpret_cast<const LeafDesc*>(c->base + p->off_leafdesc),
                                tables ? reinterpret_cast<int64_t*>(c->base + p->off_btable) : nullptr,
                                tables ? reinterpret_cast<int32_t*>(c->base + p->off_chainb) : nullptr,
-                               (int)p->steps.size(), run, p->renorm && p->chain_begin ? node_scale(p, 0) : nullptr,
+                               (int)p->steps.size(), run, p->renorm && p->chain_begin ? node_scale(p, 0) : nullptr, chain_scales(p),
                                reinterpret_cast<const GatherJob*>(c->base + p->off_jobs),
                                reinterpret_cast<const GatherBlock*>(c->base + p->off_blocks), (int)p->job_blocks.size(),
                                wl_of(p), c->base));
@@ -1531,7 +1543,7 @@ static qf_status small_call(qf_plan* p, int n_batch, const uint8_t* bits_dev, in
     if (cot_dev) continue;
     QF_HIP(c, launch_slice_accumulate_batched(c->stream, a.scratch + p->small_steps.back().c, a.chain_elems, k,
                                               p->root_pos.data(), a.grp.G, a.chain_b, reinterpret_cast<double2*>(out_dev),
-                                              nullptr, p->renorm ? a.chain_e : nullptr));
+                                              nullptr, 0, p->renorm ? a.chain_e : nullptr));
   }
   return QF_OK;
 }
@@ -1788,7 +1800,8 @@ static qf_status enqueue_group(qf_plan* p, const uint8_t* bits_dev, int64_t s_be
     }
   }
   QF_HIP(c, launch_slice_accumulate_batched(c->stream, wsp(c, p->nodes.back().offset), (int64_t)1 << k, k, p->root_pos.data(), G,
-                                            chain_b, reinterpret_cast<double2*>(out_dev), root_scale(p)));
+                                            chain_b, reinterpret_cast<double2*>(out_dev), root_scale(p),
+                                            scale_step(p, (int)p->nodes.size() - 1)));
   return QF_OK;
 }
 

@@ -343,20 +343,20 @@ hipError_t launch_zero(hipStream_t st, void* p, size_t bytes) {
 // slices sit in L2), so a launch each was all overhead: a chain of the 6x6 circuit made 75 of them.
 __global__ void __launch_bounds__(256)
 chain_begin_kernel(ChainGroup grp, int n_leaves, const LeafDesc* __restrict__ leaves, int64_t* __restrict__ base_table,
-                   int32_t* __restrict__ chain_b, int n_steps, StepMask run, NodeScale* __restrict__ scales,
+                   int32_t* __restrict__ chain_b, int n_steps, StepMask run, NodeScale* __restrict__ scales, int chain_scales,
                    const GatherJob* __restrict__ jobs, const GatherBlock* __restrict__ blocks, int setup_blocks,
                    const float2* __restrict__ wl, char* __restrict__ ws) {
   const int tid = threadIdx.x, g = blockIdx.y;
   int64_t b, s;
   if ((int)blockIdx.x <= setup_blocks) {
-    if (g) return;
     if (blockIdx.x == 0) {
-      for (int t = tid; scales && t < n_steps * kScaleSlots; t += 256) {
+      for (int t = tid; scales && g < chain_scales && t < n_steps * kScaleSlots; t += 256) {
         const int i = t / kScaleSlots;
-        if ((run.w[i >> 6] >> (i & 63)) & 1) scales[n_leaves + i].slot[t % kScaleSlots].amax = 0u;
+        if ((run.w[i >> 6] >> (i & 63)) & 1) scales[n_leaves + i * chain_scales + g].slot[t % kScaleSlots].amax = 0u;
       }
       return;
     }
+    if (g) return;
     const int t = ((int)blockIdx.x - 1) * 256 + tid;
     if (t >= grp.G * n_leaves) return;
     const int gg = t / n_leaves, l = t - gg * n_leaves;
@@ -397,11 +397,12 @@ chain_begin_kernel(ChainGroup grp, int n_leaves, const LeafDesc* __restrict__ le
 }
 
 hipError_t launch_chain_begin(hipStream_t st, const ChainGroup& grp, int n_leaves, const LeafDesc* leaves,
-                              int64_t* base_table, int32_t* chain_b, int n_steps, const StepMask& run, NodeScale* scales,
+                              int64_t* base_table, int32_t* chain_b, int n_steps, const StepMask& run, NodeScale* scales, int chain_scales,
                               const GatherJob* jobs, const GatherBlock* blocks, int n_blocks, const float2* wl, char* ws) {
   const int setup = base_table ? (grp.G * n_leaves + 255) / 256 : 0;
-  hipLaunchKernelGGL(chain_begin_kernel, dim3((unsigned)(1 + setup + n_blocks), n_blocks ? (unsigned)grp.G : 1u), dim3(256),
-                     0, st, grp, n_leaves, leaves, base_table, chain_b, n_steps, run, scales, jobs, blocks, setup, wl, ws);
+  hipLaunchKernelGGL(chain_begin_kernel, dim3((unsigned)(1 + setup + n_blocks), n_blocks || chain_scales > 1 ? (unsigned)grp.G : 1u),
+                     dim3(256), 0, st, grp, n_leaves, leaves, base_table, chain_b, n_steps, run, scales, chain_scales, jobs,
+                     blocks, setup, wl, ws);
   return hipGetLastError();
 }
 
@@ -410,14 +411,13 @@ hipError_t launch_chain_begin(hipStream_t st, const ChainGroup& grp, int n_leave
 __global__ void __launch_bounds__(256)
 slice_accumulate_batched_kernel(const float2* __restrict__ root, int64_t root_stride, AccArgs a, int G,
                                 const int32_t* __restrict__ chain_b, const int32_t* __restrict__ chain_e,
-                                double2* __restrict__ out, const NodeScale* __restrict__ root_scale) {
+                                double2* __restrict__ out, const NodeScale* __restrict__ root_scale, int root_scale_step) {
   const int g0 = blockIdx.y;
   const int32_t b = chain_b[g0];
   if (b < 0 || (g0 > 0 && chain_b[g0 - 1] == b)) return;
   int g1 = g0 + 1;
   while (g1 < G && chain_b[g1] == b) ++g1;
   const int64_t n = (int64_t)1 << a.k;
-  const double f = root_scale ? ldexp(1.0, root_scale->slot[0].e) : 1.0;
   for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < n; j += (int64_t)gridDim.x * blockDim.x) {
     int64_t src = 0;
     for (int t = 0; t < a.k; ++t) src |= ((j >> t) & 1) << a.pos[t];
@@ -425,7 +425,9 @@ slice_accumulate_batched_kernel(const float2* __restrict__ root, int64_t root_st
 #pragma unroll 8
     for (int g = g0; g < g1; ++g) {
       const float2 v = root[(int64_t)g * root_stride + src];
-      const double fg = chain_e ? ldexp(1.0, chain_e[g]) : f;
+      const double fg = chain_e      ? ldexp(1.0, chain_e[g])
+                        : root_scale ? ldexp(1.0, root_scale[(int64_t)g * root_scale_step].slot[0].e)
+                                     : 1.0;
       o.x += (double)v.x * fg;
       o.y += (double)v.y * fg;
     }
@@ -435,7 +437,7 @@ slice_accumulate_batched_kernel(const float2* __restrict__ root, int64_t root_st
 
 hipError_t launch_slice_accumulate_batched(hipStream_t st, const float2* root, int64_t root_stride, int k, const int* pos,
                                            int G, const int32_t* chain_b, double2* out, const NodeScale* root_scale,
-                                           const int32_t* chain_e) {
+                                           int root_scale_step, const int32_t* chain_e) {
   AccArgs a;
   a.k = k;
   for (int t = 0; t < 32; ++t) a.pos[t] = t < k ? pos[t] : 0;
@@ -443,7 +445,7 @@ hipError_t launch_slice_accumulate_batched(hipStream_t st, const float2* root, i
   unsigned blocks = (unsigned)((n + 255) / 256);
   if (blocks > 1024) blocks = 1024;
   hipLaunchKernelGGL(slice_accumulate_batched_kernel, dim3(blocks, (unsigned)G), dim3(256), 0, st, root, root_stride, a, G,
-                     chain_b, chain_e, out, root_scale);
+                     chain_b, chain_e, out, root_scale, root_scale_step);
   return hipGetLastError();
 }
 

@@ -299,3 +299,40 @@ def test_70_qubit_random_circuit_batched_vs_oracle_one_chain(gctx):
     gctx.synchronize()
     ref = tn.amplitudes(c.to_text(), bits, plan, slices=[5])
     assert rel_err(got.cpu().numpy(), ref) <= 1e-5
+
+
+@pytest.mark.parametrize("precision", ["fp32", "bf16x3"])
+@pytest.mark.parametrize("cuts", [False, True])
+def test_chains_of_one_call_keep_scales_of_their_own(precision, cuts):
+    """Four qubits whose bit 1 is weighed by 1e-12: bitstrings with these bits set have amplitudes below FP32's range
+    beside those without, in the same call.  The same bits as one call per bitstring, and weighed by
+    1e-48 against the plain circuit (20 qubits, the plan tests' bounds)."""
+    import torch
+    from paper_1905_00444_amd import Context, Circuit, Plan
+    _say(f"scales of chains {precision} cuts {cuts}")
+    c, plan = _setup_4x5()
+    if not cuts:
+        c = generate(4, 5, 24, 2)
+        plan, _ = region_plan(c, 2, 2, [], [(3, 4), (2, 4)])
+    heavy = [q for q in (0, 6, 11, 17) if q not in plan["open"]]
+    assert len(heavy) == 4
+    bits = random_bitstrings(6, 20, 8)
+    bits[:3, heavy] = 0
+    bits[3:, heavy] = 1
+    ctx = Context(0)
+    circ = Circuit(ctx, c.to_text())
+    p = Plan(ctx, circ, plan, precision)
+    plain = p.amplitudes(bits)
+    values = circ.values.copy()
+    for q in heavy:
+        last = max(i for i, op in enumerate(circ.ops) if op[2] == (q,))
+        values[last, 2:] *= np.complex64(1e-12)
+    circ.set_values(values)
+    one = [p.amplitudes(bits[i:i + 1]) for i in range(6)]
+    all_ = p.amplitudes(bits)
+    torch.cuda.synchronize()
+    plain, one, all_ = plain.cpu().numpy(), torch.cat(one).cpu().numpy(), all_.cpu().numpy()
+    bound = 1e-5 if precision == "fp32" else 1e-4
+    assert rel_err(one[:3], plain[:3]) <= bound
+    assert rel_err(one[3:] * 1e48, plain[3:]) <= bound
+    assert np.array_equal(all_, one)
