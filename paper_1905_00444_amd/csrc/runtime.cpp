@@ -1756,7 +1756,7 @@ static qf_status enqueue_group(qf_plan* p, const uint8_t* bits_dev, int64_t s_be
   qf_ctx* c = p->ctx;
   const int n = p->n, G = p->G, k = (int)p->open.size();
   int32_t* chain_b = reinterpret_cast<int32_t*>(c->base + p->off_chainb);
-  const int64_t gpb = p->ghoist ? (s_range + G - 1) / G : 0;  // launch groups per bitstring
+  const int64_t gpb = p->ghoist && !p->form_of ? (s_range + G - 1) / G : 0;  // launch groups per bitstring
   const ChainGroup grp = {chain0, G, n, bits_dev, s_begin, s_range, n_chains, gpb};
   qf_status e0s = begin_chain(p, grp, kAllSteps, true);
   if (e0s != QF_OK) return e0s;
@@ -1805,6 +1805,20 @@ static qf_status enqueue_group(qf_plan* p, const uint8_t* bits_dev, int64_t s_be
   return QF_OK;
 }
 
+// The groups of a call on form p: consecutive chains (of one bitstring, where they share what no cut reaches), and
+// no more in the last group than are left: three 6x6 amplitudes took as long as four.
+template <class Group>
+static qf_status form_groups(qf_plan* p, int n_batch, int64_t s_range, Group&& group) {
+  const int64_t n_chains = n_batch * s_range, run = p->ghoist ? s_range : n_chains;
+  for (int64_t first = 0; first < n_chains; first += run)
+    for (int64_t at = 0; at < run; at += p->G_max) {
+      p->G = (int)std::min<int64_t>(p->G_max, run - at);
+      const qf_status e = group(first + at);
+      if (e != QF_OK) return e;
+    }
+  return QF_OK;
+}
+
 // All groups of one call, the same launch sequence with another first chain each.
 static qf_status enqueue_call(qf_plan* p, int n_batch, const uint8_t* bits_dev, int64_t s_begin, int64_t s_end,
                               double* out_dev, bool timed_ok) {
@@ -1812,6 +1826,10 @@ static qf_status enqueue_call(qf_plan* p, int n_batch, const uint8_t* bits_dev, 
   const int64_t s_range = s_end - s_begin;
   const int64_t n_chains = (int64_t)n_batch * s_range;
   if (call_runs_small(p, n_batch, s_range)) return small_call(p, n_batch, bits_dev, s_begin, s_end, out_dev, nullptr);
+  if (p->form_of)
+    return form_groups(p, n_batch, s_range, [&](int64_t chain0) {
+      return enqueue_group(p, bits_dev, s_begin, s_range, chain0, n_chains, out_dev, timed_ok);
+    });
   // group hoisting: each bitstring's slices in groups of G (the last one of a bitstring may be
   // partly idle); otherwise consecutive chains, bitstring-major, G per group
   const int64_t groups = p->ghoist ? n_batch * ((s_range + p->G - 1) / p->G) : (n_chains + p->G - 1) / p->G;
@@ -1878,8 +1896,7 @@ extern "C" qf_status qf_plan_graph_info(const qf_plan* p, int64_t* launches, int
   return QF_OK;
 }
 
-// The batch form of plan p if this call runs on it, with its chains per launch set for the call: calls of
-// several chains for which the workspace is there.  Not while a stream capture would record the build.
+// The batch form of plan p if this call runs on it: calls of several chains for which the workspace is there.  Not while a stream capture would record the build.
 static qf_plan* multi_for_call(qf_plan* p, int n_batch, int64_t slices) {
   qf_ctx* c = p->ctx;
   if (p->G != 1 || p->form_of) return nullptr;
@@ -1890,9 +1907,6 @@ static qf_plan* multi_for_call(qf_plan* p, int n_batch, int64_t slices) {
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (c->stream && hipStreamIsCapturing(c->stream, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone) return nullptr;
   }
-  const int64_t chains = q->ghoist ? slices : n_batch * slices;  // a group's chains share a bitstring if hoisted
-  q->G = 1;
-  while (q->G < q->G_max && q->G < chains) q->G *= 2;
   return q;
 }
 
@@ -2214,8 +2228,13 @@ extern "C" qf_status qf_backward(qf_plan* p, int n_batch, const uint8_t* bits_de
   if (batched || small) {
     const int64_t s_range = s_end - s_begin;
     const int64_t n_chains = small ? 0 : (int64_t)n_batch * s_range;  // left to run
-    for (int64_t g = 0; g < (n_chains + p->G - 1) / p->G; ++g) {
-      e = backward_group(p, bits_dev, cot_dev, s_begin, s_range, g * p->G, n_chains);
+    auto group = [&](int64_t chain0) { return backward_group(p, bits_dev, cot_dev, s_begin, s_range, chain0, n_chains); };
+    if (p->form_of && !small) {
+      e = form_groups(p, n_batch, s_range, group);
+      if (e != QF_OK) return e;
+    }
+    for (int64_t g = 0; !p->form_of && g < (n_chains + p->G - 1) / p->G; ++g) {
+      e = group(g * p->G);
       if (e != QF_OK) return e;
     }
     QF_HIP(c, launch_worldline_grad(c->stream, reinterpret_cast<const WlQubit*>(c->ws + p->off_wlq), n, p->max_nbond,

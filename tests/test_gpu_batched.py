@@ -336,3 +336,28 @@ def test_chains_of_one_call_keep_scales_of_their_own(precision, cuts):
     assert rel_err(one[:3], plain[:3]) <= bound
     assert rel_err(one[3:] * 1e48, plain[3:]) <= bound
     assert np.array_equal(all_, one)
+
+
+@pytest.mark.parametrize("n,rng", [(3, (0, 1)), (67, (0, 1)), (2, (0, 11)), (1, (2, 7))])
+def test_calls_run_the_chains_they_have(n, rng):
+    """The flops of the largest products that a call of several chains launches: those of its chains, as one at a
+    time (three chains, or 67 in launches of 64, ran as four and as 128)."""
+    import torch
+    from paper_1905_00444_amd import Context, Circuit, Plan, profile_enable, profile_read
+    _say(f"chains run by a call n {n} slices {rng}")
+    c, plan = _setup_4x5()
+    if rng[1] - rng[0] == 1:
+        c = generate(4, 5, 24, 2)
+        plan, _ = region_plan(c, 2, 2, [], [(3, 4), (2, 4)])
+    bits = random_bitstrings(n, 20, 8)
+    ctx = Context(0)
+    p = Plan(ctx, Circuit(ctx, c.to_text()), plan, "fp32")
+    largest = [s for s in p.steps() if s["flops"] == max(x["flops"] for x in p.steps())]
+    profile_enable(ctx)
+    p.amplitudes(bits, *rng)
+    torch.cuda.synchronize()
+    _, _, flops = profile_read(ctx)
+    profile_enable(ctx, False)
+    chains = n * (rng[1] - rng[0])
+    assert flops <= chains * sum(s["flops"] for s in largest)
+    assert flops >= sum(s["flops"] for s in largest)
