@@ -82,9 +82,9 @@ __device__ __forceinline__ void scales_for(const Renorm& rn, const uint32_t* ama
 }
 
 // Sum of the chunks in ascending order: a workgroup takes 32 consecutive outputs, its 8 groups of 32 lanes read
-// whole 256-byte runs of 8 chunks at a time (one chunk's row per group) into LDS, and the first group adds
-// them.  Bound by reading the chunks once.
-constexpr int kReduceOut = 32, kReduceSlots = 8;
+// whole 256-byte runs of 32 chunks at a time (four chunks' rows per group) into LDS, and the first group adds
+// them.  Bound by reading the chunks once, or by latency where they are few (32 x 32 outputs of 64 chunks).
+constexpr int kReduceOut = 32, kReduceGroups = 8, kReduceSlots = 32;
 
 // A grid's z (the batch elements of P_z, C) where the elements keep scales of their own, else one z for all.
 __global__ void __launch_bounds__(256)
@@ -107,11 +107,20 @@ cgemm_split_reduce(const float2* __restrict__ P, int split, int64_t batch, int64
     const int64_t i = i0 + lane;
     float2 sum = make_float2(0.f, 0.f);
     for (int y0 = 0; y0 < split; y0 += kReduceSlots) {
-      part[t][lane] = i < total && y0 + t < split ? P[(int64_t)(y0 + t) * chunk + i] : make_float2(0.f, 0.f);
-      __syncthreads();
-      if (t == 0)
+      float2 v[kReduceSlots / kReduceGroups];
 #pragma unroll
-        for (int k = 0; k < kReduceSlots; ++k) sum = make_float2(sum.x + part[k][lane].x, sum.y + part[k][lane].y);
+      for (int u = 0; u < kReduceSlots / kReduceGroups; ++u) {
+        const int y = y0 + t + u * kReduceGroups;
+        v[u] = i < total && y < split ? P[(int64_t)y * chunk + i] : make_float2(0.f, 0.f);
+      }
+#pragma unroll
+      for (int u = 0; u < kReduceSlots / kReduceGroups; ++u) part[t + u * kReduceGroups][lane] = v[u];
+      __syncthreads();
+      if (t == 0) {
+        const int n = split - y0 < kReduceSlots ? split - y0 : kReduceSlots;
+#pragma unroll 8
+        for (int k = 0; k < n; ++k) sum = make_float2(sum.x + part[k][lane].x, sum.y + part[k][lane].y);
+      }
       __syncthreads();
     }
     if (t == 0 && i < total) {
@@ -757,14 +766,25 @@ int cgemm_default_variant(int precision, int64_t M, int64_t N, int64_t K, int64_
     return GEMM_LARGE;
   // a few dot products: a workgroup each; very long ones are spread further by the tiles' split K
   if (M * N <= 64 && K >= 32 && K <= (1 << 17)) return GEMM_SPLITK;
-  // up to 4096 of them where the sizes are no powers of two, a single product by its caller: 2 x 1078 x 3529
-  // 12 us against 33 on the tiles, 64 x 64 x 1000 7 / 33, 4 x 1000 x 40 5 / 5.  A contraction's steps are powers
-  // of two and run with many chains per launch, which the tiles suit better.
-  if (M * N > 64 && M * N <= 4096 && K >= 64 && !(pow2(M) && pow2(N) && pow2(K))) return GEMM_SPLITK;
+  // up to 256 thin ones, where a launch of many chains loses little by it: 16 x 16 x 256 4 us against 10 on tiles (32 of
+  // them 8 / 11), x 1024 4 / 21 (14 / 22), x 4096 4 / 21 (38 / 22); 256 x 16 x 256 5 / 9 (88 / 9)
+  if (M * N <= 256 && (M < 32 || N < 32) && K >= 256 && K <= 4096) return GEMM_SPLITK;
   // short K or N: the FP32 tiles would multiply zeros
   if ((K < 16 || (K < 32 && N < 32)) && cgemm_variant_fits(precision, M, N, K, GEMM_SKINNY)) return GEMM_SKINNY;
   if (K < 8 || M * N * K < 4096) return GEMM_SIMT;
   return GEMM_F32;
+}
+
+// A product of its own (qf_cgemm): dot products by a workgroup each while they are few and read less than the tiles
+// take: 64 x 64 x 1024 7 us against 9 with K cut finely, x 2048 13 / 10; of thin ones, whose tiles multiply zeros,
+// 2 x 1078 x 3529 12 / 33, 16 x 16 x 65536 19 / 29, 16 x 64 x 65536 82 / 26, 2048 x 2 x 8192 37 / 50.
+static int direct_variant(int precision, int64_t M, int64_t N, int64_t K, int64_t batch) {
+  const int v = cgemm_default_variant(precision, M, N, K);
+  if (precision == P_FP16 && pow2(M) && pow2(N) && pow2(K)) return v;
+  const int64_t outputs = batch * M * N, thin = std::min(M, N);
+  const int64_t most = (int64_t)1 << (thin <= 2 ? 25 : thin < 32 ? 24 : 22);
+  if (M * N <= 4096 && outputs <= 16384 && K >= 64 && outputs * K <= most) return GEMM_SPLITK;
+  return v == GEMM_SPLITK && M * N > 64 ? GEMM_F32 : v;
 }
 
 template <int PREC>
@@ -794,19 +814,26 @@ static hipError_t launch_mfma(hipStream_t st, int variant, int64_t M, int64_t N,
 // write and a read of its partial tile and the reduction a launch, which K < 1024 does not repay: the
 // 256 x 256 x 256 products of the 4 x 4 and 4 x 5 circuits took 332 us of split kernel and reduction per
 // 64 chains, 100 us in one pass over K on smaller tiles.
-static int split_count(int precision, int variant, int64_t M, int64_t N, int64_t K) {
+// The few tiles of one product are cut finer: one 64 x 64 x 1024 18 us in chunks of 512, 12 of 256 (64 of them 33
+// and 32).  batch > 0: a product of its own, with chunks down to 128 while the launch leaves CUs idle (9 us).
+static int split_count(int precision, int variant, int64_t M, int64_t N, int64_t K, int64_t batch = 0) {
   if (precision == P_FP16 && variant != GEMM_F32) return fp16_split(variant, M, N, K);
   if (variant == GEMM_SKINNY || variant == GEMM_SPLITK || variant == GEMM_SIMT || variant == GEMM_TALL) return 1;
   const int64_t tiles = ((M + 63) / 64) * ((N + 31) / 32);
   if (tiles >= 256) return 1;
+  const int64_t chunk = tiles <= 4 && K >= 1024 && K <= 2048 ? 256 : 512;
   int split = 1;
-  while (tiles * split * 2 <= 512 && K / (split * 2) >= 512) split *= 2;
+  while (tiles * split * 2 <= 512 && K / (split * 2) >= chunk) split *= 2;
+  while (batch > 0 && K >= (tiles * batch <= 32 ? 512 : 1024) && tiles * batch * split * 2 <= 512 && split < 64 &&
+         K / (split * 2) >= 128)
+    split *= 2;
   return split;
 }
 
-size_t cgemm_split_scratch(int precision, int64_t M, int64_t N, int64_t K, int64_t batch, int variant) {
-  if (variant == GEMM_AUTO) variant = cgemm_default_variant(precision, M, N, K);
-  const int split = split_count(precision, variant, M, N, K);
+size_t cgemm_split_scratch(int precision, int64_t M, int64_t N, int64_t K, int64_t batch, int variant, bool direct) {
+  if (variant == GEMM_AUTO)
+    variant = direct ? direct_variant(precision, M, N, K, batch) : cgemm_default_variant(precision, M, N, K);
+  const int split = split_count(precision, variant, M, N, K, direct ? batch : 0);
   return split > 1 ? (size_t)split * (size_t)(batch * M * N) * sizeof(float2) : 0;
 }
 
@@ -833,14 +860,21 @@ hipError_t launch_env_gemm(hipStream_t st, int side, int64_t M, int64_t N, int64
 hipError_t launch_cgemm_ex(hipStream_t st, int precision, int64_t M, int64_t N, int64_t K, const float2* A,
                            const float2* B, float2* C, int64_t batch, int64_t sa, int64_t sb, int64_t sc,
                            const uint32_t* amaxA, const uint32_t* amaxB, const Renorm& rn, int variant,
-                           float2* scratch, size_t scratch_bytes, const OpMap* ma, const OpMap* mb) {
+                           float2* scratch, size_t scratch_bytes, const OpMap* ma, const OpMap* mb, bool direct) {
   if (rn.c && (!rn.a || !rn.b)) return hipErrorInvalidValue;
   if (M < 1 || N < 1 || K < 1 || batch < 1) return hipErrorInvalidValue;
   if (precision != P_FP32 && precision != P_BF16X3 && precision != P_FP16) return hipErrorInvalidValue;
   if ((ma || mb) && (variant != GEMM_AUTO || !cgemm_reads_maps(precision, M, N, K, batch))) return hipErrorInvalidValue;
   const OpMap a = ma ? *ma : OpMap{}, b = mb ? *mb : OpMap{};
   const bool chosen = variant != GEMM_AUTO && cgemm_variant_fits(precision, M, N, K, variant);
-  int v = chosen ? variant : cgemm_default_variant(precision, M, N, K);
+  int v = chosen ? variant : direct ? direct_variant(precision, M, N, K, batch) : cgemm_default_variant(precision, M, N, K);
+  // split only when the caller's scratch holds every partial, otherwise one pass over K; where that leaves a few
+  // outputs to a few workgroups (16 x 16 x 65536: 2 ms), a product of its own takes a workgroup per output (69 us)
+  int split = scratch ? split_count(precision, v, M, N, K, direct ? batch : 0) : 1;
+  if (split > 1 && (size_t)split * (size_t)(batch * M * N) * sizeof(float2) > scratch_bytes) split = 1;
+  if (direct && !chosen && split == 1 && split_count(precision, v, M, N, K, batch) > 1 && M * N <= 4096 &&
+      batch * M * N <= 16384 && !(precision == P_FP16 && pow2(M) && pow2(N) && pow2(K)))
+    v = GEMM_SPLITK;
   if (rn.c && !rn.cleared) {
     const hipError_t e = launch_renorm_reset(st, rn, batch);
     if (e != hipSuccess) return e;
@@ -856,11 +890,12 @@ hipError_t launch_cgemm_ex(hipStream_t st, int precision, int64_t M, int64_t N, 
       return hipGetLastError();
     }
     case GEMM_SPLITK:
-      // a wave for the shortest sums, 16 waves from K = 4096 on (one output, K = 65536: 127 us with four)
+      // a wave for the shortest sums, 16 waves from K = 16384 on (one output, K = 65536: 127 us with four), which many
+      // outputs of K = 4096 would share out too finely (2048 of them 14 us with four waves each, 18 with 16)
       if (K < 256)
         hipLaunchKernelGGL(cgemm_splitk<64>, dim3((unsigned)(M * N), 1, (unsigned)batch), dim3(64), 0, st, M, N, K, A, B,
                            C, sa, sb, sc, rn);
-      else if (K < 4096 || precision == P_FP16)
+      else if (K < 16384 || precision == P_FP16 || (direct && batch * M * N > 512))
         hipLaunchKernelGGL(cgemm_splitk<256>, dim3((unsigned)(M * N), 1, (unsigned)batch), dim3(256), 0, st, M, N, K, A,
                            B, C, sa, sb, sc, rn);
       else
@@ -874,9 +909,6 @@ hipError_t launch_cgemm_ex(hipStream_t st, int precision, int64_t M, int64_t N, 
       return hipGetLastError();
     }
   }
-  // split only when the caller's scratch holds every partial (otherwise one pass over K)
-  int split = scratch ? split_count(precision, v, M, N, K) : 1;
-  if (split > 1 && (size_t)split * (size_t)(batch * M * N) * sizeof(float2) > scratch_bytes) split = 1;
   hipError_t e;
   if (precision == P_FP32 || v == GEMM_F32) {
     static const int tiles[] = {F32_AUTO, F32_64X64, F32_64X32, F32_32X32, F32_64X64};

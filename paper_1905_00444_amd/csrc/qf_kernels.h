@@ -266,12 +266,13 @@ constexpr int kMapKBits = 12, kMapRowBits = 24;
 
 // Same, with optional operand max magnitudes for FP16 scaling (ignored when rn is on: then the
 // FP16 operands are scaled from rn.a / rn.b), optional renormalisation, and a kernel variant
-// (one that does not fit the shape falls back to GEMM_AUTO).
+// (one that does not fit the shape falls back to GEMM_AUTO).  direct: a call of its own rather than a plan's step;
+// the kernel and the cut of K then follow the batch and the scratch too.
 hipError_t launch_cgemm_ex(hipStream_t st, int precision, int64_t M, int64_t N, int64_t K, const float2* A,
                            const float2* B, float2* C, int64_t batch, int64_t sa, int64_t sb, int64_t sc,
                            const uint32_t* amaxA, const uint32_t* amaxB, const Renorm& rn = Renorm{},
                            int variant = GEMM_AUTO, float2* scratch = nullptr, size_t scratch_bytes = 0,
-                           const OpMap* ma = nullptr, const OpMap* mb = nullptr);
+                           const OpMap* ma = nullptr, const OpMap* mb = nullptr, bool direct = false);
 // Whether that call (GEMM_AUTO) reads operands through maps.
 bool cgemm_reads_maps(int precision, int64_t M, int64_t N, int64_t K, int64_t batch);
 // ... and takes A's rows in any order (by shape alone).
@@ -300,7 +301,8 @@ hipError_t launch_cgemm_tall(hipStream_t st, int precision, int64_t M, int64_t N
                              const OpMap& ma = OpMap{}, const OpMap& mb = OpMap{});
 // Bytes of scratch that lets an MFMA launch of this shape split K over more workgroups (0: the
 // launch fills the GPU without splitting, or its variant cannot split).
-size_t cgemm_split_scratch(int precision, int64_t M, int64_t N, int64_t K, int64_t batch, int variant = GEMM_AUTO);
+size_t cgemm_split_scratch(int precision, int64_t M, int64_t N, int64_t K, int64_t batch, int variant = GEMM_AUTO,
+                           bool direct = false);
 
 // p[i] = pseudo-random complex values, re and im uniform in [-1, 1) (hash of seed and i).
 hipError_t launch_fill_random(hipStream_t st, float2* p, int64_t n, uint32_t seed);

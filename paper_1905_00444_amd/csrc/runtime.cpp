@@ -2356,7 +2356,7 @@ qf_status qf_cgemm_variant(qf_ctx* c, int precision, int variant, int64_t M, int
   // the context workspace beyond its slots holds split-K partials when it is large enough.  A plan's tables and
   // world-lines begin there: the partials take their place, and the plan's next call builds them again
   float2* scratch = nullptr;
-  size_t scratch_bytes = cgemm_split_scratch(precision, M, N, K, batch, variant);
+  size_t scratch_bytes = cgemm_split_scratch(precision, M, N, K, batch, variant, true);
   if (scratch_bytes > 0 && c->ws && c->ws_bytes > kCtxScratch && c->ws_bytes - kCtxScratch >= scratch_bytes) {
     scratch = reinterpret_cast<float2*>(c->ws + kCtxScratch);
     forget_built(c);
@@ -2365,7 +2365,7 @@ qf_status qf_cgemm_variant(qf_ctx* c, int precision, int variant, int64_t M, int
   }
   QF_HIP(c, launch_cgemm_ex(c->stream, precision, M, N, K, reinterpret_cast<const float2*>(A),
                             reinterpret_cast<const float2*>(B), reinterpret_cast<float2*>(C), batch, sa, sb, sc, amA, amB,
-                            Renorm{}, variant, scratch, scratch_bytes));
+                            Renorm{}, variant, scratch, scratch_bytes, nullptr, nullptr, true));
   return QF_OK;
 }
 
@@ -2449,10 +2449,12 @@ qf_status qf_time_cgemm(qf_ctx* c, int precision, int64_t M, int64_t N, int64_t 
   hipEvent_t e0, e1;
   QF_HIP(c, hipEventCreate(&e0));
   QF_HIP(c, hipEventCreate(&e1));
-  QF_HIP(c, launch_cgemm_ex(c->stream, precision, M, N, K, (const float2*)A, (const float2*)B, (float2*)C, 1, 0, 0, 0, amA, amB));
+  QF_HIP(c, launch_cgemm_ex(c->stream, precision, M, N, K, (const float2*)A, (const float2*)B, (float2*)C, 1, 0, 0, 0, amA, amB,
+                               Renorm{}, GEMM_AUTO, nullptr, 0, nullptr, nullptr, true));
   QF_HIP(c, hipEventRecord(e0, c->stream));
   for (int i = 0; i < reps; ++i)
-    QF_HIP(c, launch_cgemm_ex(c->stream, precision, M, N, K, (const float2*)A, (const float2*)B, (float2*)C, 1, 0, 0, 0, amA, amB));
+    QF_HIP(c, launch_cgemm_ex(c->stream, precision, M, N, K, (const float2*)A, (const float2*)B, (float2*)C, 1, 0, 0, 0, amA, amB,
+                               Renorm{}, GEMM_AUTO, nullptr, 0, nullptr, nullptr, true));
   QF_HIP(c, hipEventRecord(e1, c->stream));
   QF_HIP(c, hipEventSynchronize(e1));
   float t = 0.f;

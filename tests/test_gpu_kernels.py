@@ -519,3 +519,45 @@ def test_ceiling_copy_and_mfma_loops(ctx):
         assert 0 < fl / ms / 1e9 < 1.05 * peak, prec
     with pytest.raises(Exception):
         time_ceiling(ctx, "copy", size=3 << 10, buf=buf)
+
+
+# Dot products by a workgroup each, or tiles with K cut: the sizes, batches and scratch at which the choice turns
+DOT_SHAPES = [(16, 16, 65536, 1), (16, 16, 16384, 9), (32, 32, 4096, 1), (32, 32, 4097, 2), (64, 64, 1024, 1),
+              (64, 64, 1025, 4), (4096, 1, 64, 1), (64, 16, 1024, 33), (16, 16, 4096, 5), (8, 32, 255, 3), (1, 4096, 4100, 1)]
+
+
+@pytest.mark.parametrize("room", [False, True])
+@pytest.mark.parametrize("M,N,K,batch", DOT_SHAPES)
+def test_cgemm_few_outputs(split_ctx, room, M, N, K, batch):
+    """With and without room for partial tiles, each held to the FP32 bound."""
+    import ctypes as Cc
+    import torch
+    from paper_1905_00444_amd import Context, _lib
+    _say(f"cgemm few outputs {M}x{N}x{K} batch {batch} room {room}")
+    c = split_ctx if room else Context(0)
+    rng = np.random.default_rng(M + N + K)
+    A, B = _rand_c64(rng, (batch, M, K)), _rand_c64(rng, (batch, N, K))
+    dA, dB = torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda()
+    dC = torch.full((batch * M * N + 8,), 7.0 + 0j, dtype=torch.complex64, device="cuda")
+    p = [Cc.c_void_p(t.data_ptr()) for t in (dA, dB, dC)]
+    _lib.check(c.lib.qf_cgemm(c.h, 0, M, N, K, *p, batch, M * K, N * K, M * N), c.h)
+    torch.cuda.synchronize()
+    got = dC.cpu().numpy().astype(np.complex128)
+    for b in range(batch):
+        ref = A[b].astype(np.complex128) @ B[b].astype(np.complex128).T
+        bound = np.abs(A[b]).astype(np.float64) @ np.abs(B[b]).astype(np.float64).T
+        assert np.max(np.abs(got[b * M * N:(b + 1) * M * N].reshape(M, N) - ref) / bound) <= TOL["fp32"]
+    assert (got[batch * M * N:] == 7.0).all()
+
+
+@pytest.mark.parametrize("M,N,K,us", [(16, 16, 65536, 400), (64, 16, 65536, 500), (16, 16, 4096, 60)])
+def test_cgemm_few_outputs_without_scratch_fill_the_gpu(M, N, K, us):
+    """Long sums of few outputs on a context without a workspace: 2000, 1500 and 125 us in one pass by a few tiles,
+    20, 68 and 5 us by a workgroup per output."""
+    import torch
+    from paper_1905_00444_amd import Context, time_cgemm
+    _say(f"cgemm few outputs, time {M}x{N}x{K}")
+    rng = np.random.default_rng(1)
+    A, B = (torch.from_numpy(_rand_c64(rng, (r, K))).cuda() for r in (M, N))
+    C = torch.empty((M, N), dtype=torch.complex64, device="cuda")
+    assert min(time_cgemm(Context(0), A, B, C, "fp32", reps=10) for _ in range(3)) * 1e3 <= us
