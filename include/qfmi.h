@@ -45,7 +45,10 @@ typedef enum {
 } qf_status;
 
 typedef enum {
-  QF_FP32 = 0,   /* complex64 operands, FP32 MFMA products, FP32 accumulate */
+  QF_FP32 = 0,   /* complex64 operands, FP32 accumulate, FP32 MFMA products, or for large products (64 rows and
+                    columns, K >= 128, 2^24 multiplications) six BF16 MFMA products of operands split in three:
+                    errors against FP64 below those of FP32 products on random and on same-sign entries; of
+                    single amplitudes whose path sums cancel almost wholly 0.7 to 1.7 times theirs (rms) */
   QF_BF16X3 = 1, /* each FP32 operand split as hi + lo bfloat16; hi*hi + hi*lo + lo*hi on
                     BF16 MFMA with FP32 accumulate */
   QF_FP16 = 2    /* operands scaled by a power of two and rounded to FP16; FP16 MFMA with
@@ -81,7 +84,7 @@ enum {
                            call with the same buffers, batch and slice range is one
                            hipGraphLaunch.  Replaces the paper's pipelined execution of
                            concurrent tensor operations (Sec. III-E). */
-  QF_PLAN_NO_RENORM = 8 /* store every intermediate at its true scale.  By default (Sec. III-E:
+  QF_PLAN_NO_RENORM = 8, /* store every intermediate at its true scale.  By default (Sec. III-E:
                            normalise the inputs, renormalise at the end) each stored tensor keeps
                            a power-of-two exponent on the device: a contraction divides its
                            result by 2^(e_A + e_B), e_X the binary exponent of operand X's
@@ -89,6 +92,7 @@ enum {
                            slice sum multiplies by 2^E in FP64.  Exact in binary floating point;
                            keeps amplitudes of 2^-n scale (and far smaller slices) away from FP32
                            and FP16 underflow.  Backward plans always store true scales. */
+  QF_PLAN_PLAIN_FP32 = 16 /* QF_FP32 products on FP32 MFMAs throughout */
 };
 
 /* Contraction plan.  steps: 2*n_steps node ids (lhs, rhs) in execution order.  Ids 0..n-1
@@ -302,7 +306,8 @@ qf_status qf_cgemm(qf_ctx* ctx, int precision, int64_t M, int64_t N, int64_t K, 
  * tests):
  *   0 auto, 1 tiled 128 x 64, 2 tiled 64 x 32, 3 tiled 32 x 32, 4 large 256 x 128, 5 skinny
  *   (SIMT FP32, B in LDS), 6 split-K reduction per output, 7 one thread per output, 8 tall
- *   (M large, powers of two with 8 <= N <= 64 and 8 <= K <= 64: B in LDS, A streamed).
+ *   (M large, powers of two with 8 <= N <= 64 and 8 <= K <= 64: B in LDS, A streamed), 9 FP32 MFMA tiles of the
+ *   launch's choice (any shape).  In FP32 the tiles of 1 and 4 are 64 x 64.
  * QF_ERR_UNSUPPORTED if the variant does not fit the shape, QF_ERR_ARG if it is unknown. */
 qf_status qf_cgemm_variant(qf_ctx* ctx, int precision, int variant, int64_t M, int64_t N, int64_t K,
                            const void* A, const void* B, void* C, int64_t batch, int64_t sa, int64_t sb,

@@ -17,6 +17,7 @@ QF_PLAN_NO_HOIST = 1
 QF_PLAN_BACKWARD = 2
 QF_PLAN_GRAPH = 4
 QF_PLAN_NO_RENORM = 8
+QF_PLAN_PLAIN_FP32 = 16
 GEMM_VARIANTS = ("auto", "tiled4x4", "tiled2x2", "tiled1x2", "large", "skinny", "splitk", "simt", "tall", "f32")
 
 STATUS_NAMES = {0: "QF_OK", -1: "QF_ERR_ARG", -2: "QF_ERR_PLAN", -3: "QF_ERR_WORKSPACE", -4: "QF_ERR_HIP",

@@ -845,11 +845,11 @@ size_t env_gemm_scratch(int side, int64_t M, int64_t N, int64_t K, int64_t batch
 
 hipError_t launch_env_gemm(hipStream_t st, int side, int64_t M, int64_t N, int64_t K, const float2* env,
                            const float2* other, float2* out, int64_t batch, const Renorm& map, float2* scratch,
-                           size_t scratch_bytes) {
+                           size_t scratch_bytes, bool plain) {
   const int64_t rows = side ? N : M;
   int split = scratch ? split_count(P_FP32, GEMM_F32, rows, K, side ? M : N) : 1;
   if (env_gemm_scratch(side, M, N, K, batch) > scratch_bytes) split = 1;
-  const hipError_t e = launch_cgemm_f32_env(st, side, M, N, K, env, other, out, batch, map, &split, scratch);
+  const hipError_t e = launch_cgemm_f32_env(st, side, M, N, K, env, other, out, batch, map, &split, scratch, plain);
   if (e != hipSuccess || split == 1) return e;
   const unsigned blocks = (unsigned)std::min<int64_t>((batch * rows * K + kReduceOut - 1) / kReduceOut, 65536);
   hipLaunchKernelGGL(cgemm_split_reduce, dim3(blocks), dim3(256), 0, st, scratch, split, batch, rows * K, K, rows * K,
@@ -860,7 +860,8 @@ hipError_t launch_env_gemm(hipStream_t st, int side, int64_t M, int64_t N, int64
 hipError_t launch_cgemm_ex(hipStream_t st, int precision, int64_t M, int64_t N, int64_t K, const float2* A,
                            const float2* B, float2* C, int64_t batch, int64_t sa, int64_t sb, int64_t sc,
                            const uint32_t* amaxA, const uint32_t* amaxB, const Renorm& rn, int variant,
-                           float2* scratch, size_t scratch_bytes, const OpMap* ma, const OpMap* mb, bool direct) {
+                           float2* scratch, size_t scratch_bytes, const OpMap* ma, const OpMap* mb, int flags) {
+  const bool direct = flags & GEMM_DIRECT, plain = flags & GEMM_PLAIN;
   if (rn.c && (!rn.a || !rn.b)) return hipErrorInvalidValue;
   if (M < 1 || N < 1 || K < 1 || batch < 1) return hipErrorInvalidValue;
   if (precision != P_FP32 && precision != P_BF16X3 && precision != P_FP16) return hipErrorInvalidValue;
@@ -913,7 +914,7 @@ hipError_t launch_cgemm_ex(hipStream_t st, int precision, int64_t M, int64_t N, 
   if (precision == P_FP32 || v == GEMM_F32) {
     static const int tiles[] = {F32_AUTO, F32_64X64, F32_64X32, F32_32X32, F32_64X64};
     e = launch_cgemm_f32(st, M, N, K, A, B, C, batch, sa, sb, sc, rn, &split, scratch,
-                         v == GEMM_F32 ? F32_AUTO : tiles[v], ma, mb);
+                         v != GEMM_F32 ? tiles[v] : plain ? F32_PLAIN : F32_AUTO, ma, mb);
   } else {
     if (!chosen) v = cgemm_default_variant(precision, M, N, K, batch * split);
     e = precision == P_BF16X3

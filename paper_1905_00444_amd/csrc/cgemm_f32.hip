@@ -205,7 +205,7 @@ template <int TA, int TB, bool CONJ>
 static void f32_pick(hipStream_t st, const F32Args& g, int split, int want) {
   auto blocks = [&](int64_t bm, int64_t bn) { return ((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn) * g.batch * split; };
   int tile = want;
-  if (tile == F32_AUTO) {
+  if (tile == F32_AUTO || tile == F32_PLAIN) {
     if (g.N <= 16) tile = g.M >= 128 && blocks(128, 16) >= 256 ? F32_128X16 : F32_32X16;
     else if (g.M >= 64 && g.N >= 64 && blocks(64, 64) >= 1024) tile = F32_64X64;
     else if (g.M >= 64 && blocks(64, 32) >= 256) tile = F32_64X32;
@@ -250,7 +250,7 @@ hipError_t launch_cgemm_f32(hipStream_t st, int64_t M, int64_t N, int64_t K, con
 
 hipError_t launch_cgemm_f32_env(hipStream_t st, int side, int64_t M, int64_t N, int64_t K, const float2* env,
                                 const float2* other, float2* out, int64_t batch, const Renorm& map, int* split,
-                                float2* P) {
+                                float2* P, bool plain) {
   // out[rows][K] = sum over the other index of env and conj(other): rows = M (side 0) or N (side 1)
   F32Args g;
   const int64_t rows = side ? N : M, sum = side ? M : N;
@@ -259,7 +259,7 @@ hipError_t launch_cgemm_f32_env(hipStream_t st, int side, int64_t M, int64_t N, 
   g.lda = N;  // env's plain row pitch
   g.ldb = K;
   g.amap = map;
-  if (f32s_takes(g.M, g.N, g.K)) launch_f32s(st, g, *split, true, side);
+  if (!plain && f32s_takes(g.M, g.N, g.K)) launch_f32s(st, g, *split, true, side);
   else if (side) f32_pick<1, 1, true>(st, g, *split, F32_AUTO);
   else f32_pick<0, 1, true>(st, g, *split, F32_AUTO);
   return hipGetLastError();

@@ -4,14 +4,20 @@
 // An FP32 number is the sum of three bfloat16 numbers, x = x0 + x1 + x2 (8 bits each, rounded to nearest, so
 // |x1| <= 2^-9 |x| and |x2| <= 2^-18 |x|), and a bfloat16 MFMA multiplies 13 times faster than an FP32
 // one.  x y is taken as x0 y0 + (x0 y1 + x1 y0) + (x1 y1 + x0 y2 + x2 y0); what is left out is below 2^-26 |x y|,
-// a quarter of an FP32 product's own rounding.  The five small products have accumulators of their own,
-// so that each step of 16 complex k rounds the large sum once.  Measured against FP64 (norm-wise, normal
-// entries; FP32 MFMAs / here): 1000 x 600 x 300 4.4e-7 / 1.4e-7, K = 64 2.0e-7 / 6.4e-8; four slices of the 7x7
-// (1+32+1) circuit 1.2e-6 / 7.5e-7, 4x4 samples 3.8e-7 / 3.2e-7.  The matrix cores align a lane group's
-// 8 products to the largest and cut what falls below 2^-24 of it: with entries that spread over many
-// binades the loss is one-sided, which long chains of structured products add up (70 qubits, every CZ an
-// identity, K = 64: 3e-6 with FP32 MFMAs, 2.8e-5).  Products below K = 128 stay on FP32 MFMAs, also because
-// HBM bounds them there (2^15 x 64 x 64 by 64: 619 us against 539).
+// a quarter of an FP32 product's own rounding.
+//
+// What the instruction does to its sums (probed): a lane group's 8 products are aligned to the largest and cut at
+// 2^-24 of it, and the accumulator operand, where it is the smaller, as well and downwards.  A sum that is kept
+// in the instruction therefore loses the remainder when large products cancel, and always on the same side: of
+// amplitudes of 5x5 and 6x6 circuits of depth 32 with every CZ an identity, whose path sums cancel, the errors
+// were seven and three times those of FP32 MFMAs.  So the product of the first planes starts from zero in every
+// K-tile of 16 and is added with FP32 rounding, and A is negated in the middle half of K, which leaves no bias; the
+// five small products keep accumulators in the instruction, 2^-8 below, which are negated there too.  Relative
+// errors per amplitude there (rms; FP32 MFMAs / all sums in the instruction / here): 4x4 1.3e-6 / 1.1e-6 / 9e-7, 4x5
+// 2.1e-6 / 1.9e-6 / 1.4e-6, 5x5 2.3e-6 / 1.7e-5 / 3.3e-6, 6x6 5.3e-6 / 1.7e-5 / 8.9e-6.  Of products, norm-wise: normal
+// entries, 4096 x 1024 x 128, 3.2e-8 / 1.0e-8 / 7.6e-9, same-sign entries over 20 binades, K = 1024, 2.2e-7 / - / 5.9e-8.
+// Callers who want FP32 MFMAs throughout have QF_PLAN_PLAIN_FP32 and the variant f32.  Products below K = 128 stay
+// on FP32 MFMAs: HBM bounds them there (2^15 x 64 x 64 by 64: 619 us against 539).
 //
 // Bound by VALU issue beside the MFMAs (conversions: 11 instructions per complex element staged; the
 // arrangement of B: 2 per element and plane read), so tiles are as large as the launch allows.
@@ -22,9 +28,9 @@
 // 2^108 on, infinities and NaNs, and results from 2^88 on, leave sums that are not finite: a wave that sees
 // one computes its results again as plain FP32 sums.
 //
-// Measured (MI355X, FP32 MFMAs / here): 4096^3 140 / 234 TFLOP/s, 2^18 x 256 x 256 134 / 201, 64 products of
-// 256^3 123 / 192, 16 of them 97 / 112, one 8.7 / 9.3 us; 1500 x 700 x 300 38.9 / 32 us, the 7x7 slices
-// 388 / 206 ms.
+// Measured (MI355X, FP32 MFMAs / all sums in the instruction / here): 4096^3 140 / 238 / 231 TFLOP/s, 2^18 x 256 x 256
+// 134 / 198 / 193, 64 products of 256^3 123 / 188 / 181, 16 of them 97 / 109 / 97; 1500 x 700 x 300 39 / 33 / 36 us, the 7x7
+// slices 388 / 206 / 234 ms.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <algorithm>
@@ -48,10 +54,10 @@ struct F32sAcc {
 
 // A thread's pairs into the three planes of a tile, ROWS kSRow dwords apart.
 template <int T, int ROWS, class Loader>
-__device__ __forceinline__ void f32s_stage(uint32_t* lds, const Loader& l) {
+__device__ __forceinline__ void f32s_stage(uint32_t* lds, const Loader& l, float scale) {
   l.each([&](int row, int k, float4 v) {
     uint32_t* d = lds + row * kSRow + k;
-    v = make_float4(v.x * kSScale, v.y * kSScale, v.z * kSScale, v.w * kSScale);
+    v = make_float4(v.x * scale, v.y * scale, v.z * scale, v.w * scale);
 #pragma unroll
     for (int p = 0; p < 3; ++p) {
       const uint32_t a = pack_bf16x2(v.x, v.y), b = pack_bf16x2(v.z, v.w);
@@ -68,14 +74,19 @@ __device__ __forceinline__ void f32s_stage(uint32_t* lds, const Loader& l) {
   });
 }
 
-// The products of a K-tile: plane p of rows 16 i + (lane's) from pa, of columns 16 j + l16 from pb.
+// The products of a K-tile: plane p of rows 16 i + (lane's) from pa, of columns 16 j + l16 from pb.  The product of
+// the first planes is taken from zero and added here, times the sign that A was staged with.
 template <int TM, int TN, int BM, int BN, bool CONJ>
-__device__ __forceinline__ void f32s_multiply(const uint32_t* pa, const uint32_t* pb, F32sAcc (&acc)[TM][TN]) {
+__device__ __forceinline__ void f32s_multiply(const uint32_t* pa, const uint32_t* pb, float sign,
+                                              F32sAcc (&acc)[TM][TN]) {
   u4 a[3][TM];
 #pragma unroll
   for (int p = 0; p < 3; ++p)
 #pragma unroll
     for (int i = 0; i < TM; ++i) a[p][i] = *reinterpret_cast<const u4*>(pa + (p * BM + 16 * i) * kSRow);
+  auto product = [](const u4& x, const u4& y, f4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8, x), __builtin_bit_cast(bf8, y), c, 0, 0, 0);
+  };
 #pragma unroll
   for (int j = 0; j < TN; ++j) {
     u4 re[3], im[3];
@@ -89,21 +100,28 @@ __device__ __forceinline__ void f32s_multiply(const uint32_t* pa, const uint32_t
         im[p][e] = __builtin_amdgcn_alignbit(b[e], b[e], 16) ^ (CONJ ? 0x00008000u : 0u);
       }
     }
-    constexpr int order[6][2] = {{2, 0}, {0, 2}, {1, 1}, {1, 0}, {0, 1}, {0, 0}};
+    constexpr int order[5][2] = {{2, 0}, {0, 2}, {1, 1}, {1, 0}, {0, 1}};
 #pragma unroll
-    for (int o = 0; o < 6; ++o) {
-      const bf8 vr = __builtin_bit_cast(bf8, re[order[o][1]]), vi = __builtin_bit_cast(bf8, im[order[o][1]]);
+    for (int o = 0; o < 5; ++o) {
+      const int p = order[o][0], q = order[o][1];
 #pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        f4& c = o < 5 ? acc[i][j].re_low : acc[i][j].re;
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8, a[order[o][0]][i]), vr, c, 0, 0, 0);
-      }
+      for (int i = 0; i < TM; ++i) acc[i][j].re_low = product(a[p][i], re[q], acc[i][j].re_low);
 #pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        f4& c = o < 5 ? acc[i][j].im_low : acc[i][j].im;
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8, a[order[o][0]][i]), vi, c, 0, 0, 0);
-      }
+      for (int i = 0; i < TM; ++i) acc[i][j].im_low = product(a[p][i], im[q], acc[i][j].im_low);
     }
+    const f4 zero = {0.f, 0.f, 0.f, 0.f};
+    f4 r[TM], m[TM];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) r[i] = product(a[0][i], re[0], zero);
+#pragma unroll
+    for (int i = 0; i < TM; ++i) m[i] = product(a[0][i], im[0], zero);
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        acc[i][j].re[e] = fmaf(sign, r[i][e], acc[i][j].re[e]);
+        acc[i][j].im[e] = fmaf(sign, m[i][e], acc[i][j].im[e]);
+      }
   }
 }
 
@@ -219,9 +237,20 @@ cgemm_f32s(F32Args g) {
     else lb.load((int64_t)t * kFBK, g.ldb, nl, klen, g.amap);
   };
   auto stage_of = [&](int t) { return lds + (Tile::stages == 2 ? (t & 1) * Tile::dwords : 0); };
+  const int first_turned = (nk + 3) / 4, last_turned = (3 * nk + 3) / 4;  // K-tiles with A negated
+  auto turned = [&](int t) { return t >= first_turned && t < last_turned; };
+  auto turn = [&] {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        acc[i][j].re_low = -acc[i][j].re_low;
+        acc[i][j].im_low = -acc[i][j].im_low;
+      }
+  };
   auto stage = [&](int t) {
-    f32s_stage<TA, BM>(stage_of(t), la);
-    f32s_stage<TB, BN>(stage_of(t) + 3 * BM * kSRow, lb);
+    f32s_stage<TA, BM>(stage_of(t), la, turned(t) ? -kSScale : kSScale);
+    f32s_stage<TB, BN>(stage_of(t) + 3 * BM * kSRow, lb, kSScale);
   };
   fetch(0);
   if constexpr (Tile::stages == 2) {
@@ -229,19 +258,28 @@ cgemm_f32s(F32Args g) {
     if (nk > 1) fetch(1);
     __syncthreads();
   }
-  for (int t = 0; t < nk; ++t) {
-    if constexpr (Tile::stages == 1) {
-      stage(t);
+  // A loop over each part of K (A as it is, negated, as it is) rather than a test in one, around which the compiler
+  // moves the accumulators of every K-tile.
+  int t = 0;
+#pragma unroll 1
+  for (int part = 0; part < 3; ++part) {
+    const int end = part == 0 ? first_turned : part == 1 ? last_turned : nk;
+    const float sign = part == 1 ? -1.f : 1.f;
+    if (part > 0) turn();
+    for (; t < end; ++t) {
+      if constexpr (Tile::stages == 1) {
+        stage(t);
+        __syncthreads();
+        if (t + 1 < nk) fetch(t + 1);
+      } else if (t + 1 < nk) {
+        stage(t + 1);
+        if (t + 2 < nk) fetch(t + 2);
+      }
+      const uint32_t* st = stage_of(t);
+      f32s_multiply<TM, TN, BM, BN, CONJ>(st + (wr + 4 * (l16 & 3) + (l16 >> 2)) * kSRow + 4 * lg,
+                                          st + (3 * BM + wc + l16) * kSRow + 4 * lg, sign, acc);
       __syncthreads();
-      if (t + 1 < nk) fetch(t + 1);
-    } else if (t + 1 < nk) {
-      stage(t + 1);
-      if (t + 2 < nk) fetch(t + 2);
     }
-    const uint32_t* st = stage_of(t);
-    f32s_multiply<TM, TN, BM, BN, CONJ>(st + (wr + 4 * (l16 & 3) + (l16 >> 2)) * kSRow + 4 * lg,
-                                        st + (3 * BM + wc + l16) * kSRow + 4 * lg, acc);
-    __syncthreads();
   }
 
   if (partial) rn.om_nh = 0;

@@ -243,8 +243,8 @@ enum {
   GEMM_F32 = 9,        // FP32 MFMA tiles for any shape (the tile follows the launch)
   GEMM_N_VARIANTS = 10
 };
-// Tiles of the FP32 kernel (cgemm_f32.hip).
-enum { F32_AUTO = 0, F32_64X64, F32_64X32, F32_32X32, F32_128X16, F32_32X16 };
+// Tiles of the FP32 kernel (cgemm_f32.hip): by the launch, among them those of cgemm_f32s.hip or (plain) not, or given.
+enum { F32_AUTO = 0, F32_PLAIN, F32_64X64, F32_64X32, F32_32X32, F32_128X16, F32_32X16 };
 bool cgemm_variant_fits(int precision, int64_t M, int64_t N, int64_t K, int variant);
 // blocks_per_tile: workgroups that a launch makes per output tile (batch x K-chunks).
 int cgemm_default_variant(int precision, int64_t M, int64_t N, int64_t K, int64_t blocks_per_tile = 1);
@@ -266,13 +266,15 @@ constexpr int kMapKBits = 12, kMapRowBits = 24;
 
 // Same, with optional operand max magnitudes for FP16 scaling (ignored when rn is on: then the
 // FP16 operands are scaled from rn.a / rn.b), optional renormalisation, and a kernel variant
-// (one that does not fit the shape falls back to GEMM_AUTO).  direct: a call of its own rather than a plan's step;
-// the kernel and the cut of K then follow the batch and the scratch too.
+// (one that does not fit the shape falls back to GEMM_AUTO).  flags: GEMM_DIRECT, a call of its own
+// rather than a plan's step: the kernel and the cut of K then follow the batch and the scratch too; GEMM_PLAIN, FP32
+// products on FP32 MFMAs only.
+enum { GEMM_DIRECT = 1, GEMM_PLAIN = 2 };
 hipError_t launch_cgemm_ex(hipStream_t st, int precision, int64_t M, int64_t N, int64_t K, const float2* A,
                            const float2* B, float2* C, int64_t batch, int64_t sa, int64_t sb, int64_t sc,
                            const uint32_t* amaxA, const uint32_t* amaxB, const Renorm& rn = Renorm{},
                            int variant = GEMM_AUTO, float2* scratch = nullptr, size_t scratch_bytes = 0,
-                           const OpMap* ma = nullptr, const OpMap* mb = nullptr, bool direct = false);
+                           const OpMap* ma = nullptr, const OpMap* mb = nullptr, int flags = 0);
 // Whether that call (GEMM_AUTO) reads operands through maps.
 bool cgemm_reads_maps(int precision, int64_t M, int64_t N, int64_t K, int64_t batch);
 // ... and takes A's rows in any order (by shape alone).
@@ -287,11 +289,11 @@ hipError_t launch_cgemm_f32(hipStream_t st, int64_t M, int64_t N, int64_t K, con
 // out[N][K] = sum_m env[m][n] conj(other[m][k]) with other = A.  Dense batch strides.
 hipError_t launch_cgemm_f32_env(hipStream_t st, int side, int64_t M, int64_t N, int64_t K, const float2* env,
                                 const float2* other, float2* out, int64_t batch, const Renorm& map, int* split,
-                                float2* P);
+                                float2* P, bool plain = false);
 // The same with the split of K that the shape asks for, given the scratch (cgemm.hip).
 hipError_t launch_env_gemm(hipStream_t st, int side, int64_t M, int64_t N, int64_t K, const float2* env,
                            const float2* other, float2* out, int64_t batch, const Renorm& map, float2* scratch,
-                           size_t scratch_bytes);
+                           size_t scratch_bytes, bool plain = false);
 size_t env_gemm_scratch(int side, int64_t M, int64_t N, int64_t K, int64_t batch);
 // Tall-skinny kernel (cgemm_tall.hip): powers of two, 8 <= N <= 64, 16 <= K <= 64.
 bool cgemm_tall_fits(int precision, int64_t M, int64_t N, int64_t K);

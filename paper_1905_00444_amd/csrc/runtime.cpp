@@ -1221,7 +1221,7 @@ static qf_plan* batch_form(qf_plan* p) {
   d.open = p->open.data();
   d.precision = p->precision;
   d.flags = (p->no_hoist_asked ? QF_PLAN_NO_HOIST : 0) | (p->backward ? QF_PLAN_BACKWARD : 0) |
-            (p->renorm || p->backward ? 0 : QF_PLAN_NO_RENORM);
+            (p->renorm || p->backward ? 0 : QF_PLAN_NO_RENORM) | (p->flags & QF_PLAN_PLAIN_FP32);
   d.batch = G;
   qf_plan* q = nullptr;
   try {
@@ -1563,6 +1563,8 @@ static const NodeScale* root_scale(qf_plan* p) {
   return p->renorm ? node_scale(p, (int)p->nodes.size() - 1) : nullptr;
 }
 
+static int gemm_flags(const qf_plan* p) { return (p->flags & QF_PLAN_PLAIN_FP32) ? GEMM_PLAIN : 0; }
+
 // One GEMM of the plan's precision (FP16 without renormalisation takes the operands' max
 // magnitudes first).
 static qf_status plan_gemm(qf_plan* p, int64_t M, int64_t N, int64_t K, const float2* A, const float2* B, float2* C,
@@ -1586,7 +1588,7 @@ static qf_status plan_gemm(qf_plan* p, int64_t M, int64_t N, int64_t K, const fl
   }
   float2* scratch = p->gscratch_bytes ? wsp(c, p->off_gscratch) : nullptr;
   QF_HIP(c, launch_cgemm_ex(c->stream, p->precision, M, N, K, A, B, C, batch, sa, sb, M * N, amA, amB, rn,
-                            variant, scratch, p->gscratch_bytes, ma.on ? &ma : nullptr, mb.on ? &mb : nullptr));
+                            variant, scratch, p->gscratch_bytes, ma.on ? &ma : nullptr, mb.on ? &mb : nullptr, gemm_flags(p)));
   return QF_OK;
 }
 
@@ -2131,8 +2133,8 @@ static qf_status env_fp32(qf_plan* p, const Step& st, const float2* envC, const 
   map.om_nh = st.om_nh;
   map.om_nl = st.n_bits - st.om_nh;
   float2* scratch = p->gscratch_bytes ? wsp(c, p->off_gscratch) : nullptr;
-  QF_HIP(c, launch_env_gemm(c->stream, 0, M, N, K, envC, Bop, EA, G, map, scratch, p->gscratch_bytes));
-  QF_HIP(c, launch_env_gemm(c->stream, 1, M, N, K, envC, Aop, EB, G, map, scratch, p->gscratch_bytes));
+  QF_HIP(c, launch_env_gemm(c->stream, 0, M, N, K, envC, Bop, EA, G, map, scratch, p->gscratch_bytes, gemm_flags(p)));
+  QF_HIP(c, launch_env_gemm(c->stream, 1, M, N, K, envC, Aop, EB, G, map, scratch, p->gscratch_bytes, gemm_flags(p)));
   return QF_OK;
 }
 
@@ -2339,7 +2341,7 @@ qf_status qf_cgemm_variant(qf_ctx* c, int precision, int variant, int64_t M, int
                            const void* B, void* C, int64_t batch, int64_t sa, int64_t sb, int64_t sc) {
   if (!c || !A || !B || !C || M < 1 || N < 1 || K < 1 || batch < 1 || precision < 0 || precision > 2)
     return fail(c, QF_ERR_ARG, "qf_cgemm: bad arguments");
-  if (variant < 0 || variant > GEMM_TALL) return fail(c, QF_ERR_ARG, "qf_cgemm_variant: unknown variant");
+  if (variant < 0 || variant >= GEMM_N_VARIANTS) return fail(c, QF_ERR_ARG, "qf_cgemm_variant: unknown variant");
   if (variant != GEMM_AUTO && !cgemm_variant_fits(precision, M, N, K, variant))
     return fail(c, QF_ERR_UNSUPPORTED, std::string("qf_cgemm_variant: ") + kVariantName[variant] +
                                            " does not fit this shape");
@@ -2365,7 +2367,8 @@ qf_status qf_cgemm_variant(qf_ctx* c, int precision, int variant, int64_t M, int
   }
   QF_HIP(c, launch_cgemm_ex(c->stream, precision, M, N, K, reinterpret_cast<const float2*>(A),
                             reinterpret_cast<const float2*>(B), reinterpret_cast<float2*>(C), batch, sa, sb, sc, amA, amB,
-                            Renorm{}, variant, scratch, scratch_bytes, nullptr, nullptr, true));
+                            Renorm{}, variant, scratch, scratch_bytes, nullptr, nullptr,
+                            GEMM_DIRECT | (variant == GEMM_F32 ? GEMM_PLAIN : 0)));
   return QF_OK;
 }
 
@@ -2450,11 +2453,11 @@ qf_status qf_time_cgemm(qf_ctx* c, int precision, int64_t M, int64_t N, int64_t 
   QF_HIP(c, hipEventCreate(&e0));
   QF_HIP(c, hipEventCreate(&e1));
   QF_HIP(c, launch_cgemm_ex(c->stream, precision, M, N, K, (const float2*)A, (const float2*)B, (float2*)C, 1, 0, 0, 0, amA, amB,
-                               Renorm{}, GEMM_AUTO, nullptr, 0, nullptr, nullptr, true));
+                               Renorm{}, GEMM_AUTO, nullptr, 0, nullptr, nullptr, GEMM_DIRECT));
   QF_HIP(c, hipEventRecord(e0, c->stream));
   for (int i = 0; i < reps; ++i)
     QF_HIP(c, launch_cgemm_ex(c->stream, precision, M, N, K, (const float2*)A, (const float2*)B, (float2*)C, 1, 0, 0, 0, amA, amB,
-                               Renorm{}, GEMM_AUTO, nullptr, 0, nullptr, nullptr, true));
+                               Renorm{}, GEMM_AUTO, nullptr, 0, nullptr, nullptr, GEMM_DIRECT));
   QF_HIP(c, hipEventRecord(e1, c->stream));
   QF_HIP(c, hipEventSynchronize(e1));
   float t = 0.f;
@@ -2623,7 +2626,7 @@ static qf_status time_variant(qf_ctx* c, const qf_plan* p, int variant, int64_t 
   if (!e0 || !e1) return fail(c, QF_ERR_HIP, "hipEventCreate failed");
   auto launch = [&]() {
     return launch_cgemm_ex(c->stream, prec, M, N, K, A, B, C, G, sa, sb, M * N, nullptr, nullptr, Renorm{}, variant,
-                           scratch, p->gscratch_bytes);
+                           scratch, p->gscratch_bytes, nullptr, nullptr, gemm_flags(p));
   };
   *ms = -1.f;
   QF_HIP(c, hipEventRecord(e0, c->stream));

@@ -366,3 +366,27 @@ def test_one_call_amplitudes_function():
     torch.cuda.synchronize()
     assert got.dtype == torch.complex128 and got.shape == (8, 1)
     assert rel_err(got.cpu().numpy()[:, 0], sv.amplitudes(c.to_text(), bits)) <= 1e-5
+
+
+@pytest.mark.parametrize("plain", [False, True])
+@pytest.mark.parametrize("rows,cols,seed", [(4, 4, 0), (4, 5, 0), (4, 5, 1), (5, 5, 1)])
+def test_large_products_of_cancelling_path_sums(ctx, rows, cols, seed, plain):
+    """Every CZ an identity, depth 32 (products of K = 256 whose sums cancel almost wholly): the amplitudes are
+    products of one-qubit amplitudes.  FP32's bound, on FP32 MFMAs throughout and not."""
+    import torch
+    from oracle import gates
+    from paper_1905_00444_amd import Circuit, Plan
+    c = identity_cz(generate(rows, cols, 32, seed))
+    plan = sweep_plan(c) if rows == 5 else region_plan(c, 2, 2, [], [])[0]
+    vecs = [np.array([1, 0], dtype=np.complex128) for _ in range(c.n_qubits)]
+    for op in c.ops:
+        if len(op.qubits) == 1:
+            vecs[op.qubits[0]] = gates.one_qubit(op.name) @ vecs[op.qubits[0]]
+    bits = random_bitstrings(16, c.n_qubits, 1)
+    ref = np.array([np.prod([vecs[q][b[q]] for q in range(c.n_qubits)]) for b in bits])
+    p = Plan(ctx, Circuit(ctx, c.to_text()), plan, "fp32", plain_fp32=plain)
+    big = [s for s in p.steps() if s["k_bits"] >= 8 and min(s["m_bits"], s["n_bits"]) >= 6]
+    assert len(big) >= 5
+    got = p.amplitudes(bits)
+    torch.cuda.synchronize()
+    assert rel_err(got.cpu().numpy()[:, 0], ref) <= 1e-5

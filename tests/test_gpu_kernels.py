@@ -561,3 +561,61 @@ def test_cgemm_few_outputs_without_scratch_fill_the_gpu(M, N, K, us):
     A, B = (torch.from_numpy(_rand_c64(rng, (r, K))).cuda() for r in (M, N))
     C = torch.empty((M, N), dtype=torch.complex64, device="cuda")
     assert min(time_cgemm(Context(0), A, B, C, "fp32", reps=10) for _ in range(3)) * 1e3 <= us
+
+
+def _spread(kind, r, K, rng):
+    if kind == "normal":
+        return _rand_c64(rng, (r, K))
+    if kind == "one sign":  # over 20 binades
+        return np.exp2(-20 * rng.random((r, K))).astype(np.complex64)
+    if kind == "complex, one sign":
+        return (np.exp2(-20 * rng.random((r, K))) + 1j * np.exp2(-20 * rng.random((r, K)))).astype(np.complex64)
+    if kind == "few large":
+        return (_rand_c64(rng, (r, K)) * np.where(rng.random((r, K)) < 1 / 16, 1, 2.0 ** -14)).astype(np.complex64)
+    # pairs that cancel but for 2^-9
+    x = np.exp(1j * np.pi / 4 * rng.integers(0, 8, (r, K)))
+    x[:, 1::2] = x[:, ::2] * (1 if kind == "cancel a" else -1)
+    return (x * (1 + 2.0 ** -9 * rng.standard_normal((r, K)))).astype(np.complex64)
+
+
+@pytest.mark.parametrize("kind", ["normal", "one sign", "complex, one sign", "few large", "cancel"])
+@pytest.mark.parametrize("M,N,K", [(1024, 256, 128), (4096, 1024, 128), (4097, 513, 128), (512, 512, 1024), (256, 256, 4096)])
+def test_cgemm_six_products_against_fp32_mfmas(split_ctx, kind, M, N, K):
+    """Entries over many binades, of one sign or cancelling: the errors against FP64, largest, rms and mean, are not
+    above those of the same product on FP32 MFMAs (mean: or a tenth of their rms, the sums' own spread)."""
+    import torch
+    from paper_1905_00444_amd import cgemm
+    _say(f"six products against FP32 MFMAs {kind} {M}x{N}x{K}")
+    rng = np.random.default_rng(M + K)
+    a, b = ("cancel a", "cancel b") if kind == "cancel" else (kind, kind)
+    A, B = _spread(a, M, K, rng), _spread(b, N, K, rng)
+    ref = A.astype(np.complex128) @ B.astype(np.complex128).T
+    bound = np.abs(A).astype(np.float64) @ np.abs(B).astype(np.float64).T
+    dA, dB = torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda()
+    six, plain = ((cgemm(split_ctx, dA, dB, variant=v).cpu().numpy().astype(np.complex128) - ref) / bound
+                  for v in ("auto", "f32"))
+    rms = [np.sqrt(np.mean(np.abs(e) ** 2)) for e in (six, plain)]
+    print(f"  max {np.abs(six).max():.1e} {np.abs(plain).max():.1e} rms {rms[0]:.1e} {rms[1]:.1e} mean {six.mean():.1e} {plain.mean():.1e}")
+    assert not np.array_equal(six, plain)
+    assert np.abs(six).max() <= np.abs(plain).max()
+    assert rms[0] <= rms[1]
+    assert abs(six.mean()) <= max(abs(plain.mean()), 0.1 * rms[1])
+
+
+@pytest.mark.parametrize("M,N,K", [(4096, 1024, 128), (16384, 64, 128), (16385, 65, 129), (256, 256, 256), (64, 64, 4096)])
+def test_cgemm_six_products_one_term(split_ctx, M, N, K):
+    """Sums of a single term, of mantissas of 24 bits: 2^-26 is left out and two roundings of 2^-24 follow, so 2^-23
+    of |a| |b|; without any one of the six products it would be 2^-19 or more for some."""
+    import torch
+    from paper_1905_00444_amd import cgemm
+    _say(f"six products, one term {M}x{N}x{K}")
+    rng = np.random.default_rng(K)
+    for k in sorted({0, 5, 15, 16, 31, K // 2 + 3, K - 1}):
+        A, B = np.zeros((M, K), np.complex64), np.zeros((N, K), np.complex64)
+        A[:, k] = ((1 + rng.random(M)) + 1j * (1 + rng.random(M))).astype(np.complex64) * rng.choice([1, -1, 1j, -1j], M)
+        B[:, k] = ((1 + rng.random(N)) + 1j * (1 + rng.random(N))).astype(np.complex64) * rng.choice([1, -1, 1j, -1j], N)
+        got = cgemm(split_ctx, torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda()).cpu().numpy().astype(np.complex128)
+        a, b = A[:, k].astype(np.complex128), B[:, k].astype(np.complex128)
+        err = got - np.outer(a, b)
+        assert np.max(np.abs(err.real) / (np.outer(np.abs(a.real), np.abs(b.real)) + np.outer(np.abs(a.imag), np.abs(b.imag)))) <= 2.0 ** -23
+        assert np.max(np.abs(err.imag) / (np.outer(np.abs(a.real), np.abs(b.imag)) + np.outer(np.abs(a.imag), np.abs(b.real)))) <= 2.0 ** -23
