@@ -1565,6 +1565,13 @@ static const NodeScale* root_scale(qf_plan* p) {
 
 static int gemm_flags(const qf_plan* p) { return (p->flags & QF_PLAN_PLAIN_FP32) ? GEMM_PLAIN : 0; }
 
+// The variant installed for a product, or GEMM_AUTO.  A form takes that of its plan's own launches, so that its chains
+// add in the same order.
+static int tuned_variant(const qf_plan* p, int64_t M, int64_t N, int64_t K, int64_t batch) {
+  const auto it = p->ctx->tune.find({(int64_t)p->precision, M, N, K, p->form_of ? 1 : batch});
+  return it == p->ctx->tune.end() ? GEMM_AUTO : it->second;
+}
+
 // One GEMM of the plan's precision (FP16 without renormalisation takes the operands' max
 // magnitudes first).
 static qf_status plan_gemm(qf_plan* p, int64_t M, int64_t N, int64_t K, const float2* A, const float2* B, float2* C,
@@ -1581,14 +1588,12 @@ static qf_status plan_gemm(qf_plan* p, int64_t M, int64_t N, int64_t K, const fl
     amA = slots;
     amB = slots + 1;
   }
-  int variant = GEMM_AUTO;
-  if (!c->tune.empty()) {
-    auto it = c->tune.find({(int64_t)p->precision, M, N, K, batch});
-    if (it != c->tune.end() && !ma.on && !mb.on) variant = it->second;
-  }
+  const int variant = ma.on || mb.on ? GEMM_AUTO : tuned_variant(p, M, N, K, batch);
   float2* scratch = p->gscratch_bytes ? wsp(c, p->off_gscratch) : nullptr;
+  // a form's chains split K as they would alone, also in launches of fewer than the scratch is for
+  const size_t scratch_bytes = p->form_of ? p->gscratch_bytes / p->G_max * batch : p->gscratch_bytes;
   QF_HIP(c, launch_cgemm_ex(c->stream, p->precision, M, N, K, A, B, C, batch, sa, sb, M * N, amA, amB, rn,
-                            variant, scratch, p->gscratch_bytes, ma.on ? &ma : nullptr, mb.on ? &mb : nullptr, gemm_flags(p)));
+                            variant, scratch, scratch_bytes, ma.on ? &ma : nullptr, mb.on ? &mb : nullptr, gemm_flags(p)));
   return QF_OK;
 }
 
@@ -1596,10 +1601,8 @@ static qf_status plan_gemm(qf_plan* p, int64_t M, int64_t N, int64_t K, const fl
 static bool step_reads_maps(const qf_plan* p, const Step& st, int64_t batch) {
   if (!(st.A.gather || st.B.gather) || trace_on()) return false;
   const int64_t M = (int64_t)1 << st.m_bits, N = (int64_t)1 << st.n_bits, K = (int64_t)1 << st.k_bits;
-  if (!p->ctx->tune.empty()) {
-    auto it = p->ctx->tune.find({(int64_t)p->precision, M, N, K, batch});
-    if (it != p->ctx->tune.end() && it->second != cgemm_default_variant(p->precision, M, N, K, batch)) return false;
-  }
+  const int tuned = tuned_variant(p, M, N, K, batch);
+  if (tuned != GEMM_AUTO && tuned != cgemm_default_variant(p->precision, M, N, K, p->form_of ? 1 : batch)) return false;
   return cgemm_reads_maps(p->precision, M, N, K, batch);
 }
 

@@ -97,3 +97,37 @@ def test_every_gemm_variant_writes_the_plans_output_order(tmp_path, precision):
         err = rel_err(got.cpu().numpy()[:, 0], g["amps"])
         print(f"  {name}: rel err {err:.2e}", flush=True)
         assert err <= bound, name
+
+
+@pytest.mark.parametrize("precision", ["fp32", "bf16x3"])
+def test_tuned_variants_serve_calls_of_several_chains(tmp_path, precision):
+    """A one-chain plan's tuned variants also run its calls of several chains: each variant forced for every shape, a
+    call over six bitstrings and four slices gives the same bits as a call per bitstring and slice, and some
+    variants give other bits than the rule's."""
+    import re
+    import torch
+    from paper_1905_00444_amd import Context, Circuit, Plan, autotune, _lib
+    print(f"tuned variants and several chains, {precision}", flush=True)
+    c, plan = _setup()
+    bits = random_bitstrings(6, 20, 11)
+    ctx = Context(0)
+    p = Plan(ctx, Circuit(ctx, c.to_text()), plan, precision)
+    rule = p.amplitudes(bits, 2, 6).cpu().numpy()
+    autotune(p, str(tmp_path / "tune.json"))
+    lines = (tmp_path / "tune.json").read_text()
+    others = 0
+    for name in _lib.GEMM_VARIANTS[1:]:
+        forced = tmp_path / f"tune_{name}.json"
+        forced.write_text(re.sub(r'"variant": "[a-z0-9]+"', f'"variant": "{name}"', lines))
+        c2 = Context(0)
+        p2 = Plan(c2, Circuit(c2, c.to_text()), plan, precision)
+        autotune(p2, str(forced))
+        want = torch.zeros((6, 4), dtype=torch.complex128, device="cuda")
+        for b in range(6):
+            for s in range(2, 6):
+                p2.amplitudes(bits[b:b + 1], s, s + 1, out=want[b:b + 1])
+        got = p2.amplitudes(bits, 2, 6)
+        torch.cuda.synchronize()
+        assert np.array_equal(got.cpu().numpy(), want.cpu().numpy()), name
+        others += not np.array_equal(got.cpu().numpy(), rule)
+    assert others >= 2
