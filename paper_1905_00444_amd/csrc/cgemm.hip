@@ -39,7 +39,7 @@
 #include <stdlib.h>
 #include <algorithm>
 #include <string>
-#include "cgemm_common.h"
+#include "cgemm_f32.h"
 
 namespace qf {
 
@@ -684,22 +684,24 @@ cgemm_splitk(int64_t M, int64_t N, int64_t K, const float2* __restrict__ A, cons
 }
 
 template <int PREC, int WTM, int WTN>
-static void launch_tiled(hipStream_t st, int64_t M, int64_t N, int64_t K, const float2* A, const float2* B, float2* C,
+static hipError_t launch_tiled(hipStream_t st, int64_t M, int64_t N, int64_t K, const float2* A, const float2* B, float2* C,
                          int64_t batch, int64_t sa, int64_t sb, int64_t sc, const uint32_t* amaxA,
                          const uint32_t* amaxB, const Renorm& rn, int split, float2* P, const OpMap& ma,
                          const OpMap& mb) {
   constexpr int BM = 32 * WTM, BN = 16 * WTN;
   const int64_t tiles = (M / BM) * (N / BN);
+  if (!grid_takes(tiles * batch, kThreads)) return hipErrorInvalidConfiguration;
   auto run = [&](auto* kernel) {
     hipLaunchKernelGGL(kernel, dim3((unsigned)(tiles * batch), (unsigned)split), dim3(kThreads), 0, st, M, N, K, A, B, C,
                        sa, sb, sc, amaxA, amaxB, rn, K / split, P, batch, ma, mb);
+    return hipGetLastError();
   };
   if constexpr (PREC == P_BF16X3) {
     if (ma.on == 1 && mb.on == 1) return run(cgemm_mfma<PREC, WTM, WTN, true, true>);
     if (ma.on == 1) return run(cgemm_mfma<PREC, WTM, WTN, true, false>);
     if (mb.on == 1) return run(cgemm_mfma<PREC, WTM, WTN, false, true>);
   }
-  run(cgemm_mfma<PREC, WTM, WTN, false, false>);
+  return run(cgemm_mfma<PREC, WTM, WTN, false, false>);
 }
 
 static bool pow2(int64_t x) { return x > 0 && (x & (x - 1)) == 0; }
@@ -796,17 +798,14 @@ static hipError_t launch_mfma(hipStream_t st, int variant, int64_t M, int64_t N,
     case GEMM_LARGE:
       hipLaunchKernelGGL((cgemm_v2<PREC>), dim3((unsigned)((M / kV2BM) * (N / kV2BN)), (unsigned)split, (unsigned)batch),
                          dim3(kV2Threads), 0, st, M, N, K, A, B, C, sa, sb, sc, amaxA, amaxB, rn, K / split, P);
-      break;
+      return hipGetLastError();
     case GEMM_TILED_4X4:
-      launch_tiled<PREC, 4, 4>(st, M, N, K, A, B, C, batch, sa, sb, sc, amaxA, amaxB, rn, split, P, ma, mb);
-      break;
+      return launch_tiled<PREC, 4, 4>(st, M, N, K, A, B, C, batch, sa, sb, sc, amaxA, amaxB, rn, split, P, ma, mb);
     case GEMM_TILED_2X2:
-      launch_tiled<PREC, 2, 2>(st, M, N, K, A, B, C, batch, sa, sb, sc, amaxA, amaxB, rn, split, P, ma, mb);
-      break;
+      return launch_tiled<PREC, 2, 2>(st, M, N, K, A, B, C, batch, sa, sb, sc, amaxA, amaxB, rn, split, P, ma, mb);
     default:
-      launch_tiled<PREC, 1, 2>(st, M, N, K, A, B, C, batch, sa, sb, sc, amaxA, amaxB, rn, split, P, ma, mb);
+      return launch_tiled<PREC, 1, 2>(st, M, N, K, A, B, C, batch, sa, sb, sc, amaxA, amaxB, rn, split, P, ma, mb);
   }
-  return hipGetLastError();
 }
 
 // K-chunks of an MFMA launch: K is cut (powers of two, chunks of at least 512) while the 64 x 32 tiles
@@ -920,6 +919,28 @@ hipError_t launch_cgemm_ex(hipStream_t st, int precision, int64_t M, int64_t N, 
     e = precision == P_BF16X3
             ? launch_mfma<P_BF16X3>(st, v, M, N, K, A, B, C, batch, sa, sb, sc, amaxA, amaxB, rn, split, scratch, a, b)
             : launch_mfma<P_FP16>(st, v, M, N, K, A, B, C, batch, sa, sb, sc, amaxA, amaxB, rn, split, scratch, a, b);
+  }
+  if (e == hipErrorInvalidConfiguration) {
+    // more workgroups than a grid takes: the halves of the batch, or one product by the kernel that strides over outputs
+    // (1 x 2^29 x 8 on tiles of 32 x 32)
+    if (batch == 1) return launch_cgemm_ex(st, precision, M, N, K, A, B, C, 1, sa, sb, sc, amaxA, amaxB, rn, GEMM_SIMT);
+    const int64_t half = batch / 2;
+    e = launch_cgemm_ex(st, precision, M, N, K, A, B, C, half, sa, sb, sc, amaxA, amaxB, rn, variant, scratch, scratch_bytes,
+                        ma, mb, flags);
+    if (e != hipSuccess) return e;
+    Renorm rest = rn;
+    OpMap a2 = a, b2 = b;
+    for (OpMap* m : {&a2, &b2})
+      if (m->base_table) m->base_table += half * m->base_stride;
+    if (rn.c) {
+      rest.a += half * rn.a_step;
+      rest.b += half * rn.b_step;
+      rest.c += half * rn.c_step;
+      rest.cleared = rn.cleared || rn.c_step == 0;
+    }
+    return launch_cgemm_ex(st, precision, M, N, K, a.base_table ? A : A + half * sa, b.base_table ? B : B + half * sb,
+                           C + half * sc, batch - half, sa, sb, sc, amaxA, amaxB, rest, variant, scratch, scratch_bytes,
+                           ma ? &a2 : nullptr, mb ? &b2 : nullptr, flags);
   }
   if (e != hipSuccess || split == 1) return e;
   const unsigned apart = rn.c_step ? (unsigned)batch : 1u;

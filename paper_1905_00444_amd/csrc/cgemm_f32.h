@@ -21,10 +21,13 @@ struct F32Args {
   OpMap ma, mb;          // gathered operands (whole tiles only)
 };
 
+// Whether a grid's x takes that many workgroups: fewer than 2^32 work-items.
+inline bool grid_takes(int64_t blocks, int64_t threads) { return blocks * threads < ((int64_t)1 << 32); }
+
 // cgemm_f32s.hip: products that it takes instead (by shape alone: a result does not depend on the batch), and
 // their launches (plain, or side 0 / 1 of an environment).
 bool f32s_takes(int64_t M, int64_t N, int64_t K);
-void launch_f32s(hipStream_t st, const F32Args& g, int split, bool env, bool side);
+hipError_t launch_f32s(hipStream_t st, const F32Args& g, int split, bool env, bool side);
 
 // Loads of one operand tile (ROWS x 16 complex) into registers: pairs of neighbours along the
 // contiguous index.  T = 0: k contiguous, 8 threads per row; T = 1: rows contiguous.

@@ -181,20 +181,24 @@ cgemm_f32(F32Args g) {
 }
 
 template <int WM, int WN, int TM, int TN, int TA, int TB, bool CONJ>
-static void f32_launch(hipStream_t st, const F32Args& g, int split) {
+static hipError_t f32_launch(hipStream_t st, const F32Args& g, int split) {
   using Tile = F32Tile<WM, WN, TM, TN>;
   const int64_t tiles = ((g.M + Tile::BM - 1) / Tile::BM) * ((g.N + Tile::BN - 1) / Tile::BN) * g.batch;
+  if (!grid_takes(tiles, Tile::threads)) return hipErrorInvalidConfiguration;
   const dim3 grid((unsigned)tiles, (unsigned)split), block(Tile::threads);
   // whole tiles and pairs of elements that never straddle a row's end
   const bool whole = g.M % Tile::BM == 0 && g.N % Tile::BN == 0 && g.kc % kFBK == 0 && g.kc * split == g.K;
-  auto run = [&](auto* kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, st, g); };
+  auto run = [&](auto* kernel) {
+    hipLaunchKernelGGL(kernel, grid, block, 0, st, g);
+    return hipGetLastError();
+  };
   if constexpr (TA == 0 && TB == 0 && !CONJ) {
     if (g.ma.on == 1 && g.mb.on == 1) return run(cgemm_f32<WM, WN, TM, TN, 0, 0, false, false, true, true>);
     if (g.ma.on == 1) return run(cgemm_f32<WM, WN, TM, TN, 0, 0, false, false, true, false>);
     if (g.mb.on == 1) return run(cgemm_f32<WM, WN, TM, TN, 0, 0, false, false, false, true>);
   }
-  if (whole) run(cgemm_f32<WM, WN, TM, TN, TA, TB, CONJ, false, false, false>);
-  else run(cgemm_f32<WM, WN, TM, TN, TA, TB, CONJ, true, false, false>);
+  if (whole) return run(cgemm_f32<WM, WN, TM, TN, TA, TB, CONJ, false, false, false>);
+  return run(cgemm_f32<WM, WN, TM, TN, TA, TB, CONJ, true, false, false>);
 }
 
 // Tile of a launch: 64 x 64 where that gives every CU its four workgroups (4096^3: 140 against 138 TFLOP/s
@@ -202,7 +206,7 @@ static void f32_launch(hipStream_t st, const F32Args& g, int split) {
 // gives the 256 CUs a workgroup each.  Thin products (N <= 16) get the tiles of that width: a wider tile
 // would multiply zeros.
 template <int TA, int TB, bool CONJ>
-static void f32_pick(hipStream_t st, const F32Args& g, int split, int want) {
+static hipError_t f32_pick(hipStream_t st, const F32Args& g, int split, int want) {
   auto blocks = [&](int64_t bm, int64_t bn) { return ((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn) * g.batch * split; };
   int tile = want;
   if (tile == F32_AUTO || tile == F32_PLAIN) {
@@ -212,11 +216,11 @@ static void f32_pick(hipStream_t st, const F32Args& g, int split, int want) {
     else tile = F32_32X32;
   }
   switch (tile) {
-    case F32_64X64: f32_launch<2, 2, 2, 2, TA, TB, CONJ>(st, g, split); return;
-    case F32_64X32: f32_launch<2, 2, 2, 1, TA, TB, CONJ>(st, g, split); return;
-    case F32_128X16: f32_launch<4, 1, 2, 1, TA, TB, CONJ>(st, g, split); return;
-    case F32_32X16: f32_launch<2, 1, 1, 1, TA, TB, CONJ>(st, g, split); return;
-    default: f32_launch<2, 2, 1, 1, TA, TB, CONJ>(st, g, split); return;
+    case F32_64X64: return f32_launch<2, 2, 2, 2, TA, TB, CONJ>(st, g, split);
+    case F32_64X32: return f32_launch<2, 2, 2, 1, TA, TB, CONJ>(st, g, split);
+    case F32_128X16: return f32_launch<4, 1, 2, 1, TA, TB, CONJ>(st, g, split);
+    case F32_32X16: return f32_launch<2, 1, 1, 1, TA, TB, CONJ>(st, g, split);
+    default: return f32_launch<2, 2, 1, 1, TA, TB, CONJ>(st, g, split);
   }
 }
 
@@ -243,9 +247,8 @@ hipError_t launch_cgemm_f32(hipStream_t st, int64_t M, int64_t N, int64_t K, con
   if (e != hipSuccess) return e;
   g.lda = K;
   g.ldb = K;
-  if (tile == F32_AUTO && f32s_takes(M, N, K)) launch_f32s(st, g, *split, false, false);
-  else f32_pick<0, 0, false>(st, g, *split, tile);
-  return hipGetLastError();
+  if (tile == F32_AUTO && f32s_takes(M, N, K)) return launch_f32s(st, g, *split, false, false);
+  return f32_pick<0, 0, false>(st, g, *split, tile);
 }
 
 hipError_t launch_cgemm_f32_env(hipStream_t st, int side, int64_t M, int64_t N, int64_t K, const float2* env,
@@ -259,10 +262,8 @@ hipError_t launch_cgemm_f32_env(hipStream_t st, int side, int64_t M, int64_t N, 
   g.lda = N;  // env's plain row pitch
   g.ldb = K;
   g.amap = map;
-  if (!plain && f32s_takes(g.M, g.N, g.K)) launch_f32s(st, g, *split, true, side);
-  else if (side) f32_pick<1, 1, true>(st, g, *split, F32_AUTO);
-  else f32_pick<0, 1, true>(st, g, *split, F32_AUTO);
-  return hipGetLastError();
+  if (!plain && f32s_takes(g.M, g.N, g.K)) return launch_f32s(st, g, *split, true, side);
+  return side ? f32_pick<1, 1, true>(st, g, *split, F32_AUTO) : f32_pick<0, 1, true>(st, g, *split, F32_AUTO);
 }
 
 } // namespace qf

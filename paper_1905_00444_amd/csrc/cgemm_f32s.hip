@@ -293,30 +293,34 @@ cgemm_f32s(F32Args g) {
 }
 
 template <int WM, int WN, int TM, int TN, int TA, int TB, bool CONJ>
-static void f32s_launch(hipStream_t st, const F32Args& g, int split) {
+static hipError_t f32s_launch(hipStream_t st, const F32Args& g, int split) {
   using Tile = F32sTile<WM, WN, TM, TN>;
   const int64_t tiles = ((g.M + Tile::BM - 1) / Tile::BM) * ((g.N + Tile::BN - 1) / Tile::BN) * g.batch;
+  if (!grid_takes(tiles, Tile::threads)) return hipErrorInvalidConfiguration;
   const dim3 grid((unsigned)tiles, (unsigned)split), block(Tile::threads);
   const bool whole = g.M % Tile::BM == 0 && g.N % Tile::BN == 0 && g.kc % kFBK == 0 && g.kc * split == g.K;
-  auto run = [&](auto* kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, st, g); };
+  auto run = [&](auto* kernel) {
+    hipLaunchKernelGGL(kernel, grid, block, 0, st, g);
+    return hipGetLastError();
+  };
   if constexpr (TA == 0 && TB == 0 && !CONJ) {
     if (g.ma.on == 1 && g.mb.on == 1) return run(cgemm_f32s<WM, WN, TM, TN, 0, 0, false, false, true, true>);
     if (g.ma.on == 1) return run(cgemm_f32s<WM, WN, TM, TN, 0, 0, false, false, true, false>);
     if (g.mb.on == 1) return run(cgemm_f32s<WM, WN, TM, TN, 0, 0, false, false, false, true>);
   }
-  if (whole) run(cgemm_f32s<WM, WN, TM, TN, TA, TB, CONJ, false, false, false>);
-  else run(cgemm_f32s<WM, WN, TM, TN, TA, TB, CONJ, true, false, false>);
+  if (whole) return run(cgemm_f32s<WM, WN, TM, TN, TA, TB, CONJ, false, false, false>);
+  return run(cgemm_f32s<WM, WN, TM, TN, TA, TB, CONJ, true, false, false>);
 }
 
 // The largest tile that gives each of the 256 CUs a workgroup: 128 x 128 against 64 x 64 on 4096^3 2.34 / 2.67 ms,
 // on 64 products of 256^3 44 / 50 us.  A result does not depend on the tile.
 template <int TA, int TB, bool CONJ>
-static void f32s_pick(hipStream_t st, const F32Args& g, int split) {
+static hipError_t f32s_pick(hipStream_t st, const F32Args& g, int split) {
   auto blocks = [&](int64_t bm, int64_t bn) { return ((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn) * g.batch * split; };
-  if (g.M >= 128 && g.N >= 128 && blocks(128, 128) >= 256) f32s_launch<4, 2, 2, 4, TA, TB, CONJ>(st, g, split);
-  else if (blocks(64, 64) >= 256) f32s_launch<2, 2, 2, 2, TA, TB, CONJ>(st, g, split);
-  else if (blocks(64, 32) >= 256) f32s_launch<2, 2, 2, 1, TA, TB, CONJ>(st, g, split);
-  else f32s_launch<2, 2, 1, 1, TA, TB, CONJ>(st, g, split);
+  if (g.M >= 128 && g.N >= 128 && blocks(128, 128) >= 256) return f32s_launch<4, 2, 2, 4, TA, TB, CONJ>(st, g, split);
+  if (blocks(64, 64) >= 256) return f32s_launch<2, 2, 2, 2, TA, TB, CONJ>(st, g, split);
+  if (blocks(64, 32) >= 256) return f32s_launch<2, 2, 2, 1, TA, TB, CONJ>(st, g, split);
+  return f32s_launch<2, 2, 1, 1, TA, TB, CONJ>(st, g, split);
 }
 
 // From 2^24 products on (256^3, where a single product is 7% slower and 64 of them 35% faster), and from 64
@@ -325,10 +329,9 @@ bool f32s_takes(int64_t M, int64_t N, int64_t K) {
   return M >= 64 && N >= 64 && K >= 128 && (double)M * (double)N * (double)K >= (double)(1 << 24);
 }
 
-void launch_f32s(hipStream_t st, const F32Args& g, int split, bool env, bool side) {
-  if (!env) f32s_pick<0, 0, false>(st, g, split);
-  else if (side) f32s_pick<1, 1, true>(st, g, split);
-  else f32s_pick<0, 1, true>(st, g, split);
+hipError_t launch_f32s(hipStream_t st, const F32Args& g, int split, bool env, bool side) {
+  if (!env) return f32s_pick<0, 0, false>(st, g, split);
+  return side ? f32s_pick<1, 1, true>(st, g, split) : f32s_pick<0, 1, true>(st, g, split);
 }
 
 } // namespace qf

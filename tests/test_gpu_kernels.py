@@ -619,3 +619,52 @@ def test_cgemm_six_products_one_term(split_ctx, M, N, K):
         err = got - np.outer(a, b)
         assert np.max(np.abs(err.real) / (np.outer(np.abs(a.real), np.abs(b.real)) + np.outer(np.abs(a.imag), np.abs(b.imag)))) <= 2.0 ** -23
         assert np.max(np.abs(err.imag) / (np.outer(np.abs(a.real), np.abs(b.imag)) + np.outer(np.abs(a.imag), np.abs(b.real)))) <= 2.0 ** -23
+
+
+@pytest.mark.parametrize("M,N", [(1, (1 << 29) + 40), ((1 << 29) + 40, 1)])
+def test_cgemm_more_tiles_than_a_grid_takes(ctx, M, N):
+    """2^24 and more workgroups of 256 threads pass the 2^32 work-items of a grid's dimension: 2^29 dot products of
+    length 8, sampled."""
+    import torch
+    from paper_1905_00444_amd import cgemm
+    _say(f"cgemm beyond a grid's work-items {M}x{N}x8")
+    free, _ = torch.cuda.mem_get_info()
+    if free < 48 << 30:
+        pytest.skip("needs 48 GiB of device memory")
+    L = max(M, N)
+    a = torch.tensor([[1, 2, 3, 4, 5, 6, 7, 8j]], dtype=torch.complex64, device="cuda")
+    b = torch.zeros((L, 8), dtype=torch.complex64, device="cuda")
+    for k in range(8):
+        b.real[:, k] = ((torch.arange(L, device="cuda") >> (3 * k)) & 7).float()
+    out = cgemm(ctx, a if M == 1 else b, b if M == 1 else a)
+    torch.cuda.synchronize()
+    rng = np.random.default_rng(1)
+    at = np.unique(np.concatenate([[0, 1, 2, 31, 32, 33, L - 33, L - 2, L - 1, (1 << 29) - 1, 1 << 29], rng.integers(0, L, 10000)]))
+    want = sum(((at >> (3 * k)) & 7) * (k + 1 if k < 7 else 8j) for k in range(8))
+    assert np.array_equal(out.reshape(-1)[torch.from_numpy(at).cuda()].cpu().numpy(), want.astype(np.complex64))
+
+
+def test_cgemm_batch_of_more_tiles_than_a_grid_takes(ctx):
+    """2^24 products of 32 x 32 x 16 with the same operands (stride 0), a workgroup of 256 threads each, sampled."""
+    import ctypes as Cc
+    import torch
+    from paper_1905_00444_amd import _lib
+    _say("cgemm batch beyond a grid's work-items")
+    free, _ = torch.cuda.mem_get_info()
+    if free < 160 << 30:
+        pytest.skip("needs 160 GiB of device memory")
+    rng = np.random.default_rng(1)
+    A, B = _rand_c64(rng, (32, 16)), _rand_c64(rng, (32, 16))
+    ref = A.astype(np.complex128) @ B.astype(np.complex128).T
+    bound = np.abs(A).astype(np.float64) @ np.abs(B).astype(np.float64).T
+    dA, dB = torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda()
+    n = 1 << 24
+    C = torch.empty((n, 32, 32), dtype=torch.complex64, device="cuda")
+    probe = [0, 1, 12345, n // 2 - 1, n // 2, n // 2 + 1, n - 2, n - 1]
+    C[probe] = float("nan")
+    _lib.check(ctx.lib.qf_cgemm(ctx.h, 0, 32, 32, 16, *[Cc.c_void_p(t.data_ptr()) for t in (dA, dB, C)], n, 0, 0, 1024), ctx.h)
+    torch.cuda.synchronize()
+    got = C[probe].cpu().numpy().astype(np.complex128)
+    del C
+    torch.cuda.empty_cache()
+    assert np.max(np.abs(got - ref) / bound) <= TOL["fp32"]
