@@ -374,8 +374,8 @@ qf_status qf_time_ceiling(qf_ctx* ctx, int kind, int precision, void* buf, int64
  * shape among the plan's steps (precision, M, N, K, chains per launch) the kernel variants that
  * fit the shape are timed with HIP events on pseudo-random operands placed in the plan's own
  * workspace buffers, and the fastest is installed in the context: every later launch of that
- * shape on this context uses it.  Steps on the pre-split split-BF16 kernel have a single variant
- * and are skipped.
+ * shape on this context uses it (calls of several chains on a one-chain plan that of one chain).  Steps
+ * on the pre-split split-BF16 kernel have a single variant and are skipped.
  * cache_path: NULL, or a JSON file.  Entries it already holds for this device are installed
  * without timing; the file is then rewritten with every shape known to the context (device,
  * shape, chosen variant, microseconds per candidate).  A missing file is created.
@@ -388,7 +388,7 @@ qf_status qf_autotune(qf_ctx* ctx, const qf_plan* plan, const char* cache_path);
 /* Variant installed for a GEMM shape on this context by qf_autotune (not in the paper, see
  * there; 0: none, the shape heuristic applies;
  * 1..9: see qf_autotune's JSON names tiled4x4, tiled2x2, tiled1x2, large, skinny, splitk, simt, tall,
- * f32). */
+ * f32, here the FP32 tiles as the heuristic picks them, large products on six BF16 ones). */
 qf_status qf_tuned_variant(const qf_ctx* ctx, int precision, int64_t M, int64_t N, int64_t K, int64_t batch,
                            int* variant);
 

@@ -324,7 +324,7 @@ def permute(ctx: Context, src, dst, perm: Sequence[int], base: int = 0, scale: f
 
 def cgemm(ctx: Context, A, B, precision: str = "fp32", out=None, variant: str = "auto"):
     """C[m, n] = sum_k A[m, k] B[n, k] (complex64, no conjugation); `variant` names a kernel
-    variant (one of _lib.GEMM_VARIANTS) instead of the shape's default."""
+    variant (one of _lib.GEMM_VARIANTS) instead of the shape's default ("f32": FP32 MFMAs, any shape)."""
     torch = _torch()
     M, K = A.shape
     N, K2 = B.shape

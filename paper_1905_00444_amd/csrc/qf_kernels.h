@@ -232,10 +232,10 @@ hipError_t launch_cgemm(hipStream_t st, int precision, int64_t M, int64_t N, int
 // GEMM kernel variants (GEMM_AUTO: chosen from the shape).
 enum {
   GEMM_AUTO = 0,
-  GEMM_TILED_4X4 = 1,  // 256 threads, 128 x 64 complex block tile
+  GEMM_TILED_4X4 = 1,  // 256 threads, 128 x 64 complex block tile (FP32: 64 x 64)
   GEMM_TILED_2X2 = 2,  // 64 x 32
   GEMM_TILED_1X2 = 3,  // 32 x 32
-  GEMM_LARGE = 4,      // 512 threads, 256 x 128, double-buffered LDS
+  GEMM_LARGE = 4,      // 512 threads, 256 x 128, double-buffered LDS (FP32: 64 x 64)
   GEMM_SKINNY = 5,     // B in LDS, SIMT FP32 (N K <= 4096, K <= 64)
   GEMM_SPLITK = 6,     // one workgroup per output (M N <= 4096), SIMT FP32
   GEMM_SIMT = 7,       // one thread per output, SIMT FP32

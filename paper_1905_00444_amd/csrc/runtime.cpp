@@ -2034,7 +2034,7 @@ extern "C" qf_status qf_amplitudes_static(qf_plan* p, int n_batch, const uint8_t
   qf_status st = static_scratch_ptr(c, &ptr);
   if (st != QF_OK) return st;
   // run on the static array: the world-lines are rebuilt in it (every region that must start at a
-  // known value, the chain counter, the scale table and the max-magnitude slots, is written by
+  // known value, the tables, the scales and the max-magnitude slots, is written by
   // the call itself before it is read), profiling (which may create events) is off
   char* const ws = c->ws;
   const size_t ws_bytes = c->ws_bytes, call_ws_bytes = c->call_ws_bytes;
@@ -2668,6 +2668,7 @@ static std::vector<int> tune_candidates(int prec, int64_t M, int64_t N, int64_t 
     if (!cgemm_variant_fits(prec, M, N, K, i)) continue;
     if (mfma && (i == GEMM_SIMT || i == GEMM_SPLITK)) continue;
     if (mfma && i == GEMM_F32 && prec != QF_FP32) continue;
+    if (prec == QF_FP32 && i == GEMM_LARGE && cgemm_variant_fits(prec, M, N, K, GEMM_TILED_4X4)) continue;  // the same tile
     if (big_grid && (i == GEMM_TILED_2X2 || i == GEMM_TILED_1X2)) continue;
     v.push_back(i);
   }

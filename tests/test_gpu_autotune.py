@@ -131,3 +131,21 @@ def test_tuned_variants_serve_calls_of_several_chains(tmp_path, precision):
         assert np.array_equal(got.cpu().numpy(), want.cpu().numpy()), name
         others += not np.array_equal(got.cpu().numpy(), rule)
     assert others >= 2
+
+
+def test_tuner_times_no_kernel_twice(tmp_path):
+    """In FP32 the variants large and tiled4x4 are one kernel: no shape lists both, and each can be named in a call,
+    f32 too."""
+    import torch
+    from paper_1905_00444_amd import Context, Circuit, Plan, autotune, cgemm, _lib
+    c, plan = _setup()
+    ctx = Context(0)
+    autotune(Plan(ctx, Circuit(ctx, c.to_text()), plan, "fp32"), str(tmp_path / "t.json"))
+    entries = json.loads((tmp_path / "t.json").read_text())["entries"]
+    assert any("tiled4x4" in e["us"] for e in entries)
+    assert not any("tiled4x4" in e["us"] and "large" in e["us"] for e in entries)
+    g = torch.Generator(device="cuda").manual_seed(1)
+    a, b = (torch.randn(256, 64, dtype=torch.complex64, device="cuda", generator=g) for _ in range(2))
+    ref = torch.mm(a.to(torch.complex128), b.to(torch.complex128).T.contiguous())
+    for v in ("tiled4x4", "large", "f32"):
+        assert (cgemm(ctx, a, b, variant=v) - ref).abs().max() / ref.abs().max() <= 1e-6, v
