@@ -668,3 +668,27 @@ def test_cgemm_batch_of_more_tiles_than_a_grid_takes(ctx):
     del C
     torch.cuda.empty_cache()
     assert np.max(np.abs(got - ref) / bound) <= TOL["fp32"]
+
+
+@pytest.mark.parametrize("precision", ["fp32", "bf16x3", "fp16"])
+@pytest.mark.parametrize("M,N,K", [(4096, 1024, 128), (128, 64, 32), (64, 32, 64), (512, 512, 2048), (8192, 16, 64),
+                                   (32768, 64, 8), (1024, 16, 16), (65536, 4, 4), (4, 8, 4096), (192, 96, 48)])
+def test_cgemm_on_8_byte_aligned_buffers(ctx, precision, M, N, K):
+    """Operands or the result offset by one complex64 (8-byte, not 16-byte, aligned): the same bits as aligned."""
+    import torch
+    from paper_1905_00444_amd import cgemm
+    _say(f"cgemm 8-byte aligned {precision} {M}x{N}x{K}")
+    rng = np.random.default_rng(M + K)
+    dev = [torch.from_numpy(_rand_c64(rng, (r * K,))).cuda() for r in (M, N)]
+    want = cgemm(ctx, dev[0].view(M, K), dev[1].view(N, K), precision)
+    big = [torch.zeros(x.numel() + 1, dtype=torch.complex64, device="cuda") for x in dev]
+    for x, b in zip(dev, big):
+        b[1:] = x
+    for oa, ob, oc in ((1, 0, 0), (0, 1, 0), (0, 0, 1), (1, 1, 1)):
+        a, b = ((big[i][1:] if o else dev[i]).view(-1, K) for i, o in ((0, oa), (1, ob)))
+        c = torch.full((M * N + 2,), 7.0 + 0j, dtype=torch.complex64, device="cuda")
+        cgemm(ctx, a, b, precision, out=c[oc:oc + M * N].view(M, N))
+        torch.cuda.synchronize()
+        assert a.data_ptr() % 16 == 8 * oa and b.data_ptr() % 16 == 8 * ob
+        assert torch.equal(c[oc:oc + M * N], want.view(-1))
+        assert (c[oc + M * N:] == 7.0).all() and (c[:oc] == 7.0).all()
