@@ -124,7 +124,9 @@ typedef struct {
   double flops_hoisted;     /* part of flops_per_slice that depends on no cut value */
   double flops_first_slice; /* flops of the first slice of a bitstring, with reuse */
   double flops_next_slice;  /* average flops of each later slice of the same bitstring */
-  double permute_bytes;     /* bytes read + written by permutes per slice (no reuse) */
+  double permute_bytes;     /* bytes read + written per slice (no reuse) if every operand with
+                               qf_step_info.a_permuted / b_permuted set is copied; less is moved
+                               where a product reads one in place */
   size_t workspace_bytes;   /* workspace the plan needs */
   double mfma_flops_per_slice; /* matrix-core flops issued per slice with the default kernels:
                                   3x the algorithmic count for split-BF16 (three products), 1x
@@ -137,9 +139,12 @@ typedef struct {
   int32_t lhs, rhs;           /* node ids as given in the plan description */
   int32_t a_node, b_node;     /* the same two nodes in their A and B roles */
   int32_t m_bits, n_bits, k_bits;
-  int32_t a_permuted, b_permuted; /* the operand is copied by a permute before the GEMM */
-  int32_t a_reordered, b_reordered; /* ... and that copy changes the element order (0: the copy
-                                       only fixes bits or splits into bfloat16 planes) */
+  int32_t a_permuted, b_permuted; /* the operand does not lie as C[M][N] = sum_K A B reads it: it is
+                                     copied by a permute before the GEMM, gathered at the start of
+                                     the chain (small world-lines), or read in place by a kernel
+                                     that takes its bit order as a map */
+  int32_t a_reordered, b_reordered; /* ... and its element order differs (0: a copy would only fix
+                                       bits or split into bfloat16 planes) */
   int32_t presplit;           /* split-BF16 GEMM on operands split by their permutes */
   int32_t persistent;         /* the result is kept across slices (no cut bit it depends on changes) */
   int32_t out_q, out_nh;      /* output order: 0, 0 for C[M][N]; else the GEMM writes element (m, n)
@@ -254,7 +259,8 @@ qf_status qf_amplitudes(qf_plan* plan, int n_batch, const uint8_t* bits_dev, int
  * captured in a graph) runs G chains through every forward and reverse step at once; their
  * leaf environments add atomically into shared world-line environments, so the order of the
  * chains' terms in the gradient sums is not fixed (results differ from the one-chain-at-a-time
- * plan by rounding only).
+ * plan by rounding only).  The same holds for a one-chain plan's call of several chains where the
+ * workspace has room for them (qf_plan_call_workspace).
  *   cot_dev : device, n_batch x 2^n_open complex128 cotangents c_b of the amplitudes a_b
  *             (for L = sum |a_b|^2, c_b = 2 a_b).
  *   grad_dev: device, n_ops x 4 complex64 in the caller's gate order (2x2 row-major matrix, or
