@@ -17,7 +17,8 @@
 // 2.1e-6 / 1.9e-6 / 1.4e-6, 5x5 2.3e-6 / 1.7e-5 / 3.3e-6, 6x6 5.3e-6 / 1.7e-5 / 8.9e-6.  Of products, norm-wise: normal
 // entries, 4096 x 1024 x 128, 3.2e-8 / 1.0e-8 / 7.6e-9, same-sign entries over 20 binades, K = 1024, 2.2e-7 / - / 5.9e-8.
 // Callers who want FP32 MFMAs throughout have QF_PLAN_PLAIN_FP32 and the variant f32.  Products below K = 128 stay
-// on FP32 MFMAs: HBM bounds them there (2^15 x 64 x 64 by 64: 619 us against 539).
+// on FP32 MFMAs, where HBM is half of their time and six products gained least (2^15 x 64 x 64 by 64 619 us, 539 with
+// all sums in the instruction).
 //
 // Bound by VALU issue beside the MFMAs (conversions: 11 instructions per complex element staged; the
 // arrangement of B: 2 per element and plane read), so tiles are as large as the launch allows.
