@@ -647,9 +647,12 @@ def test_cgemm_more_tiles_than_a_grid_takes(ctx, M, N):
 def test_cgemm_batch_of_more_tiles_than_a_grid_takes(ctx):
     """2^24 products of 32 x 32 x 16 with the same operands (stride 0), a workgroup of 256 threads each, sampled."""
     import ctypes as Cc
+    import gc
     import torch
     from paper_1905_00444_amd import _lib
     _say("cgemm batch beyond a grid's work-items")
+    gc.collect()
+    torch.cuda.empty_cache()  # what earlier tests left with the allocator counts as used
     free, _ = torch.cuda.mem_get_info()
     if free < 160 << 30:
         pytest.skip("needs 160 GiB of device memory")
